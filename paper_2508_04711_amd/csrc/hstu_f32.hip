@@ -1,281 +1,450 @@
 // fp32 jagged HSTU attention (forward, dk/dv pass, dq pass): the all-fp32 data type of the
-// library, computed on the vector ALUs with IEEE division and the precise exponential so that
-// results stay within 1e-5 of a double-precision evaluation of the section 2.1 equation.
+// library, on the fp32 matrix instruction (products and sums in fp32), with IEEE division and the
+// precise exponential, so that results stay within 1e-5 of a double-precision evaluation of the
+// section 2.1 equation.
 //
-// Same schedule items as the bf16 kernels.  A workgroup of 256 threads owns a tile of 64 rows,
-// four adjacent lanes per row; lane c of a row holds elements c, c+4, c+8, ... of the row's
-// vectors, so a dot product is a per-lane partial sum plus two cross-lane adds.  The other
-// side's rows are staged through LDS 64 at a time and visited one by one.
-#include "hstu_common.h"
+//   v_mfma_f32_32x32x2_f32  D[32x32] += A[32x2] * B[2x32]   (lane l: n = l%32, hh = l/32)
+//     A: lane holds row n, k = hh      B: lane holds column n, k = hh
+//     D: lane holds column n, rows 8*(r/4) + 4*hh + r%4   for r = 0..15
+//
+// What bounds it: the fp32 matrix rate (64 flops per cycle and SIMD, a sixteenth of the bf16 rate;
+// 153 TFLOP/s in a large matrix product on this card), and on small problems the longest chain of
+// blocks one wave works through: a 32x32 block of pairs at d = 64 is 4096 cycles of matrix
+// instructions forward, so a 512-row sequence taken by one wave per 32 rows would last 30 us.
+// Hence the split: a workgroup owns 32 rows and its four waves take every fourth 32-row block of
+// the streamed side, each on its own (wave-private LDS buffers, no barrier inside the loop), and
+// add their accumulators up through LDS at the end.  LDS and L2 traffic is no concern at this
+// matrix rate: an operand read of 16 bytes per lane feeds four matrix instructions (256 cycles).
+// Each streamed tensor has one buffer per wave, refilled by an asynchronous copy as soon as the
+// block's last product that reads it has been issued; the products of the other tensor cover it.
+// Measured against the vector-ALU kernels before it (four lanes per row, key by key, one LDS read
+// per fused multiply-add): 16 sequences of 64..512 rows, H = 4, d = 64: forward 225 -> 21 us, dk/dv
+// 281 -> 35, dq 269 -> 29; 4 sequences of 1..64 rows, H = 2, d = 32: 22 -> 5.3, 27 -> 6.6, 25 -> 6.1 us.
+#include "hstu_mfma.h"
 
 namespace hstu {
 
 namespace {
 
-constexpr int TILE = 64;     // owner rows per item
-constexpr int ST = 64;       // streamed rows per LDS tile
-constexpr int THREADS = 256;
+constexpr int TILE = 32;     // owner rows per item
+constexpr int FW = 4;        // waves per workgroup
+constexpr int THREADS = FW * 64;
+constexpr int FB = 32;       // streamed rows per block
 
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f4;
+
+__device__ __forceinline__ f32x16 mfma_f32(float a, float b, const f32x16& c) {
+  return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
+}
+
+// Swizzle of a row's 16-byte chunks (see swz_rb): 16 consecutive rows at one logical chunk land on
+// 16 different positions of the 64 banks, and so do rows r and r + 4 at the eight chunks of 32
+// consecutive columns (what a transposed operand read touches), except at D = 32.
+template <int D>
+__device__ __forceinline__ int fswz(int row) {
+  if (D == 32) return (row >> 1) & 7;  // two rows per 256 bytes
+  return (row & 3) | (((row >> 3) & 1) << 2) | (((row >> 2) & 1) << 3);
+}
+
+// Waits until at most N of the wave's vector memory operations are in flight.
+template <int N>
+__device__ __forceinline__ void vm_wait() {
+  static_assert(N >= 0 && N < 64, "vmcnt");
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0x0f70 | (N & 15) | ((N >> 4) << 14));
+  asm volatile("" ::: "memory");
+}
+__device__ __forceinline__ void lds_reads_done() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+
+// A wave's copy of one block: FB rows of one head, D / 8 wave-wide loads; rows >= valid are zeros.
+template <int D>
+constexpr int block_loads() { return D / 8; }
+template <int D>
+__device__ __forceinline__ void block_copy(float* buf, const float* base, int rs, int valid, int lane) {
+  constexpr int CPR = D / 4, RPL = 64 / CPR;
+  const int rows = valid < 0 ? 0 : (valid < FB ? valid : FB);
+  const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
+      (void*)base, 0, __builtin_amdgcn_readfirstlane(rows * rs), 0x00020000);
+#pragma unroll
+  for (int i = 0; i < block_loads<D>(); ++i) {
+    const int row = i * RPL + lane / CPR;
+    const int chunk = (lane % CPR) ^ fswz<D>(row);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, HSTU_LDS(void, buf + i * 256), 16, row * rs + chunk * 16, 0, 0, 0);
+  }
+}
+
+// Owner rows as B operands: lane (n, hh) holds elements 8*t + 4*hh + {0..3} of row n.
+template <int D>
+__device__ __forceinline__ void load_rows(f4 (&reg)[D / 8], const float* base, int rs, int row, int nrows, int hh) {
+  const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
+      (void*)base, 0, __builtin_amdgcn_readfirstlane(nrows * rs), 0x00020000);
+#pragma unroll
+  for (int t = 0; t < D / 8; ++t)
+    reg[t] = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, row * rs + t * 32 + hh * 16, 0, 0));
+}
+
+// acc[streamed row][owner row] += block (rows of the block) x owners^T.
+template <int D>
+__device__ __forceinline__ void scores(f32x16& acc, const float* buf, const f4 (&own)[D / 8], int n, int hh) {
+  const int s = fswz<D>(n);
+#pragma unroll
+  for (int t = 0; t < D / 8; ++t) {
+    const f4 x = *HSTU_LDS(const f4, buf + n * D + (((2 * t + hh) ^ s) << 2));
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc = mfma_f32(x[e], own[t][e], acc);
+  }
+}
+
+// acc[column][owner row] += block^T x w, w[r] belonging to streamed row 8*(r/4) + 4*hh + r%4: the
+// accumulator layout of scores() is the B operand of this product as it stands.
+template <int D>
+__device__ __forceinline__ void contract(f32x16 (&acc)[D / 32], const float* buf, const float (&w)[16], int n, int hh) {
+  __builtin_amdgcn_sched_barrier(0);  // (operand reads hoisted further up would only take registers)
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int row = 8 * (r >> 2) + 4 * hh + (r & 3);
+    const float* p = buf + row * D;
+    const int s = fswz<D>(row);
+#pragma unroll
+    for (int c = 0; c < D / 32; ++c) {
+      const float x = *HSTU_LDS(const float, p + (((c * 8 + (n >> 2)) ^ s) << 2) + (n & 3));
+      acc[c] = mfma_f32(x, w[r], acc[c]);
+    }
+  }
+}
+
+__device__ __forceinline__ void clear(f32x16& x) {
+#pragma unroll
+  for (int r = 0; r < 16; ++r) x[r] = 0.f;
+}
+
+// Adds up the four waves' accumulators through LDS (buf: the waves' FB x D blocks, no longer
+// needed) and stores the 32 owner rows.  All threads of the workgroup call it.
+template <int D>
+__device__ __forceinline__ void sum_and_store(float* buf, const f32x16 (&acc)[D / 32], float* out, int64_t elem0,
+                                              int64_t row_stride, int nrows, float scale, int accumulate, int wave,
+                                              int lane) {
+  float* mine = buf + wave * (FB * D);
+#pragma unroll
+  for (int c = 0; c < D / 32; ++c)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const f4 x = {acc[c][4 * q], acc[c][4 * q + 1], acc[c][4 * q + 2], acc[c][4 * q + 3]};
+      *HSTU_LDS(f4, mine + ((c * 4 + q) * 64 + lane) * 4) = x;
+    }
+  __syncthreads();
+  const int n = lane & 31, hh = lane >> 5;
+#pragma unroll
+  for (int i = 0; i < D / 32; ++i) {
+    const int g = i * FW + wave;  // group c * 4 + q of the accumulators
+    f4 x = *HSTU_LDS(const f4, buf + (g * 64 + lane) * 4);
+#pragma unroll
+    for (int w = 1; w < FW; ++w) x += *HSTU_LDS(const f4, buf + w * (FB * D) + (g * 64 + lane) * 4);
+    x *= scale;
+    if (n < nrows) {
+      f4* dst = (f4*)(out + elem0 + (int64_t)n * row_stride + g * 8 + hh * 4);
+      if (accumulate) x += *dst;
+      *dst = x;
+    }
+  }
+}
+
+// sigmoid(x) = 1 / (1 + e^-x) to about an ulp.  e^y as 2^t with t = y * log2(e) rounded and the
+// product's rounding error carried as a first-order factor (1 + ln2 * error), so that a large |y|
+// costs no accuracy; the reciprocal with one Newton step.  y is kept below 87, where e^y is still
+// finite (x < -87: sigmoid is below 2e-38, and x * sigmoid below 1e-33 for any finite fp32 score of
+// this operator).  Twelve vector instructions against 27 for expf and an IEEE division.
+__device__ __forceinline__ float sigmoid_precise(float x) {
+  constexpr float LOG2E = 1.44269504088896341f, LOG2E_LO = 1.92596299e-8f, LN2 = 0.693147180559945309f;
+  const float y = __builtin_fminf(-x, 87.0f);
+  const float t = y * LOG2E;
+  const float err = __builtin_fmaf(y, LOG2E_LO, __builtin_fmaf(y, LOG2E, -t));
+  const float e = __builtin_amdgcn_exp2f(t);
+  const float d = 1.0f + __builtin_fmaf(e, err * LN2, e);
+  const float r = __builtin_amdgcn_rcpf(d);
+  return __builtin_fmaf(__builtin_fmaf(-d, r, 1.0f), r, r);
+}
+
+// The streamed blocks of an item: [first, end) of Stream's 32-row blocks, without the leading block
+// wholly before the owners and the trailing one without rows; wave w takes first + w, + FW, ...
+struct Blocks {
+  Stream st;
+  int first, end;
+};
 template <int SIDE>
-__device__ __forceinline__ void visible_range(const Item& it, int g, int causal, int& beg, int& end) {
-  beg = 0;
-  end = it.seg_len[g];
-  if (causal) {
-    if (SIDE == 0) {
-      const int e = it.pos0 + it.nrows - it.seg_pos0[g];
-      end = e < 0 ? 0 : (e < end ? e : end);
-    } else {
-      const int b = it.pos0 - it.seg_pos0[g];
-      beg = b < 0 ? 0 : (b < end ? b : end);
+__device__ __forceinline__ Blocks make_blocks(const Item& it, int causal) {
+  Blocks b;
+  b.st = make_stream<SIDE>(it, causal);
+  b.first = 0;
+  b.end = 2 * b.st.total;
+  if (b.end > 0) {
+    if (tile_ref(it, b.st, b.st.total - 1).valid <= FB) --b.end;
+    if (SIDE == 1 && causal && tile_ref(it, b.st, 0).pos + FB <= it.pos0) b.first = 1;
+  }
+  return b;
+}
+struct BlockRef { int row, valid, pos; };
+__device__ __forceinline__ BlockRef block_ref(const Item& it, const Blocks& b, int i) {
+  if (i >= b.end) return BlockRef{0, 0, 0};
+  const TileRef t = tile_ref(it, b.st, i >> 1);
+  const int o = (i & 1) * FB;
+  return BlockRef{t.row + o, t.valid - o, t.pos + o};
+}
+
+// Timestamp bias of the lane's 16 pairs (see bias_bucket): adds the table entries to the scores and
+// keeps the buckets.  Streamed rows beyond the block's valid ones take the last valid row's
+// timestamp: their products are zero whatever the score.  (The records are padded by 64 rows.)
+__device__ __forceinline__ void add_bias(f32x16& s, int (&bk)[16], const AttnArgs& a, int t_own, const BlockRef& b, int hh) {
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    int row = 8 * (r >> 2) + 4 * hh + (r & 3);
+    row = row < b.valid ? row : (b.valid > 0 ? b.valid - 1 : 0);
+    bk[r] = bias_bucket(abs_diff(t_own, a.ts_rec[(int64_t)b.row + row].ts), a.nb, a.fbits);
+    s[r] += a.ts_w[bk[r]];
+  }
+}
+
+// Waves per SIMD the kernels are built for: what the LDS of a workgroup leaves room for.
+constexpr int f32_waves(int dqk, int dv, bool one = false) { return dqk + dv <= 128 && !one ? 2 : 1; }
+
+struct Lane {
+  int tid, lane, n, hh, wave;
+  __device__ __forceinline__ Lane() {
+    tid = threadIdx.x; lane = tid & 63; n = lane & 31; hh = lane >> 5;
+    wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  }
+};
+
+// ---------------------------------------------------------------------------------------------
+template <int DQK, int DV, bool BIAS>
+__global__ void __launch_bounds__(THREADS, f32_waves(DQK, DV)) hstu_fwd_f32(AttnArgs a) {
+  __shared__ __attribute__((aligned(1024))) float kbuf[FW * FB * DQK];
+  __shared__ __attribute__((aligned(1024))) float vbuf[FW * FB * DV];
+  const int H = a.num_heads, h = blockIdx.x % H;
+  Item it;
+  if (!fetch_item(a.plan, blockIdx.x / H, it)) return;
+  const Lane l;
+  const int64_t sq = (int64_t)H * DQK, sv = (int64_t)H * DV;
+  const float* kg = (const float*)a.k + h * DQK;
+  const float* vg = (const float*)a.v + h * DV;
+  float* kb = kbuf + l.wave * (FB * DQK);
+  float* vb = vbuf + l.wave * (FB * DV);
+  f4 q[DQK / 8];
+  load_rows<DQK>(q, (const float*)a.q + (int64_t)it.row0 * sq + h * DQK, (int)sq * 4, l.n, it.nrows, l.hh);
+  const Blocks bl = make_blocks<0>(it, a.causal);
+  const int t_own = BIAS && l.n < it.nrows ? a.ts_rec_own[(int64_t)it.row0 + l.n].ts : 0;
+  auto copy_k = [&](const BlockRef& b) { block_copy<DQK>(kb, kg + (int64_t)b.row * sq, (int)sq * 4, b.valid, l.lane); };
+  auto copy_v = [&](const BlockRef& b) { block_copy<DV>(vb, vg + (int64_t)b.row * sv, (int)sv * 4, b.valid, l.lane); };
+  f32x16 o[DV / 32];
+#pragma unroll
+  for (int c = 0; c < DV / 32; ++c) clear(o[c]);
+  int i = bl.first + l.wave;
+  BlockRef b = block_ref(it, bl, i);
+  copy_k(b);
+  copy_v(b);
+  for (; i < bl.end; i += FW) {
+    const BlockRef nx = block_ref(it, bl, i + FW);
+    f32x16 s;
+    clear(s);
+    vm_wait<block_loads<DV>()>();
+    scores<DQK>(s, kb, q, l.n, l.hh);
+    lds_reads_done();
+    copy_k(nx);
+    if constexpr (BIAS) {
+      int bk[16];
+      add_bias(s, bk, a, t_own, b, l.hh);
     }
+    float p[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const float x = a.alpha * s[r];
+      p[r] = x * sigmoid_precise(x);
+    }
+    if (a.causal && b.pos + FB - 1 > it.pos0) {
+      const VisBefore vis{it.pos0 + l.n - b.pos, l.hh};
+#pragma unroll
+      for (int r = 0; r < 16; ++r) p[r] = vis(r) ? p[r] : 0.f;
+    }
+    vm_wait<block_loads<DQK>()>();
+    contract<DV>(o, vb, p, l.n, l.hh);
+    lds_reads_done();
+    copy_v(nx);
+    b = nx;
   }
-}
-
-__device__ __forceinline__ bool fetch_item(const Plan& plan, int slot, Item& it) {
-  if (slot >= plan.header[0]) return false;
-  it = plan.items[plan.order[slot]];
-  return it.nrows > 0;
-}
-
-// Sum over the four lanes of a row.
-__device__ __forceinline__ float row_sum(float x) {
-  x += __shfl_xor(x, 1);
-  x += __shfl_xor(x, 2);
-  return x;
-}
-
-// Copy `valid` rows (zero beyond) of a [*, H, D] fp32 tensor's head slice into a dense LDS tile.
-template <int D>
-__device__ __forceinline__ void stage(float* tile, const float* base, int64_t row_stride, int valid,
-                                      int tid) {
-  constexpr int V4 = D / 4;
-  for (int c = tid; c < ST * V4; c += THREADS) {
-    const int row = c / V4, col = (c % V4) * 4;
-    float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (row < valid) x = *(const float4*)(base + row * row_stride + col);
-    *(float4*)(tile + row * D + col) = x;
-  }
-}
-
-template <int D>
-__device__ __forceinline__ void load_part(float (&part)[D / 4], const float* row, bool valid, int c) {
-#pragma unroll
-  for (int i = 0; i < D / 4; ++i) part[i] = valid ? row[4 * i + c] : 0.f;
-}
-
-template <int D>
-__device__ __forceinline__ float dot_part(const float (&part)[D / 4], const float* row, int c) {
-  float s = 0.f;
-#pragma unroll
-  for (int i = 0; i < D / 4; ++i) s = fmaf(part[i], row[4 * i + c], s);
-  return s;
-}
-
-template <int D>
-__device__ __forceinline__ void axpy_part(float (&acc)[D / 4], float w, const float* row, int c) {
-#pragma unroll
-  for (int i = 0; i < D / 4; ++i) acc[i] = fmaf(w, row[4 * i + c], acc[i]);
-}
-
-template <int D>
-__device__ __forceinline__ void store_part(float* row, const float (&acc)[D / 4], float scale,
-                                           int accumulate, int c) {
-#pragma unroll
-  for (int i = 0; i < D / 4; ++i) {
-    float x = acc[i] * scale;
-    if (accumulate) x += row[4 * i + c];
-    row[4 * i + c] = x;
-  }
-}
-
-__device__ __forceinline__ float sigmoid_precise(float x) { return 1.0f / (1.0f + expf(-x)); }
-
-// Timestamp bias of one pair (0 without bias): the table entry of the bucket of the two rows'
-// timestamp difference; `bucket` receives the bucket.
-__device__ __forceinline__ float pair_bias(const AttnArgs& a, int t_own, int64_t streamed_row, int& bucket) {
-  bucket = 0;
-  if (!a.ts_rec) return 0.f;
-  bucket = bias_bucket(abs_diff(t_own, a.ts_rec[streamed_row].ts), a.nb, a.fbits);
-  return a.ts_w[bucket];
-}
-__device__ __forceinline__ int own_timestamp(const AttnArgs& a, int64_t row, bool on) {
-  return (a.ts_rec && on) ? a.ts_rec_own[row].ts : 0;
+  vm_wait<0>();
+  sum_and_store<DV>(vbuf, o, (float*)a.o, (int64_t)it.row0 * sv + h * DV, sv, it.nrows, a.inv_n, a.accumulate, l.wave,
+                    l.lane);
 }
 
 // ---------------------------------------------------------------------------------------------
-template <int DQK, int DV>
-__global__ void __launch_bounds__(THREADS) hstu_fwd_f32(AttnArgs a) {
-  __shared__ __attribute__((aligned(16))) float kt[ST * DQK];
-  __shared__ __attribute__((aligned(16))) float vt[ST * DV];
-  const int H = a.num_heads;
-  const int slot = blockIdx.x / H, h = blockIdx.x % H;
+template <int DQK, int DV, bool BIAS>
+__global__ void __launch_bounds__(THREADS, f32_waves(DQK, DV, BIAS)) hstu_dkdv_f32(AttnArgs a) {
+  __shared__ __attribute__((aligned(1024))) float qbuf[FW * FB * DQK];
+  __shared__ __attribute__((aligned(1024))) float gbuf[FW * FB * DV];
+  const int H = a.num_heads, h = blockIdx.x % H;
   Item it;
-  if (!fetch_item(a.plan, slot, it)) return;
-  const int tid = threadIdx.x, r = tid >> 2, c = tid & 3;
+  if (!fetch_item(a.plan, blockIdx.x / H, it)) return;
+  const Lane l;
   const int64_t sq = (int64_t)H * DQK, sv = (int64_t)H * DV;
-  const bool on = r < it.nrows;
-  float qp[DQK / 4], op[DV / 4];
-  load_part<DQK>(qp, (const float*)a.q + ((int64_t)it.row0 + r) * sq + h * DQK, on, c);
+  const float* qg = (const float*)a.q + h * DQK;
+  const float* gg = (const float*)a.d_o + h * DV;
+  float* qb = qbuf + l.wave * (FB * DQK);
+  float* gb = gbuf + l.wave * (FB * DV);
+  f4 k[DQK / 8], v[DV / 8];
+  load_rows<DQK>(k, (const float*)a.k + (int64_t)it.row0 * sq + h * DQK, (int)sq * 4, l.n, it.nrows, l.hh);
+  load_rows<DV>(v, (const float*)a.v + (int64_t)it.row0 * sv + h * DV, (int)sv * 4, l.n, it.nrows, l.hh);
+  const Blocks bl = make_blocks<1>(it, a.causal);
+  const int t_own = BIAS && l.n < it.nrows ? a.ts_rec_own[(int64_t)it.row0 + l.n].ts : 0;
+  auto copy_q = [&](const BlockRef& b) { block_copy<DQK>(qb, qg + (int64_t)b.row * sq, (int)sq * 4, b.valid, l.lane); };
+  auto copy_g = [&](const BlockRef& b) { block_copy<DV>(gb, gg + (int64_t)b.row * sv, (int)sv * 4, b.valid, l.lane); };
+  f32x16 dk[DQK / 32], dv[DV / 32];
 #pragma unroll
-  for (int i = 0; i < DV / 4; ++i) op[i] = 0.f;
-  const int qpos = it.pos0 + r;
-  const int t_own = own_timestamp(a, (int64_t)it.row0 + r, on);
-
-  for (int g = 0; g < it.nseg; ++g) {
-    int beg, end;
-    visible_range<0>(it, g, a.causal, beg, end);
-    for (int t0 = beg; t0 < end; t0 += ST) {
-      const int valid = end - t0 < ST ? end - t0 : ST;
-      __syncthreads();
-      stage<DQK>(kt, (const float*)a.k + ((int64_t)it.seg_row0[g] + t0) * sq + h * DQK, sq, valid, tid);
-      stage<DV>(vt, (const float*)a.v + ((int64_t)it.seg_row0[g] + t0) * sv + h * DV, sv, valid, tid);
-      __syncthreads();
-      for (int j = 0; j < valid; ++j) {
-        int bucket;
-        const float s = row_sum(dot_part<DQK>(qp, kt + j * DQK, c)) +
-                        pair_bias(a, t_own, (int64_t)it.seg_row0[g] + t0 + j, bucket);
-        const float x = a.alpha * s;
-        float p = x * sigmoid_precise(x);
-        const int kpos = it.seg_pos0[g] + t0 + j;
-        if (a.causal && kpos > qpos) p = 0.f;
-        axpy_part<DV>(op, p, vt + j * DV, c);
+  for (int c = 0; c < DQK / 32; ++c) clear(dk[c]);
+#pragma unroll
+  for (int c = 0; c < DV / 32; ++c) clear(dv[c]);
+  int i = bl.first + l.wave;
+  BlockRef b = block_ref(it, bl, i);
+  copy_g(b);
+  copy_q(b);
+  for (; i < bl.end; i += FW) {
+    const BlockRef nx = block_ref(it, bl, i + FW);
+    f32x16 s, dp;
+    clear(s); clear(dp);
+    vm_wait<block_loads<DQK>()>();
+    scores<DV>(dp, gb, v, l.n, l.hh);
+    vm_wait<0>();
+    scores<DQK>(s, qb, k, l.n, l.hh);
+    if constexpr (BIAS) {
+      int bk[16];
+      add_bias(s, bk, a, t_own, b, l.hh);
+    }
+    float p[16], ds[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const float x = a.alpha * s[r];
+      const float sg = sigmoid_precise(x);
+      p[r] = x * sg;
+      ds[r] = dp[r] * sg * (1.0f + x * (1.0f - sg));
+    }
+    if (a.causal && b.pos < it.pos0 + TILE - 1) {
+      const VisAfter vis{it.pos0 + l.n - b.pos, l.hh};
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const bool on = vis(r);
+        p[r] = on ? p[r] : 0.f;
+        ds[r] = on ? ds[r] : 0.f;
       }
     }
+    contract<DV>(dv, gb, p, l.n, l.hh);
+    lds_reads_done();
+    copy_g(nx);
+    contract<DQK>(dk, qb, ds, l.n, l.hh);
+    lds_reads_done();
+    copy_q(nx);
+    b = nx;
   }
-  if (on)
-    store_part<DV>((float*)a.o + ((int64_t)it.row0 + r) * sv + h * DV, op, a.inv_n, a.accumulate, c);
+  vm_wait<0>();
+  sum_and_store<DV>(gbuf, dv, (float*)a.dv, (int64_t)it.row0 * sv + h * DV, sv, it.nrows, a.inv_n, a.accumulate, l.wave,
+                    l.lane);
+  sum_and_store<DQK>(qbuf, dk, (float*)a.dk, (int64_t)it.row0 * sq + h * DQK, sq, it.nrows, a.alpha * a.inv_n,
+                     a.accumulate, l.wave, l.lane);
 }
 
 // ---------------------------------------------------------------------------------------------
-template <int DQK, int DV>
-__global__ void __launch_bounds__(THREADS) hstu_dkdv_f32(AttnArgs a) {
-  __shared__ __attribute__((aligned(16))) float qt[ST * DQK];
-  __shared__ __attribute__((aligned(16))) float gt[ST * DV];
-  const int H = a.num_heads;
-  const int slot = blockIdx.x / H, h = blockIdx.x % H;
+template <int DQK, int DV, bool BIAS>
+__global__ void __launch_bounds__(THREADS, f32_waves(DQK, DV)) hstu_dq_f32(AttnArgs a) {
+  __shared__ __attribute__((aligned(1024))) float kbuf[FW * FB * DQK];
+  __shared__ __attribute__((aligned(1024))) float vbuf[FW * FB * DV];
+  __shared__ unsigned long long dwl[BIAS ? MAX_TS_BUCKETS : 1];  // the workgroup's sums of dS per bucket (fixed point)
+  const int H = a.num_heads, h = blockIdx.x % H;
   Item it;
-  if (!fetch_item(a.plan, slot, it)) return;
-  const int tid = threadIdx.x, r = tid >> 2, c = tid & 3;
-  const int64_t sq = (int64_t)H * DQK, sv = (int64_t)H * DV;
-  const bool on = r < it.nrows;
-  float kp[DQK / 4], vp[DV / 4], dkp[DQK / 4], dvp[DV / 4];
-  load_part<DQK>(kp, (const float*)a.k + ((int64_t)it.row0 + r) * sq + h * DQK, on, c);
-  load_part<DV>(vp, (const float*)a.v + ((int64_t)it.row0 + r) * sv + h * DV, on, c);
-#pragma unroll
-  for (int i = 0; i < DQK / 4; ++i) dkp[i] = 0.f;
-#pragma unroll
-  for (int i = 0; i < DV / 4; ++i) dvp[i] = 0.f;
-  const int kpos = it.pos0 + r;
-  const int t_own = own_timestamp(a, (int64_t)it.row0 + r, on);
-
-  for (int g = 0; g < it.nseg; ++g) {
-    int beg, end;
-    visible_range<1>(it, g, a.causal, beg, end);
-    for (int t0 = beg; t0 < end; t0 += ST) {
-      const int valid = end - t0 < ST ? end - t0 : ST;
-      __syncthreads();
-      stage<DQK>(qt, (const float*)a.q + ((int64_t)it.seg_row0[g] + t0) * sq + h * DQK, sq, valid, tid);
-      stage<DV>(gt, (const float*)a.d_o + ((int64_t)it.seg_row0[g] + t0) * sv + h * DV, sv, valid, tid);
-      __syncthreads();
-      for (int i = 0; i < valid; ++i) {
-        int bucket;
-        const float s = row_sum(dot_part<DQK>(kp, qt + i * DQK, c)) +
-                        pair_bias(a, t_own, (int64_t)it.seg_row0[g] + t0 + i, bucket);
-        const float dp = row_sum(dot_part<DV>(vp, gt + i * DV, c));
-        const float x = a.alpha * s;
-        const float sg = sigmoid_precise(x);
-        float p = x * sg;
-        float ds = dp * sg * (1.0f + x * (1.0f - sg));
-        const int qpos = it.seg_pos0[g] + t0 + i;
-        if (a.causal && kpos > qpos) { p = 0.f; ds = 0.f; }
-        axpy_part<DV>(dvp, p, gt + i * DV, c);
-        axpy_part<DQK>(dkp, ds, qt + i * DQK, c);
-      }
-    }
-  }
-  if (on) {
-    store_part<DQK>((float*)a.dk + ((int64_t)it.row0 + r) * sq + h * DQK, dkp, a.alpha * a.inv_n,
-                    a.accumulate, c);
-    store_part<DV>((float*)a.dv + ((int64_t)it.row0 + r) * sv + h * DV, dvp, a.inv_n, a.accumulate, c);
-  }
-}
-
-// ---------------------------------------------------------------------------------------------
-template <int DQK, int DV>
-__global__ void __launch_bounds__(THREADS) hstu_dq_f32(AttnArgs a) {
-  __shared__ __attribute__((aligned(16))) float kt[ST * DQK];
-  __shared__ __attribute__((aligned(16))) float vt[ST * DV];
-  __shared__ unsigned long long dwl[MAX_TS_BUCKETS];  // the workgroup's sums of dS per bucket (fixed point)
-  const int H = a.num_heads;
-  const int slot = blockIdx.x / H, h = blockIdx.x % H;
-  Item it;
-  if (!fetch_item(a.plan, slot, it)) return;
-  const int tid = threadIdx.x, r = tid >> 2, c = tid & 3;
-  const int64_t sq = (int64_t)H * DQK, sv = (int64_t)H * DV;
-  const bool on = r < it.nrows;
-  const bool want_dw = a.ts_rec && a.d_ts_acc;
-  if (want_dw)
-    for (int i = tid; i < a.nb; i += THREADS) dwl[i] = 0ull;  // (the loop's first barrier orders this)
-  float qp[DQK / 4], gp[DV / 4], dqp[DQK / 4];
-  load_part<DQK>(qp, (const float*)a.q + ((int64_t)it.row0 + r) * sq + h * DQK, on, c);
-  load_part<DV>(gp, (const float*)a.d_o + ((int64_t)it.row0 + r) * sv + h * DV, on, c);
-#pragma unroll
-  for (int i = 0; i < DQK / 4; ++i) dqp[i] = 0.f;
-  const int qpos = it.pos0 + r;
-  const int t_own = own_timestamp(a, (int64_t)it.row0 + r, on);
-
-  for (int g = 0; g < it.nseg; ++g) {
-    int beg, end;
-    visible_range<0>(it, g, a.causal, beg, end);
-    for (int t0 = beg; t0 < end; t0 += ST) {
-      const int valid = end - t0 < ST ? end - t0 : ST;
-      __syncthreads();
-      stage<DQK>(kt, (const float*)a.k + ((int64_t)it.seg_row0[g] + t0) * sq + h * DQK, sq, valid, tid);
-      stage<DV>(vt, (const float*)a.v + ((int64_t)it.seg_row0[g] + t0) * sv + h * DV, sv, valid, tid);
-      __syncthreads();
-      for (int j = 0; j < valid; ++j) {
-        int bucket;
-        const float s = row_sum(dot_part<DQK>(qp, kt + j * DQK, c)) +
-                        pair_bias(a, t_own, (int64_t)it.seg_row0[g] + t0 + j, bucket);
-        const float dp = row_sum(dot_part<DV>(gp, vt + j * DV, c));
-        const float x = a.alpha * s;
-        const float sg = sigmoid_precise(x);
-        float ds = dp * sg * (1.0f + x * (1.0f - sg));
-        const int kpos = it.seg_pos0[g] + t0 + j;
-        if (a.causal && kpos > qpos) ds = 0.f;
-        axpy_part<DQK>(dqp, ds, kt + j * DQK, c);
-        // one of the row's four lanes adds the pair's dS to its bucket (rows without an owner
-        // have dS = 0: their q and d_o parts are zero)
-        if (want_dw && c == 0 && ds != 0.f) atomicAdd(dwl + bucket, dw_to_fixed(ds));
-      }
-    }
-  }
-  if (want_dw) {
+  if (!fetch_item(a.plan, blockIdx.x / H, it)) return;
+  const Lane l;
+  if constexpr (BIAS) {
+    for (int i = l.tid; i < a.nb; i += THREADS) dwl[i] = 0ull;
     __syncthreads();
-    for (int i = tid; i < a.nb; i += THREADS)
-      if (dwl[i] != 0ull) atomicAdd(a.d_ts_acc + i, dw_from_fixed(dwl[i]));
   }
-  if (on)
-    store_part<DQK>((float*)a.dq + ((int64_t)it.row0 + r) * sq + h * DQK, dqp, a.alpha * a.inv_n,
-                    a.accumulate, c);
+  const int64_t sq = (int64_t)H * DQK, sv = (int64_t)H * DV;
+  const float* kg = (const float*)a.k + h * DQK;
+  const float* vg = (const float*)a.v + h * DV;
+  float* kb = kbuf + l.wave * (FB * DQK);
+  float* vb = vbuf + l.wave * (FB * DV);
+  f4 q[DQK / 8], g[DV / 8];
+  load_rows<DQK>(q, (const float*)a.q + (int64_t)it.row0 * sq + h * DQK, (int)sq * 4, l.n, it.nrows, l.hh);
+  load_rows<DV>(g, (const float*)a.d_o + (int64_t)it.row0 * sv + h * DV, (int)sv * 4, l.n, it.nrows, l.hh);
+  const Blocks bl = make_blocks<0>(it, a.causal);
+  const int t_own = BIAS && l.n < it.nrows ? a.ts_rec_own[(int64_t)it.row0 + l.n].ts : 0;
+  auto copy_k = [&](const BlockRef& b) { block_copy<DQK>(kb, kg + (int64_t)b.row * sq, (int)sq * 4, b.valid, l.lane); };
+  auto copy_v = [&](const BlockRef& b) { block_copy<DV>(vb, vg + (int64_t)b.row * sv, (int)sv * 4, b.valid, l.lane); };
+  f32x16 dq[DQK / 32];
+#pragma unroll
+  for (int c = 0; c < DQK / 32; ++c) clear(dq[c]);
+  int i = bl.first + l.wave;
+  BlockRef b = block_ref(it, bl, i);
+  copy_v(b);
+  copy_k(b);
+  for (; i < bl.end; i += FW) {
+    const BlockRef nx = block_ref(it, bl, i + FW);
+    f32x16 s, dp;
+    clear(s); clear(dp);
+    vm_wait<block_loads<DQK>()>();
+    scores<DV>(dp, vb, g, l.n, l.hh);
+    lds_reads_done();
+    copy_v(nx);
+    vm_wait<block_loads<DV>()>();
+    scores<DQK>(s, kb, q, l.n, l.hh);
+    int bk[16];
+    if constexpr (BIAS) add_bias(s, bk, a, t_own, b, l.hh);
+    float ds[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const float x = a.alpha * s[r];
+      const float sg = sigmoid_precise(x);
+      ds[r] = dp[r] * sg * (1.0f + x * (1.0f - sg));
+    }
+    if (a.causal && b.pos + FB - 1 > it.pos0) {
+      const VisBefore vis{it.pos0 + l.n - b.pos, l.hh};
+#pragma unroll
+      for (int r = 0; r < 16; ++r) ds[r] = vis(r) ? ds[r] : 0.f;
+    }
+    if constexpr (BIAS)  // (pairs beyond the owner or streamed rows have dS = 0)
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        if (ds[r] != 0.f) atomicAdd(dwl + bk[r], dw_to_fixed(ds[r]));
+    contract<DQK>(dq, kb, ds, l.n, l.hh);
+    lds_reads_done();
+    copy_k(nx);
+    b = nx;
+  }
+  vm_wait<0>();
+  sum_and_store<DQK>(kbuf, dq, (float*)a.dq, (int64_t)it.row0 * sq + h * DQK, sq, it.nrows, a.alpha * a.inv_n,
+                     a.accumulate, l.wave, l.lane);
+  if constexpr (BIAS)  // (ordered by the barrier in sum_and_store)
+    for (int j = l.tid; j < a.nb; j += THREADS)
+      if (dwl[j] != 0ull) atomicAdd(a.d_ts_acc + j, dw_from_fixed(dwl[j]));
 }
 
 }  // namespace
 
 int tile_rows_f32(int /*pass*/) { return TILE; }
 
+#define HSTU_LAUNCH_F32(KERNEL, A, B)                                                      \
+  do {                                                                                     \
+    if (a.ts_rec) hipLaunchKernelGGL((KERNEL<A, B, true>), grid, block, 0, stream, a);     \
+    else hipLaunchKernelGGL((KERNEL<A, B, false>), grid, block, 0, stream, a);             \
+  } while (0)
 #define HSTU_DISPATCH_F32(KERNEL)                                                          \
   do {                                                                                     \
     const dim3 grid((unsigned)((int64_t)a.max_items * a.num_heads)), block(THREADS);       \
-    if (d_qk == 128 && d_v == 128) hipLaunchKernelGGL((KERNEL<128, 128>), grid, block, 0, stream, a); \
-    else if (d_qk == 64 && d_v == 64) hipLaunchKernelGGL((KERNEL<64, 64>), grid, block, 0, stream, a); \
-    else if (d_qk == 32 && d_v == 32) hipLaunchKernelGGL((KERNEL<32, 32>), grid, block, 0, stream, a); \
-    else if (d_qk == 128 && d_v == 64) hipLaunchKernelGGL((KERNEL<128, 64>), grid, block, 0, stream, a); \
-    else if (d_qk == 64 && d_v == 128) hipLaunchKernelGGL((KERNEL<64, 128>), grid, block, 0, stream, a); \
-    else if (d_qk == 128 && d_v == 32) hipLaunchKernelGGL((KERNEL<128, 32>), grid, block, 0, stream, a); \
-    else if (d_qk == 32 && d_v == 128) hipLaunchKernelGGL((KERNEL<32, 128>), grid, block, 0, stream, a); \
-    else if (d_qk == 64 && d_v == 32) hipLaunchKernelGGL((KERNEL<64, 32>), grid, block, 0, stream, a); \
-    else if (d_qk == 32 && d_v == 64) hipLaunchKernelGGL((KERNEL<32, 64>), grid, block, 0, stream, a); \
+    if (d_qk == 128 && d_v == 128) HSTU_LAUNCH_F32(KERNEL, 128, 128);                      \
+    else if (d_qk == 64 && d_v == 64) HSTU_LAUNCH_F32(KERNEL, 64, 64);                     \
+    else if (d_qk == 32 && d_v == 32) HSTU_LAUNCH_F32(KERNEL, 32, 32);                     \
+    else if (d_qk == 128 && d_v == 64) HSTU_LAUNCH_F32(KERNEL, 128, 64);                   \
+    else if (d_qk == 64 && d_v == 128) HSTU_LAUNCH_F32(KERNEL, 64, 128);                   \
+    else if (d_qk == 128 && d_v == 32) HSTU_LAUNCH_F32(KERNEL, 128, 32);                   \
+    else if (d_qk == 32 && d_v == 128) HSTU_LAUNCH_F32(KERNEL, 32, 128);                   \
+    else if (d_qk == 64 && d_v == 32) HSTU_LAUNCH_F32(KERNEL, 64, 32);                     \
+    else if (d_qk == 32 && d_v == 64) HSTU_LAUNCH_F32(KERNEL, 32, 64);                     \
     else return hipErrorInvalidValue;                                                      \
     return hipGetLastError();                                                              \
   } while (0)
@@ -287,6 +456,7 @@ hipError_t launch_dkdv_f32(const AttnArgs& a, int d_qk, int d_v, hipStream_t str
   HSTU_DISPATCH_F32(hstu_dkdv_f32);
 }
 hipError_t launch_dq_f32(const AttnArgs& a, int d_qk, int d_v, hipStream_t stream) {
+  if (a.ts_rec && !a.d_ts_acc) return hipErrorInvalidValue;
   HSTU_DISPATCH_F32(hstu_dq_f32);
 }
 
