@@ -87,10 +87,17 @@ bool fwd_transposed_v(const hstu_attn_params* p) {
 // 1.98 -> 1.35 ms (the per-sequence schedule build alone is 0.16 ms); 4096 of 32..256 rows 2.82 ->
 // 2.65 ms; 2048 of 200..400 rows 3.13 -> 3.06 ms; 1536 of 300..600 rows 3.94 -> 3.92 ms: beyond a mean
 // of ~300 rows the two are within noise of each other.
+// Not on batches so small that every per-sequence tile of every head has a workgroup slot of its
+// own (two per CU) at once: padding then costs nothing, and per-sequence tiles of at most 64
+// sequences need no schedule kernel (direct_item).
+constexpr int SELF_BATCH = 64;
 constexpr int PACKED_TILE = 128;
 constexpr int64_t PACKED_MEAN_LEN = 256;
 bool packed_tiles(const hstu_attn_params* p) {
   if (p->dtype != HSTU_BF16 || !short_sequences(p) || (p->flags & HSTU_FLAG_NO_PACK)) return false;
+  if (!(p->flags & HSTU_FLAG_PACK_SHORT) && p->batch <= SELF_BATCH &&
+      (p->total_rows / PACKED_TILE + p->batch) * p->num_heads <= 512)
+    return false;
   const int64_t limit = (p->flags & HSTU_FLAG_PACK_SHORT) ? 1024 : PACKED_MEAN_LEN;
   return p->total_rows / p->batch <= limit;
 }
@@ -132,6 +139,10 @@ struct BuiltPlan {
   bool large;         // short sequences, and even the heaviest item is a small share of one workgroup slot's work
   bool natural;       // the items are in their natural order (those of a sequence are neighbours)
   bool chunks;        // dK/dV workgroups walk over contiguous runs of the list
+  // How the kernels get their items: from a schedule sorted by plan_kernel, from one with a wave per
+  // item (launch_item_plans), or by working them out themselves.
+  enum { SORTED, DIRECT, SELF } form;
+  DirectPlan dp;
 };
 
 // Bound on the items of a schedule, taken with the smallest tile any kernel variant uses so that
@@ -288,6 +299,17 @@ int prepare_plan(const hstu_attn_params* p, int cp_size, const SideSpec& s, cons
   out->split = split;
   out->waves = pass_waves(p, s.pass, s.owner_rows);
   out->end = l.end;
+  out->dp = DirectPlan{off, a.batch, a.total_rows, a.cp, a.owner_rank, a.streamed_rank, a.side, a.tile, a.causal,
+                       a.owner_rows, a.streamed_rows, split, SPLIT_BLOCKS};
+  // Small batches in cost order.  Where every workgroup is resident at once, each works its
+  // own item out and no schedule is launched: 4 sequences of 1..64 rows fwd + bwd 39 -> 30 us, 32 of
+  // 1..1024 rows forward 39 -> 30 us.  Beyond that the 0.5 us per item, which nothing overlaps at one
+  // workgroup per CU, costs more than the launch (16 sequences of 512..4096 rows: dk/dv 254 -> 269 us).
+  out->form = BuiltPlan::SORTED;
+  if (p->batch <= DIRECT_BATCH && !out->natural && !large && !want_ttile) {
+    const int64_t resident = s.side == 1 && p->d_qk + p->d_v > 128 ? 256 : 512;
+    out->form = p->batch <= SELF_BATCH && split <= 1 && max_items * p->num_heads <= 2 * resident ? BuiltPlan::SELF : BuiltPlan::DIRECT;
+  }
   return HSTU_OK;
 }
 
@@ -327,6 +349,7 @@ int build_packed(const hstu_attn_params* p, const int32_t* off, char* ws, size_t
     bp.large = false;  // (the packed dK/dV kernel walks whatever the size)
     bp.natural = true;
     bp.chunks = false;
+    bp.form = BuiltPlan::SORTED;
     bp.end = at;
   }
   out->row_seq = a.row_seq;
@@ -351,23 +374,43 @@ int make_tcopy(const hstu_attn_params* p, const SideSpec& s, const BuiltPlan& bp
   return HSTU_OK;
 }
 
-int launch_built(const PlanArgs* args, int count, hipStream_t stream) {
-  TimedLaunch timed(3, stream);
-  return launch_plans(args, count, stream) == hipSuccess ? HSTU_OK : HSTU_ERR_HIP;
+// Builds those of up to three prepared schedules that the kernels will read, in one launch.
+int launch_built(const PlanArgs* args, const BuiltPlan* const* plans, int count, hipStream_t stream) {
+  PlanArgs need[3];
+  ItemPlans items;
+  int n = 0, m = 0;
+  for (int i = 0; i < count; ++i) {
+    if (plans[i]->form == BuiltPlan::SORTED) need[n++] = args[i];
+    if (plans[i]->form == BuiltPlan::DIRECT) {
+      items.p[m++] = ItemPlan{plans[i]->dp, args[i].items, args[i].header, args[i].red, args[i].max_items};
+    }
+  }
+  if (n > 0) {
+    TimedLaunch timed(3, stream);
+    if (launch_plans(need, n, stream) != hipSuccess) return HSTU_ERR_HIP;
+  }
+  if (m > 0) {
+    TimedLaunch timed(3, stream);
+    if (launch_item_plans(items, m, stream) != hipSuccess) return HSTU_ERR_HIP;
+  }
+  return HSTU_OK;
 }
 
-// One schedule: prepare and launch.
+// One schedule: prepare and launch.  `dump`: build it whether or not the kernels would read it.
 int build_plan(const hstu_attn_params* p, int cp_size, const SideSpec& s, const int32_t* off,
-               char* ws, size_t ws_bytes, size_t base, hipStream_t stream, BuiltPlan* out) {
+               char* ws, size_t ws_bytes, size_t base, hipStream_t stream, BuiltPlan* out, bool dump = false) {
   PlanArgs args;
   const int rc = prepare_plan(p, cp_size, s, off, ws, ws_bytes, base, &args, out);
   if (rc != HSTU_OK) return rc;
-  return launch_built(&args, 1, stream);
+  if (dump) out->form = BuiltPlan::SORTED;
+  return launch_built(&args, &out, 1, stream);
 }
 
 AttnArgs base_args(const hstu_attn_params* p, const BuiltPlan& bp, int accumulate) {
   AttnArgs a = {};
   a.plan = bp.plan;
+  a.plan.direct = bp.form == BuiltPlan::DIRECT;
+  if (bp.form == BuiltPlan::SELF) a.self = bp.dp;
   a.num_heads = p->num_heads;
   a.causal = p->causal ? 1 : 0;
   a.accumulate = accumulate;
@@ -720,7 +763,8 @@ static int bwd_impl(const hstu_attn_params* params, const hstu_ts_bias* bias, co
   rc = prepare_plan(params, 1, full_side(params, 0, PASS_DQ), seq_offsets, (char*)workspace,
                     workspace_bytes, pk.end, &pa[1], &pq);
   if (rc != HSTU_OK) return rc;
-  rc = launch_built(pa, 2, stream);
+  const BuiltPlan* built[2] = {&pk, &pq};
+  rc = launch_built(pa, built, 2, stream);
   if (rc != HSTU_OK) return rc;
   AttnArgs a = base_args(params, pk, 0);
   a.q = q; a.k = k; a.v = v; a.d_o = d_o; a.dk = dk; a.dv = dv;
@@ -794,6 +838,7 @@ static int cp_partial_impl(const hstu_attn_params* params, const hstu_cp_desc* c
              do_q = backward && cp->q_rows > 0;
   PlanArgs pa[3];
   BuiltPlan pf, pk, pq;
+  const BuiltPlan* built[3];
   int np = 0;
   size_t base = 0, tbase = 0, qbase = 0;
   // with bias: the records of the query side's rows, then of the key side's, come first
@@ -824,7 +869,8 @@ static int cp_partial_impl(const hstu_attn_params* params, const hstu_cp_desc* c
   };
   const SideSpec sf = cp_side(params, cp, 0, PASS_FWD), sq = cp_side(params, cp, 0, PASS_DQ);
   if (do_f) {
-    rc = prepare_plan(params, cp->cp_size, sf, seq_offsets_global, ws, workspace_bytes, base, &pa[np++], &pf);
+    rc = prepare_plan(params, cp->cp_size, sf, seq_offsets_global, ws, workspace_bytes, base, &pa[np], &pf);
+    built[np++] = &pf;
     if (rc != HSTU_OK) return rc;
     tbase = pf.end;  // the transposed copy of V and the partial results follow the schedule
     base = align_up(pf.end, 256) + tcopy_bytes(params, sf, params->d_v);
@@ -832,12 +878,14 @@ static int cp_partial_impl(const hstu_attn_params* params, const hstu_cp_desc* c
   }
   if (do_k) {
     rc = prepare_plan(params, cp->cp_size, cp_side(params, cp, 1, PASS_DKDV), seq_offsets_global, ws,
-                      workspace_bytes, base, &pa[np++], &pk);
+                      workspace_bytes, base, &pa[np], &pk);
+    built[np++] = &pk;
     if (rc != HSTU_OK) return rc;
     base = pk.end;
   }
   if (do_q) {
-    rc = prepare_plan(params, cp->cp_size, sq, seq_offsets_global, ws, workspace_bytes, base, &pa[np++], &pq);
+    rc = prepare_plan(params, cp->cp_size, sq, seq_offsets_global, ws, workspace_bytes, base, &pa[np], &pq);
+    built[np++] = &pq;
     if (rc != HSTU_OK) return rc;
     qbase = pq.end;
   }
@@ -847,7 +895,7 @@ static int cp_partial_impl(const hstu_attn_params* params, const hstu_cp_desc* c
     return finish_dw(params, ws, bias->d_ts_weights, bias->num_buckets, acc_q, stream);
   };
   if (np == 0) return finish();
-  rc = launch_built(pa, np, stream);
+  rc = launch_built(pa, built, np, stream);
   if (rc != HSTU_OK) return rc;
   if (do_f) {
     AttnArgs a = base_args(params, pf, acc_q);
@@ -1146,7 +1194,7 @@ int hstu_debug_dump_schedule(const hstu_attn_params* params, const hstu_cp_desc*
   const SideSpec s = cp ? cp_side(params, cp, side, pass) : full_side(params, side, pass);
   BuiltPlan bp;
   rc = build_plan(params, cp ? cp->cp_size : 1, s, seq_offsets, (char*)workspace, workspace_bytes,
-                  0, stream, &bp);
+                  0, stream, &bp, true);
   if (rc != HSTU_OK) return rc;
   int32_t n = 0;
   if (hipMemcpyAsync(&n, bp.plan.header, sizeof(int32_t), hipMemcpyDeviceToHost, stream) != hipSuccess)

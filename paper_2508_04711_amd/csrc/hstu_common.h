@@ -36,6 +36,8 @@ struct Plan {
   const Item* items;
   const int32_t* ttile;   // per 64-row streamed tile: first row, valid rows
   int32_t max_stiles;     // host bound on the streamed tiles; transposed copies have 64x this many columns
+  int32_t direct;         // the items are in schedule order, every slot of the grid holds one (or one
+                          // without rows): no count and no order to look up
 };
 
 // Byte offsets of one schedule's arrays inside the workspace.
@@ -69,6 +71,302 @@ inline int64_t max_items_bound(int64_t rows, int64_t batch, int segs, int tile) 
   return rows / tile + (int64_t)segs * batch + 1;
 }
 
+// The (up to two) segments one side of one sequence consists of.
+struct Side {
+  int nseg;
+  int len[2];
+  int pos[2];
+  int rows;  // len[0] + len[1]
+};
+
+__device__ __forceinline__ Side make_side(int L, int cp, int rank) {
+  Side s;
+  if (rank < 0) {
+    s.nseg = 1; s.len[0] = L; s.pos[0] = 0; s.len[1] = 0; s.pos[1] = 0;
+  } else {
+    // mini-chunk m covers positions [m*c, min((m+1)*c, L)), c = ceil(L / (2*cp))
+    const uint32_t n = 2u * (uint32_t)cp;
+    const long long c = (long long)((uint32_t)L / n + ((uint32_t)L % n ? 1u : 0u));
+    const int m0 = rank, m1 = 2 * cp - 1 - rank;
+    long long b0 = m0 * c, e0 = (m0 + 1) * c, b1 = m1 * c, e1 = (m1 + 1) * c;
+    b0 = b0 < L ? b0 : L; e0 = e0 < L ? e0 : L; b1 = b1 < L ? b1 : L; e1 = e1 < L ? e1 : L;
+    s.nseg = 2;
+    s.len[0] = (int)(e0 - b0); s.pos[0] = (int)b0;
+    s.len[1] = (int)(e1 - b1); s.pos[1] = (int)b1;
+    if (s.len[1] > 0 && s.pos[1] == s.pos[0] + s.len[0]) {  // adjacent chunks: one segment
+      s.len[0] += s.len[1]; s.len[1] = 0; s.nseg = 1;
+    }
+    if (s.len[1] == 0) s.nseg = 1;
+  }
+  s.rows = s.len[0] + s.len[1];
+  return s;
+}
+
+__device__ __forceinline__ int clampi(long long x, int lo, int hi) {
+  return x < lo ? lo : (x > hi ? hi : (int)x);
+}
+
+// Sanitised [start, end) of sequence b in the global layout: whatever the device array
+// holds, 0 <= start <= end <= total_rows.
+__device__ __forceinline__ void seq_range(const int32_t* off, int b, int total_rows, int& s, int& e) {
+  s = clampi(off[b], 0, total_rows);
+  e = clampi(off[b + 1], s, total_rows);
+}
+
+__device__ inline int tiles_of(const Side& s, int tile) {
+  return (s.len[0] + tile - 1) / tile + (s.len[1] + tile - 1) / tile;
+}
+
+// The schedule item of owner tile t of segment u (0, 1) of one sequence: its rows, and the visible
+// streamed segments, compacted to the front.  owner_base / streamed_base: first row of the sequence
+// in the two sides' layouts; tcol0: first column in the transposed copy of the streamed side; pvis:
+// visible rows of the (compacted) segments.
+__device__ __forceinline__ Item describe_item(const Side& so, const Side& ss, int u, int t, int owner_base,
+                                              int streamed_base, int tcol0, int tile, int causal, int side,
+                                              int owner_rows, int streamed_rows, int (&pvis)[2]) {
+  Item it;
+  it.row0 = owner_base + (u ? so.len[0] : 0) + t * tile;
+  it.nrows = (u ? so.len[1] : so.len[0]) - t * tile;
+  if (it.nrows > tile) it.nrows = tile;
+  it.pos0 = (u ? so.pos[1] : so.pos[0]) + t * tile;
+  // never beyond the rows the caller declared for its buffers
+  it.nrows = clampi((long long)owner_rows - it.row0, 0, it.nrows);
+  // The visible streamed segments, compacted to the front.  Written without run-time array
+  // indices so that the item stays in registers (indexed, it would live in scratch memory).
+  int vrow[2] = {0, 0}, vlen[2] = {0, 0}, vpos[2] = {0, 0}, vcol[2] = {0, 0}, vcost[2] = {0, 0};
+  int vvis[2] = {0, 0};
+  bool von[2] = {false, false};
+  int srow = streamed_base;
+#pragma unroll
+  for (int g = 0; g < 2; ++g) {
+    if (g < ss.nseg) {
+      const int len = clampi((long long)streamed_rows - srow, 0, ss.len[g]);
+      int vis;  // streamed rows that at least one owner row sees
+      if (!causal) {
+        vis = len;
+      } else if (side == 0) {  // keys at positions <= last query position
+        vis = clampi((long long)it.pos0 + it.nrows - ss.pos[g], 0, len);
+      } else {                   // queries at positions >= first key position
+        vis = len - clampi((long long)it.pos0 - ss.pos[g], 0, len);
+      }
+      von[g] = it.nrows > 0 && vis > 0;
+      vrow[g] = srow; vlen[g] = len; vpos[g] = ss.pos[g];
+      vcol[g] = tcol0 + (g ? (ss.len[0] + 63) / 64 * 64 : 0);
+      vcost[g] = (vis + 31) >> 5;
+      vvis[g] = vis;
+      srow += ss.len[g];
+    }
+  }
+  const bool first1 = !von[0] && von[1];  // only the second segment is visible: it moves to slot 0
+  it.nseg = (von[0] ? 1 : 0) + (von[1] ? 1 : 0);
+  it.cost = (von[0] ? vcost[0] : 0) + (von[1] ? vcost[1] : 0);
+  it.seg_row0[0] = von[0] ? vrow[0] : (first1 ? vrow[1] : 0);
+  it.seg_len[0] = von[0] ? vlen[0] : (first1 ? vlen[1] : 0);
+  it.seg_pos0[0] = von[0] ? vpos[0] : (first1 ? vpos[1] : 0);
+  it.seg_tcol0[0] = von[0] ? vcol[0] : (first1 ? vcol[1] : 0);
+  const bool second = von[0] && von[1];
+  it.seg_row0[1] = second ? vrow[1] : 0;
+  it.seg_len[1] = second ? vlen[1] : 0;
+  it.seg_pos0[1] = second ? vpos[1] : 0;
+  it.seg_tcol0[1] = second ? vcol[1] : 0;
+  it.part = 0;
+  it.pad[0] = it.pad[1] = 0;
+  pvis[0] = von[0] ? vvis[0] : (first1 ? vvis[1] : 0);
+  pvis[1] = second ? vvis[1] : 0;
+  return it;
+}
+
+// Inclusive prefix sums over the wave's lanes on the vector pipe (no LDS round trips); lane 63 ends
+// with the total.
+__device__ __forceinline__ int wave_scan(int x) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);  // row_shr:1, 2, 4, 8
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);  // row_bcast:15, :31
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);
+  return x;
+}
+__device__ __forceinline__ int wave_total(int x) { return __builtin_amdgcn_readlane(wave_scan(x), 63); }
+
+// Part k of ns of an item whose streamed segments have pvis visible rows: whole 64-row tiles of them;
+// `part` is the item's Item::part.
+constexpr int STILE = 64;  // rows per tile of the streamed side (what the kernels stage in LDS)
+__device__ __forceinline__ Item cut_item(const Item& it, const int (&pvis)[2], int k, int ns, int part) {
+  const int nt0 = (pvis[0] + STILE - 1) / STILE, nt = nt0 + (pvis[1] + STILE - 1) / STILE;
+  const int lo = (int)((long long)k * nt / ns), hi = (int)((long long)(k + 1) * nt / ns);
+  Item sub = it;
+  int srow2[2], slen2[2], spos2[2], scol2[2], scost = 0, n2 = 0;
+  bool son[2];
+#pragma unroll
+  for (int c = 0; c < 2; ++c) {
+    const int base = c ? nt0 : 0, ntc = c ? nt - nt0 : nt0;
+    const int l = clampi(lo - base, 0, ntc), h = clampi(hi - base, 0, ntc);
+    son[c] = h > l;
+    const int skip = l * STILE;
+    int len = it.seg_len[c] - skip;
+    if (len > (h - l) * STILE) len = (h - l) * STILE;
+    int vis = pvis[c] - skip;
+    if (vis > (h - l) * STILE) vis = (h - l) * STILE;
+    srow2[c] = it.seg_row0[c] + skip; slen2[c] = len; spos2[c] = it.seg_pos0[c] + skip;
+    scol2[c] = it.seg_tcol0[c] + skip;
+    if (son[c]) { scost += (vis + 31) >> 5; ++n2; }
+  }
+  const bool f1 = !son[0] && son[1], both = son[0] && son[1];
+  sub.nseg = n2; sub.cost = scost; sub.part = part;
+  sub.seg_row0[0] = son[0] ? srow2[0] : (f1 ? srow2[1] : 0);
+  sub.seg_len[0] = son[0] ? slen2[0] : (f1 ? slen2[1] : 0);
+  sub.seg_pos0[0] = son[0] ? spos2[0] : (f1 ? spos2[1] : 0);
+  sub.seg_tcol0[0] = son[0] ? scol2[0] : (f1 ? scol2[1] : 0);
+  sub.seg_row0[1] = both ? srow2[1] : 0;
+  sub.seg_len[1] = both ? slen2[1] : 0;
+  sub.seg_pos0[1] = both ? spos2[1] : 0;
+  sub.seg_tcol0[1] = both ? scol2[1] : 0;
+  return sub;
+}
+
+// What it takes to work an item out from the offsets (the fields are those of PlanArgs).
+struct DirectPlan {
+  const int32_t* off;
+  int32_t batch, total_rows, cp, owner_rank, streamed_rank, side, tile, causal, owner_rows, streamed_rows;
+  int32_t split_max, split_blocks;
+};
+// Where in the schedule an item is: its owner tile (counted in schedule order), which part of how many
+// of that tile it is, and how many owner tiles of the schedule are cut.
+struct DirectSlot { int tile, part, parts, cut_tiles; };
+
+// Item `slot` of a schedule, worked out by one wave from the offsets: batches of at most 64 * K
+// sequences, K per lane.  A slot beyond the last item gets no rows.
+// The order is heaviest first, with a tile's cost taken in whole tiles of what it sees ("level").
+// Per owner segment (one per sequence, two in a rank's layout) the levels either are consecutive -
+// the diagonal runs through what the segment sees: each query tile sees one tile of keys more than
+// the one before, each key tile one tile of queries less - or all the same (no mask, or another
+// rank's mini-chunks, which lie wholly before or after).  (Keys of the whole batch against one rank's
+// queries are ordered by their distance from the sequence's end, which has the same order.)  So the
+// number of tiles at or above a level is one clamp per lane and a sum over lanes; a bisection over
+// levels finds the item's, a ballot the sequence.  About 0.5 us for K = 1.
+// Cut tiles: a tile of level w has parts(w) = clamp(w * tile / 32 / split_blocks, 1, split_max) items,
+// neighbours in the order, so the items at or above a level are sums of the same counts.
+template <int K>
+__device__ __forceinline__ DirectSlot direct_item(const DirectPlan& d, int slot, Item& it) {
+  const int lane = threadIdx.x & 63;
+  int s[K], e[K], n[K][2], top[K][2], rows[K];  // per owner segment: tiles, highest level
+  bool ramp[K][2];                              // consecutive levels
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    s[k] = e[k] = n[k][0] = n[k][1] = top[k][0] = top[k][1] = rows[k] = 0;
+    ramp[k][0] = ramp[k][1] = false;
+    if (k * 64 < d.batch) {
+      if (k * 64 + lane < d.batch) seq_range(d.off, k * 64 + lane, d.total_rows, s[k], e[k]);
+      const int len = e[k] - s[k];
+      const Side so = make_side(len, d.cp, d.owner_rank);
+      Side ss = make_side(len, d.cp, d.streamed_rank);
+      if (d.side == 1 && d.owner_rank < 0) ss = make_side(len, 1, -1);  // (see above)
+      rows[k] = so.rows;
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        n[k][u] = (so.len[u] + d.tile - 1) / d.tile;
+        const int p0 = so.pos[u], p1 = p0 + so.len[u];
+        int seen = 0;  // streamed rows every tile of the segment sees
+        bool across = false;
+#pragma unroll
+        for (int g = 0; g < 2; ++g) {
+          const int b = ss.pos[g], f = b + ss.len[g];
+          if (!d.causal) { seen += ss.len[g]; continue; }
+          if (d.side == 0) seen += p0 < b ? 0 : (p0 < f ? p0 : f) - b;
+          else seen += p1 < b ? f - b : (p1 < f ? f - p1 : 0);
+          across = across || (b < p1 && p0 < f);
+        }
+        ramp[k][u] = across;
+        const int more = across ? (d.side == 0 ? n[k][u] * d.tile : so.len[u]) : 0;
+        top[k][u] = d.side == 0 && across ? seen / d.tile + n[k][u] : (seen + more + d.tile - 1) / d.tile;
+        top[k][u] = top[k][u] < 1 ? 1 : top[k][u];
+      }
+    }
+  }
+  auto at_least = [&](int k, int u, int v) {  // tiles of the lane's segment (k, u) at level v or above
+    const int x = top[k][u] - v + 1;
+    return ramp[k][u] ? (x < 0 ? 0 : (x < n[k][u] ? x : n[k][u])) : (x > 0 ? n[k][u] : 0);
+  };
+  auto lane_count = [&](int v) {
+    int c = 0;
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+      if (k * 64 < d.batch) c += at_least(k, 0, v) + at_least(k, 1, v);
+    return c;
+  };
+  // the lowest level of a tile cut into j parts
+  auto cut_level = [&](int j) { return (j * d.split_blocks * 32 + d.tile - 1) / d.tile; };
+  auto count = [&](int v) {  // items at level v or above
+    int c = lane_count(v);
+    for (int j = 2; j <= d.split_max; ++j) {
+      const int w = cut_level(j);
+      c += lane_count(v > w ? v : w);
+    }
+    return wave_total(c);
+  };
+  DirectSlot r = {0, 0, 1, 0};
+  if (d.split_max > 1 && slot == 0) r.cut_tiles = wave_total(lane_count(cut_level(2)));
+  it = Item{};
+  if (slot >= count(1)) return r;
+  int lo = 1, hi = (d.total_rows + d.tile - 1) / d.tile + 3;  // count(lo) > slot >= count(hi)
+  while (hi - lo > 1) {
+    const int mid = (lo + hi) >> 1;
+    if (count(mid) > slot) lo = mid; else hi = mid;
+  }
+  int rem = slot - count(lo + 1);
+  if (d.split_max > 1) {
+    while (r.parts < d.split_max && lo >= cut_level(r.parts + 1)) ++r.parts;
+    r.part = rem % r.parts;
+    rem /= r.parts;
+    r.tile = wave_total(lane_count(lo + 1)) + rem;
+  }
+  int b = 0, u = 0, t = 0, sb = 0, eb = 0;
+  bool found = false;
+#pragma unroll
+  for (int k = 0; k < K; ++k)
+#pragma unroll
+    for (int g = 0; g < 2; ++g)
+      if (!found && k * 64 < d.batch) {
+        const int mine = at_least(k, g, lo) - at_least(k, g, lo + 1);
+        const int inc = wave_scan(mine), tot = __builtin_amdgcn_readlane(inc, 63);
+        if (rem < tot) {
+          const int l = (int)__builtin_ctzll(__ballot(rem >= inc - mine && rem < inc));
+          b = k * 64 + l;
+          u = g;
+          sb = __builtin_amdgcn_readlane(s[k], l);
+          eb = __builtin_amdgcn_readlane(e[k], l);
+          const int below = __builtin_amdgcn_readlane(top[k][g], l) - lo;  // tiles between the item and the heaviest
+          t = !__builtin_amdgcn_readlane((int)ramp[k][g], l)
+                  ? rem - __builtin_amdgcn_readlane(inc - mine, l)
+                  : (d.side == 0 ? __builtin_amdgcn_readlane(n[k][g], l) - 1 - below : below);
+          found = true;
+        } else {
+          rem -= tot;
+        }
+      }
+  const int len = eb - sb;
+  int ob = sb, stb = sb;  // first row of the sequence in the two sides' layouts
+  if (d.owner_rank >= 0) {
+    int c = 0;
+#pragma unroll
+    for (int k = 0; k < K; ++k) c += k * 64 + lane < b ? rows[k] : 0;
+    ob = wave_total(c);
+  }
+  if (d.streamed_rank >= 0) {
+    int c = 0;
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+      if (k * 64 < d.batch) c += k * 64 + lane < b ? make_side(e[k] - s[k], d.cp, d.streamed_rank).rows : 0;
+    stb = wave_total(c);
+  }
+  int pvis[2];
+  it = describe_item(make_side(len, d.cp, d.owner_rank), make_side(len, d.cp, d.streamed_rank), u, t, ob, stb, 0,
+                     d.tile, d.causal, d.side, d.owner_rows, d.streamed_rows, pvis);
+  if (r.parts > 1) it = cut_item(it, pvis, r.part, r.parts, slot + 1);
+  return r;
+}
+
 struct PlanArgs {
   const int32_t* off;     // device, batch + 1
   int32_t batch;
@@ -98,6 +396,20 @@ struct PlanArgs {
   int32_t* order;
   Item* items;
 };
+
+// The schedules of batches of at most DIRECT_BATCH sequences in cost order: one wave per item (see
+// direct_item), up to three schedules in one launch.  Every slot below max_items is written (no rows
+// beyond the last item) and the list is in schedule order: Plan::direct.
+constexpr int DIRECT_BATCH = 512;
+struct ItemPlan {
+  DirectPlan d;
+  Item* items;
+  int32_t* header;    // [2]: owner tiles that are cut (see Plan)
+  int32_t* red;
+  int32_t max_items;
+};
+struct ItemPlans { ItemPlan p[3]; };
+hipError_t launch_item_plans(const ItemPlans& a, int count, hipStream_t stream);
 
 // Builds up to three schedules in one launch (one workgroup each).
 hipError_t launch_plans(const PlanArgs* a, int count, hipStream_t stream);
@@ -189,6 +501,7 @@ struct AttnArgs {
   void* dk;
   void* dv;
   Plan plan;
+  DirectPlan self;  // off not null: every wave works its item out by itself (see direct_item), there is no schedule
   int32_t num_heads;
   int32_t causal;
   int32_t accumulate;

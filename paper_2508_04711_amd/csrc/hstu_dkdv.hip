@@ -365,7 +365,7 @@ __global__ void __launch_bounds__(NW * 64, (DQK + DV <= 128 ? 2 : 1)) hstu_dkdv_
   constexpr bool CAN_WALK = DQK + DV > 128;
   if (!CAN_WALK || (!PACKED && gridDim.x >= bound)) {
     const Unit un = unit_of(a, blockIdx.x);
-    if (!un.on || !fetch_item<PACKED>(a.plan, un.slot, it)) return;
+    if (!un.on || !get_item<PACKED>(a, un.slot, it)) return;
     dkdv_item<DQK, DV, NW, BIAS, PACKED>(a, it, un.h);
     return;
   }

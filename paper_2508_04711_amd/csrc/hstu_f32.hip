@@ -222,7 +222,7 @@ __global__ void __launch_bounds__(THREADS, f32_waves(DQK, DV)) hstu_fwd_f32(Attn
   __shared__ __attribute__((aligned(1024))) float vbuf[FW * FB * DV];
   const int H = a.num_heads, h = blockIdx.x % H;
   Item it;
-  if (!fetch_item(a.plan, blockIdx.x / H, it)) return;
+  if (!get_item(a, blockIdx.x / H, it)) return;
   const Lane l;
   const int64_t sq = (int64_t)H * DQK, sv = (int64_t)H * DV;
   const float* kg = (const float*)a.k + h * DQK;
@@ -283,7 +283,7 @@ __global__ void __launch_bounds__(THREADS, f32_waves(DQK, DV, BIAS)) hstu_dkdv_f
   __shared__ __attribute__((aligned(1024))) float gbuf[FW * FB * DV];
   const int H = a.num_heads, h = blockIdx.x % H;
   Item it;
-  if (!fetch_item(a.plan, blockIdx.x / H, it)) return;
+  if (!get_item(a, blockIdx.x / H, it)) return;
   const Lane l;
   const int64_t sq = (int64_t)H * DQK, sv = (int64_t)H * DV;
   const float* qg = (const float*)a.q + h * DQK;
@@ -358,7 +358,7 @@ __global__ void __launch_bounds__(THREADS, f32_waves(DQK, DV)) hstu_dq_f32(AttnA
   __shared__ unsigned long long dwl[BIAS ? MAX_TS_BUCKETS : 1];  // the workgroup's sums of dS per bucket (fixed point)
   const int H = a.num_heads, h = blockIdx.x % H;
   Item it;
-  if (!fetch_item(a.plan, blockIdx.x / H, it)) return;
+  if (!get_item(a, blockIdx.x / H, it)) return;
   const Lane l;
   if constexpr (BIAS) {
     for (int i = l.tid; i < a.nb; i += THREADS) dwl[i] = 0ull;

@@ -102,7 +102,7 @@ __global__ void __launch_bounds__(NW * 64, 2) hstu_fwd_bf16(AttnArgs a) {
   const Unit un = unit_of(a, blockIdx.x);
   const int slot = un.slot, h = un.h;
   Item it;
-  if (!un.on || !fetch_item<PACKED>(a.plan, slot, it)) return;
+  if (!un.on || !get_item<PACKED>(a, slot, it)) return;
 
   const int tid = threadIdx.x, lane = tid & 63, n = lane & 31, hh = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);

@@ -418,13 +418,9 @@ __device__ __forceinline__ bool decode_item(const RawItem& r, Item& it) {
   return it.nrows > 0;
 }
 
-// DIRECT: the items are in schedule order already (packed tiles), no indirection.
-template <bool DIRECT = false>
-__device__ __forceinline__ bool fetch_item(const Plan& plan, int slot, Item& it) {
-  if (slot >= plan.header[0]) return false;
-  const Item* src = plan.items + (DIRECT ? slot : plan.order[slot]);
-  // The item is the same for every lane: keep it in scalar registers so that everything derived
-  // from it (addresses, buffer resources, loop bounds) is uniform.
+// The item is the same for every lane: keep it in scalar registers so that everything derived from
+// it (addresses, buffer resources, loop bounds) is uniform.
+__device__ __forceinline__ bool uniform_item(const Item* src, Item& it) {
   it.row0 = __builtin_amdgcn_readfirstlane(src->row0);
   it.nrows = __builtin_amdgcn_readfirstlane(src->nrows);
   it.pos0 = __builtin_amdgcn_readfirstlane(src->pos0);
@@ -439,6 +435,26 @@ __device__ __forceinline__ bool fetch_item(const Plan& plan, int slot, Item& it)
   it.cost = 0;
   it.part = __builtin_amdgcn_readfirstlane(src->part);
   return it.nrows > 0;
+}
+
+// DIRECT: the items are in schedule order already (packed tiles), no indirection.
+template <bool DIRECT = false>
+__device__ __forceinline__ bool fetch_item(const Plan& plan, int slot, Item& it) {
+  if (!DIRECT && plan.direct) return uniform_item(plan.items + slot, it);
+  if (slot >= plan.header[0]) return false;
+  return uniform_item(plan.items + (DIRECT ? slot : plan.order[slot]), it);
+}
+
+// The item a workgroup works on, from the built schedule or worked out here.
+template <bool PACKED = false>
+__device__ __forceinline__ bool get_item(const AttnArgs& a, int slot, Item& it) {
+  if constexpr (!PACKED)
+    if (a.self.off) {
+      Item x = {};
+      direct_item<1>(a.self, slot, x);
+      return uniform_item(&x, it);
+    }
+  return fetch_item<PACKED>(a.plan, slot, it);
 }
 
 // =============================================================================================

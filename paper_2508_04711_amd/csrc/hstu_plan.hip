@@ -21,53 +21,6 @@ namespace {
 constexpr int PLAN_THREADS = 1024;
 constexpr int NBINS = 2048;
 
-// The (up to two) segments one side of one sequence consists of.
-struct Side {
-  int nseg;
-  int len[2];
-  int pos[2];
-  int rows;  // len[0] + len[1]
-};
-
-__device__ inline Side make_side(int L, int cp, int rank) {
-  Side s;
-  if (rank < 0) {
-    s.nseg = 1; s.len[0] = L; s.pos[0] = 0; s.len[1] = 0; s.pos[1] = 0;
-  } else {
-    // mini-chunk m covers positions [m*c, min((m+1)*c, L)), c = ceil(L / (2*cp))
-    const long long c = ((long long)L + 2 * cp - 1) / (2 * cp);
-    const int m0 = rank, m1 = 2 * cp - 1 - rank;
-    long long b0 = m0 * c, e0 = (m0 + 1) * c, b1 = m1 * c, e1 = (m1 + 1) * c;
-    b0 = b0 < L ? b0 : L; e0 = e0 < L ? e0 : L; b1 = b1 < L ? b1 : L; e1 = e1 < L ? e1 : L;
-    s.nseg = 2;
-    s.len[0] = (int)(e0 - b0); s.pos[0] = (int)b0;
-    s.len[1] = (int)(e1 - b1); s.pos[1] = (int)b1;
-    if (s.len[1] > 0 && s.pos[1] == s.pos[0] + s.len[0]) {  // adjacent chunks: one segment
-      s.len[0] += s.len[1]; s.len[1] = 0; s.nseg = 1;
-    }
-    if (s.len[1] == 0) s.nseg = 1;
-  }
-  s.rows = s.len[0] + s.len[1];
-  return s;
-}
-
-__device__ inline int clampi(long long x, int lo, int hi) {
-  return x < lo ? lo : (x > hi ? hi : (int)x);
-}
-
-// Sanitised [start, end) of sequence b in the global layout: whatever the device array
-// holds, 0 <= start <= end <= total_rows.
-__device__ inline void seq_range(const int32_t* off, int b, int total_rows, int& s, int& e) {
-  s = clampi(off[b], 0, total_rows);
-  e = clampi(off[b + 1], s, total_rows);
-}
-
-constexpr int STILE = 64;  // rows per tile of the streamed side (what the kernels stage in LDS)
-
-__device__ inline int tiles_of(const Side& s, int tile) {
-  return (s.len[0] + tile - 1) / tile + (s.len[1] + tile - 1) / tile;
-}
-
 // Inclusive scan of one value per thread across the block; returns the inclusive prefix and
 // leaves the block total in *total.  `buf` has at least PLAN_THREADS / 64 ints.  Shuffles
 // inside each wavefront, then one pass over the wavefront totals.
@@ -230,55 +183,8 @@ __device__ __forceinline__ void plan_body(const PlanArgs& a) {
     const int nt0 = (so.len[0] + a.tile - 1) / a.tile;
     const int u = t < nt0 ? 0 : 1;
     if (u) t -= nt0;
-    it.row0 = r_owner[b] + (u ? so.len[0] : 0) + t * a.tile;
-    it.nrows = so.len[u] - t * a.tile;
-    if (it.nrows > a.tile) it.nrows = a.tile;
-    it.pos0 = so.pos[u] + t * a.tile;
-    // never beyond the rows the caller declared for its buffers
-    it.nrows = clampi((long long)a.owner_rows - it.row0, 0, it.nrows);
-    // The visible streamed segments, compacted to the front.  Written without run-time array
-    // indices so that the item stays in registers (indexed, it would live in scratch memory).
-    int vrow[2] = {0, 0}, vlen[2] = {0, 0}, vpos[2] = {0, 0}, vcol[2] = {0, 0}, vcost[2] = {0, 0};
-    int vvis[2] = {0, 0};
-    bool von[2] = {false, false};
-    int srow = r_streamed[b];
-#pragma unroll
-    for (int g = 0; g < 2; ++g) {
-      if (g < ss.nseg) {
-        const int len = clampi((long long)a.streamed_rows - srow, 0, ss.len[g]);
-        int vis;  // streamed rows that at least one owner row sees
-        if (!a.causal) {
-          vis = len;
-        } else if (a.side == 0) {  // keys at positions <= last query position
-          vis = clampi((long long)it.pos0 + it.nrows - ss.pos[g], 0, len);
-        } else {                   // queries at positions >= first key position
-          vis = len - clampi((long long)it.pos0 - ss.pos[g], 0, len);
-        }
-        von[g] = it.nrows > 0 && vis > 0;
-        vrow[g] = srow; vlen[g] = len; vpos[g] = ss.pos[g];
-        vcol[g] = STILE * (r_stile[b] + (g ? (ss.len[0] + STILE - 1) / STILE : 0));
-        vcost[g] = (vis + 31) >> 5;
-        vvis[g] = vis;
-        srow += ss.len[g];
-      }
-    }
-    const bool first1 = !von[0] && von[1];  // only the second segment is visible: it moves to slot 0
-    it.nseg = (von[0] ? 1 : 0) + (von[1] ? 1 : 0);
-    it.cost = (von[0] ? vcost[0] : 0) + (von[1] ? vcost[1] : 0);
-    it.seg_row0[0] = von[0] ? vrow[0] : (first1 ? vrow[1] : 0);
-    it.seg_len[0] = von[0] ? vlen[0] : (first1 ? vlen[1] : 0);
-    it.seg_pos0[0] = von[0] ? vpos[0] : (first1 ? vpos[1] : 0);
-    it.seg_tcol0[0] = von[0] ? vcol[0] : (first1 ? vcol[1] : 0);
-    const bool second = von[0] && von[1];
-    it.seg_row0[1] = second ? vrow[1] : 0;
-    it.seg_len[1] = second ? vlen[1] : 0;
-    it.seg_pos0[1] = second ? vpos[1] : 0;
-    it.seg_tcol0[1] = second ? vcol[1] : 0;
-    it.part = 0;
-    it.pad[0] = it.pad[1] = 0;
-    // visible rows of the (compacted) segments, for cutting the tile into parts
-    pvis[0] = von[0] ? vvis[0] : (first1 ? vvis[1] : 0);
-    pvis[1] = second ? vvis[1] : 0;
+    it = describe_item(so, ss, u, t, r_owner[b], r_streamed[b],
+                       STILE * r_stile[b], a.tile, a.causal, a.side, a.owner_rows, a.streamed_rows, pvis);
     }
     if (a.split_max <= 1 && a.cost_shift >= 30) {  // natural order: nothing to sort
       if (active) { a.items[i] = it; a.order[i] = i; }
@@ -293,7 +199,7 @@ __device__ __forceinline__ void plan_body(const PlanArgs& a) {
     }
     // ---- heavy owner tiles are cut along their streamed rows into ns parts of whole 64-row
     // tiles; each part becomes an item of its own that writes an fp32 partial result
-    const int nt0 = (pvis[0] + STILE - 1) / STILE, nt = nt0 + (pvis[1] + STILE - 1) / STILE;
+    const int nt = (pvis[0] + STILE - 1) / STILE + (pvis[1] + STILE - 1) / STILE;
     int ns = active ? it.cost / a.split_blocks : 0;
     if (ns > a.split_max) ns = a.split_max;
     if (ns > nt) ns = nt;
@@ -310,35 +216,7 @@ __device__ __forceinline__ void plan_body(const PlanArgs& a) {
     for (int k = 0; k < a.split_max; ++k) {
       const bool on = k < ns;
       Item sub = it;
-      if (on && ns > 1) {
-        const int lo = (int)((long long)k * nt / ns), hi = (int)((long long)(k + 1) * nt / ns);
-        int srow2[2], slen2[2], spos2[2], scol2[2], scost = 0, n2 = 0;
-        bool son[2];
-#pragma unroll
-        for (int c = 0; c < 2; ++c) {
-          const int base = c ? nt0 : 0, ntc = c ? nt - nt0 : nt0;
-          const int l = clampi(lo - base, 0, ntc), h = clampi(hi - base, 0, ntc);
-          son[c] = h > l;
-          const int skip = l * STILE;
-          int len = it.seg_len[c] - skip;
-          if (len > (h - l) * STILE) len = (h - l) * STILE;
-          int vis = pvis[c] - skip;
-          if (vis > (h - l) * STILE) vis = (h - l) * STILE;
-          srow2[c] = it.seg_row0[c] + skip; slen2[c] = len; spos2[c] = it.seg_pos0[c] + skip;
-          scol2[c] = it.seg_tcol0[c] + skip;
-          if (son[c]) { scost += (vis + 31) >> 5; ++n2; }
-        }
-        const bool f1 = !son[0] && son[1], both = son[0] && son[1];
-        sub.nseg = n2; sub.cost = scost; sub.part = p0 + k + 1;
-        sub.seg_row0[0] = son[0] ? srow2[0] : (f1 ? srow2[1] : 0);
-        sub.seg_len[0] = son[0] ? slen2[0] : (f1 ? slen2[1] : 0);
-        sub.seg_pos0[0] = son[0] ? spos2[0] : (f1 ? spos2[1] : 0);
-        sub.seg_tcol0[0] = son[0] ? scol2[0] : (f1 ? scol2[1] : 0);
-        sub.seg_row0[1] = both ? srow2[1] : 0;
-        sub.seg_len[1] = both ? slen2[1] : 0;
-        sub.seg_pos0[1] = both ? spos2[1] : 0;
-        sub.seg_tcol0[1] = both ? scol2[1] : 0;
-      }
+      if (on && ns > 1) sub = cut_item(it, pvis, k, ns, p0 + k + 1);
       const bool emit = on && u0 + k < a.max_items;
       if (emit) a.items[u0 + k] = sub;
       bin = sub.cost >> a.cost_shift;
@@ -660,6 +538,43 @@ hipError_t launch_packed_plan(const PackedPlanArgs& a, hipStream_t stream) {
   if (a.batch < 1 || a.total_rows < 1 || a.tile < 64 || a.tile % 64 != 0) return hipErrorInvalidValue;
   hipLaunchKernelGGL(packed_plan_kernel, dim3((unsigned)((a.total_rows + 255) / 256)), dim3(256), 0,
                      stream, a);
+  return hipGetLastError();
+}
+
+namespace {
+
+// One wave per item: 3 to 4 us per call whatever the number of items, against 10 to 18 us of the
+// one-workgroup plan_kernel, whose serial chain of scans and sort passes this replaces on batches of
+// up to DIRECT_BATCH sequences.
+__global__ void __launch_bounds__(256) item_plan_kernel(ItemPlans a) {
+  const int slot = (int)(blockIdx.x * 4 + (threadIdx.x >> 6));
+  const ItemPlan& p = a.p[blockIdx.y];
+  if (slot >= p.max_items) return;
+  const DirectPlan& d = p.d;
+  Item it = {};
+  DirectSlot where = {};
+  if (d.batch <= 64) where = direct_item<1>(d, slot, it);
+  else where = direct_item<DIRECT_BATCH / 64>(d, slot, it);
+  if ((threadIdx.x & 63) == 0) {
+    p.items[slot] = it;
+    if (slot == 0) p.header[2] = where.cut_tiles;
+    if (where.parts > 1 && where.part == 0) {
+      int32_t* r = p.red + 4 * where.tile;
+      r[0] = it.row0; r[1] = it.nrows; r[2] = slot; r[3] = where.parts;
+    }
+  }
+}
+
+}  // namespace
+
+hipError_t launch_item_plans(const ItemPlans& a, int count, hipStream_t stream) {
+  if (count < 1 || count > 3) return hipErrorInvalidValue;
+  int most = 1;
+  for (int i = 0; i < count; ++i) {
+    if (a.p[i].d.batch > DIRECT_BATCH || a.p[i].max_items < 1) return hipErrorInvalidValue;
+    most = a.p[i].max_items > most ? a.p[i].max_items : most;
+  }
+  hipLaunchKernelGGL(item_plan_kernel, dim3((unsigned)((most + 3) / 4), (unsigned)count), dim3(256), 0, stream, a);
   return hipGetLastError();
 }
 
