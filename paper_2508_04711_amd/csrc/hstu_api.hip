@@ -350,6 +350,8 @@ int build_packed(const hstu_attn_params* p, const int32_t* off, char* ws, size_t
     bp.natural = true;
     bp.chunks = false;
     bp.form = BuiltPlan::SORTED;
+    bp.dp = DirectPlan{};
+    bp.dp.streamed_rank = -1;
     bp.end = at;
   }
   out->row_seq = a.row_seq;
@@ -421,6 +423,7 @@ AttnArgs base_args(const hstu_attn_params* p, const BuiltPlan& bp, int accumulat
   a.xcd_parts = bp.natural && p->dtype == HSTU_BF16 && p->num_heads < 8 && 8 % p->num_heads == 0
                     ? 8 / p->num_heads : 1;
   a.out_f32 = p->out_dtype == HSTU_F32 ? 1 : 0;
+  a.single_segment = bp.dp.streamed_rank < 0;
   a.dkdv_one_wave = (p->flags & HSTU_FLAG_DKDV_ONE_WAVE) ? 1 : 0;
   a.bias_per_pair = (p->flags & HSTU_FLAG_BIAS_PER_PAIR) ? 1 : 0;
   a.alpha = p->alpha;

@@ -535,6 +535,7 @@ struct AttnArgs {
   // Walking workgroups take contiguous runs of their XCD's units instead of every n-th unit
   // (natural order with a head count that divides 8).
   int32_t walk_chunks;
+  int32_t single_segment;  // every item has one streamed segment at most (the streamed side is the whole batch's)
   // dk/dv pass: keep to the kernel with one wave per 32 keys where the two-wave kernel would serve.
   int32_t dkdv_one_wave;
 };
@@ -580,6 +581,8 @@ hipError_t launch_dkdv_bf16(const AttnArgs& a, int d_qk, int d_v, hipStream_t st
 // The dk/dv pass with two waves per 32 keys (plain per-sequence schedules at d_qk = d_v = 128).
 bool dkdv_pair_supported(const AttnArgs& a, int d_qk, int d_v);
 hipError_t launch_dkdv_pair_bf16(const AttnArgs& a, int d_qk, int d_v, hipStream_t stream);
+bool dkdv_walk_supported(const AttnArgs& a, int d_qk, int d_v);
+hipError_t launch_dkdv_walk_bf16(const AttnArgs& a, int d_qk, int d_v, hipStream_t stream);
 hipError_t launch_dq_bf16(const AttnArgs& a, int d_qk, int d_v, hipStream_t stream);
 hipError_t launch_fwd_f32(const AttnArgs& a, int d_qk, int d_v, hipStream_t stream);
 hipError_t launch_dkdv_f32(const AttnArgs& a, int d_qk, int d_v, hipStream_t stream);

@@ -372,19 +372,8 @@ __global__ void __launch_bounds__(NW * 64, (DQK + DV <= 128 ? 2 : 1)) hstu_dkdv_
   if constexpr (CAN_WALK) {
   const int n = a.plan.header[0];
   const int units = unit_count(a, n);
-  // Every gridDim.x-th unit from blockIdx.x on - or, for a schedule in natural order (walk_chunks),
-  // one contiguous run of this XCD's units (unit = 8 * j + XCD, see unit_of): whole sequences, whose
-  // tiles then follow each other in time on one CU and find their streamed rows in the caches,
-  // where a stride would beat against the number of tiles per sequence.
   int u = blockIdx.x, stride = (int)gridDim.x, end = units;
-  if (a.walk_chunks && (gridDim.x & 7) == 0) {
-    const int x = u & 7, m = u >> 3, wgs = (int)(gridDim.x >> 3), per = (units + 7) >> 3;
-    const int c = (per + wgs - 1) / wgs;
-    const int64_t last = (int64_t)8 * (m + 1) * c;
-    u = 8 * m * c + x;
-    stride = 8;
-    end = last < units ? (int)last : units;
-  }
+  walk_share(a, u, stride, end);
   // The description of unit u, as loaded (all zeros, i.e. no rows, for a unit that is none).
   // (The items of packed tiles are in schedule order already: no indirection.)
   auto index_of = [&](const Unit& un) { return PACKED ? un.slot : a.plan.order[un.slot]; };
@@ -425,6 +414,7 @@ __global__ void __launch_bounds__(NW * 64, (DQK + DV <= 128 ? 2 : 1)) hstu_dkdv_
 
 hipError_t launch_dkdv_bf16(const AttnArgs& a, int d_qk, int d_v, hipStream_t stream) {
   if (a.waves != 4) return hipErrorInvalidValue;
+  if (dkdv_walk_supported(a, d_qk, d_v) && !a.dkdv_one_wave) return launch_dkdv_walk_bf16(a, d_qk, d_v, stream);
   if (dkdv_pair_supported(a, d_qk, d_v) && !a.dkdv_one_wave)
     return launch_dkdv_pair_bf16(a, d_qk, d_v, stream);
   if (a.ts_rec && (a.nb < 1 || a.nb > MAX_TS_BUCKETS || !a.ts_w || !a.ts_rec_own)) return hipErrorInvalidValue;

@@ -460,6 +460,320 @@ __global__ void __launch_bounds__(PW * 64) hstu_dkdv_pair_bf16(AttnArgs a) {
                           rec3, rec4, rec5, wtab);
 }
 
+// =============================================================================================
+// The same pair of roles for large batches of short sequences (natural order; per-sequence or packed
+// tiles): 256 workgroups, one per CU, each walking over a run of (item, head) units whose blocks of
+// query rows form one stream.  Step t is what it is above, but the block of the scores, the block of
+// the SiLU and the block of the contraction may belong to different items: at an item's step 0 role A
+// scores its first block with the new K rows while it does the SiLU of the previous item's last block
+// and contracts the one before, and so on; the previous item's dV is complete after step 1, its dK
+// after step 2.  So an item costs its blocks and nothing else: no fill and drain of the pipeline (three
+// steps of the nine an item has on 300..600-row sequences), no wait for its first rows.
+// Items have at least three blocks (blocks of no rows are added to shorter ones: zeros, which
+// contribute nothing), so that at most two items are in the pipeline.  After the last unit comes an
+// item of no rows whose three steps drain it.
+// A's K rows are loaded at the end of the previous item's last step, B's V rows at the end of step 0,
+// where the registers become free; what is exposed is an L2 hit's latency, because role A touches
+// the lines of both (one dword per lane and tensor) when an item begins.  (Holding the next rows in
+// registers or LDS instead does not fit: 256 registers, 160 KB.)
+// Measured against the one-wave kernel that walks items one after the other: see launch_dkdv_bf16.
+// =============================================================================================
+
+// What the roles know about an item of one streamed segment.
+struct WalkItem {
+  int row0, nrows, pos0, h;
+  int srow, spos;  // streamed row and position of block 0
+  int rows;        // streamed rows from block 0 on
+  int nblk;        // blocks, at least three
+};
+__device__ __forceinline__ WalkItem walk_item(const Item& it, int h, int causal) {
+  int beg, end;
+  visible_range<1>(it, 0, causal, beg, end);
+  if (it.nseg < 1 || it.nrows <= 0) beg = end = 0;
+  WalkItem w;
+  w.row0 = it.row0; w.nrows = it.nrows; w.pos0 = it.pos0; w.h = h;
+  w.srow = it.seg_row0[0] + beg;
+  w.spos = it.seg_pos0[0] + beg;
+  w.rows = end - beg;
+  const int n = (w.rows + BR - 1) / BR;
+  w.nblk = n > 3 ? n : 3;
+  return w;
+}
+
+template <int D, int ROLE, bool PACKED>
+__device__ __forceinline__ void pair_walk(const AttnArgs& a, int u, int stride, int end, char* ring0, char* ring1,
+                                          char* ring2, char* ring3, char* ring4, char* ring5, float* xbuf0,
+                                          float* xbuf1) {
+  constexpr int QB = BR * D * 2;
+  auto ring = [&](int b) {
+    return b == 0 ? ring0 : (b == 1 ? ring1 : (b == 2 ? ring2 : (b == 3 ? ring3 : (b == 4 ? ring4 : ring5))));
+  };
+  const int H = a.num_heads;
+  const int tid = threadIdx.x, lane = tid & 63, n = lane & 31, hh = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int g = wave & 3;  // which 32 keys of the tile
+  const int64_t sr = (int64_t)H * D;
+  const int rs = H * D * 2;  // bytes per row
+  const int orow = g * 32 + n;
+  const float c1 = -a.alpha * 1.4426950408889634f;
+  const int count = a.plan.header[0];
+
+  // Unit v of the workgroup's share (see unit_of; the number of items is at hand here).
+  const int per = (count + a.xcd_parts - 1) / a.xcd_parts;
+  auto unit = [&](int v) {
+    Unit r;
+    if (a.xcd_parts <= 1) { r.slot = v / H; r.h = v % H; r.on = true; }
+    else { const int x = v & 7, j = v >> 3; r.h = x % H; r.slot = (x / H) * per + j; r.on = j < per; }
+    r.on = r.on && v < end && r.slot < count;
+    return r;
+  };
+  // Descriptions: `raw` is that of the unit after the next one, one of its sixteen words per lane,
+  // loaded (always from inside the list: whether it counts is decided when its turn comes) and brought
+  // into scalar registers by decode.
+  const __amdgpu_buffer_rsrc_t items =
+      __builtin_amdgcn_make_buffer_rsrc((void*)a.plan.items, 0, a.max_items * (int)sizeof(Item), 0x00020000);
+  auto load_raw = [&](int v) {
+    const Unit un = unit(v);
+    return (int)__builtin_amdgcn_raw_buffer_load_b32(items, (lane & 15) * 4, un.on ? un.slot * (int)sizeof(Item) : 0, 0);
+  };
+  auto decode = [&](int raw, int v) {
+    const Unit un = unit(v);
+    Item it = {};
+    auto word = [&](int i) { return un.on ? __builtin_amdgcn_readlane(raw, i) : 0; };
+    it.row0 = word(0); it.nrows = word(1); it.pos0 = word(2); it.nseg = word(3);
+    it.seg_row0[0] = word(4); it.seg_len[0] = word(6); it.seg_pos0[0] = word(8);
+    return walk_item(it, un.h, a.causal);
+  };
+  int raw = load_raw(u);
+  WalkItem cur = decode(raw, u), nxt = {}, prev = {};
+  raw = load_raw(u + stride);
+
+  // The rows of the item this role owns: K (role A), V (role B).
+  bf16x8 oreg[D / 16];
+  auto load_rows = [&](const WalkItem& w) {
+    load_owner<D>(oreg, (const __bf16*)(ROLE == 0 ? a.k : a.v) + (int64_t)w.row0 * sr + w.h * D, sr, orow, w.nrows, hh);
+  };
+  // One dword of each 128-byte line of the wave's 32 rows (two lines a row) of K and V.
+  int touched[2] = {0, 0};
+  auto touch_rows = [&](const WalkItem& w) {
+    int row = g * 32 + (lane >> 1);
+    row = row < w.nrows ? row : 0;
+    const int64_t off = ((int64_t)w.row0 + row) * sr + w.h * D + (lane & 1) * 64;
+    touched[0] = *(const int*)((const __bf16*)a.k + off);
+    touched[1] = *(const int*)((const __bf16*)a.v + off);
+  };
+  // The stream of blocks as role B copies it, two blocks ahead.
+  const __bf16 *cq = nullptr, *cg = nullptr;
+  int cvalid = 0, cleft = 0;  // visible rows from the block on, blocks of the item from it on
+  auto seek = [&](const WalkItem& w) {
+    const int64_t off = (int64_t)w.srow * sr + w.h * D;
+    cq = (const __bf16*)a.q + off;
+    cg = (const __bf16*)a.d_o + off;
+    cvalid = w.rows;
+    cleft = w.nblk;
+  };
+  int voff2[2] = {0, 0};
+  if constexpr (ROLE == 1) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int r2 = (2 * g + i) * (64 / (D / 8)) + lane / (D / 8);
+      voff2[i] = r2 * rs + (((lane % (D / 8)) ^ swz<D>(r2)) << 4);
+    }
+  }
+  auto copy_step = [&](char* buf) {
+    block_copy_async_half<D>(buf, cq, rs, cvalid, g, voff2);
+    block_copy_async_half<D>(buf + QB, cg, rs, cvalid, g, voff2);
+    const int64_t step = (int64_t)BR * sr;
+    cq += step; cg += step; cvalid -= BR; --cleft;
+  };
+
+  {
+    const u32x4 z = {0u, 0u, 0u, 0u};
+    for (int i = tid; i < 2 * QB / 16; i += PW * 64) {  // (the two blocks before the first one)
+      *HSTU_LDS(u32x4, ring4 + i * 16) = z;
+      *HSTU_LDS(u32x4, ring5 + i * 16) = z;
+    }
+  }
+  if constexpr (ROLE == 1) {
+    seek(cur);
+    copy_step(ring0);
+    copy_step(ring1);
+  }
+  load_rows(cur);  // (role B's first step works on a block of zeros: whatever V rows)
+
+  f32x16 acc[D / 32];  // A: dV^T, B: dK^T
+  auto clear_acc = [&] {
+#pragma unroll
+    for (int i = 0; i < D / 32; ++i)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][r] = 0.f;
+  };
+  clear_acc();
+  RowAddr<D> ra;  // A: rows of Q, B: rows of dO
+  ColAddr<D> ca;  // A: dO transposed, B: Q transposed
+  ra.init(n, hh); ca.init(lane);
+
+  // Role A's masks of the item whose block the SiLU stage works on.
+  int2 wsq = {};
+  Window win = {};
+  int m_last = -1, m_pos = 0, m_klo = 0;  // last block the diagonal touches, position of block 0, the wave's first key
+  auto bounds_of = [&](const WalkItem& w) {
+    return PACKED ? window_bounds(a.row_seq, w.row0 + orow, orow < w.nrows) : make_int2(0, 0);
+  };
+  if constexpr (ROLE == 0) wsq = bounds_of(cur);
+
+  f32x16 sd[2];     // A: S, B: dP of the blocks of even / odd index
+  bf16x8 pk[2][2];  // A: P, B: dS of the blocks of even / odd index
+#pragma unroll
+  for (int x = 0; x < 2; ++x) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) sd[x][r] = 0.f;
+#pragma unroll
+    for (int y = 0; y < 2; ++y)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) pk[x][y][e] = (__bf16)0.f;
+  }
+  float* xa0 = xbuf0 + g * XK + lane * 4;
+  float* xa1 = xbuf1 + g * XK + lane * 4;
+  lds_writes_done();
+  tile_copy_wait<0>();
+  tile_barrier();
+
+  int s = 0;            // step of the item
+  bool first = true, drain = false;
+  // The previous item's rows (see store_owner_major), through a buffer of its rows: the stores of lanes
+  // beyond them are dropped, so a wave always issues eight.
+  auto store_prev = [&] {
+    __bf16* base = (__bf16*)(ROLE == 0 ? a.dv : a.dk) + (int64_t)prev.row0 * sr + prev.h * D;
+    const __amdgpu_buffer_rsrc_t rsrc =
+        __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, __builtin_amdgcn_readfirstlane(prev.nrows * rs), 0x00020000);
+    const int voff = orow * rs + 16 * hh;
+    const float scale = a.alpha * a.inv_n;
+#pragma unroll
+    for (int c = 0; c < D / 32; ++c)
+#pragma unroll
+      for (int pr = 0; pr < 2; ++pr)
+        __builtin_amdgcn_raw_buffer_store_b128(owner_chunk(acc[c], pr, scale), rsrc, voff + c * 64 + pr * 32, 0, 0);
+    // (zeros the compiler cannot see: known ones it kept in 64 registers of their own and moved in every step)
+#pragma unroll
+    for (int i = 0; i < D / 32; ++i)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        float z;
+        asm volatile("v_mov_b32 %0, 0" : "=v"(z));
+        acc[i][r] = z;
+      }
+  };
+
+  auto step = [&](auto tag) {  // returns true when the stream has been drained
+    constexpr int S = decltype(tag)::value;  // step number mod 6
+    if (s == 1) {  // the next item's description, and the request for the one after
+      nxt = decode(raw, u + stride);
+      raw = load_raw(u + 2 * stride);
+    }
+    bool done = false;
+    if constexpr (ROLE == 0) {
+      bool mask;
+      if (s == 1) {  // from here on the SiLU stage works on this item
+        if constexpr (PACKED) {
+          win = make_window(wsq, cur.row0 + orow, orow < cur.nrows, 1, a.causal);
+          wsq = bounds_of(nxt);
+        }
+        touch_rows(nxt);
+        m_klo = cur.pos0 + g * 32;
+        m_last = !PACKED && a.causal ? (m_klo + 30 - cur.spos) >> 5 : -1;
+        m_pos = cur.spos;
+      } else {
+        m_pos += BR;
+        --m_last;
+      }
+      // m_pos: position of the block of the SiLU stage, m_last: blocks from it to the last masked one
+      mask = PACKED ? win.masks(m_pos) : m_last >= 0;
+      auto vis_of = [&] {
+        if constexpr (PACKED) return win.vis(m_pos, hh);
+        else return VisAfter{m_klo + n - m_pos, hh};
+      };
+      const ScoreInit<false> init = {nullptr, nullptr, 0, BlockBias{}};
+      role_a_step<D>(init, ring(S), ring((S + 4) % NSLOT) + QB, ra, ca, oreg, sd[(S + 1) & 1], sd[S & 1], pk[S & 1],
+                     pk[(S + 1) & 1], acc, (S + 1) & 1 ? xa1 : xa0, c1, a.alpha, mask, vis_of);
+      lds_writes_done();
+      if (s == 1) {
+        store_prev();
+        prev = cur;
+      }
+      if (s + 1 == cur.nblk) {
+        load_rows(nxt);
+        asm volatile("" ::"v"(touched[0]), "v"(touched[1]));  // (what was touched is not needed)
+      }
+      done = drain && s == 2;
+    } else {
+      if (cleft == 0) seek(nxt);  // (in step 1 at the earliest)
+      copy_step(ring((S + AHEAD_COPY) % NSLOT));
+      __builtin_amdgcn_sched_barrier(0);  // (the waits below count on this order)
+      if (!first)
+        role_b_step<D>(ring((S + 5) % NSLOT) + QB, ring((S + 3) % NSLOT), ra, ca, oreg, sd[S & 1], sd[(S + 1) & 1],
+                       pk[(S + 1) & 1], pk[S & 1], acc, S & 1 ? xa1 : xa0);
+      first = false;
+      __builtin_amdgcn_sched_barrier(0);
+      // At the end of a step the previous step's copies must have landed.  Behind them are this step's
+      // copies, 4, the V rows requested in step 0, 8 (waited for in step 1), and the stores of step 2, 8.
+      if (s == 0) {
+        load_rows(cur);
+        __builtin_amdgcn_sched_barrier(0);
+        tile_copy_wait<12>();
+      } else if (s == 2) {
+        store_prev();
+        prev = cur;
+        __builtin_amdgcn_sched_barrier(0);
+        tile_copy_wait<12>();
+      } else if (s == 3) {
+        tile_copy_wait<12>();
+      } else {
+        tile_copy_wait<4>();
+      }
+      done = drain && s == 2;
+    }
+    tile_barrier();
+    if (++s == cur.nblk) {
+      s = 0;
+      cur = nxt;
+      u += stride;
+      drain = u >= end;
+    }
+    return done;
+  };
+  while (true) {
+    if (step(std::integral_constant<int, 0>{})) break;
+    if (step(std::integral_constant<int, 1>{})) break;
+    if (step(std::integral_constant<int, 2>{})) break;
+    if (step(std::integral_constant<int, 3>{})) break;
+    if (step(std::integral_constant<int, 4>{})) break;
+    if (step(std::integral_constant<int, 5>{})) break;
+  }
+  tile_copy_wait<0>();
+}
+
+template <int D, bool PACKED>
+__global__ void __launch_bounds__(PW * 64) hstu_dkdv_walk_bf16(AttnArgs a) {
+  constexpr int QB = BR * D * 2;
+  __shared__ __attribute__((aligned(1024))) char ring0[2 * QB];
+  __shared__ __attribute__((aligned(1024))) char ring1[2 * QB];
+  __shared__ __attribute__((aligned(1024))) char ring2[2 * QB];
+  __shared__ __attribute__((aligned(1024))) char ring3[2 * QB];
+  __shared__ __attribute__((aligned(1024))) char ring4[2 * QB];
+  __shared__ __attribute__((aligned(1024))) char ring5[2 * QB];
+  __shared__ __attribute__((aligned(1024))) float xbuf0[4 * XK];
+  __shared__ __attribute__((aligned(1024))) float xbuf1[4 * XK];
+  int u = blockIdx.x, stride = (int)gridDim.x, end = unit_count(a, a.plan.header[0]);
+  walk_share(a, u, stride, end);
+  if (u >= end) return;
+  const int role = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);
+  if (role == 0)
+    pair_walk<D, 0, PACKED>(a, u, stride, end, ring0, ring1, ring2, ring3, ring4, ring5, xbuf0, xbuf1);
+  else
+    pair_walk<D, 1, PACKED>(a, u, stride, end, ring0, ring1, ring2, ring3, ring4, ring5, xbuf0, xbuf1);
+}
+
 }  // namespace
 
 // The pair kernel serves per-sequence schedules, with or without the timestamp bias (no packed
@@ -467,6 +781,24 @@ __global__ void __launch_bounds__(PW * 64) hstu_dkdv_pair_bf16(AttnArgs a) {
 bool dkdv_pair_supported(const AttnArgs& a, int d_qk, int d_v) {
   if (a.ts_rec && (a.nb < 1 || a.nb > MAX_TS_BUCKETS || !a.ts_w || !a.ts_rec_own)) return false;
   return d_qk == 128 && d_v == 128 && !a.row_seq && !a.large_batch && !a.walk_chunks && a.waves == 4;
+}
+
+// Large batches of short sequences: schedules in natural order, one streamed segment per item, bf16
+// outputs that are not added to (the steps hold six copies of the epilogue, and the general one is
+// large; fp32 outputs keep the one-wave kernel).
+bool dkdv_walk_supported(const AttnArgs& a, int d_qk, int d_v) {
+  return d_qk == 128 && d_v == 128 && !a.ts_rec && a.single_segment && (a.row_seq || a.walk_chunks) && a.waves == 4 &&
+         !a.out_f32 && !a.accumulate && (int64_t)a.max_items * (int64_t)sizeof(Item) < (1ll << 31);
+}
+
+hipError_t launch_dkdv_walk_bf16(const AttnArgs& a, int d_qk, int d_v, hipStream_t stream) {
+  if (!dkdv_walk_supported(a, d_qk, d_v)) return hipErrorInvalidValue;
+  const int64_t units = a.xcd_parts <= 1 ? (int64_t)a.max_items * a.num_heads
+                                         : 8 * (((int64_t)a.max_items + a.xcd_parts - 1) / a.xcd_parts);
+  const dim3 grid((unsigned)(units < 256 ? units : 256)), block(PW * 64);
+  if (a.row_seq) hipLaunchKernelGGL((hstu_dkdv_walk_bf16<128, true>), grid, block, 0, stream, a);
+  else hipLaunchKernelGGL((hstu_dkdv_walk_bf16<128, false>), grid, block, 0, stream, a);
+  return hipGetLastError();
 }
 
 hipError_t launch_dkdv_pair_bf16(const AttnArgs& a, int d_qk, int d_v, hipStream_t stream) {

@@ -189,8 +189,8 @@ constexpr int tile_loads() { return ST / (64 / (D / 8)); }
 // flight; loads complete in order, so the N newest may remain outstanding.
 template <int N = 0>
 __device__ __forceinline__ void tile_copy_wait() {
-  static_assert(N >= 0 && N < 16, "vmcnt immediate");
-  __builtin_amdgcn_s_waitcnt(0x0f70 | N);
+  static_assert(N >= 0 && N < 64, "vmcnt immediate");
+  __builtin_amdgcn_s_waitcnt(0x0f70 | (N & 15) | ((N >> 4) << 14));
 }
 
 // Workgroup barrier between tiles without the memory fence of __syncthreads(), which would wait
@@ -297,6 +297,25 @@ __device__ __forceinline__ TileRef tile_ref(const Item& it, const Stream& s, int
   return r;
 }
 
+// Sixteen bytes of the lane's row from half pr of a 32-element accumulator block (see
+// store_owner_major): elements 16*pr + 8*hh .. + 7 of the block, scaled and rounded to bf16.
+__device__ __forceinline__ u32x4 owner_chunk(const f32x16& acc, int pr, float scale) {
+  uint32_t w[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    bf16x2 t;
+    t[0] = (__bf16)(acc[8 * pr + 2 * e] * scale);
+    t[1] = (__bf16)(acc[8 * pr + 2 * e + 1] * scale);
+    w[e] = __builtin_bit_cast(uint32_t, t);
+  }
+  // w[0..1]: run 2*pr, w[2..3]: run 2*pr + 1 of this lane's half
+  const auto s0 = __builtin_amdgcn_permlane32_swap(w[0], w[2], false, false);
+  const auto s1 = __builtin_amdgcn_permlane32_swap(w[1], w[3], false, false);
+  u32x4 v;
+  v[0] = s0[0]; v[1] = s1[0]; v[2] = s0[1]; v[3] = s1[1];
+  return v;
+}
+
 // Epilogue for accumulators held "owner row per lane": blk[c][r] is element
 // c*32 + 8*(r/4) + 4*hh + r%4 of the lane's row.  `elem` is the element offset of the row start.
 // Lanes n and n + 32 hold the same row (hh = 0, 1) and must both be active.
@@ -313,22 +332,8 @@ __device__ __forceinline__ void store_owner_major(void* out, int64_t elem, const
 #pragma unroll
     for (int c = 0; c < D / 32; ++c)
 #pragma unroll
-      for (int pr = 0; pr < 2; ++pr) {
-        uint32_t w[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          bf16x2 t;
-          t[0] = (__bf16)(acc[c][8 * pr + 2 * e] * scale);
-          t[1] = (__bf16)(acc[c][8 * pr + 2 * e + 1] * scale);
-          w[e] = __builtin_bit_cast(uint32_t, t);
-        }
-        // w[0..1]: run 2*pr, w[2..3]: run 2*pr + 1 of this lane's half
-        const auto s0 = __builtin_amdgcn_permlane32_swap(w[0], w[2], false, false);
-        const auto s1 = __builtin_amdgcn_permlane32_swap(w[1], w[3], false, false);
-        u32x4 v;
-        v[0] = s0[0]; v[1] = s1[0]; v[2] = s0[1]; v[3] = s1[1];
-        *(u32x4*)((__bf16*)out + elem + c * 32 + 16 * pr + 8 * hh) = v;
-      }
+      for (int pr = 0; pr < 2; ++pr)
+        *(u32x4*)((__bf16*)out + elem + c * 32 + 16 * pr + 8 * hh) = owner_chunk(acc[c], pr, scale);
     return;
   }
 #pragma unroll
@@ -393,6 +398,20 @@ __device__ __forceinline__ Unit unit_of(const AttnArgs& a, int u) {
 // Units the (item, head) pairs of a schedule of n items are spread over.
 __device__ __forceinline__ int unit_count(const AttnArgs& a, int n) {
   return a.xcd_parts <= 1 ? n * a.num_heads : 8 * ((n + a.xcd_parts - 1) / a.xcd_parts);
+}
+
+// The units a workgroup that walks over them takes: every gridDim.x-th from blockIdx.x on - or, for a
+// schedule in natural order (walk_chunks), one contiguous run of its XCD's units (unit = 8 * j + XCD, see
+// unit_of): whole sequences, whose tiles then follow each other in time on one CU and find their
+// streamed rows in the caches, where a stride would beat against the number of tiles per sequence.
+__device__ __forceinline__ void walk_share(const AttnArgs& a, int& u, int& stride, int& end) {
+  if (!a.walk_chunks || (gridDim.x & 7) != 0) return;
+  const int x = u & 7, m = u >> 3, wgs = (int)(gridDim.x >> 3), per = (end + 7) >> 3;
+  const int c = (per + wgs - 1) / wgs;
+  const int64_t last = (int64_t)8 * (m + 1) * c;
+  u = 8 * m * c + x;
+  stride = 8;
+  end = last < end ? (int)last : end;
 }
 
 // An item as it lies in memory, loaded by every lane alike (what a workgroup that walks over items
@@ -549,16 +568,20 @@ __device__ __forceinline__ void rec_copy_async(char* tile, const TsRecord* rec, 
   __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, HSTU_LDS(void, tile), 16, lane * 16, 0, 0, 0);
 }
 
-__device__ __forceinline__ int wave_min(int x) {
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) { const int y = __shfl_xor(x, m); x = y < x ? y : x; }
-  return __builtin_amdgcn_readfirstlane(x);
+// Minimum and maximum over the wave's lanes, on the vector pipe (a shuffle goes through LDS: six
+// dependent round trips per reduction, and a packed item needs four of them).
+template <class F>
+__device__ __forceinline__ int wave_reduce(int x, const F& f) {
+  x = f(x, __builtin_amdgcn_update_dpp(x, x, 0x111, 0xf, 0xf, false));  // row_shr:1, 2, 4, 8
+  x = f(x, __builtin_amdgcn_update_dpp(x, x, 0x112, 0xf, 0xf, false));
+  x = f(x, __builtin_amdgcn_update_dpp(x, x, 0x114, 0xf, 0xf, false));
+  x = f(x, __builtin_amdgcn_update_dpp(x, x, 0x118, 0xf, 0xf, false));
+  x = f(x, __builtin_amdgcn_update_dpp(x, x, 0x142, 0xa, 0xf, false));  // row_bcast:15, :31
+  x = f(x, __builtin_amdgcn_update_dpp(x, x, 0x143, 0xc, 0xf, false));
+  return __builtin_amdgcn_readlane(x, 63);
 }
-__device__ __forceinline__ int wave_max(int x) {
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) { const int y = __shfl_xor(x, m); x = y > x ? y : x; }
-  return __builtin_amdgcn_readfirstlane(x);
-}
+__device__ __forceinline__ int wave_min(int x) { return wave_reduce(x, [](int a, int b) { return a < b ? a : b; }); }
+__device__ __forceinline__ int wave_max(int x) { return wave_reduce(x, [](int a, int b) { return a > b ? a : b; }); }
 __device__ __forceinline__ float wave_sum(float x) {
 #pragma unroll
   for (int m = 32; m >= 1; m >>= 1) x += __shfl_xor(x, m);
@@ -694,12 +717,8 @@ struct ScoreInit {
   }
 };
 
-// Loads the table into LDS and works out the wave's owner-side context.  All threads of the
-// workgroup call it (it contains a barrier).
-template <int NT>
-__device__ __forceinline__ BiasCtx bias_setup(const AttnArgs& a, float* wtab, const Item& it, int orow,
-                                              int tid, int hh) {
-  for (int i = tid; i < a.nb; i += NT) wtab[i] = a.ts_w[i];
+// The wave's owner-side context of an item.
+__device__ __forceinline__ BiasCtx bias_context(const AttnArgs& a, const float* wtab, const Item& it, int orow, int hh) {
   BiasCtx c;
   c.wtab = wtab;
   c.rec = a.ts_rec;
@@ -713,6 +732,15 @@ __device__ __forceinline__ BiasCtx bias_setup(const AttnArgs& a, float* wtab, co
   c.t_own = ok ? a.ts_rec_own[it.row0 + orow].ts : 0;
   c.o_lo = wave_min(ok ? c.t_own : 0x7fffffff);
   c.o_hi = wave_max(ok ? c.t_own : (int)0x80000000);
+  return c;
+}
+// The same after loading the table into LDS.  All threads of the workgroup call it (it contains a
+// barrier).
+template <int NT>
+__device__ __forceinline__ BiasCtx bias_setup(const AttnArgs& a, float* wtab, const Item& it, int orow,
+                                              int tid, int hh) {
+  for (int i = tid; i < a.nb; i += NT) wtab[i] = a.ts_w[i];
+  const BiasCtx c = bias_context(a, wtab, it, orow, hh);
   __syncthreads();
   return c;
 }

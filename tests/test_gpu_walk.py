@@ -1,0 +1,68 @@
+"""The walking dk/dv kernel with two waves per 32 keys (d = 128, large batches and packed tiles, bf16 outputs):
+items of one, two and three 32-row blocks (shorter ones are padded to three), a single item, fewer items than
+workgroups, more items than one round of workgroups, tiles that end one row after or before a block, no mask,
+head counts with and without an XCD-aware map.  Against the oracle (bf16 outputs: the stated bar plus their own
+rounding; the few-terms bar where sequences are mostly shorter than a block)."""
+import numpy as np
+import pytest
+import torch
+
+from conftest import set_flags
+import oracle
+import workloads
+from test_gpu_parity import _check, _check_few_terms, _dev
+
+pytestmark = pytest.mark.gpu
+
+RNG = np.random.default_rng(91)
+CASES = [
+    # name, lengths, heads, few terms
+    ("one_row", [1], 1, True),
+    ("one_tile", [128], 2, False),
+    ("block_edges", [31, 32, 33, 63, 64, 65, 95, 96, 97, 127, 128, 129, 161], 2, False),
+    ("three_heads", [200, 0, 7, 255, 256, 1], 3, False),
+    ("one_long", [1000], 4, False),
+    ("many_short", [int(x) for x in RNG.integers(0, 24, size=700)], 8, True),
+    ("many_items", [int(x) for x in RNG.integers(60, 200, size=300)], 4, False),
+]
+
+
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("name,lengths,H,few", CASES)
+def test_walking_dkdv(name, lengths, H, few, causal, monkeypatch):
+    set_flags(monkeypatch, remove="NO_PACK", add="PACK_SHORT")
+    import paper_2508_04711_amd as lib
+    print("walk", name, H, causal, flush=True)
+    w = workloads.custom(name, lengths, H, 128, 128, max_len=max(max(lengths), 1), dtype="bf16", seed=len(lengths))
+    vals = workloads.values(w)
+    d = _dev(vals)
+    off_np = w.seq_offsets()
+    off = torch.from_numpy(off_np).cuda()
+    f64 = {k: workloads.to_f64(v) for k, v in vals.items()}
+    want = oracle.bwd(f64["q"], f64["k"], f64["v"], f64["d_o"], off_np, w.max_len, w.alpha, causal)
+    out = [torch.full_like(d["q"], float("nan")) for _ in range(3)]  # (every row is written)
+    got = lib.hstu_jagged_attn_bwd(d["q"], d["k"], d["v"], d["d_o"], off, w.max_len, w.alpha, causal, out=tuple(out))
+    for nm, g, ref in zip(("dq", "dk", "dv"), got, want):
+        if few:
+            _check_few_terms(nm, g, ref, name)
+        else:
+            _check(nm, g, ref, "bf16", name)
+
+
+def test_walking_dkdv_over_a_large_batch_in_natural_order(monkeypatch):
+    """Per-sequence tiles in natural order (mean length above the packed tiles' limit), against the
+    one-wave kernel, which the other tests hold against the oracle: same products, same roundings."""
+    set_flags(monkeypatch, remove="NO_PACK")
+    import paper_2508_04711_amd as lib
+    lengths = [int(x) for x in np.random.default_rng(5).integers(129, 520, size=1400)]
+    w = workloads.custom("natural", lengths, 2, 128, 128, max_len=520, dtype="bf16", seed=6)
+    print("walk natural", flush=True)
+    d = {k: v.cuda() for k, v in workloads.values(w).items()}
+    off = torch.from_numpy(w.seq_offsets()).cuda()
+    args = (d["q"], d["k"], d["v"], d["d_o"], off, w.max_len, w.alpha, True)
+    _, dk, dv = lib.hstu_jagged_attn_bwd(*args)
+    set_flags(monkeypatch, add="DKDV_ONE_WAVE")
+    _, dk1, dv1 = lib.hstu_jagged_attn_bwd(*args)
+    for a, b in ((dk, dk1), (dv, dv1)):
+        # at most one bf16 unit of the value (fp32 sums of equal terms in the same order)
+        assert (a.float() - b.float()).abs().max().item() <= 2.0 ** -7 * b.float().abs().max().item()
