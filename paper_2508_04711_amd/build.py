@@ -8,7 +8,7 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libhstu_attn.so")
-SOURCES = ["hstu_api.hip", "hstu_plan.hip", "hstu_fwd.hip", "hstu_dkdv.hip", "hstu_dkdv2.hip", "hstu_dq.hip", "hstu_f32.hip", "hstu_probe.hip"]
+SOURCES = ["hstu_api.hip", "hstu_plan.hip", "hstu_fwd.hip", "hstu_dkdv.hip", "hstu_dkdv2.hip", "hstu_dq.hip", "hstu_bwd_short.hip", "hstu_f32.hip", "hstu_probe.hip"]
 FLAGS = [
     "-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC",
     # packed fp32 VALU forms are kept out of the generated code

@@ -584,6 +584,9 @@ hipError_t launch_dkdv_pair_bf16(const AttnArgs& a, int d_qk, int d_v, hipStream
 bool dkdv_walk_supported(const AttnArgs& a, int d_qk, int d_v);
 hipError_t launch_dkdv_walk_bf16(const AttnArgs& a, int d_qk, int d_v, hipStream_t stream);
 hipError_t launch_dq_bf16(const AttnArgs& a, int d_qk, int d_v, hipStream_t stream);
+// dq, dk and dv of batches of short sequences in one kernel; a.self gives offsets, batch and rows.
+bool bwd_short_supported(int d_qk, int d_v);
+hipError_t launch_bwd_short_bf16(const AttnArgs& a, int d_qk, int d_v, hipStream_t stream);
 hipError_t launch_fwd_f32(const AttnArgs& a, int d_qk, int d_v, hipStream_t stream);
 hipError_t launch_dkdv_f32(const AttnArgs& a, int d_qk, int d_v, hipStream_t stream);
 hipError_t launch_dq_f32(const AttnArgs& a, int d_qk, int d_v, hipStream_t stream);
