@@ -410,6 +410,142 @@ __global__ void __launch_bounds__(NW * 64, (DQK + DV <= 128 ? 2 : 1)) hstu_dkdv_
   }  // CAN_WALK
 }
 
+// =============================================================================================
+// The dk/dv pass at d_qk = d_v = 64 without bias: one 32-query block at a time, as the dq pass does it.
+// 168 registers and 32 KB of LDS, so three workgroups share a CU and their waves fill each other's gaps -
+// matrix against vector instructions, and above all an item's first loads and last stores, which two
+// workgroups with two blocks in flight per wave left open.  Bound by the vector pipe (~50 instructions' issue
+// per score column) and by an item's memory round trips.  1024 sequences of 400..800 rows, H = 8: 1551 -> 1298 us
+// (2.4 -> 2.9 TB/s).  For launches of many workgroups only, see many_units.
+// =============================================================================================
+template <int D, bool PACKED>
+__global__ void __launch_bounds__(256, 3) hstu_dkdv_lean_bf16(AttnArgs a) {
+  constexpr int NW = 4, QB = ST * D * 2;
+  __shared__ __attribute__((aligned(1024))) char smem0[2 * QB];
+  __shared__ __attribute__((aligned(1024))) char smem1[2 * QB];
+  auto qbuf = [&](int b) { return b ? smem1 : smem0; };
+  auto gbuf = [&](int b) { return (b ? smem1 : smem0) + QB; };
+
+  const int H = a.num_heads;
+  const Unit un = unit_of(a, blockIdx.x);
+  const int slot = un.slot, h = un.h;
+  Item it;
+  if (!un.on || !get_item<PACKED>(a, slot, it)) return;
+
+  const int tid = threadIdx.x, lane = tid & 63, n = lane & 31, hh = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int64_t sr = (int64_t)H * D;
+  const int64_t own = (int64_t)it.row0 * sr + h * D;
+  const int orow = wave * 32 + n;
+  const bool wave_on = wave * 32 < it.nrows;
+  int2 wsq = {};
+  if constexpr (PACKED) wsq = window_bounds(a.row_seq, it.row0 + orow, orow < it.nrows);
+  bf16x8 kreg[D / 16], vreg[D / 16];
+  load_owner<D>(kreg, (const __bf16*)a.k + own, sr, orow, it.nrows, hh);
+  load_owner<D>(vreg, (const __bf16*)a.v + own, sr, orow, it.nrows, hh);
+
+  f32x16 dkacc[D / 32], dvacc[D / 32];
+#pragma unroll
+  for (int i = 0; i < D / 32; ++i)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) dkacc[i][r] = dvacc[i][r] = 0.f;
+
+  const Stream st = make_stream<1>(it, a.causal);
+  const float c1 = -a.alpha * 1.4426950408889634f;
+  const int k_lo = it.pos0 + wave * 32, k_hi = k_lo + 31;
+  RowAddr<D> ra;
+  ColAddr<D> ca;
+  ra.init(n, hh);
+  ca.init(lane);
+
+  auto copy = [&](int j, int b) {
+    const TileRef t = tile_ref(it, st, j);
+    const int64_t at = (int64_t)t.row * sr + h * D;
+    tile_copy_async<D, NW>(qbuf(b), (const __bf16*)a.q + at, sr, t.valid, wave, lane);
+    tile_copy_async<D, NW>(gbuf(b), (const __bf16*)a.d_o + at, sr, t.valid, wave, lane);
+  };
+  if (st.total > 0) copy(0, 0);
+  Window win = {};
+  if constexpr (PACKED) {  // (looked at only now that the first tile copies are on their way)
+    __builtin_amdgcn_sched_barrier(0);
+    win = make_window(wsq, it.row0 + orow, orow < it.nrows, 1, a.causal);
+  }
+  tile_copy_wait<0>();
+  tile_barrier();
+
+  auto block = [&](const char* qt, const char* gt, int blk, bool mask, const auto& vis) {
+    f32x16 s, dp;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) s[r] = dp[r] = 0.f;
+#pragma unroll
+    for (int ks = 0; ks < D / 16; ++ks) s = mfma(ra.read(qt, blk, ks), kreg[ks], s);
+#pragma unroll
+    for (int ks = 0; ks < D / 16; ++ks) dp = mfma(ra.read(gt, blk, ks), vreg[ks], dp);
+    // Half a block (eight scores) at a time, stage by stage (see dq_block).
+#pragma unroll
+    for (int y = 0; y < 2; ++y) {
+      float t[8], g[8], p[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) t[j] = s[8 * y + j] * c1;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) t[j] = __builtin_amdgcn_exp2f(t[j]);
+#pragma unroll
+      for (int j = 0; j < 8; ++j) t[j] = 1.0f + t[j];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) g[j] = __builtin_amdgcn_rcpf(t[j]);
+#pragma unroll
+      for (int j = 0; j < 8; ++j) p[j] = s[8 * y + j] * g[j];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) t[j] = __builtin_fmaf(-p[j], g[j], p[j]);
+#pragma unroll
+      for (int j = 0; j < 8; ++j) t[j] = __builtin_fmaf(a.alpha, t[j], g[j]);
+#pragma unroll
+      for (int j = 0; j < 8; ++j) t[j] = dp[8 * y + j] * t[j];
+      if (mask) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          const bool v = vis(8 * y + j);
+          p[j] = v ? p[j] : 0.f;
+          t[j] = v ? t[j] : 0.f;
+        }
+      }
+      const bf16x8 pb = pack8(p), db = pack8(t);
+#pragma unroll
+      for (int c = 0; c < D / 32; ++c) dvacc[c] = mfma(ca.read(gt, blk * 2 + y, c), pb, dvacc[c]);
+#pragma unroll
+      for (int c = 0; c < D / 32; ++c) dkacc[c] = mfma(ca.read(qt, blk * 2 + y, c), db, dkacc[c]);
+    }
+  };
+  auto step = [&](int j, auto buf_tag) {
+    constexpr int BUF = decltype(buf_tag)::value;
+    const TileRef tj = tile_ref(it, st, j);
+    if (j + 1 < st.total) copy(j + 1, BUF ^ 1);
+    if (wave_on) {
+#pragma unroll
+      for (int blk = 0; blk < ST / 32; ++blk) {
+        const int q_lo = tj.pos + blk * 32;
+        // no query of the block sees a key of the wave
+        if (blk * 32 >= tj.valid || (!PACKED && a.causal && q_lo + 31 < k_lo)) continue;
+        if (PACKED && (q_lo > win.hi_max || q_lo + 31 < win.lo_min)) continue;
+        if constexpr (PACKED) block(qbuf(BUF), gbuf(BUF), blk, win.masks(q_lo), win.vis(q_lo, hh));
+        else block(qbuf(BUF), gbuf(BUF), blk, a.causal && q_lo < k_hi, VisAfter{k_lo + n - q_lo, hh});
+      }
+    }
+    tile_copy_wait<0>();
+    tile_barrier();
+  };
+  for (int j = 0; j < st.total; j += 2) {
+    step(j, std::integral_constant<int, 0>{});
+    if (j + 1 < st.total) step(j + 1, std::integral_constant<int, 1>{});
+  }
+
+  if (orow < it.nrows) {
+    const int64_t e = ((int64_t)it.row0 + orow) * sr + h * D;
+    store_owner_major<D>(a.dk, e, dkacc, a.alpha * a.inv_n, hh, a.accumulate, a.out_f32);
+    store_owner_major<D>(a.dv, e, dvacc, a.alpha * a.inv_n, hh, a.accumulate, a.out_f32);
+  }
+}
+
 }  // namespace
 
 hipError_t launch_dkdv_bf16(const AttnArgs& a, int d_qk, int d_v, hipStream_t stream) {
@@ -418,6 +554,12 @@ hipError_t launch_dkdv_bf16(const AttnArgs& a, int d_qk, int d_v, hipStream_t st
   if (dkdv_pair_supported(a, d_qk, d_v) && !a.dkdv_one_wave)
     return launch_dkdv_pair_bf16(a, d_qk, d_v, stream);
   if (a.ts_rec && (a.nb < 1 || a.nb > MAX_TS_BUCKETS || !a.ts_w || !a.ts_rec_own)) return hipErrorInvalidValue;
+  if (d_qk == 64 && d_v == 64 && !a.ts_rec && !a.dkdv_one_wave && many_units(a)) {
+    const dim3 grid((unsigned)grid_units(a));
+    if (a.row_seq) hipLaunchKernelGGL((hstu_dkdv_lean_bf16<64, true>), grid, dim3(256), 0, stream, a);
+    else hipLaunchKernelGGL((hstu_dkdv_lean_bf16<64, false>), grid, dim3(256), 0, stream, a);
+    return hipGetLastError();
+  }
   // One workgroup per CU is resident at the larger head dimensions: as many workgroups as CUs,
   // each walking over its share of the items.  Two per CU overlap each other's memory round
   // trips already, and the hardware's own dispatch serves them better (measured).

@@ -129,7 +129,7 @@ __device__ __forceinline__ void dq_block(const BiasCtx& bias, const char* trec,
 }
 
 template <int DQK, int DV, int NW, bool BIAS, bool PACKED>
-__global__ void __launch_bounds__(NW * 64, 2) hstu_dq_bf16(AttnArgs a) {
+__device__ __forceinline__ void dq_item(const AttnArgs& a) {
   constexpr int KB = ST * DQK * 2, VB = ST * DV * 2;
   __shared__ __attribute__((aligned(1024))) char smem0[KB + VB];
   __shared__ __attribute__((aligned(1024))) char smem1[KB + VB];
@@ -264,6 +264,19 @@ __global__ void __launch_bounds__(NW * 64, 2) hstu_dq_bf16(AttnArgs a) {
   }
 }
 
+template <int DQK, int DV, int NW, bool BIAS, bool PACKED>
+__global__ void __launch_bounds__(NW * 64, 2) hstu_dq_bf16(AttnArgs a) {
+  dq_item<DQK, DV, NW, BIAS, PACKED>(a);
+}
+
+// The same held to 128 registers (of 143), so that four workgroups share a CU instead of three: 1024 sequences
+// of 400..800 rows, H = 8, d = 64: 1089 -> 1054 us.  For launches of many workgroups only, see many_units (16
+// sequences of 500..4000 rows, H = 4, lose 2 %).
+template <int DQK, int DV, int NW>
+__global__ void __launch_bounds__(NW * 64, 4) hstu_dq_lean_bf16(AttnArgs a) {
+  dq_item<DQK, DV, NW, false, false>(a);
+}
+
 }  // namespace
 
 hipError_t launch_dq_bf16(const AttnArgs& a, int d_qk, int d_v, hipStream_t stream) {
@@ -273,6 +286,10 @@ hipError_t launch_dq_bf16(const AttnArgs& a, int d_qk, int d_v, hipStream_t stre
     HSTU_DISPATCH_D(hstu_dq_bf16, 4, 4, false, true);
   }
   if (a.ts_rec) HSTU_DISPATCH_BIAS(hstu_dq_bf16, 4, 4, true, false);
+  if (d_qk == 64 && d_v == 64 && many_units(a)) {
+    hipLaunchKernelGGL((hstu_dq_lean_bf16<64, 64, 4>), dim3((unsigned)grid_units(a)), dim3(256), 0, stream, a);
+    return hipGetLastError();
+  }
   HSTU_DISPATCH_D(hstu_dq_bf16, 4, 4, false, false);
 }
 

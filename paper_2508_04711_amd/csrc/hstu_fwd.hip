@@ -297,6 +297,135 @@ __global__ void __launch_bounds__(NW * 64, 2) hstu_fwd_bf16(AttnArgs a) {
 }
 
 // =============================================================================================
+// The forward pass at d_qk = d_v = 64 without bias: one 32-key block at a time, as the dq pass does it.  99
+// registers and 32 KB of LDS, so four workgroups share a CU (three of the kernel above).  1024 sequences of
+// 400..800 rows, H = 8: 880 -> 814 us (2.9 -> 3.1 TB/s).  (The kernel above held to 128 registers spills eight,
+// and their reloads wait for the tile copies in flight: 1094 us.)  For launches of many workgroups only, see
+// many_units.
+// =============================================================================================
+template <int DQK, int DV, int NW, bool PACKED>
+__global__ void __launch_bounds__(NW * 64, 4) hstu_fwd_lean_bf16(AttnArgs a) {
+  constexpr int KB = ST * DQK * 2, VB = ST * DV * 2;
+  __shared__ __attribute__((aligned(1024))) char smem0[KB + VB];
+  __shared__ __attribute__((aligned(1024))) char smem1[KB + VB];
+  auto kbuf = [&](int b) { return b ? smem1 : smem0; };
+  auto vbuf = [&](int b) { return (b ? smem1 : smem0) + KB; };
+
+  const int H = a.num_heads;
+  const Unit un = unit_of(a, blockIdx.x);
+  const int slot = un.slot, h = un.h;
+  Item it;
+  if (!un.on || !get_item<PACKED>(a, slot, it)) return;
+
+  const int tid = threadIdx.x, lane = tid & 63, n = lane & 31, hh = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int64_t sq = (int64_t)H * DQK, sv = (int64_t)H * DV;
+  const __bf16* kg = (const __bf16*)a.k + h * DQK;
+  const __bf16* vg = (const __bf16*)a.v + h * DV;
+
+  const int orow = wave * 32 + n;
+  const bool wave_on = wave * 32 < it.nrows;
+  int2 wsq = {};
+  if constexpr (PACKED) wsq = window_bounds(a.row_seq, it.row0 + orow, orow < it.nrows);
+  bf16x8 qreg[DQK / 16];
+  load_owner<DQK>(qreg, (const __bf16*)a.q + (int64_t)it.row0 * sq + h * DQK, sq, orow, it.nrows, hh);
+
+  f32x16 oacc[DV / 32];
+#pragma unroll
+  for (int i = 0; i < DV / 32; ++i)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) oacc[i][r] = 0.f;
+
+  const Stream st = make_stream<0>(it, a.causal);
+  const float c1 = -a.alpha * 1.4426950408889634f;
+  const int q_lo = it.pos0 + wave * 32, q_hi = q_lo + 31;
+  RowAddr<DQK> ra;
+  ColAddr<DV> ca;
+  ra.init(n, hh);
+  ca.init(lane);
+
+  auto copy = [&](int j, int b) {
+    const TileRef t = tile_ref(it, st, j);
+    tile_copy_async<DQK, NW>(kbuf(b), kg + (int64_t)t.row * sq, sq, t.valid, wave, lane);
+    tile_copy_async<DV, NW>(vbuf(b), vg + (int64_t)t.row * sv, sv, t.valid, wave, lane);
+  };
+  if (st.total > 0) copy(0, 0);
+  Window win = {};
+  if constexpr (PACKED) {  // (looked at only now that the first tile copies are on their way)
+    __builtin_amdgcn_sched_barrier(0);
+    win = make_window(wsq, it.row0 + orow, orow < it.nrows, 0, a.causal);
+  }
+  tile_copy_wait<0>();
+  tile_barrier();
+
+  auto block = [&](const char* kt, const char* vt, int blk, bool mask, const auto& vis) {
+    f32x16 s;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) s[r] = 0.f;
+#pragma unroll
+    for (int ks = 0; ks < DQK / 16; ++ks) s = mfma(ra.read(kt, blk, ks), qreg[ks], s);
+    float p[16];
+    // stage by stage over eight elements (see dq_block)
+#pragma unroll
+    for (int g = 0; g < 16; g += 8) {
+      float t[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) t[j] = s[g + j] * c1;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) t[j] = __builtin_amdgcn_exp2f(t[j]);
+#pragma unroll
+      for (int j = 0; j < 8; ++j) t[j] = 1.0f + t[j];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) t[j] = __builtin_amdgcn_rcpf(t[j]);
+#pragma unroll
+      for (int j = 0; j < 8; ++j) p[g + j] = s[g + j] * t[j];
+    }
+    if (mask) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) p[r] = vis(r) ? p[r] : 0.f;
+    }
+    const bf16x8 p0 = pack8(p), p1 = pack8(p + 8);
+#pragma unroll
+    for (int c = 0; c < DV / 32; ++c) {
+      oacc[c] = mfma(ca.read(vt, blk * 2, c), p0, oacc[c]);
+      oacc[c] = mfma(ca.read(vt, blk * 2 + 1, c), p1, oacc[c]);
+    }
+  };
+  auto step = [&](int j, auto buf_tag) {
+    constexpr int BUF = decltype(buf_tag)::value;
+    const TileRef tj = tile_ref(it, st, j);
+    if (j + 1 < st.total) copy(j + 1, BUF ^ 1);
+    if (wave_on) {
+#pragma unroll
+      for (int blk = 0; blk < ST / 32; ++blk) {
+        const int k_lo = tj.pos + blk * 32;
+        // no key of the block is visible (packed tiles: to no row of the wave)
+        if (blk * 32 >= tj.valid || (!PACKED && a.causal && k_lo > q_hi)) continue;
+        if (PACKED && (k_lo > win.hi_max || k_lo + 31 < win.lo_min)) continue;
+        if constexpr (PACKED) block(kbuf(BUF), vbuf(BUF), blk, win.masks(k_lo), win.vis(k_lo, hh));
+        else block(kbuf(BUF), vbuf(BUF), blk, a.causal && k_lo + 31 > q_lo, VisBefore{q_lo + n - k_lo, hh});
+      }
+    }
+    tile_copy_wait<0>();
+    tile_barrier();
+  };
+  for (int j = 0; j < st.total; j += 2) {
+    step(j, std::integral_constant<int, 0>{});
+    if (j + 1 < st.total) step(j + 1, std::integral_constant<int, 1>{});
+  }
+
+  // O^T accumulators: lane holds query row n, elements c*32 + 8*(r/4) + 4*hh + r%4.
+  if (orow < it.nrows) {
+    if (it.part > 0)
+      store_owner_major<DV>(a.partial, (((int64_t)(it.part - 1) * H + h) * (NW * 32) + orow) * DV, oacc,
+                            a.alpha * a.inv_n, hh, 0, 1);
+    else
+      store_owner_major<DV>(a.o, ((int64_t)it.row0 + orow) * sv + h * DV, oacc, a.alpha * a.inv_n, hh,
+                            a.accumulate, a.out_f32);
+  }
+}
+
+// =============================================================================================
 // Transposed copies of streamed tensors (see TrAddr): src [rows][H][D] -> dst [H][D][columns].
 // One workgroup per (64-row streamed tile, head); memory bound, a few percent of a pass.
 // =============================================================================================
@@ -356,6 +485,12 @@ hipError_t launch_transpose_bf16(const void* src, void* dst, const Plan& plan, i
 hipError_t launch_fwd_bf16(const AttnArgs& a, int d_qk, int d_v, hipStream_t stream) {
   if (a.vt == nullptr) {  // no transposed copy of V was built
     if (a.waves != 4) return hipErrorInvalidValue;
+    if (d_qk == 64 && d_v == 64 && !a.ts_rec && many_units(a)) {
+      const dim3 grid((unsigned)grid_units(a));
+      if (a.row_seq) hipLaunchKernelGGL((hstu_fwd_lean_bf16<64, 64, 4, true>), grid, dim3(256), 0, stream, a);
+      else hipLaunchKernelGGL((hstu_fwd_lean_bf16<64, 64, 4, false>), grid, dim3(256), 0, stream, a);
+      return hipGetLastError();
+    }
     if (a.row_seq) {
       if (a.ts_rec) HSTU_DISPATCH_BIAS(hstu_fwd_bf16, 4, 4, false, true, true);
       HSTU_DISPATCH_D(hstu_fwd_bf16, 4, 4, false, false, true);

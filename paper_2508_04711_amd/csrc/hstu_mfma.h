@@ -752,12 +752,26 @@ __device__ __forceinline__ void bwd_elem(float s, float dp, float c1, float alph
   ds = dp * __builtin_fmaf(alpha, __builtin_fmaf(-p, sg, p), sg);
 }
 
+// Workgroups a pass is launched with, one per unit.
+inline int64_t grid_units(const AttnArgs& a) {
+  return a.xcd_parts <= 1 ? (int64_t)a.max_items * a.num_heads
+                          : 8 * (((int64_t)a.max_items + a.xcd_parts - 1) / a.xcd_parts);
+}
+
+// Whether a pass has workgroups for at least two rounds of the 3 to 4 per CU that the one-block-at-a-time
+// kernels of d = 64 keep resident (hstu_fwd_lean_bf16, hstu_dkdv_lean_bf16): then what counts is how many waves
+// fill each other's gaps.  With fewer a workgroup's own latency decides, and the kernels that keep two blocks
+// in flight per wave are the faster ones.  Measured, d = 64, two in flight -> one (units): forward 1024
+// sequences of 400..800 rows, H = 8 (46 K) 880 -> 814 us; 64 of 100..1000, H = 8 (2.7 K) 59.9 -> 57.4; 16 of
+// 500..4000, H = 4 (1.2 K) 97.3 -> 99.6; 32 of 1..1024, H = 4 (0.6 K) 24.2 -> 26.5; backward 2711 -> 2432,
+// 168 -> 158, 279 -> 288, 62 -> 68.
+inline bool many_units(const AttnArgs& a) { return grid_units(a) > 2048; }
+
 // CAP > 0: at most that many workgroups (for kernels that walk over the (item, head) pairs).
 #define HSTU_DISPATCH_D(KERNEL, NW, ...) HSTU_DISPATCH_G(0, KERNEL, NW, __VA_ARGS__)
 #define HSTU_DISPATCH_G(CAP, KERNEL, NW, ...)                                           \
   do {                                                                                  \
-    const int64_t units_ = a.xcd_parts <= 1 ? (int64_t)a.max_items * a.num_heads        \
-                               : 8 * (((int64_t)a.max_items + a.xcd_parts - 1) / a.xcd_parts); \
+    const int64_t units_ = grid_units(a);                                               \
     const int64_t cap_ = (CAP);                                                         \
     const dim3 grid((unsigned)(cap_ > 0 && units_ > cap_ ? cap_ : units_)), block(NW * 64); \
     if (d_qk == 128 && d_v == 128) hipLaunchKernelGGL((KERNEL<128, 128, __VA_ARGS__>), grid, block, 0, stream, a); \
