@@ -149,8 +149,9 @@ struct BuiltPlan {
   bool natural;       // the items are in their natural order (those of a sequence are neighbours)
   bool chunks;        // dK/dV workgroups walk over contiguous runs of the list
   // How the kernels get their items: from a schedule sorted by plan_kernel, from one with a wave per
-  // item (launch_item_plans), or by working them out themselves.
-  enum { SORTED, DIRECT, SELF } form;
+  // item (launch_item_plans), in natural order from one built by many workgroups (launch_natural_plans),
+  // or by working them out themselves.
+  enum { SORTED, DIRECT, NATURAL, SELF } form;
   DirectPlan dp;
 };
 
@@ -252,7 +253,7 @@ int prepare_plan(const hstu_attn_params* p, int cp_size, const SideSpec& s, cons
   const int64_t longest = s.streamed_rows < p->max_len ? s.streamed_rows : (int64_t)p->max_len;
   int shift = 0;
   while (((longest / 32 + 4) >> shift) >= 2048) ++shift;
-  // When even the heaviest possible item is a small fraction of what one workgroup slot gets
+  // When even the heaviest possible item is a fraction of what one workgroup slot gets
   // to do in total (large batches), the order cannot unbalance the tail, and the natural order
   // keeps the items of a sequence, which share their streamed rows, together in time: one bin.
   // Both sides of the comparison in (owner row, streamed row) pairs: the heaviest item has at
@@ -270,7 +271,18 @@ int prepare_plan(const hstu_attn_params* p, int cp_size, const SideSpec& s, cons
   const int64_t batch = p->batch > 0 ? p->batch : 1;
   const int64_t all_pairs = s.owner_rows / batch * (s.streamed_rows / batch) / (p->causal ? 2 : 1) * batch;
   const int64_t per_slot = all_pairs / 512 * p->num_heads;
-  const bool large = (int64_t)tile_rows(p, s.pass, s.owner_rows) * longest * 8 < per_slot;
+  // How small a fraction: a half in the forward pass, which reads the streamed rows of neighbours from one
+  // L2 and loses more to the sorted order than to an uneven tail even where the longest sequences come last
+  // (H = 4, d = 128, sorted -> natural: 512 sequences of 300..600 rows 392 -> 276 us, 256 of them 162 -> 152; 768
+  // with lognormal lengths of median 256 372 -> 324, sorted by length 369 -> 364).  A third in the dq pass, whose items
+  // last longer (bwd: 256 lognormal of median 512, H = 8, a fraction of 1/3.4, 2036 -> 1917, but 64 of 500..1000, H = 8,
+  // 1/2.2, 497 -> 509 and 768 of median 256 sorted by length, 1/2.6, 1124 -> 1164).  A quarter on the key side at two
+  // and three workgroups per CU (H = 8, d = 64: 400 lognormal of median 512 fwd + bwd 2165 -> 1964; at a half 128 of
+  // 400..800 rows lose 2 %).  An eighth where walking workgroups take runs of equal numbers of items (256
+  // lognormal of median 512, H = 8, d = 128: bwd 2070 -> 2470 at a half, and 1536 of median 256 sorted by length 2262
+  // -> 2669 at a quarter).
+  const int64_t fraction = s.pass == PASS_FWD ? 2 : s.pass == PASS_DQ ? 3 : (p->d_qk + p->d_v <= 128 ? 4 : 8);
+  const bool large = (int64_t)tile_rows(p, s.pass, s.owner_rows) * longest * fraction < per_slot;
   // The dK/dV pass at one workgroup per CU walks over the list (see launch_dkdv_bf16): in natural
   // order when its workgroups can take contiguous runs of one XCD's share, which needs a head
   // count that divides 8; sorted by cost, every 256th item, otherwise.
@@ -315,6 +327,8 @@ int prepare_plan(const hstu_attn_params* p, int cp_size, const SideSpec& s, cons
   // 1..1024 rows forward 39 -> 30 us.  Beyond that the 0.5 us per item, which nothing overlaps at one
   // workgroup per CU, costs more than the launch (16 sequences of 512..4096 rows: dk/dv 254 -> 269 us).
   out->form = BuiltPlan::SORTED;
+  if (out->natural && p->batch >= 1 && p->batch <= NATURAL_BATCH && s.owner_rank < 0 && s.streamed_rank < 0 && !want_ttile)
+    out->form = BuiltPlan::NATURAL;
   if (p->batch <= DIRECT_BATCH && !out->natural && !large && !want_ttile) {
     const int64_t resident = s.side == 1 && p->d_qk + p->d_v > 128 ? 256 : 512;
     out->form = p->batch <= SELF_BATCH && split <= 1 && max_items * p->num_heads <= 2 * resident ? BuiltPlan::SELF : BuiltPlan::DIRECT;
@@ -387,10 +401,11 @@ int make_tcopy(const hstu_attn_params* p, const SideSpec& s, const BuiltPlan& bp
 
 // Builds those of up to three prepared schedules that the kernels will read, in one launch.
 int launch_built(const PlanArgs* args, const BuiltPlan* const* plans, int count, hipStream_t stream) {
-  PlanArgs need[3];
+  PlanArgs need[3], natural[3];
   ItemPlans items;
-  int n = 0, m = 0;
+  int n = 0, m = 0, k = 0;
   for (int i = 0; i < count; ++i) {
+    if (plans[i]->form == BuiltPlan::NATURAL) natural[k++] = args[i];
     if (plans[i]->form == BuiltPlan::SORTED) need[n++] = args[i];
     if (plans[i]->form == BuiltPlan::DIRECT) {
       items.p[m++] = ItemPlan{plans[i]->dp, args[i].items, args[i].header, args[i].red, args[i].max_items};
@@ -399,6 +414,10 @@ int launch_built(const PlanArgs* args, const BuiltPlan* const* plans, int count,
   if (n > 0) {
     TimedLaunch timed(3, stream);
     if (launch_plans(need, n, stream) != hipSuccess) return HSTU_ERR_HIP;
+  }
+  if (k > 0) {
+    TimedLaunch timed(3, stream);
+    if (launch_natural_plans(natural, k, stream) != hipSuccess) return HSTU_ERR_HIP;
   }
   if (m > 0) {
     TimedLaunch timed(3, stream);

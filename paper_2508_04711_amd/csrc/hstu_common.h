@@ -413,6 +413,9 @@ hipError_t launch_item_plans(const ItemPlans& a, int count, hipStream_t stream);
 
 // Builds up to three schedules in one launch (one workgroup each).
 hipError_t launch_plans(const PlanArgs* a, int count, hipStream_t stream);
+// Schedules of whole batches in natural order (uncut tiles, no table of streamed tiles) of at most that many sequences.
+constexpr int NATURAL_BATCH = 1 << 16;
+hipError_t launch_natural_plans(const PlanArgs* a, int count, hipStream_t stream);
 
 // What the kernels need to know about a row's timestamp: the timestamp itself and the range of
 // the timestamps of the (up to) 32 rows of the same sequence that start at this row, from which

@@ -578,6 +578,67 @@ hipError_t launch_item_plans(const ItemPlans& a, int count, hipStream_t stream) 
   return hipGetLastError();
 }
 
+namespace {
+
+// A schedule in natural order of a whole batch: a workgroup per NAT_SEQS sequences.  It counts the tiles of all
+// sequences before its own (every workgroup again, from the cache: 64 K sequences at most), which is where
+// its items begin in the list, and writes its items, one per thread.  plan_kernel's one workgroup took 33 us
+// on 1536 sequences of 300..600 rows, 24 us on 1024 of 400..800; now 5.
+constexpr int NAT_SEQS = 64, NAT_THREADS = 256;
+__global__ void __launch_bounds__(NAT_THREADS) natural_plan_kernel(PlanArgs a0, PlanArgs a1, PlanArgs a2) {
+  __shared__ int sums[NAT_THREADS / 64], first[NAT_SEQS + 1];
+  const PlanArgs& a = blockIdx.y == 0 ? a0 : (blockIdx.y == 1 ? a1 : a2);
+  const int tid = threadIdx.x, b0 = blockIdx.x * NAT_SEQS;
+  auto tiles = [&](int b) {
+    int s, e;
+    seq_range(a.off, b, a.total_rows, s, e);
+    return (e - s) / a.tile + ((e - s) % a.tile ? 1 : 0);
+  };
+  int before = 0;
+  for (int b = tid; b < b0; b += NAT_THREADS) before += tiles(b);
+  before = wave_total(before);
+  if ((tid & 63) == 0) sums[tid >> 6] = before;
+  if (tid < 64) {  // (NAT_SEQS is a wave's width)
+    first[tid + 1] = wave_scan(b0 + tid < a.batch ? tiles(b0 + tid) : 0);
+    if (tid == 0) first[0] = 0;
+  }
+  __syncthreads();
+  const int base = sums[0] + sums[1] + sums[2] + sums[3], count = first[NAT_SEQS];
+  for (int i = tid; i < count; i += NAT_THREADS) {
+    int lo = 0;
+#pragma unroll
+    for (int step = NAT_SEQS / 2; step >= 1; step >>= 1)
+      if (first[lo + step] <= i) lo += step;
+    int s, e, pvis[2];
+    seq_range(a.off, b0 + lo, a.total_rows, s, e);
+    const Side side = make_side(e - s, 1, -1);
+    const int slot = base + i;
+    if (slot < a.max_items) {
+      a.items[slot] = describe_item(side, side, 0, i - first[lo], s, s, 0, a.tile, a.causal, a.side, a.owner_rows,
+                                    a.streamed_rows, pvis);
+      a.order[slot] = slot;
+    }
+  }
+  if (blockIdx.x == gridDim.x - 1 && tid == 0) {
+    a.header[0] = base + count < a.max_items ? base + count : a.max_items;
+    a.header[1] = 0;
+    a.header[2] = 0;
+  }
+}
+
+}  // namespace
+
+hipError_t launch_natural_plans(const PlanArgs* a, int count, hipStream_t stream) {
+  if (count < 1 || count > 3) return hipErrorInvalidValue;
+  for (int i = 0; i < count; ++i)
+    if (a[i].batch != a[0].batch || a[i].batch < 1 || a[i].batch > NATURAL_BATCH || a[i].owner_rank >= 0 ||
+        a[i].streamed_rank >= 0 || a[i].split_max > 1)
+      return hipErrorInvalidValue;
+  hipLaunchKernelGGL(natural_plan_kernel, dim3((unsigned)((a[0].batch + NAT_SEQS - 1) / NAT_SEQS), (unsigned)count),
+                     dim3(NAT_THREADS), 0, stream, a[0], a[count > 1 ? 1 : 0], a[count - 1]);
+  return hipGetLastError();
+}
+
 hipError_t launch_plans(const PlanArgs* a, int count, hipStream_t stream) {
   static_assert(NBINS == 2 * PLAN_THREADS, "pass 3 handles two bins per thread");
   if (count < 1 || count > 3) return hipErrorInvalidValue;
