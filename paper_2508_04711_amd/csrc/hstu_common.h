@@ -241,9 +241,11 @@ struct DirectSlot { int tile, part, parts, cut_tiles; };
 // Per owner segment (one per sequence, two in a rank's layout) the levels either are consecutive -
 // the diagonal runs through what the segment sees: each query tile sees one tile of keys more than
 // the one before, each key tile one tile of queries less - or all the same (no mask, or another
-// rank's mini-chunks, which lie wholly before or after).  (Keys of the whole batch against one rank's
-// queries are ordered by their distance from the sequence's end, which has the same order.)  So the
-// number of tiles at or above a level is one clamp per lane and a sum over lanes; a bisection over
+// rank's mini-chunks, which lie wholly before or after).  Keys of the whole batch against one rank's
+// queries ("stairs") see what is left of the rank's two mini-chunks: flat, a ramp, flat, a ramp, nothing.
+// (Ordered by their distance from the sequence's end instead, heavy tiles of one sequence came after light ones
+// of a longer one: dk/dv of one of four ranks, 8 sequences of 4096..16384 rows, 371 -> 395 us.)  So the
+// number of tiles at or above a level is a clamp per lane and a sum over lanes; a bisection over
 // levels finds the item's, a ballot the sequence.  About 0.5 us for K = 1.
 // Cut tiles: a tile of level w has parts(w) = clamp(w * tile / 32 / split_blocks, 1, split_max) items,
 // neighbours in the order, so the items at or above a level are sums of the same counts.
@@ -252,16 +254,22 @@ __device__ __forceinline__ DirectSlot direct_item(const DirectPlan& d, int slot,
   const int lane = threadIdx.x & 63;
   int s[K], e[K], n[K][2], top[K][2], rows[K];  // per owner segment: tiles, highest level
   bool ramp[K][2];                              // consecutive levels
+  const bool stairs = d.side == 1 && d.owner_rank < 0 && d.streamed_rank >= 0 && d.causal;
+  int end0[K], len1[K], end1[K], all[K];        // stairs: the rank's mini-chunks of the sequence (all: rows of both)
+  const int tile_log2 = 31 - __builtin_clz(d.tile);  // (a power of two)
 #pragma unroll
   for (int k = 0; k < K; ++k) {
     s[k] = e[k] = n[k][0] = n[k][1] = top[k][0] = top[k][1] = rows[k] = 0;
     ramp[k][0] = ramp[k][1] = false;
+    end0[k] = len1[k] = end1[k] = all[k] = 0;
     if (k * 64 < d.batch) {
       if (k * 64 + lane < d.batch) seq_range(d.off, k * 64 + lane, d.total_rows, s[k], e[k]);
       const int len = e[k] - s[k];
       const Side so = make_side(len, d.cp, d.owner_rank);
       Side ss = make_side(len, d.cp, d.streamed_rank);
-      if (d.side == 1 && d.owner_rank < 0) ss = make_side(len, 1, -1);  // (see above)
+      if (stairs) {
+        end0[k] = ss.pos[0] + ss.len[0]; len1[k] = ss.len[1]; end1[k] = ss.pos[1] + ss.len[1]; all[k] = ss.rows;
+      }
       rows[k] = so.rows;
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
@@ -285,6 +293,13 @@ __device__ __forceinline__ DirectSlot direct_item(const DirectPlan& d, int slot,
     }
   }
   auto at_least = [&](int k, int u, int v) {  // tiles of the lane's segment (k, u) at level v or above
+    if (stairs) {  // keys whose tile begins at or before the last position that sees more than v - 1 tiles of queries
+      if (u || v <= 1) return u ? 0 : n[k][0];
+      const int x = (v - 1) * d.tile + 1;
+      const int last = x <= len1[k] ? end1[k] - x : end0[k] + len1[k] - x;
+      const int c = x <= all[k] ? (last >> tile_log2) + 1 : 0;
+      return c < n[k][0] ? c : n[k][0];
+    }
     const int x = top[k][u] - v + 1;
     return ramp[k][u] ? (x < 0 ? 0 : (x < n[k][u] ? x : n[k][u])) : (x > 0 ? n[k][u] : 0);
   };
@@ -337,7 +352,8 @@ __device__ __forceinline__ DirectSlot direct_item(const DirectPlan& d, int slot,
           sb = __builtin_amdgcn_readlane(s[k], l);
           eb = __builtin_amdgcn_readlane(e[k], l);
           const int below = __builtin_amdgcn_readlane(top[k][g], l) - lo;  // tiles between the item and the heaviest
-          t = !__builtin_amdgcn_readlane((int)ramp[k][g], l)
+          t = stairs ? __builtin_amdgcn_readlane(at_least(k, g, lo + 1), l) + rem - __builtin_amdgcn_readlane(inc - mine, l)
+              : !__builtin_amdgcn_readlane((int)ramp[k][g], l)
                   ? rem - __builtin_amdgcn_readlane(inc - mine, l)
                   : (d.side == 0 ? __builtin_amdgcn_readlane(n[k][g], l) - 1 - below : below);
           found = true;

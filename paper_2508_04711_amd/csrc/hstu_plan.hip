@@ -583,11 +583,12 @@ namespace {
 // A schedule in natural order of a whole batch: a workgroup per NAT_SEQS sequences.  It counts the tiles of all
 // sequences before its own (every workgroup again, from the cache: 64 K sequences at most), which is where
 // its items begin in the list, and writes its items, one per thread.  plan_kernel's one workgroup took 33 us
-// on 1536 sequences of 300..600 rows, 24 us on 1024 of 400..800; now 5.
+// on 1536 sequences of 300..600 rows, 26 us on 1024 of 400..800; now 6 on either.
 constexpr int NAT_SEQS = 64, NAT_THREADS = 256;
-__global__ void __launch_bounds__(NAT_THREADS) natural_plan_kernel(PlanArgs a0, PlanArgs a1, PlanArgs a2) {
+struct NaturalPlans { PlanArgs p[3]; };
+__global__ void __launch_bounds__(NAT_THREADS) natural_plan_kernel(NaturalPlans plans) {
   __shared__ int sums[NAT_THREADS / 64], first[NAT_SEQS + 1];
-  const PlanArgs& a = blockIdx.y == 0 ? a0 : (blockIdx.y == 1 ? a1 : a2);
+  const PlanArgs& a = plans.p[blockIdx.y];
   const int tid = threadIdx.x, b0 = blockIdx.x * NAT_SEQS;
   auto tiles = [&](int b) {
     int s, e;
@@ -634,8 +635,10 @@ hipError_t launch_natural_plans(const PlanArgs* a, int count, hipStream_t stream
     if (a[i].batch != a[0].batch || a[i].batch < 1 || a[i].batch > NATURAL_BATCH || a[i].owner_rank >= 0 ||
         a[i].streamed_rank >= 0 || a[i].split_max > 1)
       return hipErrorInvalidValue;
+  NaturalPlans plans;
+  for (int i = 0; i < 3; ++i) plans.p[i] = a[i < count ? i : 0];
   hipLaunchKernelGGL(natural_plan_kernel, dim3((unsigned)((a[0].batch + NAT_SEQS - 1) / NAT_SEQS), (unsigned)count),
-                     dim3(NAT_THREADS), 0, stream, a[0], a[count > 1 ? 1 : 0], a[count - 1]);
+                     dim3(NAT_THREADS), 0, stream, plans);
   return hipGetLastError();
 }
 
