@@ -331,9 +331,12 @@ int prepare_plan(const hstu_attn_params* p, int cp_size, const SideSpec& s, cons
     out->form = BuiltPlan::NATURAL;
   // The order is that of whole tiles' cost, so parts of a tile cut into many would run before uncut tiles of
   // more cost than a part: from three parts on plan_kernel sorts the parts (one of two ranks, 2 sequences of
-  // 4065..16260 rows, H = 2: 505 -> 469 us; with two parts the order is worth less than the launch, 908 -> 895 us for one
+  // 4065..16260 rows, H = 2: 505 -> 476 us; with two parts the order is worth less than the launch, 908 -> 895 us for one
   // of four ranks, 8 of 4096..16384, H = 4).
-  if (p->batch <= DIRECT_BATCH && split <= 2 && !out->natural && !large && !want_ttile) {
+  // (The key side follows the query side of the same call, so that all its schedules come from one launch.)
+  const SideSpec queries = {0, PASS_DQ, s.streamed_rank, s.owner_rank, s.streamed_rows, s.owner_rows, s.ssegs, s.segs};
+  const int parts = s.side == 0 ? split : split_of(p, queries);
+  if (p->batch <= DIRECT_BATCH && parts <= 2 && !out->natural && !large && !want_ttile) {
     const int64_t resident = s.side == 1 && p->d_qk + p->d_v > 128 ? 256 : 512;
     out->form = p->batch <= SELF_BATCH && split <= 1 && max_items * p->num_heads <= 2 * resident ? BuiltPlan::SELF : BuiltPlan::DIRECT;
   }
