@@ -1,6 +1,6 @@
 // fp32 jagged HSTU attention (forward, dk/dv pass, dq pass): the all-fp32 data type of the
-// library, on the fp32 matrix instruction (products and sums in fp32), with IEEE division and the
-// precise exponential, so that results stay within 1e-5 of a double-precision evaluation of the
+// library, on the fp32 matrix instruction (products and sums in fp32), with a sigmoid to about an ulp
+// (see sigmoid_precise), so that results stay within 1e-5 of a double-precision evaluation of the
 // section 2.1 equation.
 //
 //   v_mfma_f32_32x32x2_f32  D[32x32] += A[32x2] * B[2x32]   (lane l: n = l%32, hh = l/32)
@@ -149,20 +149,24 @@ __device__ __forceinline__ void sum_and_store(float* buf, const f32x16 (&acc)[D 
   }
 }
 
-// sigmoid(x) = 1 / (1 + e^-x) to about an ulp.  e^y as 2^t with t = y * log2(e) rounded and the
-// product's rounding error carried as a first-order factor (1 + ln2 * error), so that a large |y|
-// costs no accuracy; the reciprocal with one Newton step.  y is kept below 87, where e^y is still
-// finite (x < -87: sigmoid is below 2e-38, and x * sigmoid below 1e-33 for any finite fp32 score of
-// this operator).  Twelve vector instructions against 27 for expf and an IEEE division.
+// sigmoid(x) to about an ulp, from z = e^-|x| <= 1, which overflows nowhere: 1 / (1 + z) for x >= 0,
+// z / (1 + z) below.  z as 2^t with t = -|x| * log2(e) rounded and the product's rounding error carried as a
+// first-order factor (1 + ln2 * error), so that a large |x| costs no accuracy; the reciprocal with one
+// Newton step.  |x| is cut at 104, where z is exactly zero: the sigmoid of anything beyond, infinities
+// included, is exactly 0 or 1 (an |x| that were not cut would make the error term infinite times zero, a
+// z that were kept above zero would let x * sigmoid(x) grow with -x).  NaN stays NaN in x * sigmoid(x).
+// Fourteen vector instructions against 27 for expf and an IEEE division.
 __device__ __forceinline__ float sigmoid_precise(float x) {
   constexpr float LOG2E = 1.44269504088896341f, LOG2E_LO = 1.92596299e-8f, LN2 = 0.693147180559945309f;
-  const float y = __builtin_fminf(-x, 87.0f);
+  const float y = -__builtin_fminf(__builtin_fabsf(x), 104.0f);
   const float t = y * LOG2E;
   const float err = __builtin_fmaf(y, LOG2E_LO, __builtin_fmaf(y, LOG2E, -t));
   const float e = __builtin_amdgcn_exp2f(t);
-  const float d = 1.0f + __builtin_fmaf(e, err * LN2, e);
+  const float z = __builtin_fmaf(e, err * LN2, e);
+  const float d = 1.0f + z;
   const float r = __builtin_amdgcn_rcpf(d);
-  return __builtin_fmaf(__builtin_fmaf(-d, r, 1.0f), r, r);
+  const float s = __builtin_fmaf(__builtin_fmaf(-d, r, 1.0f), r, r);
+  return x < 0.0f ? z * s : s;
 }
 
 // The streamed blocks of an item: [first, end) of Stream's 32-row blocks, without the leading block

@@ -1,6 +1,8 @@
 """The fp32 kernels at the sizes where their split can go wrong: lengths around one 32-row block, around
 one block for each of a workgroup's four waves, around a 64-row step of the stream, at every head
-dimension; and scores large enough that the sigmoid saturates both ways.  Bar: the stated 1e-5 x RMS."""
+dimension; scores large enough that the sigmoid saturates both ways, and scores over the whole range of fp32.
+Bar: the stated 1e-5 x RMS, or 1e-6 of the value where a result has one term."""
+import numpy as np
 import pytest
 import torch
 
@@ -22,7 +24,72 @@ def test_block_edges(dqk, dv, causal):
 
 @pytest.mark.parametrize("d", [32, 128])
 def test_saturated_scores(d):
-    # alpha * q.k has a standard deviation of 64: beyond +-87 the exponential's argument is clamped
+    # alpha * q.k has a standard deviation of 64: many scores lie beyond what the exponential resolves
     print("f32 saturated", d, flush=True)
     w = workloads.custom("f32_saturated", [200, 33], 2, d, d, max_len=200, dtype="f32", scale=8.0, seed=43)
     _run_full(w, causal=True, backward=True)
+
+
+# x = alpha * q.k of one pair: silu(x) is x above ~17 and 0 below ~-104, to the end of fp32's range
+EXTREME = [-3.4e38, -3e37, -1e30, -1e6, -120.0, -104.5, -103.0, -30.0, -1.0, 0.0, 1.0, 30.0, 88.5, 103.0, 1e6, 1e30, 3e37,
+           2.5e38, 3.4e38]
+
+
+def _silu64(x):
+    """silu and its derivative in 64 bits; the sigmoid of the far negative side without overflow."""
+    z = np.exp(-np.abs(x))
+    sg = np.where(x >= 0, 1.0, z) / (1.0 + z)
+    return x * sg, sg * (1.0 + x * (1.0 - sg))
+
+
+@pytest.mark.parametrize("d", [32, 128])
+def test_scores_over_the_whole_range(d):
+    """Sequences of one row: one pair each, so every output is one term."""
+    import paper_2508_04711_amd as lib
+    print("f32 extreme scores", d, flush=True)
+    x = np.array(EXTREME, dtype=np.float32)
+    n = len(x)
+    zero = lambda: torch.zeros((n, 1, d), dtype=torch.float32, device="cuda")
+    q, k, v, do = zero(), zero(), zero(), zero()
+    qs = np.where(np.abs(x) > 1e6, np.float32(1e19), np.float32(1))
+    ks = (x / qs).astype(np.float32)
+    q[:, 0, 0], k[:, 0, 0] = torch.from_numpy(qs).cuda(), torch.from_numpy(ks).cuda()
+    v[:, 0, 1], do[:, 0, 1] = 0.5, 0.25
+    off = torch.arange(n + 1, dtype=torch.int32, device="cuda")
+    o = lib.hstu_jagged_attn_fwd(q, k, v, off, 1, 1.0, True)
+    dq, dk, dv = lib.hstu_jagged_attn_bwd(q, k, v, do, off, 1, 1.0, True)
+    xx = (qs * ks).astype(np.float64)  # the product as fp32 rounds it
+    p, dp = _silu64(xx)
+    ds = 0.125 * dp
+    # a term below fp32's smallest normal number may be flushed to zero
+    for name, got, want in (("o", o[:, 0, 1], p * 0.5), ("dv", dv[:, 0, 1], p * 0.25), ("dq", dq[:, 0, 0], ds * ks),
+                            ("dk", dk[:, 0, 0], ds * qs)):
+        g = got.double().cpu().numpy()
+        bad = np.abs(g - want) > 1e-6 * np.abs(want) + 1e-35
+        assert not bad.any(), (name, x[bad], g[bad], want[bad])
+
+
+def test_table_entries_at_the_ends_of_the_range():
+    """A timestamp table whose entries are fp32's lowest value (a mask), its highest and infinity."""
+    import paper_2508_04711_amd as lib
+    print("f32 extreme table", flush=True)
+    big = float(np.finfo(np.float32).max)
+    ts = torch.tensor([0, 0, 2, 4, 8], dtype=torch.int32, device="cuda")
+    off = torch.tensor([0, 2, 5], dtype=torch.int32, device="cuda")
+    g = torch.Generator(device="cuda").manual_seed(3)
+    q, k = [torch.randn((5, 1, 32), generator=g, device="cuda") for _ in range(2)]
+    v = torch.full((5, 1, 32), 1e-3, device="cuda")
+    alpha = 32 ** -0.5
+
+    def want(bias):  # o of row 4 from its pairs with rows 2, 3, 4
+        s = (q[4, 0].double() @ k[2:5, 0].double().T).cpu().numpy() + np.array(bias)
+        return float(np.sum(_silu64(alpha * s)[0]) * 1e-3)
+
+    def last(tab):
+        return float(lib.hstu_jagged_attn_bias_fwd(q, k, v, off, ts, tab, 0, 1, alpha, True)[4, 0, 0])
+    # differences 6, 4, 0 of the last row's pairs: buckets 2, 2, 0
+    masked = torch.tensor([0.25, 0.5, -big], dtype=torch.float32, device="cuda")
+    assert abs(last(masked) - want([-big, -big, 0.25])) <= 1e-5 * abs(want([-big, -big, 0.25])) + 1e-9
+    high = torch.tensor([0.25, 0.5, big / 4], dtype=torch.float32, device="cuda")
+    assert abs(last(high) / want([big / 4, big / 4, 0.25]) - 1) <= 1e-5
+    assert last(torch.tensor([0.25, 0.5, float("inf")], dtype=torch.float32, device="cuda")) == float("inf")
