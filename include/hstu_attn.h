@@ -65,7 +65,8 @@ typedef enum {
                                         >= 2^31, max_len < 1, alpha not finite              */
   HSTU_ERR_UNSUPPORTED = -3,         /* head dim not in {32,64,128}, unknown dtype, out_dtype
                                         neither dtype nor fp32, unknown bits in flags       */
-  HSTU_ERR_WORKSPACE_TOO_SMALL = -4, /* workspace_bytes below the query function's answer   */
+  HSTU_ERR_WORKSPACE_TOO_SMALL = -4, /* workspace_bytes below the query function's answer
+                                        (fp32: below what the shorter lists need)           */
   HSTU_ERR_BAD_CP = -5,              /* cp_size < 1, a rank out of range, negative rows     */
   HSTU_ERR_HIP = -6,                 /* a HIP call failed; hipGetLastError() is left intact */
   HSTU_ERR_MISALIGNED = -7,          /* a data pointer is not 16-byte aligned               */
@@ -155,7 +156,7 @@ int hstu_jagged_attn_fwd(const hstu_attn_params* params, const void* q, const vo
  * transposed copy of V and the partial results of split tiles live in a static device array of
  * HSTU_STATIC_SCRATCH_BYTES inside the library, which every GPU the library runs on holds until
  * the process ends.  A problem whose hstu_jagged_attn_workspace_bytes(params, HSTU_WS_FWD) exceeds
- * that size is refused with HSTU_ERR_STATIC_SCRATCH and nothing is launched (a schedule needs a few
+ * that size (fp32: with lists of 64-row items, see there) is refused with HSTU_ERR_STATIC_SCRATCH and nothing is launched (a schedule needs a few
  * hundred bytes per sequence and 64 per 128 rows; a forced tile height adds a copy of V; from
  * max_len 4096 on a call may need up to
  * (rows / 128 + batch + 1024 / num_heads + 2) * num_heads * 128 * d_v * 4 bytes of partial results).
@@ -354,7 +355,9 @@ int hstu_cp_reorder(int32_t batch, int64_t total_rows, int32_t cp_size, int32_t 
  * Schedules, plus for bf16 forward passes with a forced tile height a transposed copy of V, plus
  * fp32 partial results where heavy
  * query tiles may be cut along the keys, plus 8 bytes per row for packed tiles.  The flags
- * change the answer: ask with the flags of the call.
+ * change the answer: ask with the flags of the call.  (fp32 calls also take a workspace with room for
+ * lists of 64-row items, about half of the answer where rows are many, and then list those instead of
+ * 32-row items: the same results, somewhat slower.)
  * `which` is a hstu_ws_kind. */
 size_t hstu_jagged_attn_workspace_bytes(const hstu_attn_params* params, int which);
 

@@ -124,8 +124,13 @@ int pass_waves(const hstu_attn_params* p, int pass, int64_t owner_rows) {
   if (pass == PASS_FWD && (p->flags & HSTU_FLAG_FWD_TILE_256)) return 8;
   return waves_bf16(pass, owner_rows, p->num_heads);
 }
+// fp32 schedules list items of 32 rows, one workgroup each - or, where the workspace has no room for
+// that list, of 64 rows shared by two workgroups (the same results bit for bit, up to a fifth slower): a workspace
+// or the static array that holds the shorter list is enough.  An internal bit of the flags, see fits().
+constexpr int32_t F32_TALL = 1 << 30;
+int f32_parts(const hstu_attn_params* p) { return (p->flags & F32_TALL) ? 2 : 1; }
 int tile_rows(const hstu_attn_params* p, int pass, int64_t owner_rows) {
-  return p->dtype == HSTU_BF16 ? 32 * pass_waves(p, pass, owner_rows) : tile_rows_f32(pass);
+  return p->dtype == HSTU_BF16 ? 32 * pass_waves(p, pass, owner_rows) : tile_rows_f32(pass) * f32_parts(p);
 }
 
 // One schedule: who owns, who is streamed, how many rows each side's buffers hold.
@@ -159,7 +164,7 @@ struct BuiltPlan {
 // it holds whichever variant the problem size selects (surplus workgroups exit at once).
 int64_t items_bound(const hstu_attn_params* p, const SideSpec& s) {
   return max_items_bound(s.owner_rows, p->batch, s.segs,
-                         p->dtype == HSTU_BF16 ? 128 : tile_rows_f32(s.pass));
+                         p->dtype == HSTU_BF16 ? 128 : tile_rows_f32(s.pass) * f32_parts(p));
 }
 
 // Bound on the 64-row tiles of the streamed side (the transposed copies have 64 columns each).
@@ -458,6 +463,7 @@ AttnArgs base_args(const hstu_attn_params* p, const BuiltPlan& bp, int accumulat
   a.xcd_parts = bp.natural && p->dtype == HSTU_BF16 && p->num_heads < 8 && 8 % p->num_heads == 0
                     ? 8 / p->num_heads : 1;
   a.out_f32 = p->out_dtype == HSTU_F32 ? 1 : 0;
+  a.item_parts = f32_parts(p);
   a.single_segment = bp.dp.streamed_rank < 0;
   a.dkdv_one_wave = (p->flags & HSTU_FLAG_DKDV_ONE_WAVE) ? 1 : 0;
   a.bias_per_pair = (p->flags & HSTU_FLAG_BIAS_PER_PAIR) ? 1 : 0;
@@ -603,9 +609,8 @@ int hstu_schedule_tile_rows(const hstu_attn_params* params, int side) {
   return tile_rows(params, side == 0 ? PASS_FWD : PASS_DKDV, params->total_rows);
 }
 
-size_t hstu_jagged_attn_workspace_bytes(const hstu_attn_params* params, int which) {
-  if (check_params(params) != HSTU_OK) return 0;
-  const hstu_attn_params* p = params;
+// hstu_jagged_attn_workspace_bytes of checked parameters.
+static size_t workspace_bytes_of(const hstu_attn_params* p, int which) {
   size_t end = 0;
   bool too_large = false;
   // Each pass: its schedule, then the transposed copies of the tensors it streams (bf16 only).
@@ -640,12 +645,45 @@ size_t hstu_jagged_attn_workspace_bytes(const hstu_attn_params* params, int whic
   return end + 4096;  // slack for the 256-byte alignment of each piece
 }
 
-size_t hstu_jagged_attn_bias_workspace_bytes(const hstu_attn_params* params, int which) {
-  if (which != HSTU_WS_FWD && which != HSTU_WS_BWD && which != HSTU_WS_CP) return 0;
-  const size_t plain = hstu_jagged_attn_workspace_bytes(params, which);
+static size_t bias_workspace_bytes_of(const hstu_attn_params* p, int which) {
+  const size_t plain = workspace_bytes_of(p, which);
   if (!plain) return 0;
   // one array of records, or one per side (neither side holds more rows than the whole batch)
-  return plain + bias_front_bytes(params, which == HSTU_WS_CP ? 2 : 1);
+  return plain + bias_front_bytes(p, which == HSTU_WS_CP ? 2 : 1);
+}
+
+// Points `p` at `*tall`, the same parameters with the shorter fp32 list, if the longer one would need more
+// workgroups than a launch can have (2^32 threads).
+static bool f32_tall(const hstu_attn_params*& p, hstu_attn_params* tall, bool always) {
+  if (p->dtype != HSTU_F32) return false;
+  const int64_t workgroups = (p->total_rows / tile_rows_f32(PASS_FWD) + 2 * (int64_t)p->batch + 1) * p->num_heads;
+  if (!always && workgroups < (1 << 24)) return false;
+  *tall = *p;
+  tall->flags |= F32_TALL;
+  p = tall;
+  return true;
+}
+
+size_t hstu_jagged_attn_workspace_bytes(const hstu_attn_params* params, int which) {
+  if (check_params(params) != HSTU_OK) return 0;
+  hstu_attn_params tall;
+  f32_tall(params, &tall, false);
+  return workspace_bytes_of(params, which);
+}
+
+size_t hstu_jagged_attn_bias_workspace_bytes(const hstu_attn_params* params, int which) {
+  if (check_params(params) != HSTU_OK) return 0;
+  hstu_attn_params tall;
+  f32_tall(params, &tall, false);
+  return bias_workspace_bytes_of(params, which);
+}
+
+// Whether a workspace of `bytes` serves a call with checked parameters (fp32: with the shorter list, which `p` is
+// then pointed at, if not with the other).
+static bool fits(const hstu_attn_params*& p, hstu_attn_params* tall, int which, bool bias, size_t bytes) {
+  auto enough = [&] { return bytes >= (bias ? bias_workspace_bytes_of(p, which) : workspace_bytes_of(p, which)); };
+  f32_tall(p, tall, false);
+  return enough() || (f32_tall(p, tall, true) && enough());
 }
 
 // Forward over the whole batch, with the timestamp bias if `bias` is not null.
@@ -659,9 +697,8 @@ static int fwd_impl(const hstu_attn_params* params, const hstu_ts_bias* bias, co
   if (!q || !k || !v || !o || !seq_offsets || !workspace) return HSTU_ERR_NULL_PTR;
   if (!aligned16(q) || !aligned16(k) || !aligned16(v) || !aligned16(o) || !aligned16(workspace))
     return HSTU_ERR_MISALIGNED;
-  if (workspace_bytes < (bias ? hstu_jagged_attn_bias_workspace_bytes(params, HSTU_WS_FWD)
-                              : hstu_jagged_attn_workspace_bytes(params, HSTU_WS_FWD)))
-    return HSTU_ERR_WORKSPACE_TOO_SMALL;
+  hstu_attn_params tall;
+  if (!fits(params, &tall, HSTU_WS_FWD, bias != nullptr, workspace_bytes)) return HSTU_ERR_WORKSPACE_TOO_SMALL;
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
   const size_t first = bias ? bias_front_bytes(params, 1) : 0;  // the records come first
   // (packed tiles: a block's rows may belong to several sequences, so a record's range covers
@@ -744,8 +781,10 @@ int hstu_jagged_attn_fwd_static(const hstu_attn_params* params, const void* q, c
   if (rc != HSTU_OK) return rc;
   if (params->batch == 0 || params->total_rows == 0) return HSTU_OK;
   if (!q || !k || !v || !o || !seq_offsets) return HSTU_ERR_NULL_PTR;
-  const size_t need = hstu_jagged_attn_workspace_bytes(params, HSTU_WS_FWD);
-  if (need == 0 || need > STATIC_SCRATCH_BYTES) return HSTU_ERR_STATIC_SCRATCH;
+  const hstu_attn_params* p = params;
+  hstu_attn_params tall;
+  if (!fits(p, &tall, HSTU_WS_FWD, false, STATIC_SCRATCH_BYTES) || workspace_bytes_of(p, HSTU_WS_FWD) == 0)
+    return HSTU_ERR_STATIC_SCRATCH;
   void* ws = nullptr;
   const int rs = static_scratch(&ws);
   if (rs != HSTU_OK) return rs;
@@ -766,9 +805,8 @@ static int bwd_impl(const hstu_attn_params* params, const hstu_ts_bias* bias, co
   if (!aligned16(q) || !aligned16(k) || !aligned16(v) || !aligned16(d_o) || !aligned16(dq) ||
       !aligned16(dk) || !aligned16(dv) || !aligned16(workspace))
     return HSTU_ERR_MISALIGNED;
-  if (workspace_bytes < (bias ? hstu_jagged_attn_bias_workspace_bytes(params, HSTU_WS_BWD)
-                              : hstu_jagged_attn_workspace_bytes(params, HSTU_WS_BWD)))
-    return HSTU_ERR_WORKSPACE_TOO_SMALL;
+  hstu_attn_params tall;
+  if (!fits(params, &tall, HSTU_WS_BWD, bias != nullptr, workspace_bytes)) return HSTU_ERR_WORKSPACE_TOO_SMALL;
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
   const size_t first = bias ? bias_front_bytes(params, 1) : 0;  // the records come first
   const bool packed = packed_tiles(params);
@@ -876,9 +914,8 @@ static int cp_partial_impl(const hstu_attn_params* params, const hstu_cp_desc* c
         (backward && !bias->d_ts_weights))
       return HSTU_ERR_NULL_PTR;
   }
-  if (workspace_bytes < (bias ? hstu_jagged_attn_bias_workspace_bytes(params, HSTU_WS_CP)
-                              : hstu_jagged_attn_workspace_bytes(params, HSTU_WS_CP)))
-    return HSTU_ERR_WORKSPACE_TOO_SMALL;
+  hstu_attn_params tall;
+  if (!fits(params, &tall, HSTU_WS_CP, bias != nullptr, workspace_bytes)) return HSTU_ERR_WORKSPACE_TOO_SMALL;
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
   char* ws = (char*)workspace;
   // the (up to) three schedules are built by one launch

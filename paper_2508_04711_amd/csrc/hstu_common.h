@@ -527,6 +527,7 @@ struct AttnArgs {
   int32_t max_items;
   int32_t waves;    // wavefronts per workgroup (bf16 kernels): owner tile = 32 * waves rows
   int32_t out_f32;  // outputs are fp32 (bf16 kernels only; the fp32 kernels always write fp32)
+  int32_t item_parts;  // fp32 kernels: workgroups an item's rows are shared by, 32 rows each
   float* partial;   // partial results of split tiles: [slot][head][tile row][d] fp32 (or null)
   float alpha;
   float inv_n;

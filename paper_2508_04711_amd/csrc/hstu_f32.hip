@@ -26,7 +26,7 @@ namespace hstu {
 
 namespace {
 
-constexpr int TILE = 32;     // owner rows per item
+constexpr int TILE = 32;     // owner rows per workgroup
 constexpr int FW = 4;        // waves per workgroup
 constexpr int THREADS = FW * 64;
 constexpr int FB = 32;       // streamed rows per block
@@ -208,8 +208,24 @@ __device__ __forceinline__ void add_bias(f32x16& s, int (&bk)[16], const AttnArg
   }
 }
 
+// The workgroup's head and its 32 rows of an item (AttnArgs::item_parts; grid.y counts them).  False: no
+// owner rows.
+__device__ __forceinline__ bool half_item(const AttnArgs& a, Item& it, int& h) {
+  const int skip = blockIdx.y * TILE;
+  h = blockIdx.x % a.num_heads;
+  if (!get_item(a, blockIdx.x / a.num_heads, it)) return false;
+  it.row0 += skip;
+  it.pos0 += skip;
+  it.nrows -= skip;
+  if (it.nrows > TILE) it.nrows = TILE;
+  return it.nrows > 0;
+}
+
 // Waves per SIMD the kernels are built for: what the LDS of a workgroup leaves room for.
 constexpr int f32_waves(int dqk, int dv, bool one = false) { return dqk + dv <= 128 && !one ? 2 : 1; }
+// The dq pass at d_qk = d_v = 32 without bias: four, in 128 registers (with the 130 it takes if it may, 4000
+// sequences of 1..60 rows, H = 2: 80 -> 94 us).
+constexpr int f32_dq_waves(int dqk, int dv, bool bias) { return dqk + dv <= 64 && !bias ? 4 : f32_waves(dqk, dv); }
 
 struct Lane {
   int tid, lane, n, hh, wave;
@@ -224,9 +240,10 @@ template <int DQK, int DV, bool BIAS>
 __global__ void __launch_bounds__(THREADS, f32_waves(DQK, DV)) hstu_fwd_f32(AttnArgs a) {
   __shared__ __attribute__((aligned(1024))) float kbuf[FW * FB * DQK];
   __shared__ __attribute__((aligned(1024))) float vbuf[FW * FB * DV];
-  const int H = a.num_heads, h = blockIdx.x % H;
+  const int H = a.num_heads;
+  int h;
   Item it;
-  if (!get_item(a, blockIdx.x / H, it)) return;
+  if (!half_item(a, it, h)) return;
   const Lane l;
   const int64_t sq = (int64_t)H * DQK, sv = (int64_t)H * DV;
   const float* kg = (const float*)a.k + h * DQK;
@@ -285,9 +302,10 @@ template <int DQK, int DV, bool BIAS>
 __global__ void __launch_bounds__(THREADS, f32_waves(DQK, DV, BIAS)) hstu_dkdv_f32(AttnArgs a) {
   __shared__ __attribute__((aligned(1024))) float qbuf[FW * FB * DQK];
   __shared__ __attribute__((aligned(1024))) float gbuf[FW * FB * DV];
-  const int H = a.num_heads, h = blockIdx.x % H;
+  const int H = a.num_heads;
+  int h;
   Item it;
-  if (!get_item(a, blockIdx.x / H, it)) return;
+  if (!half_item(a, it, h)) return;
   const Lane l;
   const int64_t sq = (int64_t)H * DQK, sv = (int64_t)H * DV;
   const float* qg = (const float*)a.q + h * DQK;
@@ -356,13 +374,14 @@ __global__ void __launch_bounds__(THREADS, f32_waves(DQK, DV, BIAS)) hstu_dkdv_f
 
 // ---------------------------------------------------------------------------------------------
 template <int DQK, int DV, bool BIAS>
-__global__ void __launch_bounds__(THREADS, f32_waves(DQK, DV)) hstu_dq_f32(AttnArgs a) {
+__global__ void __launch_bounds__(THREADS, f32_dq_waves(DQK, DV, BIAS)) hstu_dq_f32(AttnArgs a) {
   __shared__ __attribute__((aligned(1024))) float kbuf[FW * FB * DQK];
   __shared__ __attribute__((aligned(1024))) float vbuf[FW * FB * DV];
   __shared__ unsigned long long dwl[BIAS ? MAX_TS_BUCKETS : 1];  // the workgroup's sums of dS per bucket (fixed point)
-  const int H = a.num_heads, h = blockIdx.x % H;
+  const int H = a.num_heads;
+  int h;
   Item it;
-  if (!get_item(a, blockIdx.x / H, it)) return;
+  if (!half_item(a, it, h)) return;
   const Lane l;
   if constexpr (BIAS) {
     for (int i = l.tid; i < a.nb; i += THREADS) dwl[i] = 0ull;
@@ -439,7 +458,7 @@ int tile_rows_f32(int /*pass*/) { return TILE; }
   } while (0)
 #define HSTU_DISPATCH_F32(KERNEL)                                                          \
   do {                                                                                     \
-    const dim3 grid((unsigned)((int64_t)a.max_items * a.num_heads)), block(THREADS);       \
+    const dim3 grid((unsigned)((int64_t)a.max_items * a.num_heads), (unsigned)a.item_parts), block(THREADS); \
     if (d_qk == 128 && d_v == 128) HSTU_LAUNCH_F32(KERNEL, 128, 128);                      \
     else if (d_qk == 64 && d_v == 64) HSTU_LAUNCH_F32(KERNEL, 64, 64);                     \
     else if (d_qk == 32 && d_v == 32) HSTU_LAUNCH_F32(KERNEL, 32, 32);                     \

@@ -93,3 +93,66 @@ def test_table_entries_at_the_ends_of_the_range():
     high = torch.tensor([0.25, 0.5, big / 4], dtype=torch.float32, device="cuda")
     assert abs(last(high) / want([big / 4, big / 4, 0.25]) - 1) <= 1e-5
     assert last(torch.tensor([0.25, 0.5, float("inf")], dtype=torch.float32, device="cuda")) == float("inf")
+
+
+def _short_list_bytes(rows, batch, passes):
+    """Room for one list of 64-row items per pass: per item the 64-byte record, its place in the order, an entry of
+    the (unused) table of cut tiles, 8 bytes per streamed tile; four arrays of an entry per sequence; alignment."""
+    items = rows // 64 + batch + 1
+    return passes * (items * (64 + 4 + 16 + 8) + 4 * 4 * (batch + 1) + 64 + 8 * 64 + 256) + 4096
+
+
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("dqk,dv", [(32, 32), (128, 128), (64, 128)])
+@pytest.mark.parametrize("lengths", [LENGTHS, [40, 64, 1] * 300])
+def test_a_workspace_for_64_row_items_is_enough(lengths, dqk, dv, causal):
+    """The query names the room for lists of 32-row items; with less than that the lists are of 64-row items, each
+    shared by two workgroups, and the results are the same bits."""
+    import paper_2508_04711_amd as lib
+    print("f32 short list", len(lengths), dqk, dv, causal, flush=True)
+    w = workloads.custom("f32_short_list", lengths, 3, dqk, dv, max_len=300, dtype="f32", scale=1.0, seed=47)
+    d = {k: v.cuda() for k, v in workloads.values(w).items()}
+    off = torch.from_numpy(w.seq_offsets()).cuda()
+    ws = lambda passes: torch.empty(_short_list_bytes(w.total_rows, w.batch, passes), dtype=torch.uint8, device="cuda")
+    a = (d["q"], d["k"], d["v"])
+    o = [lib.hstu_jagged_attn_fwd(*a, off, 300, w.alpha, causal, workspace=x) for x in (None, ws(1))]
+    assert torch.equal(o[0], o[1])
+    g = [lib.hstu_jagged_attn_bwd(*a, d["d_o"], off, 300, w.alpha, causal, workspace=x) for x in (None, ws(2))]
+    for x, y in zip(*g):
+        assert torch.equal(x, y)
+    with pytest.raises(lib.HstuError) as e:
+        small = torch.empty((w.total_rows // 64) * 84, dtype=torch.uint8, device="cuda")
+        lib.hstu_jagged_attn_fwd(*a, off, 300, w.alpha, causal, workspace=small)
+    assert e.value.status == -4
+
+
+def test_long_sequences_with_the_short_list():
+    """Rows enough that only the short list fits, with more than one head per tile and a sorted schedule."""
+    import paper_2508_04711_amd as lib
+    lengths = [int(x) for x in np.random.default_rng(3).integers(1, 2000, size=70)]
+    w = workloads.custom("f32_short_long", lengths, 2, 32, 32, max_len=2000, dtype="f32", scale=1.0, seed=48)
+    d = {k: v.cuda() for k, v in workloads.values(w).items()}
+    off = torch.from_numpy(w.seq_offsets()).cuda()
+    need = lib.hstu_jagged_attn_workspace_bytes((w.batch, 2, 32, 32, 2000, 1.0, True, 1, w.total_rows), 1)
+    small = _short_list_bytes(w.total_rows, w.batch, 2)
+    assert small < need
+    args = (d["q"], d["k"], d["v"], d["d_o"], off, 2000, w.alpha, True)
+    want = lib.hstu_jagged_attn_bwd(*args)
+    got = lib.hstu_jagged_attn_bwd(*args, workspace=torch.empty(small, dtype=torch.uint8, device="cuda"))
+    for x, y in zip(want, got):
+        assert torch.equal(x, y)
+
+
+def test_forward_without_a_workspace_takes_seven_million_rows():
+    """The static array holds the 64-row list of 1000 sequences with 7 M rows."""
+    import paper_2508_04711_amd as lib
+    print("f32 static", flush=True)
+    off = torch.linspace(0, 7_000_000, 1001, device="cuda").round().to(torch.int32)
+    off[:997] = torch.arange(997, device="cuda", dtype=torch.int32) * 40  # (short ones, so that this is no long run)
+    off[997:1000] = torch.tensor([40000, 41000, 42000], dtype=torch.int32, device="cuda")
+    off[1000] = 43000
+    q = torch.randn((7_000_000, 1, 32), dtype=torch.float32, device="cuda")
+    out = torch.full_like(q, 7.0)
+    lib.hstu_jagged_attn_fwd_static(q, q, q, off, 1000, 0.1, True, out)
+    want = lib.hstu_jagged_attn_fwd(q, q, q, off, 1000, 0.1, True, out=torch.full_like(q, 7.0))
+    assert torch.equal(out, want) and bool((out[43000:] == 7.0).all())
