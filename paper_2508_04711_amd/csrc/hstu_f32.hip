@@ -56,31 +56,53 @@ __device__ __forceinline__ void vm_wait() {
 }
 __device__ __forceinline__ void lds_reads_done() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 
+// Rows of so many elements (a tensor's heads together) are further apart than 32-bit offsets inside a block of
+// rows reach: the kernels have a variant for those (WIDE) that keeps its offsets inside one load's rows.
+// (One form for both costs the others 1 to 8 %, in scalar instructions and registers.)
+constexpr int64_t WIDE_ROW = 1 << 25;
+
 // A wave's copy of one block: FB rows of one head, D / 8 wave-wide loads; rows >= valid are zeros.
 template <int D>
 constexpr int block_loads() { return D / 8; }
-template <int D>
-__device__ __forceinline__ void block_copy(float* buf, const float* base, int rs, int valid, int lane) {
-  constexpr int CPR = D / 4, RPL = 64 / CPR;
-  const int rows = valid < 0 ? 0 : (valid < FB ? valid : FB);
-  const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
-      (void*)base, 0, __builtin_amdgcn_readfirstlane(rows * rs), 0x00020000);
+template <int D, bool WIDE>
+__device__ __forceinline__ void block_copy(float* buf, const float* base, int64_t row_stride, int valid, int lane) {
+  constexpr int CPR = D / 4, RPL = 64 / CPR, SPAN = WIDE ? RPL : FB;  // rows per buffer
+  const int rows = valid < 0 ? 0 : (valid < FB ? valid : FB), rs = (int)row_stride * 4;
+  __amdgpu_buffer_rsrc_t rsrc;
 #pragma unroll
   for (int i = 0; i < block_loads<D>(); ++i) {
+    if (WIDE || i == 0) {
+      const int left = rows - i * RPL;
+      rsrc = __builtin_amdgcn_make_buffer_rsrc(
+          (void*)(base + i * RPL * row_stride), 0,
+          __builtin_amdgcn_readfirstlane((left < 0 ? 0 : (left < SPAN ? left : SPAN)) * rs), 0x00020000);
+    }
     const int row = i * RPL + lane / CPR;
     const int chunk = (lane % CPR) ^ fswz<D>(row);
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, HSTU_LDS(void, buf + i * 256), 16, row * rs + chunk * 16, 0, 0, 0);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, HSTU_LDS(void, buf + i * 256), 16,
+                                             (WIDE ? lane / CPR : row) * rs + chunk * 16, 0, 0, 0);
   }
 }
 
 // Owner rows as B operands: lane (n, hh) holds elements 8*t + 4*hh + {0..3} of row n.
-template <int D>
-__device__ __forceinline__ void load_rows(f4 (&reg)[D / 8], const float* base, int rs, int row, int nrows, int hh) {
-  const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
-      (void*)base, 0, __builtin_amdgcn_readfirstlane(nrows * rs), 0x00020000);
+template <int D, bool WIDE>
+__device__ __forceinline__ void load_rows(f4 (&reg)[D / 8], const float* base, int64_t row_stride, int row, int nrows, int hh) {
+  if constexpr (WIDE) {
+    const f4* src = (const f4*)(base + (int64_t)(row < nrows ? row : 0) * row_stride + hh * 4);
 #pragma unroll
-  for (int t = 0; t < D / 8; ++t)
-    reg[t] = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, row * rs + t * 32 + hh * 16, 0, 0));
+    for (int t = 0; t < D / 8; ++t) {
+      const f4 x = src[2 * t];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) reg[t][e] = row < nrows ? x[e] : 0.f;
+    }
+  } else {
+    const int rs = (int)row_stride * 4;
+    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
+        (void*)base, 0, __builtin_amdgcn_readfirstlane(nrows * rs), 0x00020000);
+#pragma unroll
+    for (int t = 0; t < D / 8; ++t)
+      reg[t] = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, row * rs + t * 32 + hh * 16, 0, 0));
+  }
 }
 
 // acc[streamed row][owner row] += block (rows of the block) x owners^T.
@@ -236,7 +258,7 @@ struct Lane {
 };
 
 // ---------------------------------------------------------------------------------------------
-template <int DQK, int DV, bool BIAS>
+template <int DQK, int DV, bool BIAS, bool WIDE>
 __global__ void __launch_bounds__(THREADS, f32_waves(DQK, DV)) hstu_fwd_f32(AttnArgs a) {
   __shared__ __attribute__((aligned(1024))) float kbuf[FW * FB * DQK];
   __shared__ __attribute__((aligned(1024))) float vbuf[FW * FB * DV];
@@ -251,11 +273,11 @@ __global__ void __launch_bounds__(THREADS, f32_waves(DQK, DV)) hstu_fwd_f32(Attn
   float* kb = kbuf + l.wave * (FB * DQK);
   float* vb = vbuf + l.wave * (FB * DV);
   f4 q[DQK / 8];
-  load_rows<DQK>(q, (const float*)a.q + (int64_t)it.row0 * sq + h * DQK, (int)sq * 4, l.n, it.nrows, l.hh);
+  load_rows<DQK, WIDE>(q, (const float*)a.q + (int64_t)it.row0 * sq + h * DQK, sq, l.n, it.nrows, l.hh);
   const Blocks bl = make_blocks<0>(it, a.causal);
   const int t_own = BIAS && l.n < it.nrows ? a.ts_rec_own[(int64_t)it.row0 + l.n].ts : 0;
-  auto copy_k = [&](const BlockRef& b) { block_copy<DQK>(kb, kg + (int64_t)b.row * sq, (int)sq * 4, b.valid, l.lane); };
-  auto copy_v = [&](const BlockRef& b) { block_copy<DV>(vb, vg + (int64_t)b.row * sv, (int)sv * 4, b.valid, l.lane); };
+  auto copy_k = [&](const BlockRef& b) { block_copy<DQK, WIDE>(kb, kg + (int64_t)b.row * sq, sq, b.valid, l.lane); };
+  auto copy_v = [&](const BlockRef& b) { block_copy<DV, WIDE>(vb, vg + (int64_t)b.row * sv, sv, b.valid, l.lane); };
   f32x16 o[DV / 32];
 #pragma unroll
   for (int c = 0; c < DV / 32; ++c) clear(o[c]);
@@ -298,7 +320,7 @@ __global__ void __launch_bounds__(THREADS, f32_waves(DQK, DV)) hstu_fwd_f32(Attn
 }
 
 // ---------------------------------------------------------------------------------------------
-template <int DQK, int DV, bool BIAS>
+template <int DQK, int DV, bool BIAS, bool WIDE>
 __global__ void __launch_bounds__(THREADS, f32_waves(DQK, DV, BIAS)) hstu_dkdv_f32(AttnArgs a) {
   __shared__ __attribute__((aligned(1024))) float qbuf[FW * FB * DQK];
   __shared__ __attribute__((aligned(1024))) float gbuf[FW * FB * DV];
@@ -313,12 +335,12 @@ __global__ void __launch_bounds__(THREADS, f32_waves(DQK, DV, BIAS)) hstu_dkdv_f
   float* qb = qbuf + l.wave * (FB * DQK);
   float* gb = gbuf + l.wave * (FB * DV);
   f4 k[DQK / 8], v[DV / 8];
-  load_rows<DQK>(k, (const float*)a.k + (int64_t)it.row0 * sq + h * DQK, (int)sq * 4, l.n, it.nrows, l.hh);
-  load_rows<DV>(v, (const float*)a.v + (int64_t)it.row0 * sv + h * DV, (int)sv * 4, l.n, it.nrows, l.hh);
+  load_rows<DQK, WIDE>(k, (const float*)a.k + (int64_t)it.row0 * sq + h * DQK, sq, l.n, it.nrows, l.hh);
+  load_rows<DV, WIDE>(v, (const float*)a.v + (int64_t)it.row0 * sv + h * DV, sv, l.n, it.nrows, l.hh);
   const Blocks bl = make_blocks<1>(it, a.causal);
   const int t_own = BIAS && l.n < it.nrows ? a.ts_rec_own[(int64_t)it.row0 + l.n].ts : 0;
-  auto copy_q = [&](const BlockRef& b) { block_copy<DQK>(qb, qg + (int64_t)b.row * sq, (int)sq * 4, b.valid, l.lane); };
-  auto copy_g = [&](const BlockRef& b) { block_copy<DV>(gb, gg + (int64_t)b.row * sv, (int)sv * 4, b.valid, l.lane); };
+  auto copy_q = [&](const BlockRef& b) { block_copy<DQK, WIDE>(qb, qg + (int64_t)b.row * sq, sq, b.valid, l.lane); };
+  auto copy_g = [&](const BlockRef& b) { block_copy<DV, WIDE>(gb, gg + (int64_t)b.row * sv, sv, b.valid, l.lane); };
   f32x16 dk[DQK / 32], dv[DV / 32];
 #pragma unroll
   for (int c = 0; c < DQK / 32; ++c) clear(dk[c]);
@@ -373,7 +395,7 @@ __global__ void __launch_bounds__(THREADS, f32_waves(DQK, DV, BIAS)) hstu_dkdv_f
 }
 
 // ---------------------------------------------------------------------------------------------
-template <int DQK, int DV, bool BIAS>
+template <int DQK, int DV, bool BIAS, bool WIDE>
 __global__ void __launch_bounds__(THREADS, f32_dq_waves(DQK, DV, BIAS)) hstu_dq_f32(AttnArgs a) {
   __shared__ __attribute__((aligned(1024))) float kbuf[FW * FB * DQK];
   __shared__ __attribute__((aligned(1024))) float vbuf[FW * FB * DV];
@@ -393,12 +415,12 @@ __global__ void __launch_bounds__(THREADS, f32_dq_waves(DQK, DV, BIAS)) hstu_dq_
   float* kb = kbuf + l.wave * (FB * DQK);
   float* vb = vbuf + l.wave * (FB * DV);
   f4 q[DQK / 8], g[DV / 8];
-  load_rows<DQK>(q, (const float*)a.q + (int64_t)it.row0 * sq + h * DQK, (int)sq * 4, l.n, it.nrows, l.hh);
-  load_rows<DV>(g, (const float*)a.d_o + (int64_t)it.row0 * sv + h * DV, (int)sv * 4, l.n, it.nrows, l.hh);
+  load_rows<DQK, WIDE>(q, (const float*)a.q + (int64_t)it.row0 * sq + h * DQK, sq, l.n, it.nrows, l.hh);
+  load_rows<DV, WIDE>(g, (const float*)a.d_o + (int64_t)it.row0 * sv + h * DV, sv, l.n, it.nrows, l.hh);
   const Blocks bl = make_blocks<0>(it, a.causal);
   const int t_own = BIAS && l.n < it.nrows ? a.ts_rec_own[(int64_t)it.row0 + l.n].ts : 0;
-  auto copy_k = [&](const BlockRef& b) { block_copy<DQK>(kb, kg + (int64_t)b.row * sq, (int)sq * 4, b.valid, l.lane); };
-  auto copy_v = [&](const BlockRef& b) { block_copy<DV>(vb, vg + (int64_t)b.row * sv, (int)sv * 4, b.valid, l.lane); };
+  auto copy_k = [&](const BlockRef& b) { block_copy<DQK, WIDE>(kb, kg + (int64_t)b.row * sq, sq, b.valid, l.lane); };
+  auto copy_v = [&](const BlockRef& b) { block_copy<DV, WIDE>(vb, vg + (int64_t)b.row * sv, sv, b.valid, l.lane); };
   f32x16 dq[DQK / 32];
 #pragma unroll
   for (int c = 0; c < DQK / 32; ++c) clear(dq[c]);
@@ -453,8 +475,11 @@ int tile_rows_f32(int /*pass*/) { return TILE; }
 
 #define HSTU_LAUNCH_F32(KERNEL, A, B)                                                      \
   do {                                                                                     \
-    if (a.ts_rec) hipLaunchKernelGGL((KERNEL<A, B, true>), grid, block, 0, stream, a);     \
-    else hipLaunchKernelGGL((KERNEL<A, B, false>), grid, block, 0, stream, a);             \
+    const bool wide = (int64_t)a.num_heads * (A > B ? A : B) >= WIDE_ROW;                  \
+    if (a.ts_rec && wide) hipLaunchKernelGGL((KERNEL<A, B, true, true>), grid, block, 0, stream, a);   \
+    else if (a.ts_rec) hipLaunchKernelGGL((KERNEL<A, B, true, false>), grid, block, 0, stream, a);     \
+    else if (wide) hipLaunchKernelGGL((KERNEL<A, B, false, true>), grid, block, 0, stream, a);         \
+    else hipLaunchKernelGGL((KERNEL<A, B, false, false>), grid, block, 0, stream, a);      \
   } while (0)
 #define HSTU_DISPATCH_F32(KERNEL)                                                          \
   do {                                                                                     \

@@ -6,6 +6,7 @@ import numpy as np
 import pytest
 import torch
 
+import oracle
 import workloads
 from test_gpu_parity import _run_full
 
@@ -156,3 +157,26 @@ def test_forward_without_a_workspace_takes_seven_million_rows():
     lib.hstu_jagged_attn_fwd_static(q, q, q, off, 1000, 0.1, True, out)
     want = lib.hstu_jagged_attn_fwd(q, q, q, off, 1000, 0.1, True, out=torch.full_like(q, 7.0))
     assert torch.equal(out, want) and bool((out[43000:] == 7.0).all())
+
+
+@pytest.mark.parametrize("dqk,dv,heads", [(128, 128, (1 << 18) + 3), (32, 128, (1 << 18) + 1), (32, 32, (1 << 20) + 5)])
+def test_rows_of_more_than_128_megabytes(dqk, dv, heads):
+    """Heads enough that a block of rows reaches beyond 32-bit offsets; a few of them against 64 bits."""
+    import paper_2508_04711_amd as lib
+    print("f32 wide rows", dqk, dv, heads, flush=True)
+    lengths = [5, 1, 34]
+    T = sum(lengths)
+    off = torch.tensor(np.concatenate([[0], np.cumsum(lengths)]), dtype=torch.int32, device="cuda")
+    g = torch.Generator(device="cuda").manual_seed(5)
+    q, k = [torch.randn((T, heads, dqk), generator=g, device="cuda") for _ in range(2)]
+    v, do = [torch.randn((T, heads, dv), generator=g, device="cuda") for _ in range(2)]
+    alpha = dqk ** -0.5
+    o = lib.hstu_jagged_attn_fwd(q, k, v, off, 7, alpha, True)
+    dq, dk, dv_ = lib.hstu_jagged_attn_bwd(q, k, v, do, off, 7, alpha, True)
+    for h in (0, 1, heads // 2, heads - 1):
+        f = [x[:, h].double().cpu().numpy()[:, None] for x in (q, k, v, do)]
+        off_np = off.cpu().numpy()
+        want = (oracle.fwd(f[0], f[1], f[2], off_np, 7, alpha, True),) + tuple(oracle.bwd(*f, off_np, 7, alpha, True))
+        for name, got, ref in zip(("o", "dq", "dk", "dv"), (o, dq, dk, dv_), want):
+            err = np.abs(got[:, h].double().cpu().numpy() - ref[:, 0]).max() / np.sqrt(np.mean(ref ** 2))
+            assert err <= 1e-5, (name, h, err)
