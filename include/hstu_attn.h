@@ -372,13 +372,15 @@ const char* hstu_attn_status_string(int status);
  * Builds on the device, exactly as the attention entry points do (when they tile per sequence:
  * packed tiles have a schedule of their own, 128 consecutive rows per item in row order, which this
  * call does not show), the table of work items for one side of a problem and copies it to host
- * memory (this call synchronises the stream).
+ * memory (this call synchronises the stream).  Where those entry points build no table, every wave
+ * working its item out by itself, the table is what the waves find.
  *   side: 0 = items are query tiles streaming over key segments (forward, dq pass)
  *         1 = items are key tiles streaming over query segments (dk/dv pass)
  *   cp == NULL: whole-batch attention; else the context-parallel problem it describes
  *   items_host: room for max_items * 12 int32; per item
  *       {row0, nrows, pos0, nseg, seg_row0[2], seg_len[2], seg_pos0[2], cost, 0}
- *   returns the number of items (>= 0) in schedule order (non-increasing cost), or a status < 0.
+ *   returns the number of items (>= 0) in schedule order (non-increasing cost, where tiles are cut in two
+ *   that of the whole tile; large batches: the order of the rows), or a status < 0.
  */
 int hstu_debug_dump_schedule(const hstu_attn_params* params, const hstu_cp_desc* cp, int side,
                              const int32_t* seq_offsets, int32_t* items_host, int32_t max_items,

@@ -327,8 +327,8 @@ int prepare_plan(const hstu_attn_params* p, int cp_size, const SideSpec& s, cons
   out->end = l.end;
   out->dp = DirectPlan{off, a.batch, a.total_rows, a.cp, a.owner_rank, a.streamed_rank, a.side, a.tile, a.causal,
                        a.owner_rows, a.streamed_rows, split, SPLIT_BLOCKS};
-  // Small batches in cost order.  Where every workgroup is resident at once, each works its
-  // own item out and no schedule is launched: 4 sequences of 1..64 rows fwd + bwd 39 -> 30 us, 32 of
+  // Small batches in cost order.  Where the workgroups are at most two rounds of what is resident at once, each
+  // works its own item out and no schedule is launched: 4 sequences of 1..64 rows fwd + bwd 39 -> 30 us, 32 of
   // 1..1024 rows forward 39 -> 30 us.  Beyond that the 0.5 us per item, which nothing overlaps at one
   // workgroup per CU, costs more than the launch (16 sequences of 512..4096 rows: dk/dv 254 -> 269 us).
   out->form = BuiltPlan::SORTED;
@@ -412,7 +412,13 @@ int make_tcopy(const hstu_attn_params* p, const SideSpec& s, const BuiltPlan& bp
 }
 
 // Builds those of up to three prepared schedules that the kernels will read, in one launch.
-int launch_built(const PlanArgs* args, const BuiltPlan* const* plans, int count, hipStream_t stream) {
+int launch_built(const PlanArgs* args, BuiltPlan* const* plans, int count, hipStream_t stream) {
+  // (with a list to write anyway, listing the other passes' items too costs less than having their waves find them:
+  // ring pass of one of four ranks, 40 sequences of 500..4000 rows, H = 4, forward and dq 506 -> 462 us)
+  bool lists = false;
+  for (int i = 0; i < count; ++i) lists = lists || plans[i]->form == BuiltPlan::DIRECT;
+  for (int i = 0; i < count; ++i)
+    if (lists && plans[i]->form == BuiltPlan::SELF) plans[i]->form = BuiltPlan::DIRECT;
   PlanArgs need[3], natural[3];
   ItemPlans items;
   int n = 0, m = 0, k = 0;
@@ -438,13 +444,14 @@ int launch_built(const PlanArgs* args, const BuiltPlan* const* plans, int count,
   return HSTU_OK;
 }
 
-// One schedule: prepare and launch.  `dump`: build it whether or not the kernels would read it.
+// One schedule: prepare and launch.  `dump`: for inspection, where the kernels' waves would work out their items by
+// themselves, what they would find is listed.
 int build_plan(const hstu_attn_params* p, int cp_size, const SideSpec& s, const int32_t* off,
                char* ws, size_t ws_bytes, size_t base, hipStream_t stream, BuiltPlan* out, bool dump = false) {
   PlanArgs args;
   const int rc = prepare_plan(p, cp_size, s, off, ws, ws_bytes, base, &args, out);
   if (rc != HSTU_OK) return rc;
-  if (dump) out->form = BuiltPlan::SORTED;
+  if (dump && out->form == BuiltPlan::SELF) out->form = BuiltPlan::DIRECT;
   return launch_built(&args, &out, 1, stream);
 }
 
@@ -849,7 +856,7 @@ static int bwd_impl(const hstu_attn_params* params, const hstu_ts_bias* bias, co
   rc = prepare_plan(params, 1, full_side(params, 0, PASS_DQ), seq_offsets, (char*)workspace,
                     workspace_bytes, pk.end, &pa[1], &pq);
   if (rc != HSTU_OK) return rc;
-  const BuiltPlan* built[2] = {&pk, &pq};
+  BuiltPlan* built[2] = {&pk, &pq};
   rc = launch_built(pa, built, 2, stream);
   if (rc != HSTU_OK) return rc;
   AttnArgs a = base_args(params, pk, 0);
@@ -923,7 +930,7 @@ static int cp_partial_impl(const hstu_attn_params* params, const hstu_cp_desc* c
              do_q = backward && cp->q_rows > 0;
   PlanArgs pa[3];
   BuiltPlan pf, pk, pq;
-  const BuiltPlan* built[3];
+  BuiltPlan* built[3];
   int np = 0;
   size_t base = 0, tbase = 0, qbase = 0;
   // with bias: the records of the query side's rows, then of the key side's, come first
@@ -1281,30 +1288,36 @@ int hstu_debug_dump_schedule(const hstu_attn_params* params, const hstu_cp_desc*
   rc = build_plan(params, cp ? cp->cp_size : 1, s, seq_offsets, (char*)workspace, workspace_bytes,
                   0, stream, &bp, true);
   if (rc != HSTU_OK) return rc;
-  int32_t n = 0;
-  if (hipMemcpyAsync(&n, bp.plan.header, sizeof(int32_t), hipMemcpyDeviceToHost, stream) != hipSuccess)
+  // a list written by a wave per item is in schedule order, and its slots beyond the last item have no rows
+  const bool direct = bp.form == BuiltPlan::DIRECT;
+  int32_t n = (int32_t)bp.max_items;
+  if (!direct && hipMemcpyAsync(&n, bp.plan.header, sizeof(int32_t), hipMemcpyDeviceToHost, stream) != hipSuccess)
     return HSTU_ERR_HIP;
   if (hipStreamSynchronize(stream) != hipSuccess) return HSTU_ERR_HIP;
-  if (n > max_items) return HSTU_ERR_WORKSPACE_TOO_SMALL;
   if (n == 0) return 0;
   std::vector<int32_t> order(n);
   std::vector<Item> items(n);
-  if (hipMemcpyAsync(order.data(), bp.plan.order, sizeof(int32_t) * n, hipMemcpyDeviceToHost, stream) != hipSuccess ||
+  if ((!direct && hipMemcpyAsync(order.data(), bp.plan.order, sizeof(int32_t) * n, hipMemcpyDeviceToHost, stream) != hipSuccess) ||
       hipMemcpyAsync(items.data(), bp.plan.items, sizeof(Item) * n, hipMemcpyDeviceToHost, stream) != hipSuccess ||
       hipStreamSynchronize(stream) != hipSuccess)
     return HSTU_ERR_HIP;
+  if (direct)
+    for (int32_t i = 0; i < n; ++i) order[i] = i;
+  int32_t written = 0;
   for (int32_t i = 0; i < n; ++i) {
     const int32_t idx = order[i];
     if (idx < 0 || idx >= n) return HSTU_ERR_HIP;
     const Item& it = items[idx];
-    int32_t* dst = items_host + (size_t)i * 12;
+    if (direct && it.nrows <= 0) continue;
+    if (written >= max_items) return HSTU_ERR_WORKSPACE_TOO_SMALL;
+    int32_t* dst = items_host + (size_t)written++ * 12;
     dst[0] = it.row0; dst[1] = it.nrows; dst[2] = it.pos0; dst[3] = it.nseg;
     dst[4] = it.seg_row0[0]; dst[5] = it.seg_row0[1];
     dst[6] = it.seg_len[0]; dst[7] = it.seg_len[1];
     dst[8] = it.seg_pos0[0]; dst[9] = it.seg_pos0[1];
     dst[10] = it.cost; dst[11] = it.part;
   }
-  return n;
+  return written;
 }
 
 }  // extern "C"

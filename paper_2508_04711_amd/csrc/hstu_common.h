@@ -113,6 +113,9 @@ __device__ __forceinline__ void seq_range(const int32_t* off, int b, int total_r
   e = clampi(off[b + 1], s, total_rows);
 }
 
+constexpr int STILE = 64;  // rows per tile of the streamed side (what the kernels stage in LDS)
+__device__ __forceinline__ int blocks_of(int rows) { return (rows >> 5) + ((rows & 31) != 0); }  // of 32 rows
+
 __device__ inline int tiles_of(const Side& s, int tile) {
   return (s.len[0] + tile - 1) / tile + (s.len[1] + tile - 1) / tile;
 }
@@ -189,9 +192,23 @@ __device__ __forceinline__ int wave_scan(int x) {
 }
 __device__ __forceinline__ int wave_total(int x) { return __builtin_amdgcn_readlane(wave_scan(x), 63); }
 
+// Minimum and maximum over the wave's lanes, on the vector pipe (a shuffle goes through LDS: six
+// dependent round trips per reduction, and a packed item needs four of them).
+template <class F>
+__device__ __forceinline__ int wave_reduce(int x, const F& f) {
+  x = f(x, __builtin_amdgcn_update_dpp(x, x, 0x111, 0xf, 0xf, false));  // row_shr:1, 2, 4, 8
+  x = f(x, __builtin_amdgcn_update_dpp(x, x, 0x112, 0xf, 0xf, false));
+  x = f(x, __builtin_amdgcn_update_dpp(x, x, 0x114, 0xf, 0xf, false));
+  x = f(x, __builtin_amdgcn_update_dpp(x, x, 0x118, 0xf, 0xf, false));
+  x = f(x, __builtin_amdgcn_update_dpp(x, x, 0x142, 0xa, 0xf, false));  // row_bcast:15, :31
+  x = f(x, __builtin_amdgcn_update_dpp(x, x, 0x143, 0xc, 0xf, false));
+  return __builtin_amdgcn_readlane(x, 63);
+}
+__device__ __forceinline__ int wave_min(int x) { return wave_reduce(x, [](int a, int b) { return a < b ? a : b; }); }
+__device__ __forceinline__ int wave_max(int x) { return wave_reduce(x, [](int a, int b) { return a > b ? a : b; }); }
+
 // Part k of ns of an item whose streamed segments have pvis visible rows: whole 64-row tiles of them;
 // `part` is the item's Item::part.
-constexpr int STILE = 64;  // rows per tile of the streamed side (what the kernels stage in LDS)
 __device__ __forceinline__ Item cut_item(const Item& it, const int (&pvis)[2], int k, int ns, int part) {
   const int nt0 = (pvis[0] + STILE - 1) / STILE, nt = nt0 + (pvis[1] + STILE - 1) / STILE;
   const int lo = (int)((long long)k * nt / ns), hi = (int)((long long)(k + 1) * nt / ns);
@@ -237,101 +254,82 @@ struct DirectSlot { int tile, part, parts, cut_tiles; };
 
 // Item `slot` of a schedule, worked out by one wave from the offsets: batches of at most 64 * K
 // sequences, K per lane.  A slot beyond the last item gets no rows.
-// The order is heaviest first, with a tile's cost taken in whole tiles of what it sees ("level").
-// Per owner segment (one per sequence, two in a rank's layout) the levels either are consecutive -
-// the diagonal runs through what the segment sees: each query tile sees one tile of keys more than
-// the one before, each key tile one tile of queries less - or all the same (no mask, or another
-// rank's mini-chunks, which lie wholly before or after).  Keys of the whole batch against one rank's
-// queries ("stairs") see what is left of the rank's two mini-chunks: flat, a ramp, flat, a ramp, nothing.
-// (Ordered by their distance from the sequence's end instead, heavy tiles of one sequence came after light ones
-// of a longer one: dk/dv of one of four ranks, 8 sequences of 4096..16384 rows, 371 -> 395 us.)  So the
-// number of tiles at or above a level is a clamp per lane and a sum over lanes; a bisection over
-// levels finds the item's, a ballot the sequence.  About 0.5 us for K = 1.
-// Cut tiles: a tile of level w has parts(w) = clamp(w * tile / 32 / split_blocks, 1, split_max) items,
-// neighbours in the order, so the items at or above a level are sums of the same counts.
+// The order is heaviest first, by the cost that describe_item gives a tile: the 32-row blocks it sees.  Along an
+// owner segment (one per sequence, two in a rank's layout) that cost only grows (queries: each tile sees what the
+// one before sees and more) or only shrinks (keys), so the tiles that cost at least v are the last or the
+// first of the segment, and their number follows from the position at which the streamed segments have v blocks
+// before it (after it).  A bisection over v finds the item's cost, a ballot the sequence.  About 0.5 us for K = 1.
+// (With costs in whole tiles instead, launches of a few items per slot, which last as long as their worst
+// combination, took up to 10 % longer: one of four ranks, 300 sequences of 500..1500 rows, H = 4, forward 221 ->
+// 244, dq 244 -> 256 us.)
+// Cut tiles: a tile of cost v has parts(v) = clamp(v / split_blocks, 1, split_max) items, neighbours in the
+// order, so the items at or above a cost are sums of the same counts.
 template <int K>
 __device__ __forceinline__ DirectSlot direct_item(const DirectPlan& d, int slot, Item& it) {
   const int lane = threadIdx.x & 63;
-  int s[K], e[K], n[K][2], top[K][2], rows[K];  // per owner segment: tiles, highest level
-  bool ramp[K][2];                              // consecutive levels
-  const bool stairs = d.side == 1 && d.owner_rank < 0 && d.streamed_rank >= 0 && d.causal;
-  int end0[K], len1[K], end1[K], all[K];        // stairs: the rank's mini-chunks of the sequence (all: rows of both)
+  int s[K], e[K], n[K][2], pos[K][2], len[K][2];  // owner segments: tiles, first position, rows
+  int spos[K][2], slen[K][2];                     // streamed segments
   const int tile_log2 = 31 - __builtin_clz(d.tile);  // (a power of two)
+  const bool two = d.owner_rank >= 0;                // owner segments per sequence
+  int most = 0;  // cost of a tile that sees all
 #pragma unroll
   for (int k = 0; k < K; ++k) {
-    s[k] = e[k] = n[k][0] = n[k][1] = top[k][0] = top[k][1] = rows[k] = 0;
-    ramp[k][0] = ramp[k][1] = false;
-    end0[k] = len1[k] = end1[k] = all[k] = 0;
-    if (k * 64 < d.batch) {
-      if (k * 64 + lane < d.batch) seq_range(d.off, k * 64 + lane, d.total_rows, s[k], e[k]);
-      const int len = e[k] - s[k];
-      const Side so = make_side(len, d.cp, d.owner_rank);
-      Side ss = make_side(len, d.cp, d.streamed_rank);
-      if (stairs) {
-        end0[k] = ss.pos[0] + ss.len[0]; len1[k] = ss.len[1]; end1[k] = ss.pos[1] + ss.len[1]; all[k] = ss.rows;
-      }
-      rows[k] = so.rows;
+    s[k] = e[k] = 0;
+    if (k * 64 + lane < d.batch) seq_range(d.off, k * 64 + lane, d.total_rows, s[k], e[k]);
+    const Side so = make_side(e[k] - s[k], d.cp, d.owner_rank), ss = make_side(e[k] - s[k], d.cp, d.streamed_rank);
 #pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        n[k][u] = (so.len[u] + d.tile - 1) / d.tile;
-        const int p0 = so.pos[u], p1 = p0 + so.len[u];
-        int seen = 0;  // streamed rows every tile of the segment sees
-        bool across = false;
-#pragma unroll
-        for (int g = 0; g < 2; ++g) {
-          const int b = ss.pos[g], f = b + ss.len[g];
-          if (!d.causal) { seen += ss.len[g]; continue; }
-          if (d.side == 0) seen += p0 < b ? 0 : (p0 < f ? p0 : f) - b;
-          else seen += p1 < b ? f - b : (p1 < f ? f - p1 : 0);
-          across = across || (b < p1 && p0 < f);
-        }
-        ramp[k][u] = across;
-        const int more = across ? (d.side == 0 ? n[k][u] * d.tile : so.len[u]) : 0;
-        top[k][u] = d.side == 0 && across ? seen / d.tile + n[k][u] : (seen + more + d.tile - 1) / d.tile;
-        top[k][u] = top[k][u] < 1 ? 1 : top[k][u];
-      }
+    for (int u = 0; u < 2; ++u) {
+      pos[k][u] = so.pos[u]; len[k][u] = so.len[u];
+      n[k][u] = (so.len[u] >> tile_log2) + ((so.len[u] & (d.tile - 1)) != 0);
+      spos[k][u] = ss.pos[u]; slen[k][u] = ss.len[u];
     }
+    const int all = blocks_of(ss.len[0]) + blocks_of(ss.len[1]);
+    most = all > most ? all : most;
   }
-  auto at_least = [&](int k, int u, int v) {  // tiles of the lane's segment (k, u) at level v or above
-    if (stairs) {  // keys whose tile begins at or before the last position that sees more than v - 1 tiles of queries
-      if (u || v <= 1) return u ? 0 : n[k][0];
-      const int x = (v - 1) * d.tile + 1;
-      const int last = x <= len1[k] ? end1[k] - x : end0[k] + len1[k] - x;
-      const int c = x <= all[k] ? (last >> tile_log2) + 1 : 0;
-      return c < n[k][0] ? c : n[k][0];
+  auto at_least = [&](int k, int u, int v) {  // tiles of the lane's segment (k, u) that cost v or more
+    const int tiles = n[k][u];
+    if (v <= 0) return tiles;
+    const int b0 = blocks_of(slen[k][0]), b1 = blocks_of(slen[k][1]);
+    if (!d.causal) return b0 + b1 >= v ? tiles : 0;
+    if (d.side == 0) {  // the tile's end is beyond v - 1 blocks
+      const bool g = v > b0;
+      const int w = g ? v - b0 : v, x = (g ? spos[k][1] : spos[k][0]) + 32 * (w - 1) - pos[k][u];
+      const int t = x > 0 ? x >> tile_log2 : 0;
+      return (g && w > b1) || x >= len[k][u] ? 0 : tiles - t;
     }
-    const int x = top[k][u] - v + 1;
-    return ramp[k][u] ? (x < 0 ? 0 : (x < n[k][u] ? x : n[k][u])) : (x > 0 ? n[k][u] : 0);
+    const bool g = v <= b1;  // more than v - 1 blocks begin at or after the tile
+    const int w = g ? v : v - b1, x = (g ? spos[k][1] + slen[k][1] : spos[k][0] + slen[k][0]) - 32 * (w - 1) - 1 - pos[k][u];
+    const int c = (x >> tile_log2) + 1;
+    return (!g && w > b0) || x < 0 ? 0 : (c < tiles ? c : tiles);
   };
   auto lane_count = [&](int v) {
     int c = 0;
 #pragma unroll
     for (int k = 0; k < K; ++k)
-      if (k * 64 < d.batch) c += at_least(k, 0, v) + at_least(k, 1, v);
+      if (k * 64 < d.batch) {
+        c += at_least(k, 0, v);
+        if (two) c += at_least(k, 1, v);
+      }
     return c;
   };
-  // the lowest level of a tile cut into j parts
-  auto cut_level = [&](int j) { return (j * d.split_blocks * 32 + d.tile - 1) / d.tile; };
-  auto count = [&](int v) {  // items at level v or above
+  auto cut_cost = [&](int j) { return j * d.split_blocks; };  // the lowest cost of a tile cut into j parts
+  auto count = [&](int v) {  // items of tiles that cost v or more
     int c = lane_count(v);
-    for (int j = 2; j <= d.split_max; ++j) {
-      const int w = cut_level(j);
-      c += lane_count(v > w ? v : w);
-    }
+    for (int j = 2; j <= d.split_max; ++j) c += lane_count(v > cut_cost(j) ? v : cut_cost(j));
     return wave_total(c);
   };
   DirectSlot r = {0, 0, 1, 0};
-  if (d.split_max > 1 && slot == 0) r.cut_tiles = wave_total(lane_count(cut_level(2)));
+  if (d.split_max > 1 && slot == 0) r.cut_tiles = wave_total(lane_count(cut_cost(2)));
   it = Item{};
-  if (slot >= count(1)) return r;
-  int lo = 1, hi = (d.total_rows + d.tile - 1) / d.tile + 3;  // count(lo) > slot >= count(hi)
+  if (slot >= count(0)) return r;
+  int lo = 0, hi = wave_max(most) + 1;  // count(lo) > slot >= count(hi)
   while (hi - lo > 1) {
     const int mid = (lo + hi) >> 1;
     if (count(mid) > slot) lo = mid; else hi = mid;
   }
   int rem = slot - count(lo + 1);
   if (d.split_max > 1) {
-    while (r.parts < d.split_max && lo >= cut_level(r.parts + 1)) ++r.parts;
+    while (r.parts < d.split_max && lo >= cut_cost(r.parts + 1)) ++r.parts;
     r.part = rem % r.parts;
     rem /= r.parts;
     r.tile = wave_total(lane_count(lo + 1)) + rem;
@@ -342,8 +340,8 @@ __device__ __forceinline__ DirectSlot direct_item(const DirectPlan& d, int slot,
   for (int k = 0; k < K; ++k)
 #pragma unroll
     for (int g = 0; g < 2; ++g)
-      if (!found && k * 64 < d.batch) {
-        const int mine = at_least(k, g, lo) - at_least(k, g, lo + 1);
+      if (!found && k * 64 < d.batch && (g == 0 || two)) {
+        const int from = at_least(k, g, lo), above = at_least(k, g, lo + 1), mine = from - above;
         const int inc = wave_scan(mine), tot = __builtin_amdgcn_readlane(inc, 63);
         if (rem < tot) {
           const int l = (int)__builtin_ctzll(__ballot(rem >= inc - mine && rem < inc));
@@ -351,33 +349,29 @@ __device__ __forceinline__ DirectSlot direct_item(const DirectPlan& d, int slot,
           u = g;
           sb = __builtin_amdgcn_readlane(s[k], l);
           eb = __builtin_amdgcn_readlane(e[k], l);
-          const int below = __builtin_amdgcn_readlane(top[k][g], l) - lo;  // tiles between the item and the heaviest
-          t = stairs ? __builtin_amdgcn_readlane(at_least(k, g, lo + 1), l) + rem - __builtin_amdgcn_readlane(inc - mine, l)
-              : !__builtin_amdgcn_readlane((int)ramp[k][g], l)
-                  ? rem - __builtin_amdgcn_readlane(inc - mine, l)
-                  : (d.side == 0 ? __builtin_amdgcn_readlane(n[k][g], l) - 1 - below : below);
+          const int first = d.side == 0 && d.causal ? n[k][g] - from : above;  // first tile of that cost
+          t = __builtin_amdgcn_readlane(first - (inc - mine), l) + rem;
           found = true;
         } else {
           rem -= tot;
         }
       }
-  const int len = eb - sb;
+  const int rows = eb - sb;
   int ob = sb, stb = sb;  // first row of the sequence in the two sides' layouts
   if (d.owner_rank >= 0) {
     int c = 0;
 #pragma unroll
-    for (int k = 0; k < K; ++k) c += k * 64 + lane < b ? rows[k] : 0;
+    for (int k = 0; k < K; ++k) c += k * 64 + lane < b ? len[k][0] + len[k][1] : 0;
     ob = wave_total(c);
   }
   if (d.streamed_rank >= 0) {
     int c = 0;
 #pragma unroll
-    for (int k = 0; k < K; ++k)
-      if (k * 64 < d.batch) c += k * 64 + lane < b ? make_side(e[k] - s[k], d.cp, d.streamed_rank).rows : 0;
+    for (int k = 0; k < K; ++k) c += k * 64 + lane < b ? slen[k][0] + slen[k][1] : 0;
     stb = wave_total(c);
   }
   int pvis[2];
-  it = describe_item(make_side(len, d.cp, d.owner_rank), make_side(len, d.cp, d.streamed_rank), u, t, ob, stb, 0,
+  it = describe_item(make_side(rows, d.cp, d.owner_rank), make_side(rows, d.cp, d.streamed_rank), u, t, ob, stb, 0,
                      d.tile, d.causal, d.side, d.owner_rows, d.streamed_rows, pvis);
   if (r.parts > 1) it = cut_item(it, pvis, r.part, r.parts, slot + 1);
   return r;
@@ -415,8 +409,10 @@ struct PlanArgs {
 
 // The schedules of batches of at most DIRECT_BATCH sequences in cost order: one wave per item (see
 // direct_item), up to three schedules in one launch.  Every slot below max_items is written (no rows
-// beyond the last item) and the list is in schedule order: Plan::direct.
-constexpr int DIRECT_BATCH = 512;
+// beyond the last item) and the list is in schedule order: Plan::direct.  (Beyond, the work per item grows with the
+// batch and plan_kernel is faster: 300 sequences, one of four ranks, 25 us against 38 and more; 128 of median
+// 150, forward and backward, 29 -> 18.)
+constexpr int DIRECT_BATCH = 128;
 struct ItemPlan {
   DirectPlan d;
   Item* items;

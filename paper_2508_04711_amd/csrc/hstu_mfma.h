@@ -510,9 +510,6 @@ struct Window {
   __device__ __forceinline__ VisWindow vis(int b, int hh) const { return VisWindow{b - lo, span, hh}; }
 };
 
-__device__ __forceinline__ int wave_min(int x);
-__device__ __forceinline__ int wave_max(int x);
-
 // side 0: owners are queries, 1: owners are keys.  row_seq[row] = {first row, end row} of the
 // row's sequence.  Lanes without a valid owner row get an empty window.
 // The bounds are loaded on their own (window_bounds) so that a kernel can request them first of
@@ -568,20 +565,6 @@ __device__ __forceinline__ void rec_copy_async(char* tile, const TsRecord* rec, 
   __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, HSTU_LDS(void, tile), 16, lane * 16, 0, 0, 0);
 }
 
-// Minimum and maximum over the wave's lanes, on the vector pipe (a shuffle goes through LDS: six
-// dependent round trips per reduction, and a packed item needs four of them).
-template <class F>
-__device__ __forceinline__ int wave_reduce(int x, const F& f) {
-  x = f(x, __builtin_amdgcn_update_dpp(x, x, 0x111, 0xf, 0xf, false));  // row_shr:1, 2, 4, 8
-  x = f(x, __builtin_amdgcn_update_dpp(x, x, 0x112, 0xf, 0xf, false));
-  x = f(x, __builtin_amdgcn_update_dpp(x, x, 0x114, 0xf, 0xf, false));
-  x = f(x, __builtin_amdgcn_update_dpp(x, x, 0x118, 0xf, 0xf, false));
-  x = f(x, __builtin_amdgcn_update_dpp(x, x, 0x142, 0xa, 0xf, false));  // row_bcast:15, :31
-  x = f(x, __builtin_amdgcn_update_dpp(x, x, 0x143, 0xc, 0xf, false));
-  return __builtin_amdgcn_readlane(x, 63);
-}
-__device__ __forceinline__ int wave_min(int x) { return wave_reduce(x, [](int a, int b) { return a < b ? a : b; }); }
-__device__ __forceinline__ int wave_max(int x) { return wave_reduce(x, [](int a, int b) { return a > b ? a : b; }); }
 __device__ __forceinline__ float wave_sum(float x) {
 #pragma unroll
   for (int m = 32; m >= 1; m >>= 1) x += __shfl_xor(x, m);

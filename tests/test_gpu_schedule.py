@@ -171,3 +171,119 @@ def test_heavy_query_tiles_are_cut_along_the_keys(cp):
     # a tile is either whole or in parts, never both
     whole_tiles = {(int(it[0]), int(it[1])) for it in whole}
     assert not (whole_tiles & {(k[0], k[1]) for k in by_tile})
+
+
+# ---- schedules that a wave per item builds (batches of up to 512 sequences), or that the attention kernels' waves
+# work out item by item: the same items, heaviest first by their exact cost
+RNG = np.random.default_rng(11)
+BATCHES = [
+    # one sequence per lane: up to 64, two to eight per lane: up to 512, the other builder beyond
+    [int(x) for x in RNG.integers(0, 900, size=64)],
+    [int(x) for x in RNG.integers(0, 900, size=65)],
+    [int(x) for x in RNG.integers(0, 500, size=512)],
+    [int(x) for x in RNG.integers(0, 500, size=513)],
+    [0] * 63 + [4000] + [0] * 70 + [31, 32, 33, 127, 128, 129, 3990],
+    [1], [127], [128], [129],
+]
+
+
+def _dump(lib, lengths, heads, causal, side, cp=None, dtype=0):
+    import oracle
+    T = sum(lengths)
+    off_np = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32)
+    off = torch.from_numpy(off_np).cuda()
+    if cp is not None:
+        nq, nk = len(oracle.cp_global_rows(off_np, cp[0], cp[1])), len(oracle.cp_global_rows(off_np, cp[0], cp[2]))
+        cp = cp + (nq, nk)
+    got = lib.hstu_debug_dump_schedule(off, T, heads, 128, 128, causal, dtype, side, cp=cp, max_len=max(lengths + [1]))
+    return got, (None if cp is None else (nq, nk))
+
+
+def _heavy_first_or_large(got, heads):
+    """Heavy tiles first; or, where the heaviest tile is at most half of what one of 512 workgroup slots gets, the
+    order of the rows (see test_full_attention_schedule)."""
+    large = (got[:, 10].max() - 1) * 2 * 512 <= got[:, 10].astype(np.int64).sum() * heads
+    return bool(np.all(got[:-1, 10] >= got[1:, 10]) or large and np.all(got[:-1, 0] < got[1:, 0]))
+
+
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("side", [0, 1])
+@pytest.mark.parametrize("dtype", [0, 1])
+@pytest.mark.parametrize("b", range(len(BATCHES)))
+def test_items_and_exact_order_of_small_batches(b, dtype, side, causal):
+    import paper_2508_04711_amd as lib
+    lengths = BATCHES[b]
+    got, _ = _dump(lib, lengths, 4, causal, side, dtype=dtype)
+    tile = lib.hstu_schedule_tile_rows(dtype, 128, 128, side, sum(lengths), 4, len(lengths))
+    assert sorted(map(tuple, got.tolist())) == sorted(_expected_items(lengths, tile, causal, side))
+    assert _heavy_first_or_large(got, 4)
+
+
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("side", [0, 1])
+@pytest.mark.parametrize("cp,q_rank,kv_rank", [(4, 1, -1), (4, 0, -1), (4, 2, 2), (4, 1, 3), (8, 7, 0), (2, 1, -1), (1, 0, -1)])
+@pytest.mark.parametrize("lengths", [[16, 5, 0, 233, 1, 400, 64, 777, 3000], [int(x) for x in RNG.integers(0, 1500, size=40)],
+                                     [int(x) for x in RNG.integers(0, 700, size=300)]], ids=["few", "forty", "many"])
+def test_items_and_exact_order_of_a_rank(lengths, cp, q_rank, kv_rank, side, causal):
+    import paper_2508_04711_amd as lib
+    got, rows = _dump(lib, lengths, 4, causal, side, cp=(cp, q_rank, kv_rank))
+    owner, streamed = (q_rank, kv_rank) if side == 0 else (kv_rank, q_rank)
+    want = _expected_items(lengths, 128, causal, side, cp, owner, streamed)
+    assert sorted(map(tuple, got.tolist())) == sorted(want)
+    assert _heavy_first_or_large(got, 4)
+
+
+@pytest.mark.parametrize("cp,heads", [(None, 5), ((2, 1, -1), 3), ((4, 0, 2), 6)])
+def test_query_tiles_cut_in_two(cp, heads):
+    """Query tiles of few long sequences, heavy ones cut in two: a tile's two parts are neighbours in the list, cover
+    what it sees, number their partial slots in order, and tiles come heaviest first."""
+    import paper_2508_04711_amd as lib
+    lengths = [9000, 5000, 700, 64] if cp is None else [40000, 9000, 700, 64]  # (for 512 to 1023 tiles of all heads)
+    got, _ = _dump(lib, lengths, heads, True, 0, cp=cp)
+    want = {(x[0], x[1], x[2]): x for x in _expected_items(lengths, 128, True, 0, *((1, -1, -1) if cp is None else cp))}
+    seen, i, order, parts = set(), 0, [], 0
+    while i < len(got):
+        key = tuple(int(x) for x in got[i][:3])
+        n = 1
+        while i + n < len(got) and tuple(int(x) for x in got[i + n][:3]) == key:
+            n += 1
+        assert key in want and key not in seen
+        seen.add(key)
+        w = want[key]
+        # 64 visible 32-row blocks per part at least
+        assert n == (2 if w[10] >= 128 else 1), (key, n, w[10])
+        rows = np.zeros(sum(lengths) + 1, dtype=np.int64)
+        for k in range(n):
+            it = got[i + k]
+            assert int(it[11]) == (i + k + 1 if n > 1 else 0)
+            for g in range(int(it[3])):
+                hi = min(int(it[4 + g] + it[6 + g]), int(it[4 + g]) + max(0, key[2] + key[1] - int(it[8 + g])))
+                rows[int(it[4 + g]):hi] += 1
+        for g in range(w[3]):
+            hi = min(w[4 + g] + w[6 + g], w[4 + g] + max(0, key[2] + key[1] - w[8 + g]))
+            rows[w[4 + g]:hi] -= 1
+        assert not rows.any(), key
+        parts += n > 1
+        order.append(w[10])
+        i += n
+    assert len(seen) == len(want) and parts > 0
+    assert all(a >= b for a, b in zip(order, order[1:]))
+
+
+@pytest.mark.parametrize("side", [0, 1])
+@pytest.mark.parametrize("cp", [None, (4, 1, -1), (4, 1, 2)])
+@pytest.mark.parametrize("off", [[0, 100, 5000], [0, 250, 100, 280, 300], [0, -7, 90, 90, 2 ** 31 - 1], [50, 60, 10, 300]])
+def test_inconsistent_offsets_of_small_batches_stay_inside(off, cp, side):
+    """Offsets that overshoot, go back or start late: no item leaves the declared rows of either side."""
+    import paper_2508_04711_amd as lib
+    T = 300
+    rows = (T, T) if cp is None else (T // 4 + 3, T if cp[2] < 0 else T // 4 + 5)
+    desc = None if cp is None else cp + rows
+    dev = torch.tensor(off, dtype=torch.int32, device="cuda")
+    for heads in (1, 64):  # (worked out by every wave; listed by a wave per item)
+        got = lib.hstu_debug_dump_schedule(dev, T, heads, 64, 64, True, 0, side, cp=desc, max_len=T)
+        own, streamed = rows if side == 0 else rows[::-1]
+        for it in got:
+            assert 0 <= it[0] and it[0] + it[1] <= own
+            for g in range(it[3]):
+                assert 0 <= it[4 + g] and it[4 + g] + it[6 + g] <= streamed
