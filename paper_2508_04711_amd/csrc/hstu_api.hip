@@ -276,18 +276,30 @@ int prepare_plan(const hstu_attn_params* p, int cp_size, const SideSpec& s, cons
   const int64_t batch = p->batch > 0 ? p->batch : 1;
   const int64_t all_pairs = s.owner_rows / batch * (s.streamed_rows / batch) / (p->causal ? 2 : 1) * batch;
   const int64_t per_slot = all_pairs / 512 * p->num_heads;
-  // How small a fraction: a half in the forward pass, which reads the streamed rows of neighbours from one
-  // L2 and loses more to the sorted order than to an uneven tail even where the longest sequences come last
-  // (H = 4, d = 128, sorted -> natural: 512 sequences of 300..600 rows 392 -> 276 us, 256 of them 162 -> 152; 768
-  // with lognormal lengths of median 256 372 -> 324, sorted by length 369 -> 364).  A third in the dq pass, whose items
-  // last longer (bwd: 256 lognormal of median 512, H = 8, a fraction of 1/3.4, 2036 -> 1917, but 64 of 500..1000, H = 8,
-  // 1/2.2, 497 -> 509 and 768 of median 256 sorted by length, 1/2.6, 1124 -> 1164).  A quarter on the key side at two
-  // and three workgroups per CU (H = 8, d = 64: 400 lognormal of median 512 fwd + bwd 2165 -> 1964; at a half 128 of
-  // 400..800 rows lose 2 %).  An eighth where walking workgroups take runs of equal numbers of items (256
-  // lognormal of median 512, H = 8, d = 128: bwd 2070 -> 2470 at a half, and 1536 of median 256 sorted by length 2262
-  // -> 2669 at a quarter).
-  const int64_t fraction = s.pass == PASS_FWD ? 2 : s.pass == PASS_DQ ? 3 : (p->d_qk + p->d_v <= 128 ? 4 : 8);
-  const bool large = (int64_t)tile_rows(p, s.pass, s.owner_rows) * longest * fraction < per_slot;
+  // How small a fraction: an eighth always.  Some bf16 passes gain up to a larger one, `fraction`, as long as there
+  // are enough (sequence, head) pairs: what natural order saves, the streamed rows that an XCD's L2 then reads
+  // once, grows with the pairs that compete for it, and what it costs is an uneven tail of about the heaviest
+  // item's share, so the line lies where pairs / share reaches `need`.
+  // Forward, a half, H = 8 or 4, d = 128, us sorted -> natural, with pairs / share: 8 sequences of lognormal length,
+  // median 8192, 2760 -> 2935 (200), 12 of 6000..12000 1800 -> 1855 (480), 32 of 5000 +- 33 % 859 -> 897 (450), 64 of
+  // lognormal 5000 1913 -> 2010 (680), but 32 of 2500 +- 33 % 504 -> 492 (890), 64 of 700 124 -> 119 (1030), 512 of
+  // 300..600 392 -> 276 (10000), 256 lognormal of mean 1400 2920 -> 2054 (6200).  At d = 64 the rows are half as
+  // long and the gain begins later: 64 of lognormal 2500 610 -> 652 (1360), 256 of 350 111 -> 102 (8400).
+  // The dq pass, whose items last longer, a third: 32 of 5000 1278 -> 1359 (450), 32 of 2500 690 -> 719 (890), 64 of
+  // 1400 at a quarter 510 -> 507 (2060), 512 of lognormal 700 815 -> 729 (6200); at d = 64 256 of lognormal 1400
+  // 1885 -> 2022 (6200), 512 of lognormal 350 298 -> 273 (12000).
+  // The key side at two and three workgroups per CU (H = 8, d = 64) a quarter: 400 lognormal of median 512 fwd + bwd
+  // 2165 -> 1964; at a half 128 of 400..800 rows lose 2 %.  No more than an eighth where walking workgroups take
+  // runs of equal numbers of items (256 lognormal of median 512, H = 8, d = 128: bwd 2070 -> 2470 at a half, and 1536
+  // of median 256 sorted by length 2262 -> 2669 at a quarter).  fp32 keeps to an eighth (its tiles are a quarter as
+  // tall and its passes bound by the matrix rate).
+  const int64_t heaviest = (int64_t)tile_rows(p, s.pass, s.owner_rows) * longest;
+  const bool small_d = p->d_qk + p->d_v <= 128;
+  const int64_t fraction = s.pass == PASS_FWD ? 2 : s.pass == PASS_DQ ? 3 : small_d ? 4 : 8;
+  const int64_t need = s.pass == PASS_FWD ? (small_d ? 1800 : 900) : s.pass == PASS_DQ ? (small_d ? 8000 : 1300) : 3000;
+  const bool large = heaviest * 8 < per_slot ||
+                     (p->dtype == HSTU_BF16 && heaviest * fraction < per_slot &&
+                      (double)batch * p->num_heads * (double)per_slot > (double)need * (double)heaviest);
   // The dK/dV pass at one workgroup per CU walks over the list (see launch_dkdv_bf16): in natural
   // order when its workgroups can take contiguous runs of one XCD's share, which needs a head
   // count that divides 8; sorted by cost, every 256th item, otherwise.

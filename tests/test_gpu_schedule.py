@@ -287,3 +287,31 @@ def test_inconsistent_offsets_of_small_batches_stay_inside(off, cp, side):
             assert 0 <= it[0] and it[0] + it[1] <= own
             for g in range(it[3]):
                 assert 0 <= it[4 + g] and it[4 + g] + it[6 + g] <= streamed
+
+
+def _order(lengths, heads, d, side, dtype=0):
+    import paper_2508_04711_amd as lib
+    off = torch.tensor(np.concatenate([[0], np.cumsum(lengths)]), dtype=torch.int32, device="cuda")
+    got = lib.hstu_debug_dump_schedule(off, sum(lengths), heads, d, d, True, dtype, side, max_len=max(lengths))
+    heavy = bool(np.all(got[:-1, 10] >= got[1:, 10]))
+    rows = bool(np.all(got[:-1, 0] < got[1:, 0]))
+    assert heavy != rows
+    return "heavy first" if heavy else "rows"
+
+
+def test_which_batches_keep_the_order_of_the_rows():
+    """Few long sequences are sorted, whatever share of a slot's work their heaviest tile is (in the order of the rows
+    their passes end with one sequence's tiles); many short ones are not.  fp32 lists are sorted up to the share that
+    is small for any batch."""
+    rng = np.random.default_rng(0)
+    skewed = [int(x) for x in np.clip(np.rint(rng.lognormal(np.log(8192), 0.8, 8)), 64, 32768)]
+    long12 = [int(x) for x in np.random.default_rng(3).integers(6000, 12000, size=12)]
+    short = [int(x) for x in rng.integers(300, 600, size=512)]
+    for d in (64, 128):
+        for side in (0, 1):
+            assert _order(skewed, 8, d, side) == "heavy first", (d, side)
+            assert _order(long12, 8, d, side) == "heavy first", (d, side)
+        assert _order(short, 4, d, 0) == "rows", d
+    some = [int(x) for x in rng.integers(300, 900, size=60)]
+    assert _order(some, 4, 64, 0, dtype=1) == "heavy first"
+    assert _order([int(x) for x in rng.integers(100, 200, size=3000)], 4, 64, 0, dtype=1) == "rows"
