@@ -268,6 +268,7 @@ __global__ void __launch_bounds__(256, 2) hstu_bwd_short_bf16(AttnArgs a) {
 
     const int b = clampi(ob, 0, T), e = clampi(oe, b, T);
     const int b0 = __builtin_amdgcn_readfirstlane(b), e0 = __builtin_amdgcn_readfirstlane(e);
+    if (b0 >= r1) break;  // all that follow begin in other shares or have no rows
     const int before = __shfl_up(e, 1, 64);
     // the sequences that follow one another from the first on and end within 128 rows
     const bool in = i + lane < B && e - b0 <= GT && b < r1 && (lane == 0 || b == before);

@@ -26,6 +26,7 @@ CASES = [
     ("many", [int(x) for x in RNG.integers(16, 129, size=1200)], 128, 2, 64, False),
     ("too_long", [100, 129, 20, 256, 257, 3, 700, 128, 0, 385] + [30] * 60, 128, 2, 128, False),
     ("too_long", [1000] + [5] * 200 + [300], 64, 1, 64, True),
+    ("empties_between_shares", ([100, 27] + [0] * 300) * 30 + [0] * 5000, 128, 2, 64, False),
 ]
 
 
@@ -50,3 +51,31 @@ def test_short_backward(name, lengths, max_len, H, D, few, causal, monkeypatch):
                 _check_few_terms(nm, g, ref, name)
             else:
                 _check(nm, g, ref, "bf16", name)
+
+
+def _backward_us(lib, lengths, max_len, H, D):
+    """Median time of the backward pass's kernels without their schedule, and which they are."""
+    w = workloads.custom("timed", lengths, H, D, D, max_len=max_len, dtype="bf16", seed=3)
+    d = _dev(workloads.values(w))
+    off = torch.from_numpy(w.seq_offsets()).cuda()
+    times = []
+    for _ in range(9):
+        lib.hstu_debug_timing_begin(16)
+        lib.hstu_jagged_attn_bwd(d["q"], d["k"], d["v"], d["d_o"], off, max_len, w.alpha, True)
+        torch.cuda.synchronize()
+        got = [x for x in lib.hstu_debug_timing_end(16) if x[0] != "plan"]
+        times.append(1e3 * sum(x[1] for x in got))
+    return float(np.median(times)), {x[0] for x in got}
+
+
+def test_empty_sequences_at_the_end_cost_next_to_nothing(monkeypatch):
+    """(Stepped over one by one, thousands of them took 35 times as long as the batch.)"""
+    set_flags(monkeypatch, remove="NO_PACK")
+    import paper_2508_04711_amd as lib
+    print("short bwd, trailing empties", flush=True)
+    lengths = [int(x) for x in RNG.integers(16, 100, size=400)]
+    plain, kinds = _backward_us(lib, lengths, 100, 4, 128)
+    padded, kinds2 = _backward_us(lib, lengths + [0] * 20000, 100, 4, 128)
+    assert kinds == kinds2 == {"bwd"}
+    assert padded < 3 * plain + 50, (plain, padded)
+
