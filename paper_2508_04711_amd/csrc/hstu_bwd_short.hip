@@ -17,19 +17,19 @@ namespace {
 // dV^T = dO^T P and dK^T = Q^T dS over all blocks, one accumulator after the other.  Last, dS and K take
 // the place of Q and dO in LDS, and wave w owns queries 32w..32w+31: dQ^T = K^T dS^T, both operands
 // through transposing reads (dS lies key by key).  With one accumulator alive at a time the kernel fits
-// 256 registers, so that two workgroups share a CU, one computing while the other's loads and stores are
-// under way.
+// 256 registers at d = 128 (three spill, in the code for sequences of more than 128 rows) and 168 at d = 64, so that
+// two and three workgroups share a CU, some computing while the others' loads and stores are under way.
 //
 // Bound by memory: the seven tensors once.  8192 sequences of 16..64 rows, H = 4, d = 128 (2.35 GB): 848 us
 // for schedule, dk/dv and dq pass (4.3 GB) -> 537 us, 4.4 TB/s; 1024 of 120..128 rows 386 -> 220; at d = 64, 4096
 // of 64..128 rows 530 -> 360; small ones, where launches count: 256 of 64..128 rows, H = 2, d = 64 36 -> 23.
 // (With silu' of all blocks kept in fp32 instead, so that dV needs no P kept, the registers do not suffice.)
 //
-// There is no schedule: a workgroup takes the units whose first row lies in its share of the rows, one
-// head, and works the groups out from the offsets (64 sequences per look, one per lane).
+// There is no schedule: a workgroup takes the groups whose first row lies in its share of the rows, one
+// head, and works them out from the offsets (64 sequences per look, one per lane).
 // A sequence of more than 128 rows (the host sends batches whose max_len says there are none, but
-// lengths above max_len are still computed) is cut into units of 128 rows which go over the other
-// tiles of the sequence three times, once per accumulator.
+// lengths above max_len are still computed) is left to workgroups of their own at the end of the grid: see
+// long_sequences.
 // =============================================================================================
 
 constexpr int GT = 128;  // rows of a group
@@ -179,24 +179,144 @@ __device__ __forceinline__ void query_grads(const ShortWave<D>& w, const char* d
 template <int D>
 constexpr int short_lds() { return 2 * GT * D * 2 > GT * GT * 2 + GT * D * 2 ? 2 * GT * D * 2 : GT * GT * 2 + GT * D * 2; }
 
+// What a workgroup's loads and stores of one head need.
 template <int D>
-__global__ void __launch_bounds__(256, 2) hstu_bwd_short_bf16(AttnArgs a) {
+struct ShortIo {
+  const AttnArgs& a;
+  char *qt, *gt, *dst, *kt;  // LDS: Q and dO, whose place dS and K take
+  int64_t sr;                // row stride in elements
+  int h, lane, wave, orow, hh;
+  __device__ __forceinline__ void load_keys(bf16x8 (&kreg)[D / 16], bf16x8 (&vreg)[D / 16], int row, int rows) const {
+    load_owner<D>(kreg, (const __bf16*)a.k + (int64_t)row * sr + h * D, sr, orow, rows, hh);
+    load_owner<D>(vreg, (const __bf16*)a.v + (int64_t)row * sr + h * D, sr, orow, rows, hh);
+  }
+  __device__ __forceinline__ void load_queries(int row, int rows) const {  // (`rows` may be more than the 128 that are copied)
+#pragma unroll
+    for (int x = 0; x < GT / ST; ++x) {
+      const int64_t at = (int64_t)(row + x * ST) * sr + h * D;
+      tile_copy_async<D, 4>(qt + x * ST * D * 2, (const __bf16*)a.q + at, sr, rows - x * ST, wave, lane);
+      tile_copy_async<D, 4>(gt + x * ST * D * 2, (const __bf16*)a.d_o + at, sr, rows - x * ST, wave, lane);
+    }
+  }
+  __device__ __forceinline__ void landed() const {
+    tile_copy_wait<0>();
+    tile_barrier();
+  }
+  __device__ __forceinline__ void exchange(const bf16x8 (&kreg)[D / 16], const bf16x8 (&ds)[NBLK][2]) const {
+    tile_barrier();
+    hand_over<D>(dst, kt, kreg, ds, lane, wave);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    tile_barrier();
+  }
+  __device__ __forceinline__ void store(void* out, int row, int rows, const f32x16 (&acc)[D / 32]) const {
+    if (orow < rows) store_owner_major<D>(out, ((int64_t)row + orow) * sr + h * D, acc, a.alpha * a.inv_n, hh, 0, a.out_f32);
+  }
+};
+template <int D>
+__device__ __forceinline__ void clear(f32x16 (&acc)[D / 32]) {
+#pragma unroll
+  for (int c = 0; c < D / 32; ++c)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[c][r] = 0.f;
+}
+
+// The sequences of more than 128 rows, by `helpers` workgroups per head: every tile of 128 rows is three items, dV, dK and
+// dQ, each a walk over the tiles its rows see, dealt out in turn, each sequence's longest first.  The first thing
+// such a workgroup does is look whether there is any such sequence; if not, that look is all it costs, and it
+// happens in the tail of the others.  (With the long sequences' tiles computed by the workgroups in whose shares
+// of the rows they lie, three walks in a row, those were the last by far: 400 sequences of 16..100 rows and one of
+// 4096, max_len = 128, H = 4, d = 128, 629 us against 320 of the two passes; now 256.)
+template <int D>
+__device__ __forceinline__ void long_sequences(const AttnArgs& a, char* smem, int h, int me, int helpers) {
+  const int T = a.self.total_rows, B = a.self.batch, tid = threadIdx.x;
+  const int32_t* off = a.self.off;
+  int any = 0;
+#pragma unroll 8
+  for (int j = tid; j < B; j += 256) {
+    int s, e;
+    seq_range(off, j, T, s, e);
+    any |= e - s > GT;
+  }
+  if (!__syncthreads_or(any)) return;
+
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const float c1 = -a.alpha * 1.4426950408889634f;
+  bf16x8 kreg[D / 16], vreg[D / 16], pk[NBLK][2], ds[NBLK][2];
+  f32x16 acc[D / 32];
+  int turn = me;  // items until this workgroup's next one
+  for (int first = 0; first < B; first += 64) {
+    int s = 0, e = 0;
+    if (first + (tid & 63) < B) seq_range(off, first + (tid & 63), T, s, e);
+    for (unsigned long long longs = __ballot(e - s > GT); longs; longs &= longs - 1) {
+      const int l = __builtin_ctzll(longs);
+      const int b0 = __builtin_amdgcn_readlane(s, l), len = __builtin_amdgcn_readlane(e, l) - b0;
+      const int nt = (len >> 7) + ((len & (GT - 1)) != 0);
+      for (; turn < 3 * nt; turn += helpers) {
+        const int part = turn % 3, m = turn / 3, t = part < 2 ? m : nt - 1 - m;
+        const int row = b0 + t * GT, rows = len - t * GT < GT ? len - t * GT : GT;
+        const int2 whole = make_int2(0, len);
+        // (worked out again for every item, as for every group below)
+        const int lane = opaque(tid & 63), n = lane & 31, hh = lane >> 5, orow = wave * 32 + n;
+        const ShortIo<D> io = {a, smem, smem + GT * D * 2, smem, smem + GT * GT * 2, (int64_t)a.num_heads * D, h, lane, wave,
+                               orow, hh};
+        ShortWave<D> w;
+        w.ra.init(n, hh);
+        w.ca.init(lane);
+        clear<D>(acc);
+        auto key_side = [&](auto tag) {
+          constexpr bool DV = decltype(tag)::value;
+          const Window wk = make_window(whole, t * GT + orow, orow < rows, 1, a.causal);
+          io.load_keys(kreg, vreg, row, rows);
+          for (int x = a.causal ? t : 0; x < nt; ++x) {
+            io.load_queries(b0 + x * GT, len - x * GT);
+            io.landed();
+            const int seen = scores<D, DV, !DV>(w, io.qt, io.gt, kreg, vreg, pk, ds, wk, x * GT, hh, c1, a.alpha);
+            contract<D>(w, DV ? io.gt : io.qt, DV ? pk : ds, acc, seen);
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            tile_barrier();
+          }
+          io.store(DV ? a.dv : a.dk, row, rows, acc);
+        };
+        if (part == 0) { key_side(std::true_type{}); continue; }
+        if (part == 1) { key_side(std::false_type{}); continue; }
+        const Window wq = make_window(whole, t * GT + orow, orow < rows, 0, a.causal);
+        for (int x = 0; x < (a.causal ? t + 1 : nt); ++x) {
+          const int krow = x * GT, krows = len - krow < GT ? len - krow : GT;
+          io.load_keys(kreg, vreg, b0 + krow, krows);
+          io.load_queries(row, rows);
+          const Window wx = make_window(whole, krow + orow, orow < krows, 1, a.causal);
+          io.landed();
+          scores<D, false, true>(w, io.qt, io.gt, kreg, vreg, pk, ds, wx, t * GT, hh, c1, a.alpha);
+          io.exchange(kreg, ds);
+          query_grads<D>(w, io.dst, io.kt, acc, wq, krow, lane, wave);
+          asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+          tile_barrier();
+        }
+        io.store(a.dq, row, rows, acc);
+      }
+      turn -= 3 * nt;
+    }
+  }
+}
+
+// a.max_items: shares of the rows per head.  Workgroups beyond are long_sequences' helpers.
+template <int D>
+__global__ void __launch_bounds__(256, D == 64 ? 3 : 2) hstu_bwd_short_bf16(AttnArgs a) {
   __shared__ __attribute__((aligned(1024))) char smem[short_lds<D>()];
-  char* const qt = smem;               // Q, then dS
-  char* const gt = smem + GT * D * 2;  // dO
-  char* const dst = smem;
-  char* const kt = smem + GT * GT * 2;  // K
 
   const int H = a.num_heads, h = blockIdx.x % H, T = a.self.total_rows, B = a.self.batch;
+  const int shares = a.max_items, share = blockIdx.x / H;
+  if (share >= shares) {
+    long_sequences<D>(a, smem, h, share - shares, (int)(gridDim.x / H) - shares);
+    return;
+  }
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int64_t sr = (int64_t)H * D;
-  const float c1 = -a.alpha * 1.4426950408889634f, scale = a.alpha * a.inv_n;
+  const float c1 = -a.alpha * 1.4426950408889634f;
   const int32_t* off = a.self.off;
 
-  // The workgroup's share of the rows, and the first unit that begins in it.
-  const int shares = (int)(gridDim.x / H), share = blockIdx.x / H;
+  // The workgroup's share of the rows, and the first sequence that begins in it.
   const int r0 = (int)((int64_t)T * share / shares), r1 = (int)((int64_t)T * (share + 1) / shares);
-  int i = 0, t = 0;  // first sequence of the unit, tile of a long one
+  int i = 0;
   {
     int lo = 0, hi = B;
     while (hi - lo > 1) {
@@ -205,14 +325,9 @@ __global__ void __launch_bounds__(256, 2) hstu_bwd_short_bf16(AttnArgs a) {
     }
     int s, e;
     seq_range(off, lo, T, s, e);
-    i = lo;
-    if (s < r0) {
-      t = e - s > GT ? (r0 - s + GT - 1) / GT : 0;
-      if (t == 0 || t >= (e - s + GT - 1) / GT) { ++i; t = 0; }
-    }
+    i = s < r0 ? lo + 1 : lo;
   }
   i = __builtin_amdgcn_readfirstlane(i);
-  t = __builtin_amdgcn_readfirstlane(t);
 
   // Sequences i .. i + 63 as they lie in memory, one per lane, requested a unit ahead.
   int ob = 0, oe = 0;
@@ -228,127 +343,54 @@ __global__ void __launch_bounds__(256, 2) hstu_bwd_short_bf16(AttnArgs a) {
     // than there are)
     const int lane = opaque(threadIdx.x & 63);
     const int n = lane & 31, hh = lane >> 5, orow = wave * 32 + n;
+    const ShortIo<D> io = {a, smem, smem + GT * D * 2, smem, smem + GT * GT * 2, (int64_t)H * D, h, lane, wave, orow, hh};
     ShortWave<D> w;
     w.ra.init(n, hh);
     w.ca.init(lane);
-
     bf16x8 kreg[D / 16], vreg[D / 16], pk[NBLK][2], ds[NBLK][2];
     f32x16 acc[D / 32];
-    auto clear_acc = [&] {
-#pragma unroll
-      for (int c = 0; c < D / 32; ++c)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[c][r] = 0.f;
-    };
-    auto load_keys = [&](int row, int rows) {
-      load_owner<D>(kreg, (const __bf16*)a.k + (int64_t)row * sr + h * D, sr, orow, rows, hh);
-      load_owner<D>(vreg, (const __bf16*)a.v + (int64_t)row * sr + h * D, sr, orow, rows, hh);
-    };
-    auto load_queries = [&](int row, int rows) {  // (`rows` may be more than the 128 that are copied)
-#pragma unroll
-      for (int x = 0; x < GT / ST; ++x) {
-        const int64_t at = (int64_t)(row + x * ST) * sr + h * D;
-        tile_copy_async<D, 4>(qt + x * ST * D * 2, (const __bf16*)a.q + at, sr, rows - x * ST, wave, lane);
-        tile_copy_async<D, 4>(gt + x * ST * D * 2, (const __bf16*)a.d_o + at, sr, rows - x * ST, wave, lane);
-      }
-    };
-    auto landed = [&] {
-      tile_copy_wait<0>();
-      tile_barrier();
-    };
-    auto store = [&](void* out, int row, int rows) {
-      if (orow < rows) store_owner_major<D>(out, ((int64_t)row + orow) * sr + h * D, acc, scale, hh, 0, a.out_f32);
-    };
-    auto exchange = [&] {  // dS and K take the place of Q and dO
-      tile_barrier();
-      hand_over<D>(dst, kt, kreg, ds, lane, wave);
-      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-      tile_barrier();
-    };
 
     const int b = clampi(ob, 0, T), e = clampi(oe, b, T);
-    const int b0 = __builtin_amdgcn_readfirstlane(b), e0 = __builtin_amdgcn_readfirstlane(e);
+    const int b0 = __builtin_amdgcn_readfirstlane(b);
     if (b0 >= r1) break;  // all that follow begin in other shares or have no rows
     const int before = __shfl_up(e, 1, 64);
     // the sequences that follow one another from the first on and end within 128 rows
     const bool in = i + lane < B && e - b0 <= GT && b < r1 && (lane == 0 || b == before);
     const unsigned long long out = ~__ballot(in);
     const int count = out ? __builtin_ctzll(out) : 64;
-    if (count > 0) {
-      const int rows = __builtin_amdgcn_readlane(e, count - 1) - b0;
-      i += count;
-      request(i);
-      if (rows <= 0) continue;
-      load_keys(b0, rows);
-      load_queries(b0, rows);
-      // the sequence of the lane's row
-      int l = 0;
-#pragma unroll
-      for (int step = 32; step >= 1; step >>= 1) {
-        const int m = l + step, bm = __shfl(b, m & 63, 64);
-        if (m < count && bm - b0 <= orow) l = m;
-      }
-      const int2 sq = make_int2(__shfl(b, l, 64) - b0, __shfl(e, l, 64) - b0);
-      const Window wk = make_window(sq, orow, orow < rows, 1, a.causal);
-      const Window wq = make_window(sq, orow, orow < rows, 0, a.causal);
-      landed();
-      const int seen = scores<D, true, true>(w, qt, gt, kreg, vreg, pk, ds, wk, 0, hh, c1, a.alpha);
-      clear_acc();
-      contract<D>(w, gt, pk, acc, seen);
-      store(a.dv, b0, rows);
-      clear_acc();
-      contract<D>(w, qt, ds, acc, seen);
-      store(a.dk, b0, rows);
-      exchange();
-      clear_acc();
-      query_grads<D>(w, dst, kt, acc, wq, 0, lane, wave);
-      store(a.dq, b0, rows);
-      tile_barrier();
-      continue;
-    }
-    // a tile of a long sequence, or the end of the share
-    const int len = e0 - b0, nt = (len + GT - 1) / GT;
-    if (t >= nt) {
-      t = 0;
+    if (count == 0) {  // one of more than 128 rows
       request(++i);
       continue;
     }
-    const int row = b0 + t * GT;
-    if (row >= r1) break;
-    const int rows = len - t * GT < GT ? len - t * GT : GT;
-    const int2 whole = make_int2(0, len);
-    const int qfirst = a.causal ? t : 0, klast = a.causal ? t : nt - 1;
-    const Window wk = make_window(whole, t * GT + orow, orow < rows, 1, a.causal);
-    const Window wq = make_window(whole, t * GT + orow, orow < rows, 0, a.causal);
-    auto key_side = [&](auto tag) {
-      constexpr bool DV = decltype(tag)::value;
-      clear_acc();
-      for (int x = qfirst; x < nt; ++x) {
-        load_keys(row, rows);
-        load_queries(b0 + x * GT, len - x * GT);
-        landed();
-        const int seen = scores<D, DV, !DV>(w, qt, gt, kreg, vreg, pk, ds, wk, x * GT, hh, c1, a.alpha);
-        contract<D>(w, DV ? gt : qt, DV ? pk : ds, acc, seen);
-        tile_barrier();
-      }
-      store(DV ? a.dv : a.dk, row, rows);
-    };
-    key_side(std::true_type{});
-    key_side(std::false_type{});
-    clear_acc();
-    for (int x = 0; x <= klast; ++x) {
-      const int krow = x * GT, krows = len - krow < GT ? len - krow : GT;
-      load_keys(b0 + krow, krows);
-      load_queries(row, rows);
-      const Window wx = make_window(whole, krow + orow, orow < krows, 1, a.causal);
-      landed();
-      scores<D, false, true>(w, qt, gt, kreg, vreg, pk, ds, wx, t * GT, hh, c1, a.alpha);
-      exchange();
-      query_grads<D>(w, dst, kt, acc, wq, krow, lane, wave);
-      tile_barrier();
+    const int rows = __builtin_amdgcn_readlane(e, count - 1) - b0;
+    i += count;
+    request(i);
+    if (rows <= 0) continue;
+    io.load_keys(kreg, vreg, b0, rows);
+    io.load_queries(b0, rows);
+    // the sequence of the lane's row
+    int l = 0;
+#pragma unroll
+    for (int step = 32; step >= 1; step >>= 1) {
+      const int m = l + step, bm = __shfl(b, m & 63, 64);
+      if (m < count && bm - b0 <= orow) l = m;
     }
-    store(a.dq, row, rows);
-    ++t;
+    const int2 sq = make_int2(__shfl(b, l, 64) - b0, __shfl(e, l, 64) - b0);
+    const Window wk = make_window(sq, orow, orow < rows, 1, a.causal);
+    const Window wq = make_window(sq, orow, orow < rows, 0, a.causal);
+    io.landed();
+    const int seen = scores<D, true, true>(w, io.qt, io.gt, kreg, vreg, pk, ds, wk, 0, hh, c1, a.alpha);
+    clear<D>(acc);
+    contract<D>(w, io.gt, pk, acc, seen);
+    io.store(a.dv, b0, rows, acc);
+    clear<D>(acc);
+    contract<D>(w, io.qt, ds, acc, seen);
+    io.store(a.dk, b0, rows, acc);
+    io.exchange(kreg, ds);
+    clear<D>(acc);
+    query_grads<D>(w, io.dst, io.kt, acc, wq, 0, lane, wave);
+    io.store(a.dq, b0, rows, acc);
+    tile_barrier();
   }
 }
 
@@ -358,13 +400,18 @@ bool bwd_short_supported(int d_qk, int d_v) { return d_qk == d_v && (d_qk == 64 
 
 hipError_t launch_bwd_short_bf16(const AttnArgs& a, int d_qk, int d_v, hipStream_t stream) {
   if (!bwd_short_supported(d_qk, d_v) || !a.self.off || a.self.batch < 1 || a.ts_rec || a.accumulate) return hipErrorInvalidValue;
-  // as many workgroups as are resident at once, but no more shares than groups
+  // As many workgroups as are resident at once, but no more shares than groups; then the helpers of sequences
+  // of more than 128 rows, on the slots that are left over or, if those are few, on all of them in turn.
   const int64_t resident = d_qk == 128 ? 512 : 768, groups = ((int64_t)a.self.total_rows + GT - 1) / GT;
-  int64_t shares = resident / a.num_heads;
-  shares = shares < 1 ? 1 : (shares > groups ? groups : shares);
-  const dim3 grid((unsigned)(shares * a.num_heads)), block(256);
-  if (d_qk == 128) hipLaunchKernelGGL((hstu_bwd_short_bf16<128>), grid, block, 0, stream, a);
-  else hipLaunchKernelGGL((hstu_bwd_short_bf16<64>), grid, block, 0, stream, a);
+  const int64_t slots = resident / a.num_heads < 1 ? 1 : resident / a.num_heads;
+  const int64_t shares = slots > groups ? groups : slots;
+  int64_t helpers = slots - shares > slots / 4 ? slots - shares : slots;
+  if (helpers > groups) helpers = groups;
+  AttnArgs args = a;
+  args.max_items = (int32_t)shares;
+  const dim3 grid((unsigned)((shares + helpers) * a.num_heads)), block(256);
+  if (d_qk == 128) hipLaunchKernelGGL((hstu_bwd_short_bf16<128>), grid, block, 0, stream, args);
+  else hipLaunchKernelGGL((hstu_bwd_short_bf16<64>), grid, block, 0, stream, args);
   return hipGetLastError();
 }
 

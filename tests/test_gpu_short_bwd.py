@@ -26,6 +26,8 @@ CASES = [
     ("many", [int(x) for x in RNG.integers(16, 129, size=1200)], 128, 2, 64, False),
     ("too_long", [100, 129, 20, 256, 257, 3, 700, 128, 0, 385] + [30] * 60, 128, 2, 128, False),
     ("too_long", [1000] + [5] * 200 + [300], 64, 1, 64, True),
+    ("too_long_far_apart", [3] * 5 + [400] + [12] * 2300 + [129, 128, 260, 0, 0] + [7] * 700 + [500], 32, 3, 64, True),
+    ("long_ones_only", [300, 129, 700, 130] + [0] * 30, 128, 2, 128, False),
     ("empties_between_shares", ([100, 27] + [0] * 300) * 30 + [0] * 5000, 128, 2, 64, False),
 ]
 
@@ -46,6 +48,14 @@ def test_short_backward(name, lengths, max_len, H, D, few, causal, monkeypatch):
     for dtype in (torch.bfloat16, torch.float32):
         out = tuple(torch.full_like(d["q"], float("nan"), dtype=dtype) for _ in range(3))  # (every row is written)
         got = lib.hstu_jagged_attn_bwd(d["q"], d["k"], d["v"], d["d_o"], off, max_len, w.alpha, causal, out=out)
+        if name == "too_long_far_apart":
+            # The bar is a share of the RMS over rows that are sums of about as many terms: the long
+            # sequences' rows (hundreds of terms, values and errors 5.5 times the others') by themselves.
+            rows = np.repeat(np.array(lengths) >= 128, lengths)
+            for nm, g, ref in zip(("dq", "dk", "dv"), got, want):
+                _check(nm, g[torch.from_numpy(rows).cuda()], ref[rows], "bf16", name)
+                _check_few_terms(nm, g[torch.from_numpy(~rows).cuda()], ref[~rows], name)
+            continue
         for nm, g, ref in zip(("dq", "dk", "dv"), got, want):
             if few:
                 _check_few_terms(nm, g, ref, name)
@@ -79,3 +89,17 @@ def test_empty_sequences_at_the_end_cost_next_to_nothing(monkeypatch):
     assert kinds == kinds2 == {"bwd"}
     assert padded < 3 * plain + 50, (plain, padded)
 
+
+def test_a_sequence_longer_than_max_len_says_is_spread_over_the_chip(monkeypatch):
+    """Against the two passes over packed tiles, which take any lengths alike (629 us against 320 with the long
+    sequence left to the workgroups in whose share it lies)."""
+    set_flags(monkeypatch, remove="NO_PACK")
+    import paper_2508_04711_amd as lib
+    print("short bwd, one long sequence", flush=True)
+    lengths = [int(x) for x in RNG.integers(16, 100, size=400)]
+    lengths[200] = 4096
+    one, kinds = _backward_us(lib, lengths, 128, 4, 128)
+    set_flags(monkeypatch, add="DKDV_ONE_WAVE")
+    two, kinds2 = _backward_us(lib, lengths, 128, 4, 128)
+    assert kinds == {"bwd"} and kinds2 == {"dkdv", "dq"}
+    assert one < 1.3 * two, (one, two)
