@@ -109,8 +109,8 @@ size_t packed_bytes(const hstu_attn_params* p) {
 
 // The backward pass in one kernel, which reads every input once: batches of packed tiles whose sequences fit
 // one tile.  Faster than the two passes wherever it was measured, 1.4 to 1.9 times: see hstu_bwd_short.hip for
-// figures from 300 sequences of 12..24 rows to 8192 of 16..64.  (max_len is the normaliser and no bound: a mean above it shows that it is not used as one.
-// Sequences longer than it says are computed there too, in 128-row tiles.)
+// figures from 300 sequences of 12..24 rows to 8192 of 16..64.  (max_len is the normaliser and no bound: a mean above it
+// shows that it is not used as one.  Sequences longer than it says are computed there too, by workgroups of their own.)
 bool short_backward(const hstu_attn_params* p) {
   return packed_tiles(p) && p->max_len <= PACKED_TILE && p->total_rows / p->batch <= p->max_len &&
          bwd_short_supported(p->d_qk, p->d_v) && !(p->flags & HSTU_FLAG_DKDV_ONE_WAVE);
@@ -291,16 +291,22 @@ int prepare_plan(const hstu_attn_params* p, int cp_size, const SideSpec& s, cons
   // The key side at two and three workgroups per CU (H = 8, d = 64) a quarter: 400 lognormal of median 512 fwd + bwd
   // 2165 -> 1964; at a half 128 of 400..800 rows lose 2 %.  No more than an eighth where walking workgroups take
   // runs of equal numbers of items (256 lognormal of median 512, H = 8, d = 128: bwd 2070 -> 2470 at a half, and 1536
-  // of median 256 sorted by length 2262 -> 2669 at a quarter).  fp32 keeps to an eighth (its tiles are a quarter as
-  // tall and its passes bound by the matrix rate).
+  // of median 256 sorted by length 2262 -> 2669 at a quarter).
+  // fp32 passes are bound by the matrix rate and only lose by the tail (256 sequences of 64..512 rows, H = 4, d = 64,
+  // forward, dk/dv and dq 941 -> 875 us sorted), so they keep to an eighth up to 512 sequences; beyond, the
+  // sorted build costs more than its order gains (4000 of 1..60, H = 2, d = 32, with the builds 319 -> 350 us sorted, 600
+  // of 16..200, H = 2, d = 128, 855 -> 875).
   const int64_t heaviest = (int64_t)tile_rows(p, s.pass, s.owner_rows) * longest;
   const bool small_d = p->d_qk + p->d_v <= 128;
   const int64_t fraction = s.pass == PASS_FWD ? 2 : s.pass == PASS_DQ ? 3 : small_d ? 4 : 8;
   const int64_t need = s.pass == PASS_FWD ? (small_d ? 1800 : 900) : s.pass == PASS_DQ ? (small_d ? 8000 : 1300) : 3000;
-  const bool large = heaviest * 8 < per_slot ||
-                     (p->dtype == HSTU_BF16 && heaviest * fraction < per_slot &&
-                      (double)batch * p->num_heads * (double)per_slot > (double)need * (double)heaviest);
-  // The dK/dV pass at one workgroup per CU walks over the list (see launch_dkdv_bf16): in natural
+  const bool large =
+      heaviest * 8 < per_slot ||
+      (heaviest * fraction < per_slot &&
+       (p->dtype == HSTU_F32 ? batch > 512
+                             : (double)batch * p->num_heads * (double)per_slot > (double)need * (double)heaviest));
+  // The dK/dV pass at one workgroup per CU walks over the list (see launch_dkdv_bf16 and
+  // launch_dkdv_walk_bf16): in natural
   // order when its workgroups can take contiguous runs of one XCD's share, which needs a head
   // count that divides 8; sorted by cost, every 256th item, otherwise.
   const bool chunks = large && s.side == 1 && short_sequences(p) && p->d_qk + p->d_v > 128 &&
