@@ -15,6 +15,7 @@ from test_gpu_parity import _check, _check_few_terms, _dev
 pytestmark = pytest.mark.gpu
 
 RNG = np.random.default_rng(91)
+# (max_len, the normaliser, is more than 128 throughout: below, packed tiles take the backward pass in one kernel)
 CASES = [
     # name, lengths, heads, few terms
     ("one_row", [1], 1, True),
@@ -33,7 +34,7 @@ def test_walking_dkdv(name, lengths, H, few, causal, monkeypatch):
     set_flags(monkeypatch, remove="NO_PACK", add="PACK_SHORT")
     import paper_2508_04711_amd as lib
     print("walk", name, H, causal, flush=True)
-    w = workloads.custom(name, lengths, H, 128, 128, max_len=max(max(lengths), 1), dtype="bf16", seed=len(lengths))
+    w = workloads.custom(name, lengths, H, 128, 128, max_len=max(max(lengths), 129), dtype="bf16", seed=len(lengths))
     vals = workloads.values(w)
     d = _dev(vals)
     off_np = w.seq_offsets()
@@ -41,7 +42,9 @@ def test_walking_dkdv(name, lengths, H, few, causal, monkeypatch):
     f64 = {k: workloads.to_f64(v) for k, v in vals.items()}
     want = oracle.bwd(f64["q"], f64["k"], f64["v"], f64["d_o"], off_np, w.max_len, w.alpha, causal)
     out = [torch.full_like(d["q"], float("nan")) for _ in range(3)]  # (every row is written)
+    lib.hstu_debug_timing_begin(16)
     got = lib.hstu_jagged_attn_bwd(d["q"], d["k"], d["v"], d["d_o"], off, w.max_len, w.alpha, causal, out=tuple(out))
+    assert [x[0] for x in lib.hstu_debug_timing_end(16)] == ["plan", "dkdv", "dq"]
     for nm, g, ref in zip(("dq", "dk", "dv"), got, want):
         if few:
             _check_few_terms(nm, g, ref, name)
@@ -49,23 +52,29 @@ def test_walking_dkdv(name, lengths, H, few, causal, monkeypatch):
             _check(nm, g, ref, "bf16", name)
 
 
-def test_walking_dkdv_over_a_large_batch_in_natural_order(monkeypatch):
+@pytest.mark.parametrize("causal", [True, False])
+def test_walking_dkdv_over_a_large_batch_in_natural_order(causal, monkeypatch):
     """Per-sequence tiles in natural order (mean length above the packed tiles' limit), against the
-    one-wave kernel, which the other tests hold against the oracle: same products, same roundings."""
+    one-wave kernel, which the other tests hold against the oracle: the same products with the same operand
+    roundings, so the two differ by their fp32 sums' order and one rounding to bf16."""
     set_flags(monkeypatch, remove="NO_PACK")
     import paper_2508_04711_amd as lib
     lengths = [int(x) for x in np.random.default_rng(5).integers(129, 520, size=1400)]
     w = workloads.custom("natural", lengths, 4, 128, 128, max_len=520, dtype="bf16", seed=6)
     # (the rule: the heaviest item is less than an eighth of what one of 512 workgroup slots gets)
     mean = w.total_rows // w.batch
-    assert 128 * w.max_len * 8 < mean * mean // 2 * w.batch // 512 * 4
-    print("walk natural", flush=True)
+    assert 128 * w.max_len * 8 < mean * mean // (2 if causal else 1) * w.batch // 512 * 4
+    print("walk natural", causal, flush=True)
     d = {k: v.cuda() for k, v in workloads.values(w).items()}
     off = torch.from_numpy(w.seq_offsets()).cuda()
-    args = (d["q"], d["k"], d["v"], d["d_o"], off, w.max_len, w.alpha, True)
+    args = (d["q"], d["k"], d["v"], d["d_o"], off, w.max_len, w.alpha, causal)
     _, dk, dv = lib.hstu_jagged_attn_bwd(*args)
     set_flags(monkeypatch, add="DKDV_ONE_WAVE")
     _, dk1, dv1 = lib.hstu_jagged_attn_bwd(*args)
     for a, b in ((dk, dk1), (dv, dv1)):
-        # at most one bf16 unit of the value (fp32 sums of equal terms in the same order)
-        assert (a.float() - b.float()).abs().max().item() <= 2.0 ** -7 * b.float().abs().max().item()
+        # two neighbouring bf16 values are 2^-7 of the value apart at most; sums of up to 520 terms in
+        # another order differ by up to 520 * 2^-24 of the terms' magnitudes, of the order of the RMS
+        a, b = a.float(), b.float()
+        rms = b.pow(2).mean().sqrt()
+        excess = (a - b).abs() - (2.0 ** -7 * torch.maximum(a.abs(), b.abs()) + 520 * 2.0 ** -24 * rms)
+        assert excess.max().item() <= 0, excess.max().item()

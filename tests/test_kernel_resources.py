@@ -1,6 +1,6 @@
 """What the compiler reports for the built kernels (paper_2508_04711_amd/kernel_resources.txt, written
-by the build): the hot variants must not spill vector registers, and every kernel must keep the
-occupancy and the LDS footprint its launch configuration counts on.  CPU only; skipped when the
+by the build): the hot variants must not spill vector registers (a few kernels spill a stated number), and every
+kernel must keep the occupancy and the LDS footprint its launch configuration counts on.  CPU only; skipped when the
 library has not been built here."""
 import os
 import re
@@ -75,6 +75,50 @@ def test_occupancy_and_lds_match_the_launch_configuration():
             assert waves_per_simd >= 2 and lds <= 80 * 1024, (dqk, dv, flags, waves_per_simd, lds)
         else:
             assert waves_per_simd >= 1 and lds <= 160 * 1024, (dqk, dv, flags, waves_per_simd, lds)
+
+
+# name, waves per SIMD and workgroups per CU the launch counts on, waves per workgroup, vector registers that may spill.
+# Spilled: in the walking kernel's six-fold unrolled step (its waits count vector memory operations, which
+# spills can only make stricter); three in the d = 64 dq kernel held to 128 registers; three in the short backward
+# kernel's code for sequences of more than 128 rows, none in that for groups of whole sequences.
+EXPECTED = [
+    (r"hstu_fwd_lean_bf16ILi64E", 4, 4, 4, 0),
+    (r"hstu_dkdv_lean_bf16ILi64E", 3, 3, 4, 0),
+    (r"hstu_dq_lean_bf16ILi64E", 4, 4, 4, 3),
+    (r"hstu_dkdv_walk_bf16ILi128E", 2, 1, 8, 9),
+    (r"hstu_dkdv_pair_bf16ILi128E", 2, 1, 8, 0),
+    (r"hstu_bwd_short_bf16ILi128E", 2, 2, 4, 3),
+    (r"hstu_bwd_short_bf16ILi64E", 3, 3, 4, 0),
+    # fp32 (d_qk, d_v, bias, wide rows): two workgroups per CU up to d_qk + d_v = 128, without bias in dk/dv, one
+    # beyond; four in dq at d = 32 without bias
+    (r"hstu_(fwd|dq)_f32ILi64ELi64ELb[01]E", 2, 2, 4, 0),
+    (r"hstu_dkdv_f32ILi64ELi64ELb0E", 2, 2, 4, 0),
+    (r"hstu_dq_f32ILi32ELi32ELb0E", 4, 4, 4, 1),
+    (r"hstu_(fwd|dq)_f32ILi128ELi128ELb[01]E", 1, 1, 4, 0),
+    (r"hstu_dkdv_f32ILi128ELi128ELb0E", 1, 1, 4, 0),
+    (r"hstu_dkdv_f32ILi128ELi128ELb1E", 1, 1, 4, 8),
+    (r"hstu_(fwd|dkdv|dq)_f32ILi(32|64|128)ELi(32|64|128)ELb[01]E", 1, 1, 4, 8),
+]
+
+
+@pytest.mark.parametrize("pattern,waves_per_simd,per_cu,waves,spills", EXPECTED, ids=[e[0] for e in EXPECTED])
+def test_the_other_attention_kernels(pattern, waves_per_simd, per_cu, waves, spills):
+    found = [(sym, v) for sym, v in _kernels().items() if re.search(pattern, sym)]
+    assert found, pattern
+    assert waves * per_cu <= 4 * waves_per_simd  # (four SIMDs per CU)
+    for sym, v in found:
+        assert int(v["Occupancy_[waves/SIMD]"]) >= waves_per_simd, (sym, v)
+        assert int(v["LDS_Size_[bytes/block]"]) * per_cu <= 160 * 1024, (sym, v)
+        assert int(v["VGPRs_Spill"]) <= spills, (sym, v)
+        assert (int(v["ScratchSize_[bytes/lane]"]) == 0) == (int(v["VGPRs_Spill"]) == 0), (sym, v)
+
+
+def test_every_attention_kernel_has_an_expectation():
+    """No kernel of the passes is left out above: neither a family nor, of a family, a head dimension."""
+    known = [e[0] for e in EXPECTED] + [r"hstu_(fwd|dkdv|dq)_bf16ILi\d+ELi\d+ELi\d+E"]
+    for sym in _kernels():
+        if re.search(r"hstu_\w+_(bf16|f32)I", sym) and "transpose" not in sym:
+            assert any(re.search(k, sym) for k in known), sym
 
 
 def test_helper_kernels_use_no_scratch():
