@@ -89,16 +89,19 @@ typedef enum {
   HSTU_FLAG_NO_PACK = 2,        /* never tile across sequence boundaries ("packed tiles": bf16
                                    whole-batch calls whose mean length total_rows / batch is at
                                    most 256 tile the batch 128 rows at a time whatever sequences
-                                   the rows belong to; the last bits of a row's result then depend
-                                   on the sequences that share its tile)                          */
+                                   the rows belong to, except batches of at most 64 sequences with
+                                   at most 512 per-sequence tiles of all heads; the last bits of a
+                                   row's result then depend on the sequences that share its tile)  */
   HSTU_FLAG_PACK_SHORT = 4,     /* packed tiles up to a mean length of 1024 instead of 256         */
   HSTU_FLAG_FWD_TILE_128 = 8,   /* bf16 forward: the form that first builds a transposed copy of V in
                                    the workspace and reads that (one LDS instruction per matrix
                                    instruction instead of one and a half), with 128-row query tiles;
                                    the default reads V row-major and builds nothing               */
   HSTU_FLAG_FWD_TILE_256 = 16,  /* ... with 256-row query tiles                                    */
-  HSTU_FLAG_DKDV_ONE_WAVE = 32, /* dk/dv pass at d_qk = d_v = 128: the kernel with one wave per 32
-                                   keys instead of the one that splits the work over two          */
+  HSTU_FLAG_DKDV_ONE_WAVE = 32, /* dk/dv pass: the kernel with one wave per 32 keys and two blocks
+                                   in flight, instead of the ones that split the work over two waves
+                                   (d_qk = d_v = 128), keep one block in flight (64), or compute the
+                                   whole backward pass of packed tiles with max_len <= 128 at once  */
   HSTU_FLAG_BIAS_PER_PAIR = 64  /* calls with the timestamp bias (bf16): every block of pairs looks
                                    up the fp32 table entry of each pair; without it a block whose
                                    pairs share a bucket takes the entry as two bf16 halves (exact

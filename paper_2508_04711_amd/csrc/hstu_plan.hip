@@ -1,11 +1,12 @@
 // Schedule ("tile table") construction on the device.
 //
-// From the int32 seq_offsets of a jagged batch (paper, section 2.2) this kernel lists every
+// From the int32 seq_offsets of a jagged batch (paper, section 2.2) plan_kernel lists every
 // owner tile of every sequence together with the streamed segments it has to be computed
 // against, and orders the list by non-increasing cost so that the hardware dispatcher, which
 // hands out workgroups in index order, sees the heavy tiles first (longest-processing-time
 // order; the cost of a causal tile grows with its position in the sequence).  Tiles that lie
-// wholly above the diagonal never appear.  For a context-parallel rank (section 2.3) each
+// wholly above the diagonal never appear.  item_plan_kernel builds the same list for small batches,
+// natural_plan_kernel that of large ones in the order of the rows.  For a context-parallel rank (section 2.3) each
 // side of a sequence consists of the two mini-chunks the rank owns.
 //
 // Nothing here needs the host to know the offsets: the grid of the attention kernels is
