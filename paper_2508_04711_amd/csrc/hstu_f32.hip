@@ -105,16 +105,32 @@ __device__ __forceinline__ void load_rows(f4 (&reg)[D / 8], const float* base, i
   }
 }
 
-// acc[streamed row][owner row] += block (rows of the block) x owners^T.
+__device__ __forceinline__ void clear(f32x16& x) {
+#pragma unroll
+  for (int r = 0; r < 16; ++r) x[r] = 0.f;
+}
+
+// acc[streamed row][owner row] += block (rows of the block) x owners^T.  At D = 128 in two chains of half the
+// elements each: a sum's rounding error grows with its chain (outputs off 64 bits by 2.70e-7 of their norm in one
+// chain, 2.14e-7 in two, where one key after the other on the vector pipe had been off by 2.42e-7; 1.5 % slower.
+// At 64 and 32 one chain is within 2.4e-7, and at 32 a second one takes dk/dv from three waves per SIMD to two).
 template <int D>
 __device__ __forceinline__ void scores(f32x16& acc, const float* buf, const f4 (&own)[D / 8], int n, int hh) {
   const int s = fswz<D>(n);
+  f32x16 odd;
+  clear(odd);
 #pragma unroll
   for (int t = 0; t < D / 8; ++t) {
     const f4 x = *HSTU_LDS(const f4, buf + n * D + (((2 * t + hh) ^ s) << 2));
 #pragma unroll
-    for (int e = 0; e < 4; ++e) acc = mfma_f32(x[e], own[t][e], acc);
+    for (int e = 0; e < 4; ++e) {
+      if (D == 128 && (t & 1)) odd = mfma_f32(x[e], own[t][e], odd);
+      else acc = mfma_f32(x[e], own[t][e], acc);
+    }
   }
+  if constexpr (D == 128)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] += odd[r];
 }
 
 // acc[column][owner row] += block^T x w, w[r] belonging to streamed row 8*(r/4) + 4*hh + r%4: the
@@ -133,11 +149,6 @@ __device__ __forceinline__ void contract(f32x16 (&acc)[D / 32], const float* buf
       acc[c] = mfma_f32(x, w[r], acc[c]);
     }
   }
-}
-
-__device__ __forceinline__ void clear(f32x16& x) {
-#pragma unroll
-  for (int r = 0; r < 16; ++r) x[r] = 0.f;
 }
 
 // Adds up the four waves' accumulators through LDS (buf: the waves' FB x D blocks, no longer
@@ -172,13 +183,17 @@ __device__ __forceinline__ void sum_and_store(float* buf, const f32x16 (&acc)[D 
 }
 
 // sigmoid(x) to about an ulp, from z = e^-|x| <= 1, which overflows nowhere: 1 / (1 + z) for x >= 0,
-// z / (1 + z) below.  z as 2^t with t = -|x| * log2(e) rounded and the product's rounding error carried as a
+// z / (1 + z) below, and 1 - sigmoid(x) the other way round (subtracted, it would have no digits left where
+// the sigmoid saturates, and the derivative multiplies it by x).  z as 2^t with t = -|x| * log2(e) rounded and the product's rounding error carried as a
 // first-order factor (1 + ln2 * error), so that a large |x| costs no accuracy; the reciprocal with one
 // Newton step.  |x| is cut at 104, where z is exactly zero: the sigmoid of anything beyond, infinities
 // included, is exactly 0 or 1 (an |x| that were not cut would make the error term infinite times zero, a
 // z that were kept above zero would let x * sigmoid(x) grow with -x).  NaN stays NaN in x * sigmoid(x).
-// Fourteen vector instructions against 27 for expf and an IEEE division.
-__device__ __forceinline__ float sigmoid_precise(float x) {
+// Fifteen vector instructions against 27 for expf and an IEEE division.
+struct Sigmoid {
+  float sg, rest;  // sigmoid(x), 1 - sigmoid(x)
+};
+__device__ __forceinline__ Sigmoid sigmoid_precise(float x) {
   constexpr float LOG2E = 1.44269504088896341f, LOG2E_LO = 1.92596299e-8f, LN2 = 0.693147180559945309f;
   const float y = -__builtin_fminf(__builtin_fabsf(x), 104.0f);
   const float t = y * LOG2E;
@@ -188,8 +203,11 @@ __device__ __forceinline__ float sigmoid_precise(float x) {
   const float d = 1.0f + z;
   const float r = __builtin_amdgcn_rcpf(d);
   const float s = __builtin_fmaf(__builtin_fmaf(-d, r, 1.0f), r, r);
-  return x < 0.0f ? z * s : s;
+  const bool below = x < 0.0f;
+  return Sigmoid{below ? z * s : s, below ? s : z * s};
 }
+// silu'(x) = sg * (1 + x * (1 - sg))
+__device__ __forceinline__ float silu_slope(float x, const Sigmoid& g) { return g.sg * __builtin_fmaf(x, g.rest, 1.0f); }
 
 // The streamed blocks of an item: [first, end) of Stream's 32-row blocks, without the leading block
 // wholly before the owners and the trailing one without rows; wave w takes first + w, + FW, ...
@@ -301,7 +319,7 @@ __global__ void __launch_bounds__(THREADS, f32_waves(DQK, DV)) hstu_fwd_f32(Attn
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const float x = a.alpha * s[r];
-      p[r] = x * sigmoid_precise(x);
+      p[r] = x * sigmoid_precise(x).sg;
     }
     if (a.causal && b.pos + FB - 1 > it.pos0) {
       const VisBefore vis{it.pos0 + l.n - b.pos, l.hh};
@@ -366,9 +384,9 @@ __global__ void __launch_bounds__(THREADS, f32_waves(DQK, DV, BIAS)) hstu_dkdv_f
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const float x = a.alpha * s[r];
-      const float sg = sigmoid_precise(x);
-      p[r] = x * sg;
-      ds[r] = dp[r] * sg * (1.0f + x * (1.0f - sg));
+      const Sigmoid g = sigmoid_precise(x);
+      p[r] = x * g.sg;
+      ds[r] = dp[r] * silu_slope(x, g);
     }
     if (a.causal && b.pos < it.pos0 + TILE - 1) {
       const VisAfter vis{it.pos0 + l.n - b.pos, l.hh};
@@ -444,8 +462,7 @@ __global__ void __launch_bounds__(THREADS, f32_dq_waves(DQK, DV, BIAS)) hstu_dq_
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const float x = a.alpha * s[r];
-      const float sg = sigmoid_precise(x);
-      ds[r] = dp[r] * sg * (1.0f + x * (1.0f - sg));
+      ds[r] = dp[r] * silu_slope(x, sigmoid_precise(x));
     }
     if (a.causal && b.pos + FB - 1 > it.pos0) {
       const VisBefore vis{it.pos0 + l.n - b.pos, l.hh};

@@ -180,3 +180,26 @@ def test_rows_of_more_than_128_megabytes(dqk, dv, heads):
         for name, got, ref in zip(("o", "dq", "dk", "dv"), (o, dq, dk, dv_), want):
             err = np.abs(got[:, h].double().cpu().numpy() - ref[:, 0]).max() / np.sqrt(np.mean(ref ** 2))
             assert err <= 1e-5, (name, h, err)
+
+
+@pytest.mark.parametrize("d,scale,bound", [(128, 1.0, 2.42e-7), (64, 1.0, 3.2e-7), (32, 1.0, 3.3e-7), (64, 3.0, 3.8e-7),
+                                           (64, 8.0, 4.1e-7)])
+def test_error_against_64_bits(d, scale, bound):
+    """The 2-norm of each output's error over the output's, at most what sums taken key by key in fp32, with the
+    precise exponential and IEEE division, were off for the same inputs (the bound; the largest of the four outputs)."""
+    import paper_2508_04711_amd as lib
+    lengths = {128: [200, 129, 33], 32: [40, 64, 3, 500]}.get(d, [300, 1, 77, 512, 64] if scale == 1.0 else [300, 100])
+    print("f32 error", d, scale, flush=True)
+    w = workloads.custom("e", lengths, 2, d, d, max_len=max(lengths), dtype="f32", scale=scale, seed=9)
+    vals = workloads.values(w)
+    x = {k: v.cuda() for k, v in vals.items()}
+    f = {k: workloads.to_f64(v) for k, v in vals.items()}
+    off_np = w.seq_offsets()
+    off = torch.from_numpy(off_np).cuda()
+    want = (oracle.fwd(f["q"], f["k"], f["v"], off_np, w.max_len, w.alpha, True),) + tuple(
+        oracle.bwd(f["q"], f["k"], f["v"], f["d_o"], off_np, w.max_len, w.alpha, True))
+    got = (lib.hstu_jagged_attn_fwd(x["q"], x["k"], x["v"], off, w.max_len, w.alpha, True),) + tuple(
+        lib.hstu_jagged_attn_bwd(x["q"], x["k"], x["v"], x["d_o"], off, w.max_len, w.alpha, True))
+    for name, g, ref in zip(("o", "dq", "dk", "dv"), got, want):
+        err = np.linalg.norm(g.double().cpu().numpy() - ref) / np.linalg.norm(ref)
+        assert err <= bound, (name, err)

@@ -96,8 +96,8 @@ EXPECTED = [
     (r"hstu_dq_f32ILi32ELi32ELb0E", 4, 4, 4, 1),
     (r"hstu_(fwd|dq)_f32ILi128ELi128ELb[01]E", 1, 1, 4, 0),
     (r"hstu_dkdv_f32ILi128ELi128ELb0E", 1, 1, 4, 0),
-    (r"hstu_dkdv_f32ILi128ELi128ELb1E", 1, 1, 4, 8),
-    (r"hstu_(fwd|dkdv|dq)_f32ILi(32|64|128)ELi(32|64|128)ELb[01]E", 1, 1, 4, 8),
+    (r"hstu_dkdv_f32ILi128ELi128ELb1E", 1, 1, 4, 12),
+    (r"hstu_(fwd|dkdv|dq)_f32ILi(32|64|128)ELi(32|64|128)ELb[01]E", 1, 1, 4, 12),
 ]
 
 
