@@ -173,16 +173,18 @@ def test_heavy_query_tiles_are_cut_along_the_keys(cp):
     assert not (whole_tiles & {(k[0], k[1]) for k in by_tile})
 
 
-# ---- schedules that a wave per item builds (batches of up to 512 sequences), or that the attention kernels' waves
+# ---- schedules that a wave per item builds (batches of up to 128 sequences), or that the attention kernels' waves
 # work out item by item: the same items, heaviest first by their exact cost
 RNG = np.random.default_rng(11)
 BATCHES = [
-    # one sequence per lane: up to 64, two to eight per lane: up to 512, the other builder beyond
+    # one sequence per lane: up to 64, two: up to 128, the sorting builder beyond
     [int(x) for x in RNG.integers(0, 900, size=64)],
     [int(x) for x in RNG.integers(0, 900, size=65)],
     [int(x) for x in RNG.integers(0, 500, size=512)],
     [int(x) for x in RNG.integers(0, 500, size=513)],
-    [0] * 63 + [4000] + [0] * 70 + [31, 32, 33, 127, 128, 129, 3990],
+    [0] * 63 + [4000] + [0] * 56 + [31, 32, 33, 127, 128, 129, 3990, 0],
+    [int(x) for x in RNG.integers(0, 900, size=128)],
+    [int(x) for x in RNG.integers(0, 900, size=129)],
     [1], [127], [128], [129],
 ]
 
@@ -223,7 +225,8 @@ def test_items_and_exact_order_of_small_batches(b, dtype, side, causal):
 @pytest.mark.parametrize("side", [0, 1])
 @pytest.mark.parametrize("cp,q_rank,kv_rank", [(4, 1, -1), (4, 0, -1), (4, 2, 2), (4, 1, 3), (8, 7, 0), (2, 1, -1), (1, 0, -1)])
 @pytest.mark.parametrize("lengths", [[16, 5, 0, 233, 1, 400, 64, 777, 3000], [int(x) for x in RNG.integers(0, 1500, size=40)],
-                                     [int(x) for x in RNG.integers(0, 700, size=300)]], ids=["few", "forty", "many"])
+                                     [int(x) for x in RNG.integers(0, 900, size=100)],
+                                     [int(x) for x in RNG.integers(0, 700, size=300)]], ids=["few", "forty", "hundred", "many"])
 def test_items_and_exact_order_of_a_rank(lengths, cp, q_rank, kv_rank, side, causal):
     import paper_2508_04711_amd as lib
     got, rows = _dump(lib, lengths, 4, causal, side, cp=(cp, q_rank, kv_rank))
