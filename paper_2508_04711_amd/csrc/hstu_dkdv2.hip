@@ -119,6 +119,35 @@ __device__ __forceinline__ void lds_writes_done() { asm volatile("s_waitcnt lgkm
 
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 
+// The ring buffers: six for the blocks of Q, six for those of dO.  One array per buffer, so that the compiler can see
+// that a copy into one cannot alias operand reads from another.  The larger exchange buffers come to lie at 0..32 KB, then
+// Q's buffers and then dO's in the order of their declaration (at D = 128), and the reads of each tensor stay
+// within the reach of one set of addresses (see raised; another layout would only cost additions).
+struct Rings {
+  char *q0, *q1, *q2, *q3, *q4, *q5, *g0, *g1, *g2, *g3, *g4, *g5;
+  __device__ __forceinline__ char* q(int b) const {
+    return b == 0 ? q0 : (b == 1 ? q1 : (b == 2 ? q2 : (b == 3 ? q3 : (b == 4 ? q4 : q5))));
+  }
+  __device__ __forceinline__ char* g(int b) const {
+    return b == 0 ? g0 : (b == 1 ? g1 : (b == 2 ? g2 : (b == 3 ? g3 : (b == 4 ? g4 : g5))));
+  }
+};
+constexpr int UP_Q = 0, UP_G = 32768;
+#define HSTU_RINGS(QB)                                       \
+  __shared__ __attribute__((aligned(4096))) char rq0[QB];    \
+  __shared__ __attribute__((aligned(4096))) char rq1[QB];    \
+  __shared__ __attribute__((aligned(4096))) char rq2[QB];    \
+  __shared__ __attribute__((aligned(4096))) char rq3[QB];    \
+  __shared__ __attribute__((aligned(4096))) char rq4[QB];    \
+  __shared__ __attribute__((aligned(4096))) char rq5[QB];    \
+  __shared__ __attribute__((aligned(2048))) char rg0[QB];    \
+  __shared__ __attribute__((aligned(2048))) char rg1[QB];    \
+  __shared__ __attribute__((aligned(2048))) char rg2[QB];    \
+  __shared__ __attribute__((aligned(2048))) char rg3[QB];    \
+  __shared__ __attribute__((aligned(2048))) char rg4[QB];    \
+  __shared__ __attribute__((aligned(2048))) char rg5[QB];    \
+  const Rings ring = {rq0, rq1, rq2, rq3, rq4, rq5, rg0, rg1, rg2, rg3, rg4, rg5}
+
 // Exchange buffer of one (parity, 32 keys): [four accumulator elements][lane] as 16-byte groups;
 // xw points at the lane's first group.
 constexpr int XG = 256;        // floats between the groups of four elements
@@ -127,8 +156,8 @@ constexpr int XK = 4 * XG;     // floats per 32 keys
 // Role A, one step: scores of the block at qn into s_out, SiLU of s_in (p' packed into p_cur,
 // silu' written to xw), dV^T += dO^T P with the block at gp and p_prev.
 template <int D, class Init, class Vis>
-__device__ __forceinline__ void role_a_step(const Init& init, const char* qn, const char* gp, const RowAddr<D>& raq,
-                                            const ColAddr<D>& cag, const bf16x8 (&kreg)[D / 16],
+__device__ __forceinline__ void role_a_step(const Init& init, const char* qn, const char* gp, const RowAddr<D, UP_Q>& raq,
+                                            const ColAddr<D, UP_G>& cag, const bf16x8 (&kreg)[D / 16],
                                             const f32x16& s_in, f32x16& s_out,
                                             const bf16x8 (&p_prev)[2], bf16x8 (&p_cur)[2],
                                             f32x16 (&dvacc)[D / 32], float* xw, float c1, float alpha,
@@ -206,8 +235,8 @@ __device__ __forceinline__ void role_a_step(const Init& init, const char* qn, co
 // Role B, one step: dP of the block at gn into d_out, dS = d_in * silu' (read from xr) packed into
 // ds_cur, dK^T += Q^T dS with the block at qp and ds_prev.
 template <int D>
-__device__ __forceinline__ void role_b_step(const char* gn, const char* qp, const RowAddr<D>& rag,
-                                            const ColAddr<D>& caq, const bf16x8 (&vreg)[D / 16],
+__device__ __forceinline__ void role_b_step(const char* gn, const char* qp, const RowAddr<D, UP_G>& rag,
+                                            const ColAddr<D, UP_Q>& caq, const bf16x8 (&vreg)[D / 16],
                                             const f32x16& d_in, f32x16& d_out,
                                             const bf16x8 (&ds_prev)[2], bf16x8 (&ds_cur)[2],
                                             f32x16 (&dkacc)[D / 32], const float* xr) {
@@ -246,14 +275,9 @@ __device__ __forceinline__ void role_b_step(const char* gn, const char* qp, cons
 
 // The whole item for one role (ROLE 0: A, 1: B).
 template <int D, int ROLE, bool BIAS>
-__device__ __forceinline__ void pair_body(const AttnArgs& a, const Item& it, int h, char* ring0,
-                                          char* ring1, char* ring2, char* ring3, char* ring4,
-                                          char* ring5, float* xbuf0, float* xbuf1, char* rec0, char* rec1,
+__device__ __forceinline__ void pair_body(const AttnArgs& a, const Item& it, int h, const Rings& ring, float* xbuf0, float* xbuf1, char* rec0, char* rec1,
                                           char* rec2, char* rec3, char* rec4, char* rec5, float* wtab) {
   constexpr int QB = BR * D * 2;
-  auto ring = [&](int b) {
-    return b == 0 ? ring0 : (b == 1 ? ring1 : (b == 2 ? ring2 : (b == 3 ? ring3 : (b == 4 ? ring4 : ring5))));
-  };
   auto recb = [&](int b) {  // the records of the block in ring buffer b (bias variant)
     return b == 0 ? rec0 : (b == 1 ? rec1 : (b == 2 ? rec2 : (b == 3 ? rec3 : (b == 4 ? rec4 : rec5))));
   };
@@ -271,9 +295,9 @@ __device__ __forceinline__ void pair_body(const AttnArgs& a, const Item& it, int
   const int crow = wave * (64 / (D / 8)) + lane / (D / 8);
   const int voff = crow * rs + (((lane % (D / 8)) ^ swz<D>(crow)) << 4);
   BlockCursor<D> cur;
-  auto copy_next = [&](char* buf, char* rbuf) {  // copies block cur.b, then moves on
-    block_copy_async<D>(buf, cur.q, rs, cur.valid, wave, voff);
-    block_copy_async<D>(buf + QB, cur.g, rs, cur.valid, wave, voff);
+  auto copy_next = [&](char* qbuf, char* gbuf, char* rbuf) {  // copies block cur.b, then moves on
+    block_copy_async<D>(qbuf, cur.q, rs, cur.valid, wave, voff);
+    block_copy_async<D>(gbuf, cur.g, rs, cur.valid, wave, voff);
     if (BIAS && wave == 0) rec_block_copy_async(rbuf, a.ts_rec + cur.row, cur.valid, lane);
     cur.next(a, it, st, h);
   };
@@ -293,10 +317,10 @@ __device__ __forceinline__ void pair_body(const AttnArgs& a, const Item& it, int
   }
   // (With the bias every wave of role B also issues the load of the block's records: the same
   // kilobyte four times, so that all four keep the same count of loads in flight.)
-  auto copy_step = [&](char* buf, char* rbuf, bool live) {
+  auto copy_step = [&](char* qbuf, char* gbuf, char* rbuf, bool live) {
     const int valid = live ? cur.valid : 0;
-    block_copy_async_half<D>(buf, cur.q, rs, valid, g, voff2);
-    block_copy_async_half<D>(buf + QB, cur.g, rs, valid, g, voff2);
+    block_copy_async_half<D>(qbuf, cur.q, rs, valid, g, voff2);
+    block_copy_async_half<D>(gbuf, cur.g, rs, valid, g, voff2);
     if constexpr (BIAS) rec_block_copy_async(rbuf, a.ts_rec + (live ? cur.row : 0), valid, lane);
     if (live) cur.next(a, it, st, h);
   };
@@ -307,10 +331,11 @@ __device__ __forceinline__ void pair_body(const AttnArgs& a, const Item& it, int
   // are zeros whatever the memory held.
   {
     const u32x4 z = {0u, 0u, 0u, 0u};
-    for (int i = tid; i < 2 * QB / 16; i += PW * 64) {
-      *HSTU_LDS(u32x4, ring4 + i * 16) = z;
-      *HSTU_LDS(u32x4, ring5 + i * 16) = z;
-    }
+    static_assert(QB / 16 == PW * 64, "one chunk per thread");
+    *HSTU_LDS(u32x4, ring.q4 + tid * 16) = z;
+    *HSTU_LDS(u32x4, ring.q5 + tid * 16) = z;
+    *HSTU_LDS(u32x4, ring.g4 + tid * 16) = z;
+    *HSTU_LDS(u32x4, ring.g5 + tid * 16) = z;
   }
   bf16x8 oreg[D / 16];  // A: the K rows, B: the V rows
   {
@@ -319,8 +344,8 @@ __device__ __forceinline__ void pair_body(const AttnArgs& a, const Item& it, int
   }
   if (NBLK > 0) {
     cur.seek(a, it, st, h, 0);
-    copy_next(ring0, rec0);
-    copy_next(ring1, rec1);  // (NBLK is even)
+    copy_next(ring.q0, ring.g0, rec0);
+    copy_next(ring.q1, ring.g1, rec1);  // (NBLK is even)
   }
   // The bias enters the scores only, i.e. role A's product (the table's gradient is the dq pass's).
   BiasCtx bias = {};
@@ -348,8 +373,8 @@ __device__ __forceinline__ void pair_body(const AttnArgs& a, const Item& it, int
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[i][r] = 0.f;
 
-  RowAddr<D> ra;  // A: rows of Q, B: rows of dO
-  ColAddr<D> ca;  // A: dO transposed, B: Q transposed
+  RowAddr<D, ROLE == 0 ? UP_Q : UP_G> ra;  // A: rows of Q, B: rows of dO
+  ColAddr<D, ROLE == 0 ? UP_G : UP_Q> ca;  // A: dO transposed, B: Q transposed
   ra.init(n, hh); ca.init(lane);
 
   lds_writes_done();
@@ -380,7 +405,8 @@ __device__ __forceinline__ void pair_body(const AttnArgs& a, const Item& it, int
     auto step = [&](int t, auto tag) {
       constexpr int S = decltype(tag)::value;  // t mod 6; S & 1 is the parity of t
       if constexpr (ROLE == 1)
-        copy_step(ring((S + AHEAD_COPY) % NSLOT), recb((S + AHEAD_COPY) % NSLOT), t + AHEAD_COPY < NBLK);
+        copy_step(ring.q((S + AHEAD_COPY) % NSLOT), ring.g((S + AHEAD_COPY) % NSLOT), recb((S + AHEAD_COPY) % NSLOT),
+                  t + AHEAD_COPY < NBLK);
       if constexpr (ROLE == 0) {
         if constexpr (BIAS)  // the stream enters one set of the block table: refill the other
           if (t > 0 && (t & 63) == 0) tab.fill(bias, t + 64, NBLK, it, st, lane);
@@ -393,13 +419,13 @@ __device__ __forceinline__ void pair_body(const AttnArgs& a, const Item& it, int
             return VisAfter{rel, hh};
           };
           const ScoreInit<BIAS> init = {&bias, recb(S), 0, BIAS ? tab.get(t) : BlockBias{}};
-          role_a_step<D>(init, ring(S), ring((S + 4) % NSLOT) + QB, ra, ca, oreg, sd[(S + 1) & 1], sd[S & 1],
+          role_a_step<D>(init, ring.q(S), ring.g((S + 4) % NSLOT), ra, ca, oreg, sd[(S + 1) & 1], sd[S & 1],
                          pk[S & 1], pk[(S + 1) & 1], acc, (S + 1) & 1 ? xa1 : xa0, c1, a.alpha, mask, vis_of);
           lds_writes_done();
         }
       } else {
         if (t >= 1)  // (nothing to work on in the first step)
-          role_b_step<D>(ring((S + 5) % NSLOT) + QB, ring((S + 3) % NSLOT), ra, ca, oreg, sd[S & 1],
+          role_b_step<D>(ring.g((S + 5) % NSLOT), ring.q((S + 3) % NSLOT), ra, ca, oreg, sd[S & 1],
                          sd[(S + 1) & 1], pk[(S + 1) & 1], pk[S & 1], acc, S & 1 ? xa1 : xa0);
       }
       // block t+1 must have landed; the copies of the later blocks may stay in flight
@@ -429,14 +455,7 @@ __device__ __forceinline__ void pair_body(const AttnArgs& a, const Item& it, int
 template <int D, bool BIAS, bool SELF>
 __global__ void __launch_bounds__(PW * 64) hstu_dkdv_pair_bf16(AttnArgs a) {
   constexpr int QB = BR * D * 2;
-  // One array per ring buffer (the Q block, then the dO block), so that the compiler can see that
-  // a copy into one cannot alias operand reads from another.
-  __shared__ __attribute__((aligned(1024))) char ring0[2 * QB];
-  __shared__ __attribute__((aligned(1024))) char ring1[2 * QB];
-  __shared__ __attribute__((aligned(1024))) char ring2[2 * QB];
-  __shared__ __attribute__((aligned(1024))) char ring3[2 * QB];
-  __shared__ __attribute__((aligned(1024))) char ring4[2 * QB];
-  __shared__ __attribute__((aligned(1024))) char ring5[2 * QB];
+  HSTU_RINGS(QB);
   __shared__ __attribute__((aligned(1024))) float xbuf0[4 * XK];  // silu' of blocks of even index
   __shared__ __attribute__((aligned(1024))) float xbuf1[4 * XK];  // ... of odd index
   // bias variant: the timestamp records of the blocks in the ring buffers, and the table
@@ -453,10 +472,10 @@ __global__ void __launch_bounds__(PW * 64) hstu_dkdv_pair_bf16(AttnArgs a) {
   if (!un.on || !(SELF ? get_item(a, un.slot, it) : fetch_item<false>(a.plan, un.slot, it))) return;
   const int role = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);
   if (role == 0)
-    pair_body<D, 0, BIAS>(a, it, un.h, ring0, ring1, ring2, ring3, ring4, ring5, xbuf0, xbuf1, rec0, rec1, rec2,
+    pair_body<D, 0, BIAS>(a, it, un.h, ring, xbuf0, xbuf1, rec0, rec1, rec2,
                           rec3, rec4, rec5, wtab);
   else
-    pair_body<D, 1, BIAS>(a, it, un.h, ring0, ring1, ring2, ring3, ring4, ring5, xbuf0, xbuf1, rec0, rec1, rec2,
+    pair_body<D, 1, BIAS>(a, it, un.h, ring, xbuf0, xbuf1, rec0, rec1, rec2,
                           rec3, rec4, rec5, wtab);
 }
 
@@ -504,13 +523,9 @@ __device__ __forceinline__ WalkItem walk_item(const Item& it, int h, int causal)
 }
 
 template <int D, int ROLE, bool PACKED>
-__device__ __forceinline__ void pair_walk(const AttnArgs& a, int u, int stride, int end, char* ring0, char* ring1,
-                                          char* ring2, char* ring3, char* ring4, char* ring5, float* xbuf0,
-                                          float* xbuf1) {
+__device__ __forceinline__ void pair_walk(const AttnArgs& a, int u, int stride, int end, const Rings& ring,
+                                          float* xbuf0, float* xbuf1) {
   constexpr int QB = BR * D * 2;
-  auto ring = [&](int b) {
-    return b == 0 ? ring0 : (b == 1 ? ring1 : (b == 2 ? ring2 : (b == 3 ? ring3 : (b == 4 ? ring4 : ring5))));
-  };
   const int H = a.num_heads;
   const int tid = threadIdx.x, lane = tid & 63, n = lane & 31, hh = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -583,24 +598,26 @@ __device__ __forceinline__ void pair_walk(const AttnArgs& a, int u, int stride, 
       voff2[i] = r2 * rs + (((lane % (D / 8)) ^ swz<D>(r2)) << 4);
     }
   }
-  auto copy_step = [&](char* buf) {
-    block_copy_async_half<D>(buf, cq, rs, cvalid, g, voff2);
-    block_copy_async_half<D>(buf + QB, cg, rs, cvalid, g, voff2);
+  auto copy_step = [&](char* qbuf, char* gbuf) {
+    block_copy_async_half<D>(qbuf, cq, rs, cvalid, g, voff2);
+    block_copy_async_half<D>(gbuf, cg, rs, cvalid, g, voff2);
     const int64_t step = (int64_t)BR * sr;
     cq += step; cg += step; cvalid -= BR; --cleft;
   };
 
   {
     const u32x4 z = {0u, 0u, 0u, 0u};
-    for (int i = tid; i < 2 * QB / 16; i += PW * 64) {  // (the two blocks before the first one)
-      *HSTU_LDS(u32x4, ring4 + i * 16) = z;
-      *HSTU_LDS(u32x4, ring5 + i * 16) = z;
-    }
+    // (the two blocks before the first one)
+    static_assert(QB / 16 == PW * 64, "one chunk per thread");
+    *HSTU_LDS(u32x4, ring.q4 + tid * 16) = z;
+    *HSTU_LDS(u32x4, ring.q5 + tid * 16) = z;
+    *HSTU_LDS(u32x4, ring.g4 + tid * 16) = z;
+    *HSTU_LDS(u32x4, ring.g5 + tid * 16) = z;
   }
   if constexpr (ROLE == 1) {
     seek(cur);
-    copy_step(ring0);
-    copy_step(ring1);
+    copy_step(ring.q0, ring.g0);
+    copy_step(ring.q1, ring.g1);
   }
   load_rows(cur);  // (role B's first step works on a block of zeros: whatever V rows)
 
@@ -612,8 +629,8 @@ __device__ __forceinline__ void pair_walk(const AttnArgs& a, int u, int stride, 
       for (int r = 0; r < 16; ++r) acc[i][r] = 0.f;
   };
   clear_acc();
-  RowAddr<D> ra;  // A: rows of Q, B: rows of dO
-  ColAddr<D> ca;  // A: dO transposed, B: Q transposed
+  RowAddr<D, ROLE == 0 ? UP_Q : UP_G> ra;  // A: rows of Q, B: rows of dO
+  ColAddr<D, ROLE == 0 ? UP_G : UP_Q> ca;  // A: dO transposed, B: Q transposed
   ra.init(n, hh); ca.init(lane);
 
   // Role A's masks of the item whose block the SiLU stage works on.
@@ -697,7 +714,7 @@ __device__ __forceinline__ void pair_walk(const AttnArgs& a, int u, int stride, 
         else return VisAfter{m_klo + n - m_pos, hh};
       };
       const ScoreInit<false> init = {nullptr, nullptr, 0, BlockBias{}};
-      role_a_step<D>(init, ring(S), ring((S + 4) % NSLOT) + QB, ra, ca, oreg, sd[(S + 1) & 1], sd[S & 1], pk[S & 1],
+      role_a_step<D>(init, ring.q(S), ring.g((S + 4) % NSLOT), ra, ca, oreg, sd[(S + 1) & 1], sd[S & 1], pk[S & 1],
                      pk[(S + 1) & 1], acc, (S + 1) & 1 ? xa1 : xa0, c1, a.alpha, mask, vis_of);
       lds_writes_done();
       if (s == 1) {
@@ -711,10 +728,10 @@ __device__ __forceinline__ void pair_walk(const AttnArgs& a, int u, int stride, 
       done = drain && s == 2;
     } else {
       if (cleft == 0) seek(nxt);  // (in step 1 at the earliest)
-      copy_step(ring((S + AHEAD_COPY) % NSLOT));
+      copy_step(ring.q((S + AHEAD_COPY) % NSLOT), ring.g((S + AHEAD_COPY) % NSLOT));
       __builtin_amdgcn_sched_barrier(0);  // (the waits below count on this order)
       if (!first)
-        role_b_step<D>(ring((S + 5) % NSLOT) + QB, ring((S + 3) % NSLOT), ra, ca, oreg, sd[S & 1], sd[(S + 1) & 1],
+        role_b_step<D>(ring.g((S + 5) % NSLOT), ring.q((S + 3) % NSLOT), ra, ca, oreg, sd[S & 1], sd[(S + 1) & 1],
                        pk[(S + 1) & 1], pk[S & 1], acc, S & 1 ? xa1 : xa0);
       first = false;
       __builtin_amdgcn_sched_barrier(0);
@@ -759,12 +776,7 @@ __device__ __forceinline__ void pair_walk(const AttnArgs& a, int u, int stride, 
 template <int D, bool PACKED>
 __global__ void __launch_bounds__(PW * 64) hstu_dkdv_walk_bf16(AttnArgs a) {
   constexpr int QB = BR * D * 2;
-  __shared__ __attribute__((aligned(1024))) char ring0[2 * QB];
-  __shared__ __attribute__((aligned(1024))) char ring1[2 * QB];
-  __shared__ __attribute__((aligned(1024))) char ring2[2 * QB];
-  __shared__ __attribute__((aligned(1024))) char ring3[2 * QB];
-  __shared__ __attribute__((aligned(1024))) char ring4[2 * QB];
-  __shared__ __attribute__((aligned(1024))) char ring5[2 * QB];
+  HSTU_RINGS(QB);
   __shared__ __attribute__((aligned(1024))) float xbuf0[4 * XK];
   __shared__ __attribute__((aligned(1024))) float xbuf1[4 * XK];
   int u = blockIdx.x, stride = (int)gridDim.x, end = unit_count(a, a.plan.header[0]);
@@ -772,9 +784,9 @@ __global__ void __launch_bounds__(PW * 64) hstu_dkdv_walk_bf16(AttnArgs a) {
   if (u >= end) return;
   const int role = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);
   if (role == 0)
-    pair_walk<D, 0, PACKED>(a, u, stride, end, ring0, ring1, ring2, ring3, ring4, ring5, xbuf0, xbuf1);
+    pair_walk<D, 0, PACKED>(a, u, stride, end, ring, xbuf0, xbuf1);
   else
-    pair_walk<D, 1, PACKED>(a, u, stride, end, ring0, ring1, ring2, ring3, ring4, ring5, xbuf0, xbuf1);
+    pair_walk<D, 1, PACKED>(a, u, stride, end, ring, xbuf0, xbuf1);
 }
 
 }  // namespace

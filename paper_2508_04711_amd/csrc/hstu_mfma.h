@@ -79,19 +79,31 @@ __device__ __forceinline__ int lds_off(int row, int chunk) { return lds_off_rb<D
 // 8c..8c+7 belong to.  The swizzle
 // depends on row mod 16 only, so a read of block blk (rows 32*blk + ...) is the same offset plus
 // a constant, which the compiler folds into the instruction's immediate offset.
-template <int D>
+//
+// UP: the addresses are kept UP bytes too high and the reads subtract it.  An instruction's immediate offset has 16
+// bits, so a kernel that reads tiles all over its LDS would need a second set of addresses for those beyond 64 KB
+// (sixteen registers, or as many additions per step); raised by UP, one set serves tiles at UP .. UP + 64 KB.
+template <int UP>
+__device__ __forceinline__ int raised(int off) {
+  if constexpr (UP != 0) {
+    off += UP;
+    asm("" : "+v"(off));  // (or the compiler would cancel the two)
+  }
+  return off;
+}
+template <int D, int UP = 0>
 struct RowAddr {  // row-wise operand reads of row n (+32*blk): one address per 16-element step
   int a[D / 16];
   __device__ __forceinline__ void init(int n, int hh) {
 #pragma unroll
-    for (int ks = 0; ks < D / 16; ++ks) a[ks] = lds_off<D>(n, ks * 2 + hh);
+    for (int ks = 0; ks < D / 16; ++ks) a[ks] = raised<UP>(lds_off<D>(n, ks * 2 + hh));
   }
   __device__ __forceinline__ bf16x8 read(const char* tile, int blk, int ks) const {
-    return *HSTU_LDS(bf16x8, tile + blk * 32 * D * 2 + a[ks]);
+    return *HSTU_LDS(bf16x8, tile + (blk * 32 * D * 2 + a[ks] - UP));
   }
 };
 
-template <int D>
+template <int D, int UP = 0>
 struct ColAddr {  // transposing reads: per 32-column block, the lane's address in rows 0..7 and 8..15
   int a[D / 32][2];
   __device__ __forceinline__ void init(int lane) {
@@ -100,15 +112,15 @@ struct ColAddr {  // transposing reads: per 32-column block, the lane's address 
 #pragma unroll
     for (int c = 0; c < D / 32; ++c) {
       const int col = c * 32 + ((g & 1) << 4) + ((i & 3) << 2);
-      a[c][0] = lds_off<D>(row, col >> 3) + ((col & 7) << 1);
-      a[c][1] = lds_off<D>(row + 8, col >> 3) + ((col & 7) << 1);
+      a[c][0] = raised<UP>(lds_off<D>(row, col >> 3) + ((col & 7) << 1));
+      a[c][1] = raised<UP>(lds_off<D>(row + 8, col >> 3) + ((col & 7) << 1));
     }
   }
   // operand for streamed rows 16*half16 .. 16*half16+15 of the tile (half16 = 2*blk + c), columns 32*cb ..
   __device__ __forceinline__ bf16x8 read(const char* tile, int half16, int cb) const {
-    const char* base = tile + half16 * 16 * D * 2;
-    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(HSTU_LDS(s16x4, base + a[cb][0]));
-    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(HSTU_LDS(s16x4, base + a[cb][1]));
+    const int at = half16 * 16 * D * 2 - UP;
+    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(HSTU_LDS(s16x4, tile + (at + a[cb][0])));
+    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(HSTU_LDS(s16x4, tile + (at + a[cb][1])));
     typedef __attribute__((__vector_size__(8 * sizeof(short)))) short s16x8;
     const s16x8 both = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
     return __builtin_bit_cast(bf16x8, both);
@@ -480,13 +492,17 @@ __device__ __forceinline__ bool get_item(const AttnArgs& a, int slot, Item& it) 
 // Which streamed rows of a 32-row block the lane's owner row sees; r is the accumulator element,
 // i.e. streamed row 8*(r/4) + 4*hh + r%4 of the block.
 // =============================================================================================
+// (The lane's half is folded into rel, so that the comparisons are with constants: with 4 * hh on the other side
+// the compiler kept sixteen sums in registers over the whole kernel.)
 struct VisBefore {  // owners are queries, causal: keys at or before the query; rel = query - block position
-  int rel, hh;
-  __device__ __forceinline__ bool operator()(int r) const { return 8 * (r >> 2) + 4 * hh + (r & 3) <= rel; }
+  int rel;
+  __device__ __forceinline__ VisBefore(int rel_, int hh) : rel(rel_ - 4 * hh) {}
+  __device__ __forceinline__ bool operator()(int r) const { return 8 * (r >> 2) + (r & 3) <= rel; }
 };
 struct VisAfter {   // owners are keys, causal: queries at or after the key; rel = key - block position
-  int rel, hh;
-  __device__ __forceinline__ bool operator()(int r) const { return rel <= 8 * (r >> 2) + 4 * hh + (r & 3); }
+  int rel;
+  __device__ __forceinline__ VisAfter(int rel_, int hh) : rel(rel_ - 4 * hh) {}
+  __device__ __forceinline__ bool operator()(int r) const { return rel <= 8 * (r >> 2) + (r & 3); }
 };
 struct VisWindow {  // packed tiles: positions [lo, lo + span]; base = block position - lo
   int base;
