@@ -153,6 +153,10 @@ constexpr int UP_Q = 0, UP_G = 32768;
 constexpr int XG = 256;        // floats between the groups of four elements
 constexpr int XK = 4 * XG;     // floats per 32 keys
 
+// The operand is complete here.  (Its use is in the next step; with a branch in between the compiler would move the
+// instructions that make it there, in front of that step's first operand reads.)
+__device__ __forceinline__ void complete(const bf16x8& x) { asm volatile("" ::"v"(__builtin_bit_cast(u32x4, x))); }
+
 // Role A, one step: scores of the block at qn into s_out, SiLU of s_in (p' packed into p_cur,
 // silu' written to xw), dV^T += dO^T P with the block at gp and p_prev.
 template <int D, class Init, class Vis>
@@ -216,6 +220,7 @@ __device__ __forceinline__ void role_a_step(const Init& init, const char* qn, co
         *HSTU_LDS(f32x4, xw + (e0 / 4 + q4) * XG) = vf;
       }
       p_cur[G] = pack8(p[G]);
+      complete(p_cur[G]);
     }
   };
 #pragma unroll
@@ -270,6 +275,8 @@ __device__ __forceinline__ void role_b_step(const char* gn, const char* qp, cons
   }
   ds_cur[0] = pack8(ds);
   ds_cur[1] = pack8(ds + 8);
+  complete(ds_cur[0]);
+  complete(ds_cur[1]);
   fence();
 }
 
@@ -501,6 +508,10 @@ __global__ void __launch_bounds__(PW * 64) hstu_dkdv_pair_bf16(AttnArgs a) {
 // 1560 -> 1415 us, 1024 of 350 +- 33 % 751 -> 659, 512 of 700 +- 33 % 1010 -> 977.
 // =============================================================================================
 
+// What a step of an item's middle does not take: kept out of line, so that such a step runs straight through (a branch
+// taken costs some 30 cycles, and role A's issue is the step's time).
+__device__ __forceinline__ bool rare(bool x) { return __builtin_expect(x, false); }
+
 // What the roles know about an item of one streamed segment.
 struct WalkItem {
   int row0, nrows, pos0, h;
@@ -523,7 +534,7 @@ __device__ __forceinline__ WalkItem walk_item(const Item& it, int h, int causal)
 }
 
 template <int D, int ROLE, bool PACKED>
-__device__ __forceinline__ void pair_walk(const AttnArgs& a, int u, int stride, int end, const Rings& ring,
+__device__ __forceinline__ void pair_walk(const AttnArgs& a, int u, int stride, int end, const Rings& ring, char* vrows,
                                           float* xbuf0, float* xbuf1) {
   constexpr int QB = BR * D * 2;
   const int H = a.num_heads;
@@ -536,49 +547,64 @@ __device__ __forceinline__ void pair_walk(const AttnArgs& a, int u, int stride, 
   const float c1 = -a.alpha * 1.4426950408889634f;
   const int count = a.plan.header[0];
 
-  // Unit v of the workgroup's share (see unit_of; the number of items is at hand here).
-  const int per = (count + a.xcd_parts - 1) / a.xcd_parts;
-  auto unit = [&](int v) {
-    Unit r;
-    if (a.xcd_parts <= 1) { r.slot = v / H; r.h = v % H; r.on = true; }
-    else { const int x = v & 7, j = v >> 3; r.h = x % H; r.slot = (x / H) * per + j; r.on = j < per; }
-    r.on = r.on && v < end && r.slot < count;
-    return r;
-  };
-  // Descriptions: `raw` is that of the unit after the next one, one of its sixteen words per lane,
-  // loaded (always from inside the list: whether it counts is decided when its turn comes) and brought
-  // into scalar registers by decode.
+  // The workgroup's share, `left` units of `stride`: slot and head of the next one to be looked up (see unit_of).
+  int slot, h, left, dslot, dh;
+  if (a.xcd_parts <= 1) {
+    slot = u / H; h = u % H; dslot = stride / H; dh = stride % H;
+    left = (end - u + stride - 1) / stride;  // (end <= count * H)
+  } else {  // stride is a multiple of 8: the same head and the same part of the list throughout
+    const int per = (count + a.xcd_parts - 1) / a.xcd_parts, x = u & 7, part = (x / H) * per;
+    slot = part + (u >> 3); h = x % H; dslot = stride >> 3; dh = 0;
+    int last = part + ((end - x + 7) >> 3);
+    last = last < part + per ? last : part + per;
+    last = last < count ? last : count;
+    left = last > slot ? (last - slot + dslot - 1) / dslot : 0;
+  }
+  if (left <= 0) return;  // (every wave alike; the loop below counts on one unit at least)
+  // Descriptions: `raw` is that of the unit after the next one, one of its sixteen words per lane (zeros beyond the last
+  // unit), brought into scalar registers by decode.
   const __amdgpu_buffer_rsrc_t items =
       __builtin_amdgcn_make_buffer_rsrc((void*)a.plan.items, 0, a.max_items * (int)sizeof(Item), 0x00020000);
-  auto load_raw = [&](int v) {
-    const Unit un = unit(v);
-    return (int)__builtin_amdgcn_raw_buffer_load_b32(items, (lane & 15) * 4, un.on ? un.slot * (int)sizeof(Item) : 0, 0);
+  int raw_h = 0;
+  auto load_raw = [&] {
+    raw_h = h;
+    const int r = (int)__builtin_amdgcn_raw_buffer_load_b32(
+        items, left > 0 ? (lane & 15) * 4 : -4, left > 0 ? slot * (int)sizeof(Item) : 0, 0);
+    --left;
+    slot += dslot;
+    h += dh;
+    if (h >= H) { h -= H; ++slot; }
+    return r;
   };
-  auto decode = [&](int raw, int v) {
-    const Unit un = unit(v);
+  auto decode = [&](int raw) {
     Item it = {};
-    auto word = [&](int i) { return un.on ? __builtin_amdgcn_readlane(raw, i) : 0; };
+    auto word = [&](int i) { return __builtin_amdgcn_readlane(raw, i); };
     it.row0 = word(0); it.nrows = word(1); it.pos0 = word(2); it.nseg = word(3);
     it.seg_row0[0] = word(4); it.seg_len[0] = word(6); it.seg_pos0[0] = word(8);
-    return walk_item(it, un.h, a.causal);
+    return walk_item(it, raw_h, a.causal);
   };
-  int raw = load_raw(u);
-  WalkItem cur = decode(raw, u), nxt = {}, prev = {};
-  raw = load_raw(u + stride);
+  int todo = left;  // units whose first step is still to come
+  int raw = load_raw();
+  WalkItem cur = decode(raw), nxt = {}, prev = {};
+  raw = load_raw();
 
-  // The rows of the item this role owns: K (role A), V (role B).
+  // The rows of the item this role owns: K (role A), V (role B).  While an item is worked on role A has the next one's V
+  // rows copied into LDS, where role B picks them up, and touches the lines of its K rows (one dword per 128 bytes, two
+  // lines a row), so that the loads that follow when the registers become free find them in the L2.
   bf16x8 oreg[D / 16];
-  auto load_rows = [&](const WalkItem& w) {
-    load_owner<D>(oreg, (const __bf16*)(ROLE == 0 ? a.k : a.v) + (int64_t)w.row0 * sr + w.h * D, sr, orow, w.nrows, hh);
-  };
-  // One dword of each 128-byte line of the wave's 32 rows (two lines a row) of K and V.
-  int touched[2] = {0, 0};
-  auto touch_rows = [&](const WalkItem& w) {
-    int row = g * 32 + (lane >> 1);
-    row = row < w.nrows ? row : 0;
-    const int64_t off = ((int64_t)w.row0 + row) * sr + w.h * D + (lane & 1) * 64;
-    touched[0] = *(const int*)((const __bf16*)a.k + off);
-    touched[1] = *(const int*)((const __bf16*)a.v + off);
+  int touched = 0;
+  auto request_rows = [&](const WalkItem& w) {  // (role A)
+    const int64_t off = (int64_t)w.row0 * sr + w.h * D;
+    const int row = g * 32 + (lane >> 1);
+    touched = *(const int*)((const __bf16*)a.k + off + (row < w.nrows ? row : 0) * sr + (lane & 1) * 64);
+    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
+        (void*)((const __bf16*)a.v + off), 0, __builtin_amdgcn_readfirstlane(w.nrows * rs), 0x00020000);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int r = g * 32 + i * (64 / (D / 8)) + lane / (D / 8);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, HSTU_LDS(void, vrows + (g * 8 + i) * 1024), 16,
+                                               r * rs + (((lane % (D / 8)) ^ swz<D>(r)) << 4), 0, 0, 0);
+    }
   };
   // The stream of blocks as role B copies it, two blocks ahead.
   const __bf16 *cq = nullptr, *cg = nullptr;
@@ -619,7 +645,15 @@ __device__ __forceinline__ void pair_walk(const AttnArgs& a, int u, int stride, 
     copy_step(ring.q0, ring.g0);
     copy_step(ring.q1, ring.g1);
   }
-  load_rows(cur);  // (role B's first step works on a block of zeros: whatever V rows)
+  if constexpr (ROLE == 0) {
+    request_rows(cur);
+    load_owner<D>(oreg, (const __bf16*)a.k + (int64_t)cur.row0 * sr + cur.h * D, sr, orow, cur.nrows, hh);
+  } else {
+#pragma unroll
+    for (int i = 0; i < D / 16; ++i)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) oreg[i][e] = (__bf16)0.f;
+  }
 
   f32x16 acc[D / 32];  // A: dV^T, B: dK^T
   auto clear_acc = [&] {
@@ -660,7 +694,7 @@ __device__ __forceinline__ void pair_walk(const AttnArgs& a, int u, int stride, 
   tile_barrier();
 
   int s = 0;            // step of the item
-  bool first = true, drain = false;
+  bool first = true, drain = false, stored = false;  // stored: role B wrote the previous item's rows in the last step
   // The previous item's rows (see store_owner_major), through a buffer of its rows: the stores of lanes
   // beyond them are dropped, so a wave always issues eight.
   auto store_prev = [&] {
@@ -687,19 +721,18 @@ __device__ __forceinline__ void pair_walk(const AttnArgs& a, int u, int stride, 
 
   auto step = [&](auto tag) {  // returns true when the stream has been drained
     constexpr int S = decltype(tag)::value;  // step number mod 6
-    if (s == 1) {  // the next item's description, and the request for the one after
-      nxt = decode(raw, u + stride);
-      raw = load_raw(u + 2 * stride);
+    if (rare(s == 1)) {  // the next item's description, and the request for the one after
+      nxt = decode(raw);
+      raw = load_raw();
     }
-    bool done = false;
     if constexpr (ROLE == 0) {
       bool mask;
-      if (s == 1) {  // from here on the SiLU stage works on this item
+      if (rare(s == 1)) {  // from here on the SiLU stage works on this item
         if constexpr (PACKED) {
           win = make_window(wsq, cur.row0 + orow, orow < cur.nrows, 1, a.causal);
           wsq = bounds_of(nxt);
         }
-        touch_rows(nxt);
+        request_rows(nxt);
         m_klo = cur.pos0 + g * 32;
         m_last = !PACKED && a.causal ? (m_klo + 30 - cur.spos) >> 5 : -1;
         m_pos = cur.spos;
@@ -717,50 +750,53 @@ __device__ __forceinline__ void pair_walk(const AttnArgs& a, int u, int stride, 
       role_a_step<D>(init, ring.q(S), ring.g((S + 4) % NSLOT), ra, ca, oreg, sd[(S + 1) & 1], sd[S & 1], pk[S & 1],
                      pk[(S + 1) & 1], acc, (S + 1) & 1 ? xa1 : xa0, c1, a.alpha, mask, vis_of);
       lds_writes_done();
-      if (s == 1) {
+      if (rare(s == 1)) {
         store_prev();
         prev = cur;
       }
-      if (s + 1 == cur.nblk) {
-        load_rows(nxt);
-        asm volatile("" ::"v"(touched[0]), "v"(touched[1]));  // (what was touched is not needed)
+      if (rare(s + 1 == cur.nblk)) {
+        // (Waited for here, and V's rows with them: with loads that may be pending when a step begins the compiler makes
+        // every step wait for all of the wave's memory operations, the stores above among them.)
+        load_owner<D>(oreg, (const __bf16*)a.k + (int64_t)nxt.row0 * sr + nxt.h * D, sr, orow, nxt.nrows, hh);
+        asm volatile("" ::"v"(touched));  // (what was touched is not needed)
+        tile_copy_wait<0>();
       }
-      done = drain && s == 2;
     } else {
-      if (cleft == 0) seek(nxt);  // (in step 1 at the earliest)
+      if (rare(cleft == 0)) seek(nxt);  // (in step 1 at the earliest)
       copy_step(ring.q((S + AHEAD_COPY) % NSLOT), ring.g((S + AHEAD_COPY) % NSLOT));
       __builtin_amdgcn_sched_barrier(0);  // (the waits below count on this order)
-      if (!first)
+      if (!rare(first))
         role_b_step<D>(ring.g((S + 5) % NSLOT), ring.q((S + 3) % NSLOT), ra, ca, oreg, sd[S & 1], sd[(S + 1) & 1],
                        pk[(S + 1) & 1], pk[S & 1], acc, S & 1 ? xa1 : xa0);
       first = false;
       __builtin_amdgcn_sched_barrier(0);
-      // At the end of a step the previous step's copies must have landed.  Behind them are this step's
-      // copies, 4, the V rows requested in step 0, 8 (waited for in step 1), and the stores of step 2, 8.
-      if (s == 0) {
-        load_rows(cur);
-        __builtin_amdgcn_sched_barrier(0);
-        tile_copy_wait<12>();
-      } else if (s == 2) {
+      if (rare(s == 0)) {  // the item's V rows (they landed before the last barrier)
+#pragma unroll
+        for (int ks = 0; ks < D / 16; ++ks) oreg[ks] = ra.read(vrows, g, ks);
+        lds_writes_done();  // (role A has the next ones copied there in the next step)
+      }
+      // At the end of a step the previous step's copies must have landed.  Behind them are this step's copies, 4, and
+      // the 8 stores of step 2.
+      if (rare(s == 2)) {
         store_prev();
         prev = cur;
         __builtin_amdgcn_sched_barrier(0);
         tile_copy_wait<12>();
-      } else if (s == 3) {
+      } else if (rare(stored)) {
         tile_copy_wait<12>();
       } else {
         tile_copy_wait<4>();
       }
-      done = drain && s == 2;
+      stored = s == 2;
     }
     tile_barrier();
-    if (++s == cur.nblk) {
+    if (rare(++s == cur.nblk)) {
+      if (drain) return true;
       s = 0;
       cur = nxt;
-      u += stride;
-      drain = u >= end;
+      drain = --todo <= 0;
     }
-    return done;
+    return false;
   };
   while (true) {
     if (step(std::integral_constant<int, 0>{})) break;
@@ -777,6 +813,7 @@ template <int D, bool PACKED>
 __global__ void __launch_bounds__(PW * 64) hstu_dkdv_walk_bf16(AttnArgs a) {
   constexpr int QB = BR * D * 2;
   HSTU_RINGS(QB);
+  __shared__ __attribute__((aligned(1024))) char vrows[128 * D * 2];  // V rows of the next item
   __shared__ __attribute__((aligned(1024))) float xbuf0[4 * XK];
   __shared__ __attribute__((aligned(1024))) float xbuf1[4 * XK];
   int u = blockIdx.x, stride = (int)gridDim.x, end = unit_count(a, a.plan.header[0]);
@@ -784,9 +821,9 @@ __global__ void __launch_bounds__(PW * 64) hstu_dkdv_walk_bf16(AttnArgs a) {
   if (u >= end) return;
   const int role = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);
   if (role == 0)
-    pair_walk<D, 0, PACKED>(a, u, stride, end, ring, xbuf0, xbuf1);
+    pair_walk<D, 0, PACKED>(a, u, stride, end, ring, vrows, xbuf0, xbuf1);
   else
-    pair_walk<D, 1, PACKED>(a, u, stride, end, ring, xbuf0, xbuf1);
+    pair_walk<D, 1, PACKED>(a, u, stride, end, ring, vrows, xbuf0, xbuf1);
 }
 
 }  // namespace
