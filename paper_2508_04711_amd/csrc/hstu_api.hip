@@ -880,11 +880,15 @@ static int bwd_impl(const hstu_attn_params* params, const hstu_ts_bias* bias, co
   AttnArgs a = base_args(params, pk, 0);
   a.q = q; a.k = k; a.v = v; a.d_o = d_o; a.dk = dk; a.dv = dv;
   if (bias) set_bias(a, bias, (char*)workspace, true);
-  rc = run_pass(params, PASS_DKDV, a, stream);
-  if (rc != HSTU_OK) return rc;
   AttnArgs b = base_args(params, pq, 0);
   b.q = q; b.k = k; b.v = v; b.d_o = d_o; b.dq = dq;
   if (bias) set_bias(b, bias, (char*)workspace, true);
+  if (params->dtype == HSTU_F32 && bwd_f32_supported(a, b, params->d_qk, params->d_v)) {
+    TimedLaunch timed(11, stream);
+    return launch_bwd_f32(a, b, params->d_qk, params->d_v, stream) == hipSuccess ? HSTU_OK : HSTU_ERR_HIP;
+  }
+  rc = run_pass(params, PASS_DKDV, a, stream);
+  if (rc != HSTU_OK) return rc;
   size_t base = pq.end;
   rc = run_query_pass(params, PASS_DQ, b, pq, full_side(params, 0, PASS_DQ), dq, params->d_qk,
                       (char*)workspace, workspace_bytes, &base, stream);

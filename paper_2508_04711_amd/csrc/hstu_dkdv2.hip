@@ -588,15 +588,12 @@ __device__ __forceinline__ void pair_walk(const AttnArgs& a, int u, int stride, 
   WalkItem cur = decode(raw), nxt = {}, prev = {};
   raw = load_raw();
 
-  // The rows of the item this role owns: K (role A), V (role B).  While an item is worked on role A has the next one's V
-  // rows copied into LDS, where role B picks them up, and touches the lines of its K rows (one dword per 128 bytes, two
-  // lines a row), so that the loads that follow when the registers become free find them in the L2.
-  bf16x8 oreg[D / 16];
-  int touched = 0;
-  auto request_rows = [&](const WalkItem& w) {  // (role A)
+  // The rows of the item this role owns: K (role A), V (role B).  While an item is worked on role A loads the next one's K
+  // rows into registers of their own and has its V rows copied into LDS, where role B picks them up.
+  bf16x8 oreg[D / 16], knext[ROLE == 0 ? D / 16 : 1];
+  auto request_rows = [&](const WalkItem& w, bf16x8 (&k)[D / 16]) {  // (role A)
     const int64_t off = (int64_t)w.row0 * sr + w.h * D;
-    const int row = g * 32 + (lane >> 1);
-    touched = *(const int*)((const __bf16*)a.k + off + (row < w.nrows ? row : 0) * sr + (lane & 1) * 64);
+    load_owner<D>(k, (const __bf16*)a.k + off, sr, orow, w.nrows, hh);
     const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
         (void*)((const __bf16*)a.v + off), 0, __builtin_amdgcn_readfirstlane(w.nrows * rs), 0x00020000);
 #pragma unroll
@@ -646,8 +643,7 @@ __device__ __forceinline__ void pair_walk(const AttnArgs& a, int u, int stride, 
     copy_step(ring.q1, ring.g1);
   }
   if constexpr (ROLE == 0) {
-    request_rows(cur);
-    load_owner<D>(oreg, (const __bf16*)a.k + (int64_t)cur.row0 * sr + cur.h * D, sr, orow, cur.nrows, hh);
+    request_rows(cur, oreg);
   } else {
 #pragma unroll
     for (int i = 0; i < D / 16; ++i)
@@ -732,7 +728,7 @@ __device__ __forceinline__ void pair_walk(const AttnArgs& a, int u, int stride, 
           win = make_window(wsq, cur.row0 + orow, orow < cur.nrows, 1, a.causal);
           wsq = bounds_of(nxt);
         }
-        request_rows(nxt);
+        request_rows(nxt, knext);
         m_klo = cur.pos0 + g * 32;
         m_last = !PACKED && a.causal ? (m_klo + 30 - cur.spos) >> 5 : -1;
         m_pos = cur.spos;
@@ -755,11 +751,11 @@ __device__ __forceinline__ void pair_walk(const AttnArgs& a, int u, int stride, 
         prev = cur;
       }
       if (rare(s + 1 == cur.nblk)) {
-        // (Waited for here, and V's rows with them: with loads that may be pending when a step begins the compiler makes
-        // every step wait for all of the wave's memory operations, the stores above among them.)
-        load_owner<D>(oreg, (const __bf16*)a.k + (int64_t)nxt.row0 * sr + nxt.h * D, sr, orow, nxt.nrows, hh);
-        asm volatile("" ::"v"(touched));  // (what was touched is not needed)
+        // (Waited for here: with loads that may be pending when a step begins the compiler makes every step wait for all
+        // of the wave's memory operations, the stores above among them.)
         tile_copy_wait<0>();
+#pragma unroll
+        for (int ks = 0; ks < D / 16; ++ks) oreg[ks] = knext[ks];
       }
     } else {
       if (rare(cleft == 0)) seek(nxt);  // (in step 1 at the earliest)

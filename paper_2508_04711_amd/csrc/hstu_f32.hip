@@ -248,12 +248,12 @@ __device__ __forceinline__ void add_bias(f32x16& s, int (&bk)[16], const AttnArg
   }
 }
 
-// The workgroup's head and its 32 rows of an item (AttnArgs::item_parts; grid.y counts them).  False: no
-// owner rows.
-__device__ __forceinline__ bool half_item(const AttnArgs& a, Item& it, int& h) {
+// The head and the 32 rows of an item (AttnArgs::item_parts; grid.y counts them) that are (item, head) pair `unit`.
+// False: no owner rows.
+__device__ __forceinline__ bool half_item(const AttnArgs& a, int unit, Item& it, int& h) {
   const int skip = blockIdx.y * TILE;
-  h = blockIdx.x % a.num_heads;
-  if (!get_item(a, blockIdx.x / a.num_heads, it)) return false;
+  h = unit % a.num_heads;
+  if (!get_item(a, unit / a.num_heads, it)) return false;
   it.row0 += skip;
   it.pos0 += skip;
   it.nrows -= skip;
@@ -283,7 +283,7 @@ __global__ void __launch_bounds__(THREADS, f32_waves(DQK, DV)) hstu_fwd_f32(Attn
   const int H = a.num_heads;
   int h;
   Item it;
-  if (!half_item(a, it, h)) return;
+  if (!half_item(a, blockIdx.x, it, h)) return;
   const Lane l;
   const int64_t sq = (int64_t)H * DQK, sv = (int64_t)H * DV;
   const float* kg = (const float*)a.k + h * DQK;
@@ -338,14 +338,13 @@ __global__ void __launch_bounds__(THREADS, f32_waves(DQK, DV)) hstu_fwd_f32(Attn
 }
 
 // ---------------------------------------------------------------------------------------------
+// qbuf, gbuf: FW blocks of DQK and of DV columns (LDS).
 template <int DQK, int DV, bool BIAS, bool WIDE>
-__global__ void __launch_bounds__(THREADS, f32_waves(DQK, DV, BIAS)) hstu_dkdv_f32(AttnArgs a) {
-  __shared__ __attribute__((aligned(1024))) float qbuf[FW * FB * DQK];
-  __shared__ __attribute__((aligned(1024))) float gbuf[FW * FB * DV];
+__device__ __forceinline__ void dkdv_unit(const AttnArgs& a, int unit, float* qbuf, float* gbuf) {
   const int H = a.num_heads;
   int h;
   Item it;
-  if (!half_item(a, it, h)) return;
+  if (!half_item(a, unit, it, h)) return;
   const Lane l;
   const int64_t sq = (int64_t)H * DQK, sv = (int64_t)H * DV;
   const float* qg = (const float*)a.q + h * DQK;
@@ -412,16 +411,21 @@ __global__ void __launch_bounds__(THREADS, f32_waves(DQK, DV, BIAS)) hstu_dkdv_f
                      a.accumulate, l.wave, l.lane);
 }
 
-// ---------------------------------------------------------------------------------------------
 template <int DQK, int DV, bool BIAS, bool WIDE>
-__global__ void __launch_bounds__(THREADS, f32_dq_waves(DQK, DV, BIAS)) hstu_dq_f32(AttnArgs a) {
-  __shared__ __attribute__((aligned(1024))) float kbuf[FW * FB * DQK];
-  __shared__ __attribute__((aligned(1024))) float vbuf[FW * FB * DV];
-  __shared__ unsigned long long dwl[BIAS ? MAX_TS_BUCKETS : 1];  // the workgroup's sums of dS per bucket (fixed point)
+__global__ void __launch_bounds__(THREADS, f32_waves(DQK, DV, BIAS)) hstu_dkdv_f32(AttnArgs a) {
+  __shared__ __attribute__((aligned(1024))) float qbuf[FW * FB * DQK];
+  __shared__ __attribute__((aligned(1024))) float gbuf[FW * FB * DV];
+  dkdv_unit<DQK, DV, BIAS, WIDE>(a, blockIdx.x, qbuf, gbuf);
+}
+
+// ---------------------------------------------------------------------------------------------
+// kbuf, vbuf: FW blocks of DQK and of DV columns; dwl: the workgroup's sums of dS per bucket (fixed point, BIAS only).
+template <int DQK, int DV, bool BIAS, bool WIDE>
+__device__ __forceinline__ void dq_unit(const AttnArgs& a, int unit, float* kbuf, float* vbuf, unsigned long long* dwl) {
   const int H = a.num_heads;
   int h;
   Item it;
-  if (!half_item(a, it, h)) return;
+  if (!half_item(a, unit, it, h)) return;
   const Lane l;
   if constexpr (BIAS) {
     for (int i = l.tid; i < a.nb; i += THREADS) dwl[i] = 0ull;
@@ -486,6 +490,29 @@ __global__ void __launch_bounds__(THREADS, f32_dq_waves(DQK, DV, BIAS)) hstu_dq_
       if (dwl[j] != 0ull) atomicAdd(a.d_ts_acc + j, dw_from_fixed(dwl[j]));
 }
 
+template <int DQK, int DV, bool BIAS, bool WIDE>
+__global__ void __launch_bounds__(THREADS, f32_dq_waves(DQK, DV, BIAS)) hstu_dq_f32(AttnArgs a) {
+  __shared__ __attribute__((aligned(1024))) float kbuf[FW * FB * DQK];
+  __shared__ __attribute__((aligned(1024))) float vbuf[FW * FB * DV];
+  __shared__ unsigned long long dwl[BIAS ? MAX_TS_BUCKETS : 1];
+  dq_unit<DQK, DV, BIAS, WIDE>(a, blockIdx.x, kbuf, vbuf, dwl);
+}
+
+// Both backward passes in one launch, for calls whose workgroups are a few rounds at most: the passes do not depend
+// on each other, and each by itself lasts as long as its longest items while other CUs idle, and as a launch.  Groups of
+// eight workgroups (one per XCD) alternate between the passes, so that both lists run heaviest first.
+template <int D>
+__global__ void __launch_bounds__(THREADS, f32_waves(D, D)) hstu_bwd_f32(AttnArgs k, AttnArgs q) {
+  __shared__ __attribute__((aligned(1024))) float buf0[FW * FB * D];
+  __shared__ __attribute__((aligned(1024))) float buf1[FW * FB * D];
+  const int unit = (blockIdx.x >> 4) * 8 + (blockIdx.x & 7);
+  if (blockIdx.x & 8) {
+    if (unit < q.max_items * q.num_heads) dq_unit<D, D, false, false>(q, unit, buf0, buf1, nullptr);
+  } else {
+    if (unit < k.max_items * k.num_heads) dkdv_unit<D, D, false, false>(k, unit, buf0, buf1);
+  }
+}
+
 }  // namespace
 
 int tile_rows_f32(int /*pass*/) { return TILE; }
@@ -519,6 +546,27 @@ hipError_t launch_fwd_f32(const AttnArgs& a, int d_qk, int d_v, hipStream_t stre
 }
 hipError_t launch_dkdv_f32(const AttnArgs& a, int d_qk, int d_v, hipStream_t stream) {
   HSTU_DISPATCH_F32(hstu_dkdv_f32);
+}
+// Where the two passes in one launch are the faster form: up to three rounds of the two workgroups a CU holds, and at d =
+// 128, where it holds one, while the workgroups of both passes are resident at once.  (Beyond, the register allocation of
+// the larger pass costs the other one more than the shared tail gives.)  Measured, two launches -> one (workgroups
+// per pass), H = 2 and 4: d = 32 4 sequences of 1..64 rows (20) 20.1 -> 15.6 us, 16 of 64..512 (656) 48.8 -> 39.6, 64 of
+// 32..256 (1384) 48.8 -> 46.0, 64 of 64..512 (2508) 102 -> 101, 128 (5232) 182 -> 188; d = 64 22.6 -> 16.0, 68.8 ->
+// 63.7, 80.1 -> 77.5, 172 -> 180, 339 -> 352, 8 of 500..1024 (420) 102 -> 76; d = 128 (20) 35.6 -> 20.9, (420) 155 ->
+// 162, (656) 130 -> 134.
+bool bwd_f32_supported(const AttnArgs& k, const AttnArgs& q, int d_qk, int d_v) {
+  const int64_t most = k.max_items > q.max_items ? k.max_items : q.max_items;
+  return d_qk == d_v && !k.ts_rec && !q.ts_rec && (int64_t)k.num_heads * d_qk < WIDE_ROW &&
+         most * k.num_heads * k.item_parts <= (d_qk == 128 ? 128 : 1536);
+}
+hipError_t launch_bwd_f32(const AttnArgs& k, const AttnArgs& q, int d_qk, int d_v, hipStream_t stream) {
+  if (!bwd_f32_supported(k, q, d_qk, d_v)) return hipErrorInvalidValue;
+  const int64_t most = (k.max_items > q.max_items ? k.max_items : q.max_items) * (int64_t)k.num_heads;
+  const dim3 grid((unsigned)((most + 7) / 8 * 16), (unsigned)k.item_parts), block(THREADS);
+  if (d_qk == 128) hipLaunchKernelGGL((hstu_bwd_f32<128>), grid, block, 0, stream, k, q);
+  else if (d_qk == 64) hipLaunchKernelGGL((hstu_bwd_f32<64>), grid, block, 0, stream, k, q);
+  else hipLaunchKernelGGL((hstu_bwd_f32<32>), grid, block, 0, stream, k, q);
+  return hipGetLastError();
 }
 hipError_t launch_dq_f32(const AttnArgs& a, int d_qk, int d_v, hipStream_t stream) {
   if (a.ts_rec && !a.d_ts_acc) return hipErrorInvalidValue;

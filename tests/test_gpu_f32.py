@@ -23,6 +23,25 @@ def test_block_edges(dqk, dv, causal):
     _run_full(w, causal=causal, backward=True)
 
 
+@pytest.mark.parametrize("d,heads,batch,one", [(32, 4, 191, True), (32, 4, 192, False), (64, 4, 191, True),
+                                               (128, 2, 31, True), (128, 2, 32, False), (64, 3, 1, True)])
+def test_both_passes_in_one_launch(d, heads, batch, one):
+    """The backward pass on both sides of the limits up to which it is one launch (counted in the workgroups that
+    rows and batch allow for: 1536, and 128 at d = 128), and with a number of them that is no multiple of eight."""
+    import paper_2508_04711_amd as lib
+    print("f32 one launch", d, heads, batch, flush=True)
+    lengths = [32 + (i % 3) - 1 for i in range(batch)]
+    lengths[-1] += 32 * batch - sum(lengths)
+    w = workloads.custom("f32_one", lengths, heads, d, d, max_len=64, dtype="f32", scale=1.0, seed=47)
+    _run_full(w, causal=True, backward=True)
+    t = {k: v.cuda() for k, v in workloads.values(w).items()}
+    off = torch.from_numpy(w.seq_offsets()).cuda()
+    lib.hstu_debug_timing_begin(16)
+    lib.hstu_jagged_attn_bwd(t["q"], t["k"], t["v"], t["d_o"], off, w.max_len, w.alpha, True)
+    kinds = [x[0] for x in lib.hstu_debug_timing_end(16) if x[0] != "plan"]
+    assert kinds == (["bwd"] if one else ["dkdv", "dq"])
+
+
 @pytest.mark.parametrize("d", [32, 128])
 def test_saturated_scores(d):
     # alpha * q.k has a standard deviation of 64: many scores lie beyond what the exponential resolves
