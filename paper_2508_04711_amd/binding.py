@@ -193,8 +193,8 @@ def _dtype_code(t: torch.Tensor) -> int:
 def _params(batch, num_heads, d_qk, d_v, max_len, alpha, causal, dtype_code, total_rows,
             out_dtype_code=None) -> _Params:
     return _Params(int(batch), int(num_heads), int(d_qk), int(d_v), int(max_len), float(alpha),
-                   int(bool(causal)), int(dtype_code), int(total_rows),
-                   int(dtype_code if out_dtype_code is None else out_dtype_code), int(default_flags))
+                   1 if causal else 0, dtype_code, int(total_rows),
+                   dtype_code if out_dtype_code is None else out_dtype_code, default_flags)
 
 
 def _out_dtype(in_dtype: torch.dtype, out_dtype: Optional[torch.dtype]) -> torch.dtype:
@@ -210,19 +210,20 @@ def _code(dt: torch.dtype) -> int:
 
 
 def _ptr(t: Optional[torch.Tensor]):
-    return ctypes.c_void_p(t.data_ptr()) if t is not None else None
+    # (a plain integer: the functions' argtypes make the pointer of it, without an object of its own)
+    return t.data_ptr() if t is not None else None
 
 
 # The current stream's handle without the Stream object around it, which costs 2.7 us a call.
 _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
-def _stream(stream) -> ctypes.c_void_p:
+def _stream(stream) -> int:
     if stream is not None:
-        return ctypes.c_void_p(stream.cuda_stream)
+        return stream.cuda_stream
     if _raw_stream is not None:
-        return ctypes.c_void_p(_raw_stream(torch.cuda.current_device()))
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+        return _raw_stream(torch.cuda.current_device())
+    return torch.cuda.current_stream().cuda_stream
 
 
 def _empty(like: torch.Tensor, dtype) -> torch.Tensor:
@@ -247,6 +248,8 @@ def _allocates_on_its_stream(fn):
 
 
 def _check_tensor(t: torch.Tensor, name: str, rows: int, heads: int, dim: int, dtype) -> None:
+    if t.is_cuda and t.dtype is dtype and t.shape == (rows, heads, dim) and t.is_contiguous():
+        return
     if not t.is_cuda:
         raise ValueError("%s must be a device tensor" % name)
     if not t.is_contiguous():
@@ -257,10 +260,10 @@ def _check_tensor(t: torch.Tensor, name: str, rows: int, heads: int, dim: int, d
 
 
 def _workspace(params: _Params, which: int, workspace: Optional[torch.Tensor], device) -> torch.Tensor:
-    need = hstu_jagged_attn_workspace_bytes(params, which)
-    if workspace is None:
-        workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=device)
-    return workspace
+    if workspace is not None:
+        return workspace  # (the library checks that it is large enough)
+    need = load_library().hstu_jagged_attn_workspace_bytes(ctypes.byref(params), which)
+    return torch.empty(max(need, 256), dtype=torch.uint8, device=device)
 
 
 def hstu_jagged_attn_workspace_bytes(params_or_tuple, which: int) -> int:
@@ -347,8 +350,8 @@ def hstu_jagged_attn_bwd(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, d_o:
     B = seq_offsets.numel() - 1
     odt = out[0].dtype if out is not None else _out_dtype(q.dtype, out_dtype)
     if out is None:
-        dq = torch.empty_like(q, dtype=odt); dk = torch.empty_like(k, dtype=odt)
-        dvv = torch.empty_like(v, dtype=odt)
+        dq = _empty(q, odt); dk = _empty(k, odt)
+        dvv = _empty(v, odt)
     else:
         dq, dk, dvv = out
         _check_tensor(dq, "dq", T, H, dqk, odt); _check_tensor(dk, "dk", T, H, dqk, odt)
