@@ -141,6 +141,7 @@ struct SideSpec {
   int64_t owner_rows, streamed_rows;
   int segs;           // segments per sequence on the owner side (1 global, 2 rank-local)
   int ssegs;          // segments per sequence on the streamed side
+  bool joint = false; // the call's forward and dq pass are one kernel (see joint_query_pass)
 };
 
 struct BuiltPlan {
@@ -179,17 +180,42 @@ int64_t stiles_bound(const hstu_attn_params* p, const SideSpec& s) {
 // under a causal mask sees twice the average number of keys (a context-parallel rank's share
 // and small batches of long sequences are such problems).
 constexpr int SPLIT_BLOCKS = 64;  // a part covers at least this many visible 32-row blocks
-int split_of(const hstu_attn_params* p, const SideSpec& s) {
-  if (p->dtype != HSTU_BF16 || s.side != 0 || (p->flags & HSTU_FLAG_NO_SPLIT)) return 1;
+struct Split {
+  int max, blocks;  // at most so many parts, of at least so many visible 32-row blocks each
+};
+Split joint_split(const hstu_attn_params* p, const SideSpec& s);
+Split split_of(const hstu_attn_params* p, const SideSpec& s) {
+  if (p->dtype != HSTU_BF16 || s.side != 0 || (p->flags & HSTU_FLAG_NO_SPLIT)) return {1, SPLIT_BLOCKS};
   // no sequence is long enough for two parts (when the lengths respect max_len)
-  if ((int64_t)p->max_len < 2 * SPLIT_BLOCKS * 32) return 1;
+  if ((int64_t)p->max_len < 2 * SPLIT_BLOCKS * 32) return {1, SPLIT_BLOCKS};
+  if (s.joint) return joint_split(p, s);
   const int64_t wgs = items_bound(p, s) * p->num_heads;
   const int64_t slots = pass_waves(p, s.pass, s.owner_rows) == 8 ? 256 : 512;
   // Measured on the context-parallel workload (548 workgroups for 512 slots): two parts of at
   // least 64 blocks 574 TFLOP/s for the step, four parts of 16 blocks 522, none 507; on the
   // 16-sequence workload (1224 workgroups) splitting loses to the cost of the partial results.
   const int64_t n = (2 * slots + wgs - 1) / wgs;
-  return n < 1 ? 1 : (n > 8 ? 8 : (int)n);
+  return {n < 1 ? 1 : (n > 8 ? 8 : (int)n), SPLIT_BLOCKS};
+}
+
+// Visible (owner row, streamed row) pairs of a schedule at least, per head: batch x mean owner rows x mean streamed
+// rows (half of it under the causal mask), the sum of products being smallest when every sequence has the mean length.
+int64_t pairs_bound(const hstu_attn_params* p, const SideSpec& s) {
+  const int64_t batch = p->batch > 0 ? p->batch : 1;
+  return s.owner_rows / batch * (s.streamed_rows / batch) / (p->causal ? 2 : 1) * batch;
+}
+
+// Forward and dq pass in one (one workgroup per CU): a tile that lasts longer than three quarters of what a CU gets to
+// do in total is cut in parts of about that, so that the launch does not end with it.  (The workspace query counts
+// on no more items than the passes by themselves would have, see split_items_bound.)
+Split joint_split(const hstu_attn_params* p, const SideSpec& s) {
+  const int64_t longest = (s.streamed_rows < p->max_len ? s.streamed_rows : (int64_t)p->max_len) / 32;
+  const int64_t share = pairs_bound(p, s) / (128 * 32) * p->num_heads / 256 * 3 / 4;
+  const int64_t blocks = share < SPLIT_BLOCKS ? SPLIT_BLOCKS : share;
+  const int64_t tiles = items_bound(p, s), room = 1 + (2 * 512 / p->num_heads + 1) / tiles;
+  int64_t n = longest / blocks;
+  n = n < room ? n : room;
+  return {n < 1 ? 1 : (n > 8 ? 8 : (int)n), (int)(blocks < (1 << 20) ? blocks : 1 << 20)};
 }
 
 // Bounds for the workspace query that hold for every number of owner rows up to s.owner_rows
@@ -229,7 +255,8 @@ size_t tcopy_bytes(const hstu_attn_params* p, const SideSpec& s, int d) {
 // its build (launched by launch_built).
 int prepare_plan(const hstu_attn_params* p, int cp_size, const SideSpec& s, const int32_t* off,
                  char* ws, size_t ws_bytes, size_t base, PlanArgs* args, BuiltPlan* out) {
-  const int split = split_of(p, s);
+  const Split cut = split_of(p, s);
+  const int split = cut.max;
   const int64_t max_tiles = items_bound(p, s), max_items = max_tiles * split, max_stiles = stiles_bound(p, s);
   // only the forward pass with a transposed copy of V reads the streamed side's tile table (see make_tcopy)
   const bool want_ttile = s.pass == PASS_FWD && fwd_transposed_v(p);
@@ -262,9 +289,7 @@ int prepare_plan(const hstu_attn_params* p, int cp_size, const SideSpec& s, cons
   // to do in total (large batches), the order cannot unbalance the tail, and the natural order
   // keeps the items of a sequence, which share their streamed rows, together in time: one bin.
   // Both sides of the comparison in (owner row, streamed row) pairs: the heaviest item has at
-  // most tile x longest; all items together at least batch x mean owner rows x mean streamed
-  // rows (half of it under the causal mask), the sum of products being smallest when every
-  // sequence has the mean length.
+  // most tile x longest; all items together see pairs_bound.
   // Measured, H = 4, d = 128, sorted -> natural: 1536 sequences of 300..600 rows forward 1.18 ->
   // 0.86 ms, dQ 1.32 -> 1.07, dK/dV 1.94 -> 2.06; 768 of 600..1200 forward 1.68 -> 1.15, dQ 1.83 ->
   // 1.53, dK/dV 2.68 -> 2.94; 512 of 1000..2000 forward 2.17 -> 2.10, dQ 2.91 -> 2.29, dK/dV 4.25
@@ -274,8 +299,7 @@ int prepare_plan(const hstu_attn_params* p, int cp_size, const SideSpec& s, cons
   // walking workgroups take contiguous runs (2 to 5 %), but loses 4 % when they take every 256th
   // item, whose stride beats against the tiles per sequence.
   const int64_t batch = p->batch > 0 ? p->batch : 1;
-  const int64_t all_pairs = s.owner_rows / batch * (s.streamed_rows / batch) / (p->causal ? 2 : 1) * batch;
-  const int64_t per_slot = all_pairs / 512 * p->num_heads;
+  const int64_t per_slot = pairs_bound(p, s) / 512 * p->num_heads;
   // How small a fraction: an eighth always.  Some bf16 passes gain up to a larger one, `fraction`, as long as there
   // are enough (sequence, head) pairs: what natural order saves, the streamed rows that an XCD's L2 then reads
   // once, grows with the pairs that compete for it, and what it costs is an uneven tail of about the heaviest
@@ -320,7 +344,7 @@ int prepare_plan(const hstu_attn_params* p, int cp_size, const SideSpec& s, cons
   out->large = large && short_sequences(p);
   a.cost_shift = shift;
   a.split_max = split;
-  a.split_blocks = SPLIT_BLOCKS;
+  a.split_blocks = cut.blocks;
   a.red = reinterpret_cast<int32_t*>(ws + l.red);
   a.header = reinterpret_cast<int32_t*>(ws + l.header);
   a.owner_base = reinterpret_cast<int32_t*>(ws + l.owner_base);
@@ -344,7 +368,7 @@ int prepare_plan(const hstu_attn_params* p, int cp_size, const SideSpec& s, cons
   out->waves = pass_waves(p, s.pass, s.owner_rows);
   out->end = l.end;
   out->dp = DirectPlan{off, a.batch, a.total_rows, a.cp, a.owner_rank, a.streamed_rank, a.side, a.tile, a.causal,
-                       a.owner_rows, a.streamed_rows, split, SPLIT_BLOCKS};
+                       a.owner_rows, a.streamed_rows, split, cut.blocks};
   // Small batches in cost order.  Where the workgroups are at most two rounds of what is resident at once, each
   // works its own item out and no schedule is launched: 4 sequences of 1..64 rows fwd + bwd 39 -> 30 us, 32 of
   // 1..1024 rows forward 39 -> 30 us.  Beyond that the 0.5 us per item, which nothing overlaps at one
@@ -357,10 +381,10 @@ int prepare_plan(const hstu_attn_params* p, int cp_size, const SideSpec& s, cons
   // 4065..16260 rows, H = 2: 505 -> 476 us; with two parts the order is worth less than the launch, 908 -> 895 us for one
   // of four ranks, 8 of 4096..16384, H = 4).
   // (The key side follows the query side of the same call, so that all its schedules come from one launch.)
-  const SideSpec queries = {0, PASS_DQ, s.streamed_rank, s.owner_rank, s.streamed_rows, s.owner_rows, s.ssegs, s.segs};
-  const int parts = s.side == 0 ? split : split_of(p, queries);
+  const SideSpec queries = {0, PASS_DQ, s.streamed_rank, s.owner_rank, s.streamed_rows, s.owner_rows, s.ssegs, s.segs, s.joint};
+  const int parts = s.side == 0 ? split : split_of(p, queries).max;
   if (p->batch <= DIRECT_BATCH && parts <= 2 && !out->natural && !large && !want_ttile) {
-    const int64_t resident = s.side == 1 && p->d_qk + p->d_v > 128 ? 256 : 512;
+    const int64_t resident = (s.side == 1 || s.joint) && p->d_qk + p->d_v > 128 ? 256 : 512;
     out->form = p->batch <= SELF_BATCH && split <= 1 && max_items * p->num_heads <= 2 * resident ? BuiltPlan::SELF : BuiltPlan::DIRECT;
   }
   return HSTU_OK;
@@ -533,6 +557,32 @@ int run_query_pass(const hstu_attn_params* p, int pass, AttnArgs& a, const Built
                                 a.accumulate, a.out_f32, stream) == hipSuccess ? HSTU_OK : HSTU_ERR_HIP;
 }
 
+// Forward and dq pass of a call in one kernel (see joint_query_pass): the partial results of both outputs, if tiles are cut,
+// lie at `base` of the workspace.  `a`: the schedule's arguments.
+int run_joint_pass(const hstu_attn_params* p, AttnArgs a, const BuiltPlan& bp, const void* q, const void* k, const void* v,
+                   const void* d_o, void* o, void* dq, char* ws, size_t ws_bytes, size_t base, hipStream_t stream) {
+  // (in the names of the dk/dv pass, whose roles it shares: see hstu_fwd_dq_pair_bf16)
+  a.k = q; a.v = d_o; a.q = k; a.d_o = v; a.dv = o; a.dk = dq;
+  const int rows = 32 * bp.waves;
+  if (bp.split > 1) {
+    const size_t at = align_up(base, 256), bytes = partial_bytes(p, bp.max_items, rows, p->d_v);
+    if (at + bytes + partial_bytes(p, bp.max_items, rows, p->d_qk) > ws_bytes) return HSTU_ERR_WORKSPACE_TOO_SMALL;
+    a.partial = reinterpret_cast<float*>(ws + at);
+    a.partial2 = reinterpret_cast<float*>(ws + at + bytes);
+  }
+  {
+    TimedLaunch timed(12, stream);
+    if (launch_fwd_dq_pair_bf16(a, p->d_qk, p->d_v, stream) != hipSuccess) return HSTU_ERR_HIP;
+  }
+  if (bp.split <= 1) return HSTU_OK;
+  TimedLaunch timed(6, stream);
+  return launch_reduce_partials(bp.plan, bp.max_tiles, a.partial, o, p->num_heads, p->d_v, rows, a.accumulate, a.out_f32,
+                                stream) == hipSuccess &&
+                 launch_reduce_partials(bp.plan, bp.max_tiles, a.partial2, dq, p->num_heads, p->d_qk, rows, a.accumulate,
+                                        a.out_f32, stream) == hipSuccess
+             ? HSTU_OK : HSTU_ERR_HIP;
+}
+
 // Timestamp bias: argument checks and the per-row records at the start of the workspace.
 int check_bias(const hstu_attn_params* p, const hstu_ts_bias* b, bool backward) {
   if (!b) return HSTU_ERR_NULL_PTR;
@@ -582,6 +632,15 @@ SideSpec full_side(const hstu_attn_params* p, int side, int pass) {
 }
 
 int64_t clamp_rows(int64_t rows, int64_t total) { return rows < total ? rows : total; }
+
+// A context-parallel rank's forward and dq pass in one kernel (hstu_fwd_dq_pair_bf16), for calls that want both: the two
+// passes by themselves take the scores, their exponentials and the copies of K and V twice.  One of four ranks, 8 sequences of
+// 4096..16384 rows, H = 4, d = 128, with the reorders: 904 -> 763 us, as a ring 1237 -> 1033; 19 more ranks of 2 to 300 sequences
+// 1.05 to 1.47 times as fast.  A forced form of a pass keeps the passes apart.
+bool joint_query_pass(const hstu_attn_params* p, bool bias) {
+  return p->dtype == HSTU_BF16 && p->d_qk == 128 && p->d_v == 128 && !bias &&
+         !(p->flags & (HSTU_FLAG_FWD_TILE_128 | HSTU_FLAG_FWD_TILE_256 | HSTU_FLAG_DKDV_ONE_WAVE));
+}
 
 SideSpec cp_side(const hstu_attn_params* p, const hstu_cp_desc* cp, int side, int pass) {
   const int64_t qr = clamp_rows(cp->q_rows, p->total_rows), kr = clamp_rows(cp->kv_rows, p->total_rows);
@@ -981,8 +1040,10 @@ static int cp_partial_impl(const hstu_attn_params* params, const hstu_cp_desc* c
     a.nb = bias->num_buckets;
     a.fbits = bias->groups_log2;
   };
-  const SideSpec sf = cp_side(params, cp, 0, PASS_FWD), sq = cp_side(params, cp, 0, PASS_DQ);
-  if (do_f) {
+  SideSpec sf = cp_side(params, cp, 0, PASS_FWD), sk = cp_side(params, cp, 1, PASS_DKDV), sq = cp_side(params, cp, 0, PASS_DQ);
+  const bool joint = do_f && do_q && joint_query_pass(params, bias != nullptr);  // one schedule, in pq's place
+  sk.joint = sq.joint = joint;
+  if (do_f && !joint) {
     rc = prepare_plan(params, cp->cp_size, sf, seq_offsets_global, ws, workspace_bytes, base, &pa[np], &pf);
     built[np++] = &pf;
     if (rc != HSTU_OK) return rc;
@@ -991,8 +1052,7 @@ static int cp_partial_impl(const hstu_attn_params* params, const hstu_cp_desc* c
     if (pf.split > 1) base = align_up(base, 256) + partial_bytes(params, pf.max_items, 32 * pf.waves, params->d_v);
   }
   if (do_k) {
-    rc = prepare_plan(params, cp->cp_size, cp_side(params, cp, 1, PASS_DKDV), seq_offsets_global, ws,
-                      workspace_bytes, base, &pa[np], &pk);
+    rc = prepare_plan(params, cp->cp_size, sk, seq_offsets_global, ws, workspace_bytes, base, &pa[np], &pk);
     built[np++] = &pk;
     if (rc != HSTU_OK) return rc;
     base = pk.end;
@@ -1011,7 +1071,11 @@ static int cp_partial_impl(const hstu_attn_params* params, const hstu_cp_desc* c
   if (np == 0) return finish();
   rc = launch_built(pa, built, np, stream);
   if (rc != HSTU_OK) return rc;
-  if (do_f) {
+  if (joint) {
+    rc = run_joint_pass(params, base_args(params, pq, acc_q), pq, q_local, k_part, v_part, d_o_local, o_local, dq_local, ws,
+                        workspace_bytes, qbase, stream);
+    if (rc != HSTU_OK) return rc;
+  } else if (do_f) {
     AttnArgs a = base_args(params, pf, acc_q);
     a.q = q_local; a.k = k_part; a.v = v_part; a.o = o_local;
     with_bias(a, true);
@@ -1027,7 +1091,7 @@ static int cp_partial_impl(const hstu_attn_params* params, const hstu_cp_desc* c
     rc = run_pass(params, PASS_DKDV, a, stream);
     if (rc != HSTU_OK) return rc;
   }
-  if (do_q) {
+  if (do_q && !joint) {
     AttnArgs b = base_args(params, pq, acc_q);
     b.q = q_local; b.k = k_part; b.v = v_part; b.d_o = d_o_local; b.dq = dq_local;
     with_bias(b, true);

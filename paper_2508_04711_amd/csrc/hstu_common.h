@@ -525,6 +525,7 @@ struct AttnArgs {
   int32_t out_f32;  // outputs are fp32 (bf16 kernels only; the fp32 kernels always write fp32)
   int32_t item_parts;  // fp32 kernels: workgroups an item's rows are shared by, 32 rows each
   float* partial;   // partial results of split tiles: [slot][head][tile row][d] fp32 (or null)
+  float* partial2;  // the same of the second result (forward and dq pass in one)
   float alpha;
   float inv_n;
   // Timestamp bias (ts_rec == null: no bias).
@@ -597,6 +598,8 @@ hipError_t launch_dkdv_bf16(const AttnArgs& a, int d_qk, int d_v, hipStream_t st
 // The dk/dv pass with two waves per 32 keys (plain per-sequence schedules at d_qk = d_v = 128).
 bool dkdv_pair_supported(const AttnArgs& a, int d_qk, int d_v);
 hipError_t launch_dkdv_pair_bf16(const AttnArgs& a, int d_qk, int d_v, hipStream_t stream);
+// Forward and dq pass in one kernel, d_qk = d_v = 128, no bias (a: its fields as hstu_fwd_dq_pair_bf16 names them).
+hipError_t launch_fwd_dq_pair_bf16(const AttnArgs& a, int d_qk, int d_v, hipStream_t stream);
 bool dkdv_walk_supported(const AttnArgs& a, int d_qk, int d_v);
 hipError_t launch_dkdv_walk_bf16(const AttnArgs& a, int d_qk, int d_v, hipStream_t stream);
 hipError_t launch_dq_bf16(const AttnArgs& a, int d_qk, int d_v, hipStream_t stream);

@@ -280,8 +280,10 @@ __device__ __forceinline__ void role_b_step(const char* gn, const char* qp, cons
   fence();
 }
 
-// The whole item for one role (ROLE 0: A, 1: B).
-template <int D, int ROLE, bool BIAS>
+// The whole item for one role (ROLE 0: A, 1: B).  SIDE 1: owners are keys, the dk/dv pass.  SIDE 0: owners are queries,
+// forward and dq pass in one (see hstu_fwd_dq_pair_bf16), with the names of the other side:
+// a.k, a.v: the rows owned (Q and dO); a.q, a.d_o: the rows streamed (K and V); a.dv, a.dk: the results (O and dQ).
+template <int D, int ROLE, bool BIAS, int SIDE>
 __device__ __forceinline__ void pair_body(const AttnArgs& a, const Item& it, int h, const Rings& ring, float* xbuf0, float* xbuf1, char* rec0, char* rec1,
                                           char* rec2, char* rec3, char* rec4, char* rec5, float* wtab) {
   constexpr int QB = BR * D * 2;
@@ -296,7 +298,7 @@ __device__ __forceinline__ void pair_body(const AttnArgs& a, const Item& it, int
   const int rs = H * D * 2;  // bytes per row
   const int orow = g * 32 + n;
 
-  const Stream st = make_stream<1>(it, a.causal);
+  const Stream st = make_stream<SIDE>(it, a.causal);
   const int NBLK = 2 * st.total;  // 32-row blocks of the stream
   // the lane's part of a block copy: row wave * RPL + lane / CPR, swizzled chunk
   const int crow = wave * (64 / (D / 8)) + lane / (D / 8);
@@ -359,17 +361,20 @@ __device__ __forceinline__ void pair_body(const AttnArgs& a, const Item& it, int
   if constexpr (BIAS) bias = bias_setup<PW * 64>(a, wtab, it, orow, tid, hh);  // (all waves: has a barrier)
 
   const float c1 = -a.alpha * 1.4426950408889634f;
-  const int k_lo = it.pos0 + g * 32, k_hi = k_lo + 31;
-  // The last block the diagonal touches (position < k_hi); block positions grow with the index.
-  int last_masked = -1;
+  const int o_lo = it.pos0 + g * 32, o_hi = o_lo + 31;  // positions of the wave's owner rows
+  // The blocks the diagonal touches or hides: the first ones up to last_masked (keys own: position < o_hi), or the
+  // last ones from first_masked on (queries own: position + 31 > o_lo); block positions grow with the index.
+  int last_masked = -1, first_masked = NBLK;
   if (ROLE == 0 && a.causal) {
 #pragma unroll
     for (int s = 1; s >= 0; --s) {
       const int i0 = s ? 2 * st.n[0] : 0, nb = 2 * st.n[s];
       const int p0 = it.seg_pos0[s] + st.beg[s];
       if (nb > 0) {
-        const int m = (k_hi - 1 - p0) >> 5;
+        const int m = (o_hi - 1 - p0) >> 5;
         if (m >= 0 && last_masked < 0) last_masked = i0 + (m < nb - 1 ? m : nb - 1);
+        const int f0 = ((o_lo - 31 - p0) >> 5) + 1, f = f0 < 0 ? 0 : f0;
+        if (f < nb) first_masked = i0 + f;
       }
     }
   }
@@ -420,10 +425,11 @@ __device__ __forceinline__ void pair_body(const AttnArgs& a, const Item& it, int
         if (t <= NBLK + 1) {  // (nothing left to contract in the last step)
           // block t-1: masked when the diagonal touches it or when it lies beyond the stream
           const int b = t - 1;
-          const bool mask = b <= last_masked || b >= NBLK;
+          const bool mask = SIDE == 1 ? b <= last_masked || b >= NBLK : b >= first_masked;
           auto vis_of = [&] {
-            const int rel = b >= NBLK ? (1 << 20) : k_lo + n - block_pos(b < 0 ? 0 : b);
-            return VisAfter{rel, hh};
+            const int rel = o_lo + n - block_pos(b < 0 ? 0 : b);
+            if constexpr (SIDE == 1) return VisAfter{b >= NBLK ? (1 << 20) : rel, hh};
+            else return VisBefore{b >= NBLK ? -(1 << 20) : rel, hh};
           };
           const ScoreInit<BIAS> init = {&bias, recb(S), 0, BIAS ? tab.get(t) : BlockBias{}};
           role_a_step<D>(init, ring.q(S), ring.g((S + 4) % NSLOT), ra, ca, oreg, sd[(S + 1) & 1], sd[S & 1],
@@ -452,17 +458,34 @@ __device__ __forceinline__ void pair_body(const AttnArgs& a, const Item& it, int
 
   // Accumulators: lane holds key row n, elements c*32 + 8*(r/4) + 4*hh + r%4 (P and dS are held
   // without their factor alpha / N).
-  if (orow < it.nrows)
-    store_owner_major<D>(ROLE == 0 ? a.dv : a.dk, ((int64_t)it.row0 + orow) * sr + h * D, acc,
-                         a.alpha * a.inv_n, hh, a.accumulate, a.out_f32);
+  if (orow < it.nrows) {
+    if (SIDE == 0 && it.part > 0)  // one part of a split tile: an fp32 partial result, summed by the reduce kernel
+      store_owner_major<D>(ROLE == 0 ? a.partial : a.partial2, (((int64_t)(it.part - 1) * H + h) * 128 + orow) * D, acc,
+                           a.alpha * a.inv_n, hh, 0, 1);
+    else
+      store_owner_major<D>(ROLE == 0 ? a.dv : a.dk, ((int64_t)it.row0 + orow) * sr + h * D, acc, a.alpha * a.inv_n, hh,
+                           a.accumulate, a.out_f32);
+  }
 }
 
 // SELF: the workgroup works its item out from the offsets (a variant of its own: with both ways in one
 // kernel the long skewed batch took 1.6 % longer, the register allocation of the steps being different).
+template <int D, bool BIAS, bool SELF, int SIDE>
+__device__ __forceinline__ void pair_item(const AttnArgs& a, int unit, const Rings& ring, float* xbuf0, float* xbuf1, char* rec0,
+                                          char* rec1, char* rec2, char* rec3, char* rec4, char* rec5, float* wtab) {
+  const Unit un = unit_of(a, unit);
+  Item it;
+  if (!un.on || !(SELF ? get_item(a, un.slot, it) : fetch_item<false>(a.plan, un.slot, it))) return;
+  const int role = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);
+  if (role == 0)
+    pair_body<D, 0, BIAS, SIDE>(a, it, un.h, ring, xbuf0, xbuf1, rec0, rec1, rec2, rec3, rec4, rec5, wtab);
+  else
+    pair_body<D, 1, BIAS, SIDE>(a, it, un.h, ring, xbuf0, xbuf1, rec0, rec1, rec2, rec3, rec4, rec5, wtab);
+}
+
 template <int D, bool BIAS, bool SELF>
 __global__ void __launch_bounds__(PW * 64) hstu_dkdv_pair_bf16(AttnArgs a) {
-  constexpr int QB = BR * D * 2;
-  HSTU_RINGS(QB);
+  HSTU_RINGS(BR * D * 2);
   __shared__ __attribute__((aligned(1024))) float xbuf0[4 * XK];  // silu' of blocks of even index
   __shared__ __attribute__((aligned(1024))) float xbuf1[4 * XK];  // ... of odd index
   // bias variant: the timestamp records of the blocks in the ring buffers, and the table
@@ -473,17 +496,22 @@ __global__ void __launch_bounds__(PW * 64) hstu_dkdv_pair_bf16(AttnArgs a) {
   __shared__ __attribute__((aligned(1024))) char rec4[BIAS ? 1024 : 16];
   __shared__ __attribute__((aligned(1024))) char rec5[BIAS ? 1024 : 16];
   __shared__ float wtab[BIAS ? MAX_TS_BUCKETS : 1];
+  pair_item<D, BIAS, SELF, 1>(a, blockIdx.x, ring, xbuf0, xbuf1, rec0, rec1, rec2, rec3, rec4, rec5, wtab);
+}
 
-  const Unit un = unit_of(a, blockIdx.x);
-  Item it;
-  if (!un.on || !(SELF ? get_item(a, un.slot, it) : fetch_item<false>(a.plan, un.slot, it))) return;
-  const int role = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);
-  if (role == 0)
-    pair_body<D, 0, BIAS>(a, it, un.h, ring, xbuf0, xbuf1, rec0, rec1, rec2,
-                          rec3, rec4, rec5, wtab);
-  else
-    pair_body<D, 1, BIAS>(a, it, un.h, ring, xbuf0, xbuf1, rec0, rec1, rec2,
-                          rec3, rec4, rec5, wtab);
+// Forward and dq pass in one, for calls that want both (a context-parallel rank's partial): the dk/dv pass with the
+// sides' parts exchanged.  Queries own, K and V are streamed,
+//   role A:  S^T = K Q^T,  the SiLU arithmetic,  O^T += V^T P^T
+//   role B:  dP^T = V dO^T,  dS^T = dP^T * silu',  dQ^T += K^T dS^T
+// so the steps, the hand-over and the buffers are the same to the instruction.  The scores, their exponentials and
+// the copies of K and V are done once where the two passes did them twice: 8 units of matrix work (2 d flops per pair)
+// instead of 10, one schedule instead of two.
+template <int D, bool SELF>
+__global__ void __launch_bounds__(PW * 64) hstu_fwd_dq_pair_bf16(AttnArgs a) {
+  HSTU_RINGS(BR * D * 2);
+  __shared__ __attribute__((aligned(1024))) float xbuf0[4 * XK];
+  __shared__ __attribute__((aligned(1024))) float xbuf1[4 * XK];
+  pair_item<D, false, SELF, 0>(a, blockIdx.x, ring, xbuf0, xbuf1, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr);
 }
 
 // =============================================================================================
@@ -858,6 +886,14 @@ hipError_t launch_dkdv_pair_bf16(const AttnArgs& a, int d_qk, int d_v, hipStream
   if (a.self.off) { if (a.ts_rec) HSTU_PAIR(true, true); else HSTU_PAIR(false, true); }
   else { if (a.ts_rec) HSTU_PAIR(true, false); else HSTU_PAIR(false, false); }
 #undef HSTU_PAIR
+  return hipGetLastError();
+}
+
+hipError_t launch_fwd_dq_pair_bf16(const AttnArgs& a, int d_qk, int d_v, hipStream_t stream) {
+  if (d_qk != 128 || d_v != 128 || a.ts_rec || a.row_seq || a.waves != 4) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)grid_units(a)), block(PW * 64);
+  if (a.self.off) hipLaunchKernelGGL((hstu_fwd_dq_pair_bf16<128, true>), grid, block, 0, stream, a);
+  else hipLaunchKernelGGL((hstu_fwd_dq_pair_bf16<128, false>), grid, block, 0, stream, a);
   return hipGetLastError();
 }
 
