@@ -142,6 +142,7 @@ struct SideSpec {
   int segs;           // segments per sequence on the owner side (1 global, 2 rank-local)
   int ssegs;          // segments per sequence on the streamed side
   bool joint = false; // the call's forward and dq pass are one kernel (see joint_query_pass)
+  bool walk = false;  // the key side of a whole batch, without the timestamp bias (see walks_in_runs)
 };
 
 struct BuiltPlan {
@@ -251,6 +252,14 @@ size_t tcopy_bytes(const hstu_attn_params* p, const SideSpec& s, int d) {
   return align_up((size_t)p->num_heads * d * 64 * stiles_bound(p, s) * 2, 256);
 }
 
+// Whether the walking kernel (launch_dkdv_walk_bf16) serves a dk/dv pass whose schedule is in natural order, its
+// workgroups taking runs of equal work (balanced_run).
+bool walks_in_runs(const hstu_attn_params* p, const SideSpec& s, int split) {
+  return s.walk && p->dtype == HSTU_BF16 && p->out_dtype == HSTU_BF16 && p->d_qk == 128 && p->d_v == 128 &&
+         p->batch <= NATURAL_BATCH && split <= 1 && short_sequences(p) && p->num_heads <= 8 && 8 % p->num_heads == 0 &&
+         !(p->flags & HSTU_FLAG_DKDV_ONE_WAVE);
+}
+
 // Carves one schedule out of the workspace at byte offset `base` and fills the arguments of
 // its build (launched by launch_built).
 int prepare_plan(const hstu_attn_params* p, int cp_size, const SideSpec& s, const int32_t* off,
@@ -314,8 +323,13 @@ int prepare_plan(const hstu_attn_params* p, int cp_size, const SideSpec& s, cons
   // 1885 -> 2022 (6200), 512 of lognormal 350 298 -> 273 (12000).
   // The key side at two and three workgroups per CU (H = 8, d = 64) a quarter: 400 lognormal of median 512 fwd + bwd
   // 2165 -> 1964; at a half 128 of 400..800 rows lose 2 %.  No more than an eighth where walking workgroups take
-  // runs of equal numbers of items (256 lognormal of median 512, H = 8, d = 128: bwd 2070 -> 2470 at a half, and 1536
-  // of median 256 sorted by length 2262 -> 2669 at a quarter).
+  // runs of equal numbers of items or every 256th (1536 lognormal of median 256 sorted by length, H = 8, d = 128: bwd
+  // 2262 -> 2669 us at a quarter).
+  // Where they take runs of equal work (walks_in_runs) the whole of it: an item in the stream costs its blocks and some
+  // three more where the sorted list's costs its blocks and ten, and no plan is sorted.  Backward, d = 128, H = 4, us
+  // sorted -> walking: 256 sequences of 512 rows 545 -> 471, 256 of 400..800 706 -> 618, 128 of 300..600 239 -> 216, 96 of
+  // 512 190 -> 177, 300 of 200..1200 1120 -> 1020, 64 of 1024 350 -> 337.  At twice the share 200 lognormal of median 400
+  // lose (263 -> 273, H = 2) and 64 of 400..800 gain 1 %: the tail is then an item's length.
   // fp32 passes are bound by the matrix rate and only lose by the tail (256 sequences of 64..512 rows, H = 4, d = 64,
   // forward, dk/dv and dq 941 -> 875 us sorted), so they keep to an eighth up to 512 sequences; beyond, the
   // sorted build costs more than its order gains (4000 of 1..60, H = 2, d = 32, with the builds 319 -> 350 us sorted, 600
@@ -325,7 +339,7 @@ int prepare_plan(const hstu_attn_params* p, int cp_size, const SideSpec& s, cons
   const int64_t fraction = s.pass == PASS_FWD ? 2 : s.pass == PASS_DQ ? 3 : small_d ? 4 : 8;
   const int64_t need = s.pass == PASS_FWD ? (small_d ? 1800 : 900) : s.pass == PASS_DQ ? (small_d ? 8000 : 1300) : 3000;
   const bool large =
-      heaviest * 8 < per_slot ||
+      heaviest * 8 < per_slot || (walks_in_runs(p, s, split) && heaviest < per_slot) ||
       (heaviest * fraction < per_slot &&
        (p->dtype == HSTU_F32 ? batch > 512
                              : (double)batch * p->num_heads * (double)per_slot > (double)need * (double)heaviest));
@@ -509,6 +523,7 @@ AttnArgs base_args(const hstu_attn_params* p, const BuiltPlan& bp, int accumulat
   a.waves = bp.waves;
   a.large_batch = bp.large ? 1 : 0;
   a.walk_chunks = bp.chunks ? 1 : 0;
+  a.walk_costs = bp.chunks && bp.form == BuiltPlan::NATURAL ? 1 : 0;
   a.xcd_parts = bp.natural && p->dtype == HSTU_BF16 && p->num_heads < 8 && 8 % p->num_heads == 0
                     ? 8 / p->num_heads : 1;
   a.out_f32 = p->out_dtype == HSTU_F32 ? 1 : 0;
@@ -927,8 +942,9 @@ static int bwd_impl(const hstu_attn_params* params, const hstu_ts_bias* bias, co
   }
   BuiltPlan pk, pq;
   PlanArgs pa[2];
-  rc = prepare_plan(params, 1, full_side(params, 1, PASS_DKDV), seq_offsets, (char*)workspace,
-                    workspace_bytes, first, &pa[0], &pk);
+  SideSpec keys = full_side(params, 1, PASS_DKDV);
+  keys.walk = !bias;
+  rc = prepare_plan(params, 1, keys, seq_offsets, (char*)workspace, workspace_bytes, first, &pa[0], &pk);
   if (rc != HSTU_OK) return rc;
   rc = prepare_plan(params, 1, full_side(params, 0, PASS_DQ), seq_offsets, (char*)workspace,
                     workspace_bytes, pk.end, &pa[1], &pq);

@@ -23,14 +23,27 @@ struct Item {
   int32_t cost;         // visible 32-row streamed blocks (the sort key)
   int32_t part;         // 0: the item writes its output rows; p > 0: it covers only a part of the
                         // streamed rows and writes an fp32 partial result into slot p - 1
-  int32_t pad[2];
+  int32_t before;       // natural order of whole batches, key side: work of all items before this one
+  int32_t pad;
 };
 static_assert(sizeof(Item) == 64, "Item is one 64-byte record");
+
+// Blocks of `streamed` visible rows that the walking dk/dv kernel works through for an item: three at least.
+constexpr int WALK_BLOCKS_MIN = 3;
+// What an item costs besides, in blocks: its rows' loads, stores and masked blocks.  Backward of 1536 sequences of lognormal
+// length (median 256), sorted by length, with 0, 1, 2 and 4: 5475, 4916, 4635 and 4552 us; 512 of median 300, not sorted:
+// 1018, 1014, 992 and 1024 (H = 8 and 4, d = 128).
+constexpr int WALK_ITEM_BLOCKS = 3;
+__host__ __device__ inline int walk_blocks(int streamed) {
+  const int n = streamed / 32 + (streamed % 32 ? 1 : 0);
+  return n > WALK_BLOCKS_MIN ? n : WALK_BLOCKS_MIN;
+}
 
 // Device view of a built schedule.
 struct Plan {
   const int32_t* header;  // [0] = number of items, [1] = number of 64-row streamed tiles,
-                          // [2] = number of owner tiles whose partial results have to be summed
+                          // [2] = number of owner tiles whose partial results have to be summed,
+                          // [3] = work of all items (where Item::before is filled in)
   const int32_t* red;     // per such tile: first owner row, rows, first partial slot, slots
   const int32_t* order;   // order[slot] = item index, non-increasing cost
   const Item* items;
@@ -173,7 +186,7 @@ __device__ __forceinline__ Item describe_item(const Side& so, const Side& ss, in
   it.seg_pos0[1] = second ? vpos[1] : 0;
   it.seg_tcol0[1] = second ? vcol[1] : 0;
   it.part = 0;
-  it.pad[0] = it.pad[1] = 0;
+  it.before = it.pad = 0;
   pvis[0] = von[0] ? vvis[0] : (first1 ? vvis[1] : 0);
   pvis[1] = second ? vvis[1] : 0;
   return it;
@@ -552,6 +565,8 @@ struct AttnArgs {
   // Walking workgroups take contiguous runs of their XCD's units instead of every n-th unit
   // (natural order with a head count that divides 8).
   int32_t walk_chunks;
+  // ... of equal work instead of equal numbers of units (Item::before and header[3] are filled in).
+  int32_t walk_costs;
   int32_t single_segment;  // every item has one streamed segment at most (the streamed side is the whole batch's)
   // dk/dv pass: keep to the kernel with one wave per 32 keys where the two-wave kernel would serve.
   int32_t dkdv_one_wave;

@@ -526,14 +526,12 @@ __global__ void __launch_bounds__(PW * 64) hstu_fwd_dq_pair_bf16(AttnArgs a) {
 // Items have at least three blocks (blocks of no rows are added to shorter ones: zeros, which
 // contribute nothing), so that at most two items are in the pipeline.  After the last unit comes an
 // item of no rows whose three steps drain it.
-// A's K rows are loaded at the end of the previous item's last step, B's V rows at the end of step 0,
-// where the registers become free; what is exposed is an L2 hit's latency, because role A touches
-// the lines of both (one dword per lane and tensor) when an item begins.  (Holding the next rows in
-// registers or LDS instead does not fit: 256 registers, 160 KB.)
-// Nine vector registers spill (40 bytes a lane) in the six-fold unrolled step; the waits below count vector memory
-// operations, which that traffic can only make stricter.
+// The next item's rows are on their way while an item is worked on: role A loads the K rows into registers of their own
+// (32 a lane, which the ring's addresses within reach of one set of LDS offsets left free) and has the V rows copied into
+// 32 KB of LDS, the last of the CU's 160, from which role B takes them after step 0.
 // Measured against the one-wave kernel that walks items one after the other, H = 4: 1536 sequences of 300..600 rows
-// 1560 -> 1415 us, 1024 of 350 +- 33 % 751 -> 659, 512 of 700 +- 33 % 1010 -> 977.
+// 1560 -> 1415 us, 1024 of 350 +- 33 % 751 -> 659, 512 of 700 +- 33 % 1010 -> 977; with the next rows ahead and runs of
+// equal work (balanced_run) the first 1466 -> 1320 in another session.
 // =============================================================================================
 
 // What a step of an item's middle does not take: kept out of line, so that such a step runs straight through (a branch
@@ -561,6 +559,49 @@ __device__ __forceinline__ WalkItem walk_item(const Item& it, int h, int causal)
   return w;
 }
 
+// Workgroup u's run of a list in natural order, of equal work for each of the workgroups of a head
+// (Item::before): slots [slot, slot + left).  The XCD of workgroup u works on head (u mod 8) mod H and, of 8 / H
+// neighbouring parts of the list, on one.  Both ends are searched at once, 64 items at a time; whatever the
+// items hold, the runs cover the list (every end is found by one rule, the first is 0 and the last the list's).
+// Runs of equal numbers of items had 941 blocks at most where 862 are the mean for 1536 sequences of 300..600 rows, H = 4, and
+// 848 of 691 for 512 of 200..1200; of equal work 874 and 721, and lists sorted by length no longer differ from shuffled ones
+// (1536 sequences of median 256, H = 8, backward 5298 -> 4590 us sorted, 4993 -> 4230 shuffled).
+__device__ __forceinline__ void balanced_run(const AttnArgs& a, int u, int count, int& slot, int& left) {
+  const int lane = threadIdx.x & 63, x = u & 7, wgs = (int)(gridDim.x >> 3);
+  const int runs = a.xcd_parts * wgs, run = (x / a.num_heads) * wgs + (u >> 3);
+  const unsigned total = (unsigned)a.plan.header[3];
+  int lo[2], hi[2];
+  unsigned want[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int r = run + i;
+    want[i] = (unsigned)((uint64_t)total * (unsigned)r / (unsigned)runs);
+    lo[i] = r < runs ? 0 : count;
+    hi[i] = r > 0 ? count : 0;
+  }
+  while (lo[0] < hi[0] || lo[1] < hi[1]) {  // (the first item of `want` blocks before it lies in lo..hi)
+    int step[2];
+    unsigned v[2];
+    bool on[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      step[i] = (hi[i] - lo[i] + 63) >> 6;
+      const int64_t at = lo[i] + (int64_t)lane * step[i];
+      on[i] = at < hi[i];
+      v[i] = on[i] ? (unsigned)a.plan.items[at].before : 0u;
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int below = __builtin_popcountll(__ballot(on[i] && v[i] < want[i]));
+      const int64_t upper = lo[i] + (int64_t)below * step[i];
+      hi[i] = upper < hi[i] ? (int)upper : hi[i];
+      if (below > 0) lo[i] += (below - 1) * step[i] + 1;
+    }
+  }
+  slot = __builtin_amdgcn_readfirstlane(lo[0]);
+  left = __builtin_amdgcn_readfirstlane(lo[1]) - slot;
+}
+
 template <int D, int ROLE, bool PACKED>
 __device__ __forceinline__ void pair_walk(const AttnArgs& a, int u, int stride, int end, const Rings& ring, char* vrows,
                                           float* xbuf0, float* xbuf1) {
@@ -577,7 +618,10 @@ __device__ __forceinline__ void pair_walk(const AttnArgs& a, int u, int stride, 
 
   // The workgroup's share, `left` units of `stride`: slot and head of the next one to be looked up (see unit_of).
   int slot, h, left, dslot, dh;
-  if (a.xcd_parts <= 1) {
+  if (!PACKED && a.walk_costs) {
+    balanced_run(a, u, count, slot, left);
+    h = (u & 7) % H; dslot = 1; dh = 0;
+  } else if (a.xcd_parts <= 1) {
     slot = u / H; h = u % H; dslot = stride / H; dh = stride % H;
     left = (end - u + stride - 1) / stride;  // (end <= count * H)
   } else {  // stride is a multiple of 8: the same head and the same part of the list throughout
@@ -841,8 +885,10 @@ __global__ void __launch_bounds__(PW * 64) hstu_dkdv_walk_bf16(AttnArgs a) {
   __shared__ __attribute__((aligned(1024))) float xbuf0[4 * XK];
   __shared__ __attribute__((aligned(1024))) float xbuf1[4 * XK];
   int u = blockIdx.x, stride = (int)gridDim.x, end = unit_count(a, a.plan.header[0]);
-  walk_share(a, u, stride, end);
-  if (u >= end) return;
+  if (!a.walk_costs) {
+    walk_share(a, u, stride, end);
+    if (u >= end) return;
+  }
   const int role = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);
   if (role == 0)
     pair_walk<D, 0, PACKED>(a, u, stride, end, ring, vrows, xbuf0, xbuf1);

@@ -586,27 +586,51 @@ namespace {
 // sequences before its own (every workgroup again, from the cache: 64 K sequences at most), which is where
 // its items begin in the list, and writes its items, one per thread.  plan_kernel's one workgroup took 33 us
 // on 1536 sequences of 300..600 rows, 26 us on 1024 of 400..800; now 6 on either.
+// For the key side each item also gets the work of all items before it, in blocks: walk_blocks and WALK_ITEM_BLOCKS
+// for each, from which walking workgroups take runs of equal work.  A sequence's tiles shrink by tile / 32 blocks from one to the next under
+// the causal mask, so its sums are closed forms; only its last tile can see fewer than WALK_BLOCKS_MIN blocks.
 constexpr int NAT_SEQS = 64, NAT_THREADS = 256;
 struct NaturalPlans { PlanArgs p[3]; };
 __global__ void __launch_bounds__(NAT_THREADS) natural_plan_kernel(NaturalPlans plans) {
-  __shared__ int sums[NAT_THREADS / 64], first[NAT_SEQS + 1];
+  __shared__ int sums[2][NAT_THREADS / 64], first[NAT_SEQS + 1], blocks[NAT_SEQS + 1];
   const PlanArgs& a = plans.p[blockIdx.y];
   const int tid = threadIdx.x, b0 = blockIdx.x * NAT_SEQS;
-  auto tiles = [&](int b) {
+  auto rows = [&](int b) {
     int s, e;
     seq_range(a.off, b, a.total_rows, s, e);
-    return (e - s) / a.tile + ((e - s) % a.tile ? 1 : 0);
+    return e - s;
+  };
+  auto tiles = [&](int n) { return n / a.tile + (n % a.tile ? 1 : 0); };
+  const bool weigh = a.side == 1 && a.tile >= 64;
+  // Work of the first t of a sequence's tiles, and of all of them (n rows; unsigned: sums that wrap only cost balance).
+  auto blocks_of = [&](int n, int t, bool all) {
+    if (!weigh || t < 1) return 0u;
+    const unsigned step = (unsigned)a.tile / 32, more = WALK_ITEM_BLOCKS;
+    if (!a.causal) return (unsigned)t * ((unsigned)walk_blocks(n) + more);
+    const unsigned full = (unsigned)(n / 32 + (n % 32 ? 1 : 0));
+    unsigned sum = (unsigned)t * (full + more) - step * ((unsigned)t * (unsigned)(t - 1) / 2);
+    if (all) sum += (unsigned)walk_blocks(n - (t - 1) * a.tile) - (full - step * (unsigned)(t - 1));
+    return sum;
   };
   int before = 0;
-  for (int b = tid; b < b0; b += NAT_THREADS) before += tiles(b);
+  unsigned work = 0;
+  for (int b = tid; b < b0; b += NAT_THREADS) {
+    const int n = rows(b), t = tiles(n);
+    before += t;
+    work += blocks_of(n, t, true);
+  }
   before = wave_total(before);
-  if ((tid & 63) == 0) sums[tid >> 6] = before;
+  work = (unsigned)wave_total((int)work);
+  if ((tid & 63) == 0) { sums[0][tid >> 6] = before; sums[1][tid >> 6] = (int)work; }
   if (tid < 64) {  // (NAT_SEQS is a wave's width)
-    first[tid + 1] = wave_scan(b0 + tid < a.batch ? tiles(b0 + tid) : 0);
-    if (tid == 0) first[0] = 0;
+    const int n = b0 + tid < a.batch ? rows(b0 + tid) : 0, t = tiles(n);
+    first[tid + 1] = wave_scan(t);
+    blocks[tid + 1] = wave_scan((int)blocks_of(n, t, true));
+    if (tid == 0) first[0] = blocks[0] = 0;
   }
   __syncthreads();
-  const int base = sums[0] + sums[1] + sums[2] + sums[3], count = first[NAT_SEQS];
+  const int base = sums[0][0] + sums[0][1] + sums[0][2] + sums[0][3], count = first[NAT_SEQS];
+  const int done = sums[1][0] + sums[1][1] + sums[1][2] + sums[1][3];
   for (int i = tid; i < count; i += NAT_THREADS) {
     int lo = 0;
 #pragma unroll
@@ -617,8 +641,10 @@ __global__ void __launch_bounds__(NAT_THREADS) natural_plan_kernel(NaturalPlans 
     const Side side = make_side(e - s, 1, -1);
     const int slot = base + i;
     if (slot < a.max_items) {
-      a.items[slot] = describe_item(side, side, 0, i - first[lo], s, s, 0, a.tile, a.causal, a.side, a.owner_rows,
-                                    a.streamed_rows, pvis);
+      Item it = describe_item(side, side, 0, i - first[lo], s, s, 0, a.tile, a.causal, a.side, a.owner_rows,
+                              a.streamed_rows, pvis);
+      it.before = (int)((unsigned)done + (unsigned)blocks[lo] + blocks_of(e - s, i - first[lo], false));
+      a.items[slot] = it;
       a.order[slot] = slot;
     }
   }
@@ -626,6 +652,7 @@ __global__ void __launch_bounds__(NAT_THREADS) natural_plan_kernel(NaturalPlans 
     a.header[0] = base + count < a.max_items ? base + count : a.max_items;
     a.header[1] = 0;
     a.header[2] = 0;
+    a.header[3] = (int)((unsigned)done + (unsigned)blocks[NAT_SEQS]);
   }
 }
 

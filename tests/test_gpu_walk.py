@@ -78,3 +78,40 @@ def test_walking_dkdv_over_a_large_batch_in_natural_order(causal, monkeypatch):
         rms = b.pow(2).mean().sqrt()
         excess = (a - b).abs() - (2.0 ** -7 * torch.maximum(a.abs(), b.abs()) + 520 * 2.0 ** -24 * rms)
         assert excess.max().item() <= 0, excess.max().item()
+
+
+RUNS = [
+    # name, lengths, heads: sorted ascending and descending, with empty sequences and tiles of one row, few items a run
+    ("ascending", sorted(int(x) for x in RNG.integers(1, 700, size=700)), 4),
+    ("descending", sorted((int(x) for x in RNG.integers(1, 900, size=401)), reverse=True), 8),
+    ("empty_ones", [int(x) for x in RNG.integers(200, 420, size=450) * RNG.integers(0, 2, size=450)], 8),
+    ("one_row_tiles", [129, 257, 385] * 301, 2),
+    ("one_head", [int(x) for x in RNG.integers(100, 260, size=1701)], 1),
+    ("few", [512] * 96, 4),
+]
+
+
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("name,lengths,H", RUNS)
+def test_runs_of_equal_work(name, lengths, H, causal, monkeypatch):
+    """Per-sequence tiles in natural order from where the heaviest item is less than a slot's share (1 of 512) on, the
+    workgroups walking runs of equal work, against the one-wave kernel within the bound of the test above; every
+    row is written."""
+    import paper_2508_04711_amd as lib
+    longest = max(lengths)
+    w = workloads.custom(name, lengths, H, 128, 128, max_len=longest, dtype="bf16", seed=8)
+    mean = w.total_rows // w.batch
+    assert 128 * longest < mean * mean // (2 if causal else 1) * w.batch // 512 * H
+    print("runs", name, causal, flush=True)
+    d = {k: v.cuda() for k, v in workloads.values(w).items()}
+    off = torch.from_numpy(w.seq_offsets()).cuda()
+    args = (d["q"], d["k"], d["v"], d["d_o"], off, w.max_len, w.alpha, causal)
+    out = tuple(torch.full_like(d["q"], float("nan")) for _ in range(3))
+    _, dk, dv = lib.hstu_jagged_attn_bwd(*args, out=out)
+    set_flags(monkeypatch, add="DKDV_ONE_WAVE")
+    _, dk1, dv1 = lib.hstu_jagged_attn_bwd(*args)
+    for a, b in ((dk, dk1), (dv, dv1)):
+        a, b = a.float(), b.float()
+        rms = b.pow(2).mean().sqrt()
+        excess = (a - b).abs() - (2.0 ** -7 * torch.maximum(a.abs(), b.abs()) + longest * 2.0 ** -24 * rms)
+        assert excess.max().item() <= 0, excess.max().item()  # (NaN fails too)
