@@ -128,7 +128,8 @@ __device__ __forceinline__ void dq_block(const BiasCtx& bias, const char* trec,
   }
 }
 
-template <int DQK, int DV, int NW, bool BIAS, bool PACKED>
+// HELD: the mask's sums held in registers (VisBeforeHeld).
+template <int DQK, int DV, int NW, bool BIAS, bool PACKED, bool HELD>
 __device__ __forceinline__ void dq_item(const AttnArgs& a) {
   constexpr int KB = ST * DQK * 2, VB = ST * DV * 2;
   __shared__ __attribute__((aligned(1024))) char smem0[KB + VB];
@@ -229,7 +230,8 @@ __device__ __forceinline__ void dq_item(const AttnArgs& a) {
                                   a.alpha, win.masks(k_lo), win.vis(k_lo, hh), n, hh);
         else
           dq_block<DQK, DV, BIAS>(bias, tbuf(BUF), bb, dwa, kt, vt, blk, rak, rav, cak, qreg, greg, dqacc, c1,
-                                  a.alpha, a.causal && k_lo + 31 > q_lo, VisBefore{q_lo + n - k_lo, hh}, n, hh);
+                                  a.alpha, a.causal && k_lo + 31 > q_lo,
+                                  std::conditional_t<HELD, VisBeforeHeld, VisBefore>{q_lo + n - k_lo, hh}, n, hh);
       }
     }
     tile_copy_wait<0>();
@@ -264,17 +266,24 @@ __device__ __forceinline__ void dq_item(const AttnArgs& a) {
   }
 }
 
-template <int DQK, int DV, int NW, bool BIAS, bool PACKED>
-__global__ void __launch_bounds__(NW * 64, 2) hstu_dq_bf16(AttnArgs a) {
-  dq_item<DQK, DV, NW, BIAS, PACKED>(a);
+// Whether the mask's sums are held in registers: where three workgroups share a CU then (134 to 158 registers) and four
+// otherwise (122 and 126).  Four are slower for calls of few workgroups, which last as long as their longest items:
+// fwd + bwd of 16 sequences of 500..4000 rows, H = 4, d = 64, 324 us against 321, 32 of lognormal length (median 1024)
+// 346 against 341, d_v = 32 297 against 294.
+constexpr bool dq_held(int dqk, int dv, bool bias) {
+  return bias ? dqk == 32 && dv == 32 : (dqk == 64 && dv <= 64) || (dqk == 32 && dv == 128);
 }
 
-// The same held to 128 registers (of 143), so that four workgroups share a CU instead of three: 1024 sequences
-// of 400..800 rows, H = 8, d = 64: 1089 -> 1054 us.  For launches of many workgroups only, see many_units (16
-// sequences of 500..4000 rows, H = 4, lose 2 %).
-template <int DQK, int DV, int NW>
+template <int DQK, int DV, int NW, bool BIAS, bool PACKED>
+__global__ void __launch_bounds__(NW * 64, 2) hstu_dq_bf16(AttnArgs a) {
+  dq_item<DQK, DV, NW, BIAS, PACKED, dq_held(DQK, DV, BIAS)>(a);
+}
+
+// Four workgroups a CU for launches of many workgroups (see many_units): dq pass of 1024 sequences of 400..800 rows, H = 8,
+// d = 64, 1089 -> 1054 us.
+template <int DQK, int DV, int NW, bool BIAS>
 __global__ void __launch_bounds__(NW * 64, 4) hstu_dq_lean_bf16(AttnArgs a) {
-  dq_item<DQK, DV, NW, false, false>(a);
+  dq_item<DQK, DV, NW, BIAS, false, false>(a);
 }
 
 }  // namespace
@@ -285,11 +294,15 @@ hipError_t launch_dq_bf16(const AttnArgs& a, int d_qk, int d_v, hipStream_t stre
     if (a.ts_rec) HSTU_DISPATCH_BIAS(hstu_dq_bf16, 4, 4, true, true);
     HSTU_DISPATCH_D(hstu_dq_bf16, 4, 4, false, true);
   }
-  if (a.ts_rec) HSTU_DISPATCH_BIAS(hstu_dq_bf16, 4, 4, true, false);
-  if (d_qk == 64 && d_v == 64 && many_units(a)) {
-    hipLaunchKernelGGL((hstu_dq_lean_bf16<64, 64, 4>), dim3((unsigned)grid_units(a)), dim3(256), 0, stream, a);
+  if (dq_held(d_qk, d_v, a.ts_rec != nullptr) && many_units(a)) {
+    const dim3 grid((unsigned)grid_units(a)), block(256);
+    if (a.ts_rec) hipLaunchKernelGGL((hstu_dq_lean_bf16<32, 32, 4, true>), grid, block, 0, stream, a);
+    else if (d_qk == 32) hipLaunchKernelGGL((hstu_dq_lean_bf16<32, 128, 4, false>), grid, block, 0, stream, a);
+    else if (d_v == 64) hipLaunchKernelGGL((hstu_dq_lean_bf16<64, 64, 4, false>), grid, block, 0, stream, a);
+    else hipLaunchKernelGGL((hstu_dq_lean_bf16<64, 32, 4, false>), grid, block, 0, stream, a);
     return hipGetLastError();
   }
+  if (a.ts_rec) HSTU_DISPATCH_BIAS(hstu_dq_bf16, 4, 4, true, false);
   HSTU_DISPATCH_D(hstu_dq_bf16, 4, 4, false, false);
 }
 

@@ -74,7 +74,8 @@ __device__ __forceinline__ void fwd_step(const Init& init, const char* kn, int b
 // instruction, but no transposed copy has to be built first: the choice for small problems).
 // BIAS: with the timestamp bias (the records of the streamed rows travel with the K tiles).
 // PACKED: packed tiles (see Window).
-template <int DQK, int DV, int NW, bool VT, bool BIAS, bool PACKED>
+// HELD: the mask's sums held in registers (VisBeforeHeld).
+template <int DQK, int DV, int NW, bool VT, bool BIAS, bool PACKED, bool HELD = false>
 __global__ void __launch_bounds__(NW * 64, 2) hstu_fwd_bf16(AttnArgs a) {
   static_assert(!(PACKED && VT), "packed tiles: row-major V tiles");
   constexpr int KB = ST * DQK * 2, VB = ST * DV * 2;
@@ -221,7 +222,7 @@ __global__ void __launch_bounds__(NW * 64, 2) hstu_fwd_bf16(AttnArgs a) {
       return [&, i] {
         const int pos = block_pos(i);
         if constexpr (PACKED) return win.vis(pos, hh);
-        else return VisBefore{q_lo + n - pos, hh};
+        else return std::conditional_t<HELD, VisBeforeHeld, VisBefore>{q_lo + n - pos, hh};
       };
     };
     BlockTable tab = {};
@@ -297,9 +298,9 @@ __global__ void __launch_bounds__(NW * 64, 2) hstu_fwd_bf16(AttnArgs a) {
 }
 
 // =============================================================================================
-// The forward pass at d_qk = d_v = 64 without bias: one 32-key block at a time, as the dq pass does it.  99
-// registers and 32 KB of LDS, so four workgroups share a CU (three of the kernel above).  1024 sequences of
-// 400..800 rows, H = 8: 880 -> 814 us (2.9 -> 3.1 TB/s).  (The kernel above held to 128 registers spills eight,
+// The forward pass at d_qk = d_v = 64 without bias: one 32-key block at a time, as the dq pass does it.  87
+// registers and 32 KB of LDS, so five workgroups share a CU (three of the kernel above).  1024
+// sequences of 400..800 rows, H = 8: 880 -> 814 us (2.9 -> 3.1 TB/s); with 99 registers and four workgroups the same.  (The kernel above held to 128 registers spills eight,
 // and their reloads wait for the tile copies in flight: 1094 us.)  For launches of many workgroups only, see
 // many_units.
 // =============================================================================================
@@ -489,6 +490,13 @@ hipError_t launch_fwd_bf16(const AttnArgs& a, int d_qk, int d_v, hipStream_t str
       const dim3 grid((unsigned)grid_units(a));
       if (a.row_seq) hipLaunchKernelGGL((hstu_fwd_lean_bf16<64, 64, 4, true>), grid, dim3(256), 0, stream, a);
       else hipLaunchKernelGGL((hstu_fwd_lean_bf16<64, 64, 4, false>), grid, dim3(256), 0, stream, a);
+      return hipGetLastError();
+    }
+    // 134 registers and three workgroups a CU where the other form has 122 and four: 16 sequences of 500..4000 rows, H = 4,
+    // 77.1 -> 73.9 us; many prefer four (512 of 300..600 131 -> 122).
+    if (d_qk == 32 && d_v == 64 && !a.ts_rec && !a.row_seq && !many_units(a)) {
+      hipLaunchKernelGGL((hstu_fwd_bf16<32, 64, 4, false, false, false, true>), dim3((unsigned)grid_units(a)), dim3(256), 0,
+                         stream, a);
       return hipGetLastError();
     }
     if (a.row_seq) {

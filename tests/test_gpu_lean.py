@@ -8,6 +8,7 @@ import torch
 from conftest import set_flags
 import oracle
 import workloads
+from test_gpu_bias import _run as _run_bias
 from test_gpu_parity import _check_few_terms, _dev
 
 pytestmark = pytest.mark.gpu
@@ -51,3 +52,30 @@ def test_many_workgroups(name, lengths, H, packed, causal, monkeypatch):
             # 8 M elements some such are over 7 RMS: an operand's rounding (2^-9 of a term) and the output's own
             # (2^-9) are then 2.7e-2 RMS, more than the many-terms bar gives.
             _check_few_terms(nm, g, ref, name)
+
+
+@pytest.mark.parametrize("repeat,H,many", [(2, 4, False), (16, 8, True)])
+@pytest.mark.parametrize("dqk,dv,bias", [(64, 32, False), (32, 128, False), (32, 64, False), (32, 32, True)])
+def test_forms_on_both_sides_of_the_limit(dqk, dv, bias, repeat, H, many, monkeypatch):
+    """The other head dimensions whose masks have a form for few workgroups and one for many (dq pass, and the forward pass at
+    32 / 64)."""
+    set_flags(monkeypatch, add="NO_PACK")
+    lengths = EDGES * repeat
+    assert ((sum(lengths) // 128 + len(lengths) + 1) * H > 2048) == many
+    print("lean", dqk, dv, bias, many, flush=True)
+    w = workloads.custom("lean_dims", lengths, H, dqk, dv, max_len=257, dtype="bf16", seed=dqk + dv)
+    if bias:
+        _run_bias(w, "events", nb=40, f=2, seed=3, check=_check_few_terms)
+        return
+    import paper_2508_04711_amd as lib
+    vals = workloads.values(w)
+    d = _dev(vals)
+    off_np = w.seq_offsets()
+    off = torch.from_numpy(off_np).cuda()
+    f64 = {k: workloads.to_f64(v) for k, v in vals.items()}
+    want = (oracle.fwd(f64["q"], f64["k"], f64["v"], off_np, w.max_len, w.alpha, True),) + tuple(
+        oracle.bwd(f64["q"], f64["k"], f64["v"], f64["d_o"], off_np, w.max_len, w.alpha, True))
+    got = (lib.hstu_jagged_attn_fwd(d["q"], d["k"], d["v"], off, w.max_len, w.alpha, True),) + tuple(
+        lib.hstu_jagged_attn_bwd(d["q"], d["k"], d["v"], d["d_o"], off, w.max_len, w.alpha, True))
+    for nm, g, ref in zip(("o", "dq", "dk", "dv"), got, want):
+        _check_few_terms(nm, g, ref, "lean")
