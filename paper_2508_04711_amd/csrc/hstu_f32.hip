@@ -267,6 +267,13 @@ constexpr int f32_waves(int dqk, int dv, bool one = false) { return dqk + dv <= 
 // sequences of 1..60 rows, H = 2: 80 -> 94 us).
 constexpr int f32_dq_waves(int dqk, int dv, bool bias) { return dqk + dv <= 64 && !bias ? 4 : f32_waves(dqk, dv); }
 
+// The masks' form: sums held in registers at d_qk + d_v <= 96 without the bias.  There the compiler needs fewer registers so
+// in the d = 32 forward kernel (93 against 121, five workgroups a CU against four: 128 sequences of 64..512 rows, H = 4, 60.4
+// -> 58.0 us; fwd + bwd of 64 128 -> 123, of 4 of 1000..3000, H = 2, 185 -> 171).  Beyond, and with the bias, they only
+// take registers (d = 64 within 0.7 % either way; the bias's dk/dv kernel at d = 128 spills 13 with them and 3 without).
+template <int DQK, int DV, bool BIAS>
+constexpr bool f32_held = DQK + DV <= 96 && !BIAS;
+
 struct Lane {
   int tid, lane, n, hh, wave;
   __device__ __forceinline__ Lane() {
@@ -322,7 +329,7 @@ __global__ void __launch_bounds__(THREADS, f32_waves(DQK, DV)) hstu_fwd_f32(Attn
       p[r] = x * sigmoid_precise(x).sg;
     }
     if (a.causal && b.pos + FB - 1 > it.pos0) {
-      const VisBefore vis{it.pos0 + l.n - b.pos, l.hh};
+      const std::conditional_t<f32_held<DQK, DV, BIAS>, VisBeforeHeld, VisBefore> vis{it.pos0 + l.n - b.pos, l.hh};
 #pragma unroll
       for (int r = 0; r < 16; ++r) p[r] = vis(r) ? p[r] : 0.f;
     }
@@ -388,7 +395,7 @@ __device__ __forceinline__ void dkdv_unit(const AttnArgs& a, int unit, float* qb
       ds[r] = dp[r] * silu_slope(x, g);
     }
     if (a.causal && b.pos < it.pos0 + TILE - 1) {
-      const VisAfter vis{it.pos0 + l.n - b.pos, l.hh};
+      const std::conditional_t<f32_held<DQK, DV, BIAS>, VisAfterHeld, VisAfter> vis{it.pos0 + l.n - b.pos, l.hh};
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         const bool on = vis(r);
@@ -469,7 +476,7 @@ __device__ __forceinline__ void dq_unit(const AttnArgs& a, int unit, float* kbuf
       ds[r] = dp[r] * silu_slope(x, sigmoid_precise(x));
     }
     if (a.causal && b.pos + FB - 1 > it.pos0) {
-      const VisBefore vis{it.pos0 + l.n - b.pos, l.hh};
+      const std::conditional_t<f32_held<DQK, DV, BIAS>, VisBeforeHeld, VisBefore> vis{it.pos0 + l.n - b.pos, l.hh};
 #pragma unroll
       for (int r = 0; r < 16; ++r) ds[r] = vis(r) ? ds[r] : 0.f;
     }

@@ -504,10 +504,14 @@ struct VisAfter {   // owners are keys, causal: queries at or after the key; rel
   __device__ __forceinline__ VisAfter(int rel_, int hh) : rel(rel_ - 4 * hh) {}
   __device__ __forceinline__ bool operator()(int r) const { return rel <= 8 * (r >> 2) + (r & 3); }
 };
-// The same with the sixteen sums held in registers: the faster form of some kernels (see dq_held).
+// The same with the sixteen sums held in registers: the faster form of some kernels (see dq_held and f32_held).
 struct VisBeforeHeld {
   int rel, hh;
   __device__ __forceinline__ bool operator()(int r) const { return 8 * (r >> 2) + 4 * hh + (r & 3) <= rel; }
+};
+struct VisAfterHeld {
+  int rel, hh;
+  __device__ __forceinline__ bool operator()(int r) const { return rel <= 8 * (r >> 2) + 4 * hh + (r & 3); }
 };
 struct VisWindow {  // packed tiles: positions [lo, lo + span]; base = block position - lo
   int base;

@@ -99,6 +99,7 @@ EXPECTED = [
     (r"hstu_dkdv_f32ILi128ELi128ELb1E", 1, 1, 4, 12),
     (r"hstu_bwd_f32ILi(32|64)E", 2, 2, 4, 0),  # (both passes in one: what their kernels have)
     (r"hstu_bwd_f32ILi128E", 1, 1, 4, 0),
+    (r"hstu_fwd_f32ILi32ELi32ELb0E", 5, 5, 4, 0),
     (r"hstu_(fwd|dkdv|dq)_f32ILi(32|64|128)ELi(32|64|128)ELb[01]E", 1, 1, 4, 12),
 ]
 
