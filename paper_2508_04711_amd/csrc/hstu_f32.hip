@@ -267,6 +267,11 @@ constexpr int f32_waves(int dqk, int dv, bool one = false) { return dqk + dv <= 
 // sequences of 1..60 rows, H = 2: 80 -> 94 us).
 constexpr int f32_dq_waves(int dqk, int dv, bool bias) { return dqk + dv <= 64 && !bias ? 4 : f32_waves(dqk, dv); }
 
+// The dk/dv pass with the bias: one, except at d_qk + d_v = 96, where it fits two if it must and a few registers more keep one
+// workgroup on a CU if it need not (24 sequences of 64..512 rows, H = 2, fwd + bwd, d_qk = 64 123 -> 118 us, 32 110 -> 102;
+// at d_qk = d_v = 32 the bound makes the pass slower, 91 -> 96).
+constexpr int f32_dkdv_waves(int dqk, int dv, bool bias) { return dqk + dv == 96 ? 2 : f32_waves(dqk, dv, bias); }
+
 // The masks' form: sums held in registers at d_qk + d_v <= 96 without the bias.  There the compiler needs fewer registers so
 // in the d = 32 forward kernel (93 against 121, five workgroups a CU against four: 128 sequences of 64..512 rows, H = 4, 60.4
 // -> 58.0 us; fwd + bwd of 64 128 -> 123, of 4 of 1000..3000, H = 2, 185 -> 171).  Beyond, and with the bias, they only
@@ -419,7 +424,7 @@ __device__ __forceinline__ void dkdv_unit(const AttnArgs& a, int unit, float* qb
 }
 
 template <int DQK, int DV, bool BIAS, bool WIDE>
-__global__ void __launch_bounds__(THREADS, f32_waves(DQK, DV, BIAS)) hstu_dkdv_f32(AttnArgs a) {
+__global__ void __launch_bounds__(THREADS, f32_dkdv_waves(DQK, DV, BIAS)) hstu_dkdv_f32(AttnArgs a) {
   __shared__ __attribute__((aligned(1024))) float qbuf[FW * FB * DQK];
   __shared__ __attribute__((aligned(1024))) float gbuf[FW * FB * DV];
   dkdv_unit<DQK, DV, BIAS, WIDE>(a, blockIdx.x, qbuf, gbuf);

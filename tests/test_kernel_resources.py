@@ -89,10 +89,11 @@ EXPECTED = [
     (r"hstu_fwd_dq_pair_bf16ILi128E", 2, 1, 8, 0),
     (r"hstu_bwd_short_bf16ILi128E", 2, 2, 4, 3),
     (r"hstu_bwd_short_bf16ILi64E", 3, 3, 4, 0),
-    # fp32 (d_qk, d_v, bias, wide rows): two workgroups per CU up to d_qk + d_v = 128, without bias in dk/dv, one
+    # fp32 (d_qk, d_v, bias, wide rows): two workgroups per CU up to d_qk + d_v = 128, in dk/dv with the bias up to 96, one
     # beyond; four in dq at d = 32 without bias
     (r"hstu_(fwd|dq)_f32ILi64ELi64ELb[01]E", 2, 2, 4, 0),
     (r"hstu_dkdv_f32ILi64ELi64ELb0E", 2, 2, 4, 0),
+    (r"hstu_dkdv_f32ILi(64ELi32|32ELi64)ELb[01]E", 2, 2, 4, 0),
     (r"hstu_dq_f32ILi32ELi32ELb0E", 4, 4, 4, 1),
     (r"hstu_(fwd|dq)_f32ILi128ELi128ELb[01]E", 1, 1, 4, 0),
     (r"hstu_dkdv_f32ILi128ELi128ELb0E", 1, 1, 4, 0),
