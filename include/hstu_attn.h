@@ -377,11 +377,15 @@ const char* hstu_attn_status_string(int status);
  * call does not show), the table of work items for one side of a problem and copies it to host
  * memory (this call synchronises the stream).  Where those entry points build no table, every wave
  * working its item out by itself, the table is what the waves find.
- *   side: 0 = items are query tiles streaming over key segments (forward, dq pass)
- *         1 = items are key tiles streaming over query segments (dk/dv pass)
+ *   side: 0 = items are query tiles streaming over key segments, as a forward call builds them
+ *         1 = items are key tiles streaming over query segments (dk/dv pass), as a call with the timestamp bias
+ *             builds them
+ *         2, 3 = the query and the key tiles as a call for all outputs without the timestamp bias builds them: a
+ *             backward call, with cp a partial for o_local and the gradients
  *   cp == NULL: whole-batch attention; else the context-parallel problem it describes
  *   items_host: room for max_items * 12 int32; per item
- *       {row0, nrows, pos0, nseg, seg_row0[2], seg_len[2], seg_pos0[2], cost, 0}
+ *       {row0, nrows, pos0, nseg, seg_row0[2], seg_len[2], seg_pos0[2], cost, part}, part being 0 or, for a
+ *       part of a tile that is cut along the keys, its partial slot + 1
  *   returns the number of items (>= 0) in schedule order (non-increasing cost, where tiles are cut in two
  *   that of the whole tile; large batches: the order of the rows), or a status < 0.
  */

@@ -594,6 +594,8 @@ def hstu_debug_dump_schedule(seq_offsets: torch.Tensor, total_rows: int, num_hea
                              max_len: int = 1, workspace: Optional[torch.Tensor] = None) -> np.ndarray:
     """The device-built schedule as an int32 array [n_items, 12] in schedule order.
 
+    side: 0 / 1 the query side of a forward call / the key side of a call with the timestamp bias; 2 / 3 the query / key side
+    of a call for all outputs without it.
     cp = (cp_size, q_rank, kv_rank, q_rows, kv_rows) for a context-parallel problem.  The last
     column is 0, or p > 0 for an item that covers a part of its tile's keys (partial slot p - 1).
     """

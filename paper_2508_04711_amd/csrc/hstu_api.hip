@@ -646,6 +646,13 @@ SideSpec full_side(const hstu_attn_params* p, int side, int pass) {
   return SideSpec{side, pass, -1, -1, p->total_rows, p->total_rows, 1, 1};
 }
 
+// The key side of a whole-batch backward pass.
+SideSpec key_side(const hstu_attn_params* p, bool bias) {
+  SideSpec s = full_side(p, 1, PASS_DKDV);
+  s.walk = !bias;
+  return s;
+}
+
 int64_t clamp_rows(int64_t rows, int64_t total) { return rows < total ? rows : total; }
 
 // A context-parallel rank's forward and dq pass in one kernel (hstu_fwd_dq_pair_bf16), for calls that want both: the two
@@ -942,9 +949,7 @@ static int bwd_impl(const hstu_attn_params* params, const hstu_ts_bias* bias, co
   }
   BuiltPlan pk, pq;
   PlanArgs pa[2];
-  SideSpec keys = full_side(params, 1, PASS_DKDV);
-  keys.walk = !bias;
-  rc = prepare_plan(params, 1, keys, seq_offsets, (char*)workspace, workspace_bytes, first, &pa[0], &pk);
+  rc = prepare_plan(params, 1, key_side(params, bias != nullptr), seq_offsets, (char*)workspace, workspace_bytes, first, &pa[0], &pk);
   if (rc != HSTU_OK) return rc;
   rc = prepare_plan(params, 1, full_side(params, 0, PASS_DQ), seq_offsets, (char*)workspace,
                     workspace_bytes, pk.end, &pa[1], &pq);
@@ -1378,14 +1383,17 @@ int hstu_debug_dump_schedule(const hstu_attn_params* params, const hstu_cp_desc*
     rc = check_cp(params, cp);
     if (rc != HSTU_OK) return rc;
   }
-  if (side != 0 && side != 1) return HSTU_ERR_BAD_SHAPE;
+  if (side < 0 || side > 3) return HSTU_ERR_BAD_SHAPE;
   if (params->batch == 0 || params->total_rows == 0) return 0;
   if (!seq_offsets || !items_host || !workspace) return HSTU_ERR_NULL_PTR;
   if (workspace_bytes < hstu_jagged_attn_workspace_bytes(params, cp ? HSTU_WS_CP : HSTU_WS_FWD))
     return HSTU_ERR_WORKSPACE_TOO_SMALL;
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-  const int pass = side == 0 ? PASS_FWD : PASS_DKDV;
-  const SideSpec s = cp ? cp_side(params, cp, side, pass) : full_side(params, side, pass);
+  // (2, 3: as a call for all outputs without the timestamp bias builds them; 0 and 1: as a forward call and one with it)
+  const bool grads = side >= 2;
+  const int pass = (side & 1) ? PASS_DKDV : grads ? PASS_DQ : PASS_FWD;
+  SideSpec s = cp ? cp_side(params, cp, side & 1, pass) : (side & 1) ? key_side(params, !grads) : full_side(params, 0, pass);
+  s.joint = cp && grads && joint_query_pass(params, false);
   BuiltPlan bp;
   rc = build_plan(params, cp ? cp->cp_size : 1, s, seq_offsets, (char*)workspace, workspace_bytes,
                   0, stream, &bp, true);

@@ -318,3 +318,69 @@ def test_which_batches_keep_the_order_of_the_rows():
     some = [int(x) for x in rng.integers(300, 900, size=60)]
     assert _order(some, 4, 64, 0, dtype=1) == "heavy first"
     assert _order([int(x) for x in rng.integers(100, 200, size=3000)], 4, 64, 0, dtype=1) == "rows"
+
+
+@pytest.mark.parametrize("lengths,heads,cp,kv_rank,cut", [
+    ([16384] * 8, 4, 4, -1, False), ([16384] * 2, 4, 4, -1, True), ([9000, 300], 1, 2, -1, True), ([16384], 2, 2, 0, True), ([2000, 1500, 900], 4, 2, 1, False)])
+def test_query_tiles_of_a_partial_with_gradients(lengths, heads, cp, kv_rank, cut):
+    """Side 2: what forward and dq pass in one kernel read; its tiles are cut by a rule of their own, and cut in the table
+    just where the call sums partial results."""
+    import oracle
+    import paper_2508_04711_amd as lib
+    print("dump of a partial", lengths, flush=True)
+    T, r = sum(lengths), 0  # (the rank of the last positions)
+    off_np = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32)
+    off = torch.from_numpy(off_np).cuda()
+    nq, nk = (len(oracle.cp_global_rows(off_np, cp, x)) for x in (r, kv_rank))
+    desc = (cp, r, kv_rank, nq, nk)
+    got = lib.hstu_debug_dump_schedule(off, T, heads, 128, 128, True, 0, 2, cp=desc, max_len=max(lengths))
+    assert bool((got[:, 11] > 0).any()) == cut
+    covered = np.zeros(nq, dtype=np.int64)
+    for it in got[(got[:, 11] == 0)]:
+        covered[it[0]:it[0] + it[1]] += 1
+    for row0, nrows in {(int(x[0]), int(x[1])) for x in got[got[:, 11] > 0]}:
+        covered[row0:row0 + nrows] += 1
+    assert np.all(covered == 1)
+    q, do = (torch.zeros((nq, heads, 128), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    k, v = (torch.zeros((nk, heads, 128), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    lib.hstu_debug_timing_begin(32)
+    lib.hstu_jagged_attn_cp_partial(q, k, v, do, off, T, max(lengths), 0.1, True, cp, r, kv_rank)
+    kinds = [x[0] for x in lib.hstu_debug_timing_end(32)]
+    assert "fwd_dq" in kinds and ("reduce" in kinds) == cut
+
+
+def _order3(lengths, heads, d):
+    """The order of the key side's table as a backward call without bias builds it."""
+    import paper_2508_04711_amd as lib
+    off = torch.tensor(np.concatenate([[0], np.cumsum(lengths)]), dtype=torch.int32, device="cuda")
+    got = lib.hstu_debug_dump_schedule(off, sum(lengths), heads, d, d, True, 0, 3, max_len=max(lengths))
+    heavy = bool(np.all(got[:-1, 10] >= got[1:, 10]))
+    assert heavy != bool(np.all(got[:-1, 0] < got[1:, 0]))
+    return "heavy first" if heavy else "rows"
+
+
+def test_the_key_sides_order_is_that_of_the_backward_pass(monkeypatch):
+    """Where the heaviest key tile is less than a slot's share, a pass whose workgroups walk over runs keeps the order of
+    the rows; at other head dimensions, with the one-wave kernel and with the bias that takes an eighth of a share."""
+    from conftest import set_flags
+    lengths = [512] * 96
+    assert _order3(lengths, 4, 128) == "rows"
+    assert _order(lengths, 4, 128, 1) == "heavy first"
+    assert _order3(lengths, 4, 64) == "heavy first"
+    assert _order3(lengths[:64], 4, 128) == "heavy first"
+    set_flags(monkeypatch, add="DKDV_ONE_WAVE")
+    assert _order3(lengths, 4, 128) == "heavy first"
+
+
+@pytest.mark.parametrize("side", [2, 3])
+@pytest.mark.parametrize("cp,d", [(None, 128), (None, 64), ((4, 1, -1), 128), ((4, 1, 3), 128), ((4, 1, 3), 64)])
+def test_tables_of_a_call_with_gradients_hold_the_same_items(cp, d, side):
+    import oracle
+    import paper_2508_04711_amd as lib
+    lengths = [int(x) for x in np.random.default_rng(2).integers(0, 900, size=70)]
+    T = sum(lengths)
+    off_np = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32)
+    off = torch.from_numpy(off_np).cuda()
+    desc = None if cp is None else cp + tuple(len(oracle.cp_global_rows(off_np, cp[0], x)) for x in cp[1:])
+    got, plain = (lib.hstu_debug_dump_schedule(off, T, 4, d, d, True, 0, s, cp=desc, max_len=900) for s in (side, side - 2))
+    assert sorted(map(tuple, got.tolist())) == sorted(map(tuple, plain.tolist()))
