@@ -316,6 +316,7 @@ def measure(args):
            "fwd_dq": (4 * w.d_qk + 2 * w.d_v) * pairs}  # (forward and dq pass in one: the scores once, dP recomputed)
     hw = {"fwd": alg["fwd"], "dkdv": alg["dkdv"], "dq": (4 * w.d_qk + 2 * w.d_v) * pairs, "bwd": alg["bwd"],
           "fwd_dq": (4 * w.d_qk + 4 * w.d_v) * pairs}
+    alg["dkdv_runs"], hw["dkdv_runs"] = alg["dkdv"], hw["dkdv"]  # (the form of large batches)
     dom = max((k for k in ms_by_kind_per_step if k in alg), key=lambda k: ms_by_kind_per_step[k])
     n_launch = launches_per_step[dom]
     dom_ms = avg_ms[dom]
@@ -324,7 +325,8 @@ def measure(args):
     pair = (w.d_qk == 128 and w.d_v == 128 and not (args.flags & lib.HSTU_FLAG_DKDV_ONE_WAVE)
             and args.workload not in ("short", "mid", "cfg2"))
     kernel_name = {"fwd": "hstu_fwd_bf16", "dkdv": "hstu_dkdv_pair_bf16" if pair else "hstu_dkdv_walk_bf16",
-                   "dq": "hstu_dq_bf16", "bwd": "hstu_bwd_short_bf16", "fwd_dq": "hstu_fwd_dq_pair_bf16"}[dom]
+                   "dq": "hstu_dq_bf16", "bwd": "hstu_bwd_short_bf16", "fwd_dq": "hstu_fwd_dq_pair_bf16",
+                   "dkdv_runs": "hstu_dkdv_walk_bf16"}[dom]
     if args.flags & lib.HSTU_FLAG_DKDV_ONE_WAVE and dom == "dkdv":
         kernel_name = "hstu_dkdv_bf16"
     # What this machine sustains on matrix instructions alone, measured now: the published peak
@@ -354,6 +356,7 @@ def measure(args):
     bytes_alg = {"fwd": row * (2 * w.d_qk + 2 * w.d_v), "dkdv": row * (3 * w.d_qk + 3 * w.d_v),
                  "dq": row * (3 * w.d_qk + 2 * w.d_v), "bwd": row * (4 * w.d_qk + 3 * w.d_v),
                  "fwd_dq": row * (3 * w.d_qk + 3 * w.d_v)}
+    bytes_alg["dkdv_runs"] = bytes_alg["dkdv"]
     if not w.cp_size and alg[dom] / bytes_alg[dom] < PEAK_BF16_TFLOPS * 1e3 / PEAK_HBM_GBS:
         # below the ridge (flops per byte under peak flops / peak bandwidth): the dominant kernel
         # is reported against HBM bandwidth over its algorithmic bytes

@@ -402,7 +402,10 @@ int hstu_debug_dump_schedule(const hstu_attn_params* params, const hstu_cp_desc*
  *          (0 forward, 1 dk/dv pass, 2 dq pass, 3 schedule build, 4 transposed copy,
  *          5 reorder, 6 sum of the partial results of split tiles, 7 timestamp records,
  *          8 scaling of the bias table's gradient, 9 matrix-instruction loop, 10 atomic-rate kernel,
- *          11 backward of short sequences in one kernel) and its duration in milliseconds; returns the number written (<= capacity) or a status < 0.
+ *          11 backward in one launch (short sequences; small fp32 calls), 12 forward and dq pass of a partial in
+ *          one kernel, 13 dk/dv pass of a large batch whose workgroups walk over runs of equal work; every other
+ *          form of the dk/dv pass is 1) and its duration in milliseconds; returns the number written (<= capacity)
+ *          or a status < 0.
  */
 int hstu_debug_timing_begin(int max_records);
 int hstu_debug_timing_end(int32_t* kinds, float* milliseconds, int capacity);

@@ -617,7 +617,8 @@ def hstu_debug_dump_schedule(seq_offsets: torch.Tensor, total_rows: int, num_hea
 
 
 KERNEL_KINDS = {0: "fwd", 1: "dkdv", 2: "dq", 3: "plan", 4: "transpose", 5: "reorder", 6: "reduce",
-                7: "ts_records", 8: "dw_finish", 9: "mfma_loop", 10: "dq_atomic", 11: "bwd", 12: "fwd_dq"}
+                7: "ts_records", 8: "dw_finish", 9: "mfma_loop", 10: "dq_atomic", 11: "bwd", 12: "fwd_dq",
+                13: "dkdv_runs"}
 
 
 def hstu_debug_mfma_loop(random_operands: bool, iterations: int, sink: torch.Tensor, stream=None) -> float:

@@ -538,7 +538,9 @@ AttnArgs base_args(const hstu_attn_params* p, const BuiltPlan& bp, int accumulat
 
 int run_pass(const hstu_attn_params* p, int pass, const AttnArgs& a, hipStream_t stream) {
   hipError_t e;
-  TimedLaunch timed(pass, stream);
+  // (as launch_dkdv_bf16 decides)
+  const bool runs = pass == PASS_DKDV && p->dtype == HSTU_BF16 && a.walk_costs && !a.dkdv_one_wave && dkdv_walk_supported(a, p->d_qk, p->d_v);
+  TimedLaunch timed(runs ? 13 : pass, stream);
   if (p->dtype == HSTU_BF16) {
     e = pass == PASS_FWD ? launch_fwd_bf16(a, p->d_qk, p->d_v, stream)
         : pass == PASS_DKDV ? launch_dkdv_bf16(a, p->d_qk, p->d_v, stream)

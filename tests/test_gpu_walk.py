@@ -91,12 +91,20 @@ RUNS = [
 ]
 
 
+def _walked(lib, *args, **kw):
+    """The backward pass's gradients and the form of its dk/dv kernel."""
+    lib.hstu_debug_timing_begin(16)
+    got = lib.hstu_jagged_attn_bwd(*args, **kw)
+    return got, [x[0] for x in lib.hstu_debug_timing_end(16) if x[0] != "plan"][0]
+
+
 @pytest.mark.parametrize("causal", [True, False])
 @pytest.mark.parametrize("name,lengths,H", RUNS)
 def test_runs_of_equal_work(name, lengths, H, causal, monkeypatch):
     """Per-sequence tiles in natural order from where the heaviest item is less than a slot's share (1 of 512) on, the
     workgroups walking runs of equal work, against the one-wave kernel within the bound of the test above; every
     row is written."""
+    set_flags(monkeypatch, add="NO_PACK")  # (two of the batches have a mean below the packed tiles' limit)
     import paper_2508_04711_amd as lib
     longest = max(lengths)
     w = workloads.custom(name, lengths, H, 128, 128, max_len=longest, dtype="bf16", seed=8)
@@ -107,11 +115,48 @@ def test_runs_of_equal_work(name, lengths, H, causal, monkeypatch):
     off = torch.from_numpy(w.seq_offsets()).cuda()
     args = (d["q"], d["k"], d["v"], d["d_o"], off, w.max_len, w.alpha, causal)
     out = tuple(torch.full_like(d["q"], float("nan")) for _ in range(3))
-    _, dk, dv = lib.hstu_jagged_attn_bwd(*args, out=out)
+    (_, dk, dv), form = _walked(lib, *args, out=out)
+    assert form == "dkdv_runs"
     set_flags(monkeypatch, add="DKDV_ONE_WAVE")
-    _, dk1, dv1 = lib.hstu_jagged_attn_bwd(*args)
+    (_, dk1, dv1), form = _walked(lib, *args)
+    assert form == "dkdv"
     for a, b in ((dk, dk1), (dv, dv1)):
         a, b = a.float(), b.float()
         rms = b.pow(2).mean().sqrt()
         excess = (a - b).abs() - (2.0 ** -7 * torch.maximum(a.abs(), b.abs()) + longest * 2.0 ** -24 * rms)
         assert excess.max().item() <= 0, excess.max().item()  # (NaN fails too)
+
+
+@pytest.mark.parametrize("lengths,H,form", [
+    ([512] * 96, 4, "dkdv_runs"), ([512] * 64, 4, "dkdv"), ([512] * 96, 3, "dkdv"), ([256] * 500, 4, "dkdv")])
+def test_which_batches_are_walked_in_runs(lengths, H, form):
+    """(The last: packed tiles, whose walk has no runs of equal work.)"""
+    import paper_2508_04711_amd as lib
+    w = workloads.custom("which", lengths, H, 128, 128, max_len=512, dtype="bf16", seed=9)
+    d = {k: v.cuda() for k, v in workloads.values(w).items()}
+    off = torch.from_numpy(w.seq_offsets()).cuda()
+    _, got = _walked(lib, d["q"], d["k"], d["v"], d["d_o"], off, w.max_len, w.alpha, True)
+    assert got == form
+
+
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("name,lengths,H", RUNS)
+def test_work_before_every_item(name, lengths, H, causal, monkeypatch):
+    """What the runs are taken from: each item's record holds the work of all items before it, the header all of it (an
+    item's 32-row blocks, three at least, and three more), with sequences without rows in between."""
+    set_flags(monkeypatch, add="NO_PACK")
+    import paper_2508_04711_amd as lib
+    T = sum(lengths)
+    off = torch.tensor(np.concatenate([[0], np.cumsum(lengths)]), dtype=torch.int32, device="cuda")
+    nbytes = lib.hstu_jagged_attn_workspace_bytes((len(lengths), H, 128, 128, max(lengths), 1.0, causal, 0, T), 0)
+    ws = torch.zeros((nbytes + 63) // 64 * 64, dtype=torch.uint8, device="cuda")
+    items = lib.hstu_debug_dump_schedule(off, T, H, 128, 128, causal, 0, 3, max_len=max(lengths), workspace=ws)
+    assert np.all(items[:-1, 0] < items[1:, 0]), "the order of the rows"
+    records = ws.view(torch.int32).reshape(-1, 16).cpu().numpy()  # (an item is a 64-byte record; the header is the first)
+    first = [i for i in range(len(records) - len(items) + 1)
+             if np.array_equal(records[i, :4], items[0, :4]) and np.array_equal(records[i:i + len(items), :4], items[:, :4])]
+    assert len(first) == 1
+    streamed = items[:, 6] - (items[:, 2] if causal else 0)  # rows of the sequence at or after the tile's first key
+    work = np.maximum(3, (streamed + 31) // 32) + 3
+    assert np.array_equal(records[first[0]:first[0] + len(items), 14], np.cumsum(work) - work)
+    assert records[0, 3] == work.sum()
