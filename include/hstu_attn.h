@@ -96,12 +96,16 @@ typedef enum {
   HSTU_FLAG_FWD_TILE_128 = 8,   /* bf16 forward: the form that first builds a transposed copy of V in
                                    the workspace and reads that (one LDS instruction per matrix
                                    instruction instead of one and a half), with 128-row query tiles;
-                                   the default reads V row-major and builds nothing               */
+                                   the default reads V row-major and builds nothing.  A partial with
+                                   gradients then computes o_local and dq_local in separate passes
+                                   (see hstu_jagged_attn_cp_partial)                              */
   HSTU_FLAG_FWD_TILE_256 = 16,  /* ... with 256-row query tiles                                    */
   HSTU_FLAG_DKDV_ONE_WAVE = 32, /* dk/dv pass: the kernel with one wave per 32 keys and two blocks
                                    in flight, instead of the ones that split the work over two waves
                                    (d_qk = d_v = 128), keep one block in flight (64), or compute the
-                                   whole backward pass of packed tiles with max_len <= 128 at once  */
+                                   whole backward pass of packed tiles with max_len <= 128 at once.
+                                   A partial with gradients then also computes o_local and dq_local
+                                   in separate passes, each with cuts of its own                   */
   HSTU_FLAG_BIAS_PER_PAIR = 64  /* calls with the timestamp bias (bf16): every block of pairs looks
                                    up the fp32 table entry of each pair; without it a block whose
                                    pairs share a bucket takes the entry as two bf16 halves (exact
@@ -255,6 +259,10 @@ typedef struct {
  *       (outputs, required iff d_o_local != NULL)
  * Summing o_local (dq_local) over kv_rank = 0..CP-1 gives q_rank's rows of the
  * full result; summing dk_part (dv_part) over q_rank gives kv_rank's rows.
+ * bf16 at d_qk = d_v = 128 without the bias: a call that wants o_local and the gradients computes o_local and
+ * dq_local in one kernel, whose tiles are cut along the keys by a rule of its own, a forward-only call o_local in the
+ * forward pass; the fp32 sums of o_local may then be ordered differently in the two calls.  HSTU_FLAG_DKDV_ONE_WAVE and
+ * the two HSTU_FLAG_FWD_TILE bits keep the passes apart, and o_local is the forward-only call's bit for bit.
  */
 int hstu_jagged_attn_cp_partial(const hstu_attn_params* params, const hstu_cp_desc* cp,
                                 const void* q_local, const void* k_part, const void* v_part,

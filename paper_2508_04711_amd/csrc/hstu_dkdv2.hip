@@ -120,9 +120,10 @@ __device__ __forceinline__ void lds_writes_done() { asm volatile("s_waitcnt lgkm
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 
 // The ring buffers: six for the blocks of Q, six for those of dO.  One array per buffer, so that the compiler can see
-// that a copy into one cannot alias operand reads from another.  The larger exchange buffers come to lie at 0..32 KB, then
-// Q's buffers and then dO's in the order of their declaration (at D = 128), and the reads of each tensor stay
-// within the reach of one set of addresses (see raised; another layout would only cost additions).
+// that a copy into one cannot alias operand reads from another.  The compiler lays LDS out by falling alignment, which is
+// why the alignments differ (at D = 128): Q's buffers at 0..48 KB, dO's at 48..96 KB, the exchange buffers and the
+// rest above.  An address reaches 64 KB: from 0 for Q's, from UP_G = 32 KB, i.e. 32..96 KB, for dO's, so that one set of
+// addresses per tensor serves all reads (see raised; another layout would only cost additions).
 struct Rings {
   char *q0, *q1, *q2, *q3, *q4, *q5, *g0, *g1, *g2, *g3, *g4, *g5;
   __device__ __forceinline__ char* q(int b) const {

@@ -85,3 +85,29 @@ def test_cut_tiles(lengths, heads, cp, kv_rank, monkeypatch):
     # dS whose last bits differ may round to the neighbouring bf16 operand, 2^-8 of one term of thousands
     for name, a, b in zip(("o", "dq", "dk", "dv"), got, want):
         assert (a - b).abs().max().item() <= 2e-4 * b.abs().max().item(), name
+
+
+@pytest.mark.parametrize("flag", ["DKDV_ONE_WAVE", "FWD_TILE_128", "FWD_TILE_256"])
+def test_passes_kept_apart(flag, monkeypatch):
+    """The flags that keep a partial's forward and dq pass apart: its o is the forward-only partial's, bit for bit."""
+    import paper_2508_04711_amd as lib
+    print("joint apart", flag, flush=True)
+    set_flags(monkeypatch, add=flag)
+    lengths, heads, cp, r = [5000, 300, 0, 129], 2, 2, 1
+    T = sum(lengths)
+    gen = torch.Generator(device="cuda").manual_seed(4)
+    off_np = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32)
+    off = torch.from_numpy(off_np).cuda()
+    nq = len(oracle.cp_global_rows(off_np, cp, r))
+    val = lambda n: (torch.randn((n, heads, 128), generator=gen, device="cuda") * 0.5).bfloat16()
+    q, do, k, v = val(nq), val(nq), val(T), val(T)
+
+    def call(d_o):
+        lib.hstu_debug_timing_begin(32)
+        res = lib.hstu_jagged_attn_cp_partial(q, k, v, d_o, off, T, max(lengths), 128 ** -0.5, True, cp, r, -1,
+                                              out_dtype=torch.float32)
+        return res[0], [x[0] for x in lib.hstu_debug_timing_end(32)]
+
+    (with_gradients, kinds), (alone, _) = call(do), call(None)
+    assert "fwd" in kinds and "dq" in kinds and "fwd_dq" not in kinds
+    assert torch.equal(with_gradients, alone)
