@@ -965,9 +965,9 @@ static int bwd_impl(const hstu_attn_params* params, const hstu_ts_bias* bias, co
   AttnArgs b = base_args(params, pq, 0);
   b.q = q; b.k = k; b.v = v; b.d_o = d_o; b.dq = dq;
   if (bias) set_bias(b, bias, (char*)workspace, true);
-  if (params->dtype == HSTU_F32 && bwd_f32_supported(a, b, params->d_qk, params->d_v)) {
+  if (params->dtype == HSTU_F32 && bwd_f32_supported(a, b, params->d_qk, params->d_v, params->max_len)) {
     TimedLaunch timed(11, stream);
-    return launch_bwd_f32(a, b, params->d_qk, params->d_v, stream) == hipSuccess ? HSTU_OK : HSTU_ERR_HIP;
+    return launch_bwd_f32(a, b, params->d_qk, params->d_v, params->max_len, stream) == hipSuccess ? HSTU_OK : HSTU_ERR_HIP;
   }
   rc = run_pass(params, PASS_DKDV, a, stream);
   if (rc != HSTU_OK) return rc;

@@ -624,8 +624,8 @@ hipError_t launch_bwd_short_bf16(const AttnArgs& a, int d_qk, int d_v, hipStream
 hipError_t launch_fwd_f32(const AttnArgs& a, int d_qk, int d_v, hipStream_t stream);
 hipError_t launch_dkdv_f32(const AttnArgs& a, int d_qk, int d_v, hipStream_t stream);
 // dk/dv and dq pass in one launch (k, q: their arguments), for small calls without bias.
-bool bwd_f32_supported(const AttnArgs& k, const AttnArgs& q, int d_qk, int d_v);
-hipError_t launch_bwd_f32(const AttnArgs& k, const AttnArgs& q, int d_qk, int d_v, hipStream_t stream);
+bool bwd_f32_supported(const AttnArgs& k, const AttnArgs& q, int d_qk, int d_v, int max_len);
+hipError_t launch_bwd_f32(const AttnArgs& k, const AttnArgs& q, int d_qk, int d_v, int max_len, hipStream_t stream);
 hipError_t launch_dq_f32(const AttnArgs& a, int d_qk, int d_v, hipStream_t stream);
 
 // Measurement kernels (hstu_probe.hip): a loop of matrix instructions only (flops per launch

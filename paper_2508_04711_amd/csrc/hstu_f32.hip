@@ -566,13 +566,17 @@ hipError_t launch_dkdv_f32(const AttnArgs& a, int d_qk, int d_v, hipStream_t str
 // 32..256 (1384) 48.8 -> 46.0, 64 of 64..512 (2508) 102 -> 101, 128 (5232) 182 -> 188; d = 64 22.6 -> 16.0, 68.8 ->
 // 63.7, 80.1 -> 77.5, 172 -> 180, 339 -> 352, 8 of 500..1024 (420) 102 -> 76; d = 128 (20) 35.6 -> 20.9, (420) 155 ->
 // 162, (656) 130 -> 134.
-bool bwd_f32_supported(const AttnArgs& k, const AttnArgs& q, int d_qk, int d_v) {
+// At d = 64 sequences of more than 1024 rows (max_len) only up to 600 workgroups a pass: their items are long beside the
+// tail that the passes share.  4 sequences of 1000..3000 rows (520) 261 -> 214 us and (1050) 374 -> 394, 4 of 2000..5000 (440)
+// 404 -> 295 and (880) 530 -> 568, 3 of 3000..8000 (520) 577 -> 459 and (1040) 814 -> 870; 8 of 500..1024 (780) 130 -> 126.  (At d =
+// 32 such calls gain up to the limit: 226 -> 217, 342 -> 310, 503 -> 481.)
+bool bwd_f32_supported(const AttnArgs& k, const AttnArgs& q, int d_qk, int d_v, int max_len) {
   const int64_t most = k.max_items > q.max_items ? k.max_items : q.max_items;
   return d_qk == d_v && !k.ts_rec && !q.ts_rec && (int64_t)k.num_heads * d_qk < WIDE_ROW &&
-         most * k.num_heads * k.item_parts <= (d_qk == 128 ? 128 : 1536);
+         most * k.num_heads * k.item_parts <= (d_qk == 128 ? 128 : d_qk == 64 && max_len > 1024 ? 600 : 1536);
 }
-hipError_t launch_bwd_f32(const AttnArgs& k, const AttnArgs& q, int d_qk, int d_v, hipStream_t stream) {
-  if (!bwd_f32_supported(k, q, d_qk, d_v)) return hipErrorInvalidValue;
+hipError_t launch_bwd_f32(const AttnArgs& k, const AttnArgs& q, int d_qk, int d_v, int max_len, hipStream_t stream) {
+  if (!bwd_f32_supported(k, q, d_qk, d_v, max_len)) return hipErrorInvalidValue;
   const int64_t most = (k.max_items > q.max_items ? k.max_items : q.max_items) * (int64_t)k.num_heads;
   const dim3 grid((unsigned)((most + 7) / 8 * 16), (unsigned)k.item_parts), block(THREADS);
   if (d_qk == 128) hipLaunchKernelGGL((hstu_bwd_f32<128>), grid, block, 0, stream, k, q);

@@ -42,6 +42,22 @@ def test_both_passes_in_one_launch(d, heads, batch, one):
     assert kinds == (["bwd"] if one else ["dkdv", "dq"])
 
 
+@pytest.mark.parametrize("d,batch,max_len,one", [(64, 74, 1025, True), (64, 75, 1025, False), (64, 75, 1024, True),
+                                                 (32, 75, 1025, True)])
+def test_one_launch_of_long_sequences(d, batch, max_len, one):
+    """d = 64 and a max_len beyond 1024: one launch up to 600 workgroups that rows and batch allow for, 4 heads."""
+    import paper_2508_04711_amd as lib
+    print("f32 one launch, long", d, batch, max_len, flush=True)
+    w = workloads.custom("f32_one_long", [32] * batch, 4, d, d, max_len=max_len, dtype="f32", scale=1.0, seed=48)
+    _run_full(w, causal=True, backward=True)
+    t = {k: v.cuda() for k, v in workloads.values(w).items()}
+    off = torch.from_numpy(w.seq_offsets()).cuda()
+    lib.hstu_debug_timing_begin(16)
+    lib.hstu_jagged_attn_bwd(t["q"], t["k"], t["v"], t["d_o"], off, w.max_len, w.alpha, True)
+    kinds = [x[0] for x in lib.hstu_debug_timing_end(16) if x[0] != "plan"]
+    assert kinds == (["bwd"] if one else ["dkdv", "dq"])
+
+
 @pytest.mark.parametrize("d", [32, 128])
 def test_saturated_scores(d):
     # alpha * q.k has a standard deviation of 64: many scores lie beyond what the exponential resolves
