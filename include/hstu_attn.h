@@ -260,7 +260,7 @@ typedef struct {
  * Summing o_local (dq_local) over kv_rank = 0..CP-1 gives q_rank's rows of the
  * full result; summing dk_part (dv_part) over q_rank gives kv_rank's rows.
  * bf16 at d_qk = d_v = 128 without the bias: a call that wants o_local and the gradients computes o_local and
- * dq_local in one kernel, whose tiles are cut along the keys by a rule of its own, a forward-only call o_local in the
+ * dq_local in one kernel (unless it has many short sequences), whose tiles are cut along the keys by a rule of its own, a forward-only call o_local in the
  * forward pass; the fp32 sums of o_local may then be ordered differently in the two calls.  HSTU_FLAG_DKDV_ONE_WAVE and
  * the two HSTU_FLAG_FWD_TILE bits keep the passes apart, and o_local is the forward-only call's bit for bit.
  */

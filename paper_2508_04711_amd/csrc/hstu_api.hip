@@ -321,6 +321,9 @@ int prepare_plan(const hstu_attn_params* p, int cp_size, const SideSpec& s, cons
   // The dq pass, whose items last longer, a third: 32 of 5000 1278 -> 1359 (450), 32 of 2500 690 -> 719 (890), 64 of
   // 1400 at a quarter 510 -> 507 (2060), 512 of lognormal 700 815 -> 729 (6200); at d = 64 256 of lognormal 1400
   // 1885 -> 2022 (6200), 512 of lognormal 350 298 -> 273 (12000).
+  // Forward and dq pass in one goes by the dq pass's line, which neither gains nor loses much there: one of two ranks, sorted ->
+  // natural, 600 of 600..1200 rows H = 2 1113 -> 1142 and 1072 -> 1048, H = 8 4570 -> 4429 and 4420 -> 4107, 128 of 1500..2500
+  // H = 4 1578 -> 1610, H = 8 3190 -> 3115, 300 of 300..600 H = 8 918 -> 961; others within 2 %.
   // The key side at two and three workgroups per CU (H = 8, d = 64) a quarter: 400 lognormal of median 512 fwd + bwd
   // 2165 -> 1964; at a half 128 of 400..800 rows lose 2 %.  No more than an eighth where walking workgroups take
   // runs of equal numbers of items or every 256th (1536 lognormal of median 256 sorted by length, H = 8, d = 128: bwd
@@ -657,19 +660,31 @@ SideSpec key_side(const hstu_attn_params* p, bool bias) {
 
 int64_t clamp_rows(int64_t rows, int64_t total) { return rows < total ? rows : total; }
 
-// A context-parallel rank's forward and dq pass in one kernel (hstu_fwd_dq_pair_bf16), for calls that want both: the two
-// passes by themselves take the scores, their exponentials and the copies of K and V twice.  One of four ranks, 8 sequences of
-// 4096..16384 rows, H = 4, d = 128, with the reorders: 904 -> 763 us, as a ring 1237 -> 1033; 19 more ranks of 2 to 300 sequences
-// 1.05 to 1.47 times as fast.  A forced form of a pass keeps the passes apart.
-bool joint_query_pass(const hstu_attn_params* p, bool bias) {
-  return p->dtype == HSTU_BF16 && p->d_qk == 128 && p->d_v == 128 && !bias &&
-         !(p->flags & (HSTU_FLAG_FWD_TILE_128 | HSTU_FLAG_FWD_TILE_256 | HSTU_FLAG_DKDV_ONE_WAVE));
-}
-
 SideSpec cp_side(const hstu_attn_params* p, const hstu_cp_desc* cp, int side, int pass) {
   const int64_t qr = clamp_rows(cp->q_rows, p->total_rows), kr = clamp_rows(cp->kv_rows, p->total_rows);
   if (side == 0) return SideSpec{0, pass, cp->q_rank, cp->kv_rank, qr, kr, 2, cp->kv_rank < 0 ? 1 : 2};
   return SideSpec{1, pass, cp->kv_rank, cp->q_rank, kr, qr, cp->kv_rank < 0 ? 1 : 2, 2};
+}
+
+// A context-parallel rank's forward and dq pass in one kernel (hstu_fwd_dq_pair_bf16), for calls that want both: the two
+// passes by themselves take the scores, their exponentials and the copies of K and V twice.  One of four ranks, 8 sequences of
+// 4096..16384 rows, H = 4, d = 128, with the reorders: 904 -> 763 us, as a ring 1237 -> 1033; ranks of longer sequences than the
+// lines below 1.0 to 1.5 times as fast.  A forced form of a pass keeps the passes apart.
+// So do many short sequences: at one workgroup per CU an item's start and end, about ten blocks' time, is not overlapped,
+// which items of few blocks do not win back.  The lines, in streamed rows of a sequence: with sequences of s +- 33 %, H = 4 and 8,
+// apart -> one kernel, from 2048 workgroups on one kernel loses up to 12 % at s = 64, 7 % at 128, 4 % at 192, and gains -2 to 8 % at
+// 208 against all keys or the rank's own; against an earlier rank's, of which every item sees half, it loses up to 4 % at 208, 3 % at
+// 256, 1 % at 320; against a later rank's, of which half of the items see nothing and the others every row, up to 6 % at 96, and
+// gains -1 to 3 % at 112, -1 to 9 % at 128; without the mask -3 to 5 % at 160.  From 1024 workgroups on it loses up to 9 % at 64 and gains
+// 0 to 7 % at 160.  With 512 it gains up to 25 % from 64 on.
+bool joint_query_pass(const hstu_attn_params* p, const hstu_cp_desc* cp, bool bias) {
+  if (p->dtype != HSTU_BF16 || p->d_qk != 128 || p->d_v != 128 || bias || p->batch < 1 ||
+      (p->flags & (HSTU_FLAG_FWD_TILE_128 | HSTU_FLAG_FWD_TILE_256 | HSTU_FLAG_DKDV_ONE_WAVE)))
+    return false;
+  const SideSpec s = cp_side(p, cp, 0, PASS_DQ);
+  const int64_t workgroups = items_bound(p, s) * p->num_heads, rows = s.streamed_rows / p->batch;
+  const int64_t line = !p->causal ? 160 : cp->kv_rank > cp->q_rank ? 112 : cp->kv_rank < 0 || cp->kv_rank == cp->q_rank ? 200 : 320;
+  return workgroups < 1024 || rows >= line || (workgroups < 2048 && rows >= line / 2);
 }
 
 int check_cp(const hstu_attn_params* p, const hstu_cp_desc* cp) {
@@ -1064,7 +1079,7 @@ static int cp_partial_impl(const hstu_attn_params* params, const hstu_cp_desc* c
     a.fbits = bias->groups_log2;
   };
   SideSpec sf = cp_side(params, cp, 0, PASS_FWD), sk = cp_side(params, cp, 1, PASS_DKDV), sq = cp_side(params, cp, 0, PASS_DQ);
-  const bool joint = do_f && do_q && joint_query_pass(params, bias != nullptr);  // one schedule, in pq's place
+  const bool joint = do_f && do_q && joint_query_pass(params, cp, bias != nullptr);  // one schedule, in pq's place
   sk.joint = sq.joint = joint;
   if (do_f && !joint) {
     rc = prepare_plan(params, cp->cp_size, sf, seq_offsets_global, ws, workspace_bytes, base, &pa[np], &pf);
@@ -1395,7 +1410,7 @@ int hstu_debug_dump_schedule(const hstu_attn_params* params, const hstu_cp_desc*
   const bool grads = side >= 2;
   const int pass = (side & 1) ? PASS_DKDV : grads ? PASS_DQ : PASS_FWD;
   SideSpec s = cp ? cp_side(params, cp, side & 1, pass) : (side & 1) ? key_side(params, !grads) : full_side(params, 0, pass);
-  s.joint = cp && grads && joint_query_pass(params, false);
+  s.joint = cp && grads && joint_query_pass(params, cp, false);
   BuiltPlan bp;
   rc = build_plan(params, cp ? cp->cp_size : 1, s, seq_offsets, (char*)workspace, workspace_bytes,
                   0, stream, &bp, true);

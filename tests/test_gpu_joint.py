@@ -9,7 +9,7 @@ import torch
 from conftest import set_flags
 import oracle
 import workloads
-from test_gpu_parity import _check, _dev
+from test_gpu_parity import _check, _check_few_terms, _dev
 
 pytestmark = pytest.mark.gpu
 
@@ -111,3 +111,34 @@ def test_passes_kept_apart(flag, monkeypatch):
     (with_gradients, kinds), (alone, _) = call(do), call(None)
     assert "fwd" in kinds and "dq" in kinds and "fwd_dq" not in kinds
     assert torch.equal(with_gradients, alone)
+
+
+@pytest.mark.parametrize("batch,length,q_rank,kv_rank,causal,joint", [
+    (50, 64, 1, -1, True, True), (60, 99, 1, -1, True, False), (60, 101, 1, -1, True, True), (120, 101, 1, -1, True, False),
+    (60, 108, 0, 1, True, False), (60, 112, 0, 1, True, True), (60, 312, 1, 0, True, False), (60, 324, 1, 0, True, True),
+    (60, 196, 1, 1, True, False), (60, 204, 1, 1, True, True), (60, 78, 0, -1, False, False), (60, 80, 0, -1, False, True),
+    (130, 198, 1, -1, True, False), (130, 201, 1, -1, True, True)])
+def test_many_short_sequences(batch, length, q_rank, kv_rank, causal, joint):
+    """Both sides of the lines below which the passes of many short sequences are apart (streamed rows of a sequence by the
+    workgroups that rows and batch allow for), two ranks, 8 heads."""
+    import paper_2508_04711_amd as lib
+    print("joint short", batch, length, q_rank, kv_rank, causal, flush=True)
+    lengths = [length + (i % 3) - 1 for i in range(batch)]
+    lengths[-1] += length * batch - sum(lengths)
+    w = workloads.custom("joint_short", lengths, 8, 128, 128, 256, dtype="bf16", seed=batch + length)
+    vals = workloads.values(w)
+    dev, f64 = _dev(vals), {k: workloads.to_f64(v) for k, v in vals.items()}
+    off_np = w.seq_offsets()
+    off, T = torch.from_numpy(off_np).cuda(), w.total_rows
+    mine = oracle.cp_global_rows(off_np, 2, q_rank)
+    keys = oracle.cp_global_rows(off_np, 2, kv_rank) if kv_rank >= 0 else np.arange(T)
+    pick = lambda t, rows: t[torch.from_numpy(rows).cuda()].contiguous()
+    lib.hstu_debug_timing_begin(16)
+    got = lib.hstu_jagged_attn_cp_partial(pick(dev["q"], mine), pick(dev["k"], keys), pick(dev["v"], keys), pick(dev["d_o"], mine),
+                                          off, T, w.max_len, w.alpha, causal, 2, q_rank, kv_rank, out_dtype=torch.float32)
+    kinds = [x[0] for x in lib.hstu_debug_timing_end(16)]
+    assert ("fwd_dq" in kinds) == joint and ("fwd" in kinds) == ("dq" in kinds) == (not joint)
+    want = oracle.cp_partial(f64["q"][mine], f64["k"][keys], f64["v"][keys], f64["d_o"][mine], off_np, w.max_len, w.alpha,
+                             causal, 2, q_rank, kv_rank)
+    for name, g, ref in zip(("o", "dq", "dk", "dv"), got, want):
+        _check_few_terms(name, g, ref, "joint")
