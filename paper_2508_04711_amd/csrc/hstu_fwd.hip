@@ -492,11 +492,17 @@ hipError_t launch_fwd_bf16(const AttnArgs& a, int d_qk, int d_v, hipStream_t str
       else hipLaunchKernelGGL((hstu_fwd_lean_bf16<64, 64, 4, false>), grid, dim3(256), 0, stream, a);
       return hipGetLastError();
     }
-    // 134 registers and three workgroups a CU where the other form has 122 and four: 16 sequences of 500..4000 rows, H = 4,
-    // 77.1 -> 73.9 us; many prefer four (512 of 300..600 131 -> 122).
-    if (d_qk == 32 && d_v == 64 && !a.ts_rec && !a.row_seq && !many_units(a)) {
-      hipLaunchKernelGGL((hstu_fwd_bf16<32, 64, 4, false, false, false, true>), dim3((unsigned)grid_units(a)), dim3(256), 0,
-                         stream, a);
+    // With the mask's sums held 134, 172, 170 and 106 registers and three, two, two and four workgroups a CU where the other form
+    // has 122, 160, 164 and 94 and one more.  H = 4, us, held and not: 16 sequences of 500..4000 rows 32/64 73.9 and 77.1, 32 of
+    // lognormal length (median 1024) 32/128 104 and 108, 128/64 110 and 115, with H = 8 (3.1 K workgroups) 32/32 103 and 107.
+    // Many prefer more: 512 of 300..600 131 and 122, 203 and 168, 228 and 192; 32/32 102 and 101 (9.2 K), with H = 8 207 and 197.
+    const bool few = grid_units(a) <= (d_qk == 32 && d_v == 32 ? 4096 : 2048);
+    if ((d_qk == 32 || (d_qk == 128 && d_v == 64)) && few && !a.ts_rec && !a.row_seq) {
+      const dim3 grid((unsigned)grid_units(a)), block(256);
+      if (d_qk == 128) hipLaunchKernelGGL((hstu_fwd_bf16<128, 64, 4, false, false, false, true>), grid, block, 0, stream, a);
+      else if (d_v == 128) hipLaunchKernelGGL((hstu_fwd_bf16<32, 128, 4, false, false, false, true>), grid, block, 0, stream, a);
+      else if (d_v == 64) hipLaunchKernelGGL((hstu_fwd_bf16<32, 64, 4, false, false, false, true>), grid, block, 0, stream, a);
+      else hipLaunchKernelGGL((hstu_fwd_bf16<32, 32, 4, false, false, false, true>), grid, block, 0, stream, a);
       return hipGetLastError();
     }
     if (a.row_seq) {

@@ -54,11 +54,11 @@ def test_many_workgroups(name, lengths, H, packed, causal, monkeypatch):
             _check_few_terms(nm, g, ref, name)
 
 
-@pytest.mark.parametrize("repeat,H,many", [(2, 4, False), (16, 8, True)])
-@pytest.mark.parametrize("dqk,dv,bias", [(64, 32, False), (32, 128, False), (32, 64, False), (32, 32, True)])
+@pytest.mark.parametrize("repeat,H,many", [(2, 4, False), (18, 8, True)])
+@pytest.mark.parametrize("dqk,dv,bias", [(64, 32, False), (32, 128, False), (32, 64, False), (32, 32, True), (128, 64, False), (32, 32, False)])
 def test_forms_on_both_sides_of_the_limit(dqk, dv, bias, repeat, H, many, monkeypatch):
     """The other head dimensions whose masks have a form for few workgroups and one for many (dq pass, and the forward pass at
-    32 / 64)."""
+    32 / 64, 32 / 128, 128 / 64 and 32 / 32)."""
     set_flags(monkeypatch, add="NO_PACK")
     lengths = EDGES * repeat
     assert ((sum(lengths) // 128 + len(lengths) + 1) * H > 2048) == many

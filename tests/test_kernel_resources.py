@@ -121,7 +121,8 @@ def test_the_other_attention_kernels(pattern, waves_per_simd, per_cu, waves, spi
 RESIDENCY = [
     (r"hstu_dq_bf16ILi64ELi64ELi4ELb0ELb0E", 3), (r"hstu_dq_bf16ILi64ELi32ELi4ELb0ELb0E", 3),
     (r"hstu_dq_bf16ILi32ELi128ELi4ELb0ELb0E", 3), (r"hstu_dq_bf16ILi32ELi32ELi4ELb1ELb0E", 3),
-    (r"hstu_fwd_bf16ILi32ELi64ELi4ELb0ELb0ELb0ELb1E", 3),
+    (r"hstu_fwd_bf16ILi32ELi64ELi4ELb0ELb0ELb0ELb1E", 3), (r"hstu_fwd_bf16ILi32ELi128ELi4ELb0ELb0ELb0ELb1E", 2),
+    (r"hstu_fwd_bf16ILi128ELi64ELi4ELb0ELb0ELb0ELb1E", 2), (r"hstu_fwd_bf16ILi32ELi32ELi4ELb0ELb0ELb0ELb1E", 4),
 ]
 
 
