@@ -130,8 +130,8 @@ __device__ __forceinline__ void dkdv_step(const Init& init, const char* qn, cons
   fence();
 }
 
-// Head dimensions up to 64 + 64 fit two workgroups per CU (256 registers per lane, a handful
-// spilled at 64 + 64): measured 1.36x faster than one on long sequences (H = 8, d = 64, the skewed
+// Head dimensions up to 64 + 64 fit two workgroups per CU (256 registers per
+// lane): measured 1.36x faster than one on long sequences (H = 8, d = 64, the skewed
 // 96 K-row batch: 4.32 -> 3.18 ms) and 1.67x on 4096 short ones.  At d = 128 the two accumulator
 // sets alone take 128 registers and the kernel runs one wave per SIMD with the full register file.
 // One item (owner tile) of one head.
