@@ -677,6 +677,11 @@ SideSpec cp_side(const hstu_attn_params* p, const hstu_cp_desc* cp, int side, in
 // 256, 1 % at 320; against a later rank's, of which half of the items see nothing and the others every row, up to 6 % at 96, and
 // gains -1 to 3 % at 112, -1 to 9 % at 128; without the mask -3 to 5 % at 160.  From 1024 workgroups on it loses up to 9 % at 64 and gains
 // 0 to 7 % at 160.  With 512 it gains up to 25 % from 64 on.
+// A batch of few long sequences among many short ones lasts as long as its longest items, and those one kernel is faster at: where
+// the longest possible is half of what the starts and ends of a CU's items take, or more.  500 of 20..60 rows and 4 of 4000..8000, H = 2, 4
+// and 8, all keys 497 -> 337, 649 -> 551, 1142 -> 1092 us (3.0, 1.5 and 0.8 of it), one of four ranks 196 -> 168, 282 -> 302,
+// 516 -> 572 (0.8, 0.4 and 0.2); 500 of lognormal length (median 400) at 0.4 level, at 0.2 505 -> 556.  (Empty sequences count as short
+// ones here, the host not seeing them.)
 bool joint_query_pass(const hstu_attn_params* p, const hstu_cp_desc* cp, bool bias) {
   if (p->dtype != HSTU_BF16 || p->d_qk != 128 || p->d_v != 128 || bias || p->batch < 1 ||
       (p->flags & (HSTU_FLAG_FWD_TILE_128 | HSTU_FLAG_FWD_TILE_256 | HSTU_FLAG_DKDV_ONE_WAVE)))
@@ -684,7 +689,9 @@ bool joint_query_pass(const hstu_attn_params* p, const hstu_cp_desc* cp, bool bi
   const SideSpec s = cp_side(p, cp, 0, PASS_DQ);
   const int64_t workgroups = items_bound(p, s) * p->num_heads, rows = s.streamed_rows / p->batch;
   const int64_t line = !p->causal ? 160 : cp->kv_rank > cp->q_rank ? 112 : cp->kv_rank < 0 || cp->kv_rank == cp->q_rank ? 200 : 320;
-  return workgroups < 1024 || rows >= line || (workgroups < 2048 && rows >= line / 2);
+  const int64_t share = cp->kv_rank < 0 ? p->max_len : p->max_len / cp->cp_size;
+  const int64_t longest = (s.streamed_rows < share ? s.streamed_rows : share) / 32;
+  return workgroups < 1024 || rows >= line || (workgroups < 2048 && rows >= line / 2) || longest * 2 >= workgroups * 10 / 256;
 }
 
 int check_cp(const hstu_attn_params* p, const hstu_cp_desc* cp) {

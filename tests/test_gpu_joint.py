@@ -113,19 +113,20 @@ def test_passes_kept_apart(flag, monkeypatch):
     assert torch.equal(with_gradients, alone)
 
 
-@pytest.mark.parametrize("batch,length,q_rank,kv_rank,causal,joint", [
-    (50, 64, 1, -1, True, True), (60, 99, 1, -1, True, False), (60, 101, 1, -1, True, True), (120, 101, 1, -1, True, False),
-    (60, 108, 0, 1, True, False), (60, 112, 0, 1, True, True), (60, 312, 1, 0, True, False), (60, 324, 1, 0, True, True),
-    (60, 196, 1, 1, True, False), (60, 204, 1, 1, True, True), (60, 78, 0, -1, False, False), (60, 80, 0, -1, False, True),
-    (130, 198, 1, -1, True, False), (130, 201, 1, -1, True, True)])
-def test_many_short_sequences(batch, length, q_rank, kv_rank, causal, joint):
+@pytest.mark.parametrize("batch,length,q_rank,kv_rank,causal,max_len,joint", [
+    (50, 64, 1, -1, True, 256, True), (60, 99, 1, -1, True, 256, False), (60, 101, 1, -1, True, 256, True), (120, 101, 1, -1, True, 256, False),
+    (60, 108, 0, 1, True, 256, False), (60, 112, 0, 1, True, 256, True), (60, 312, 1, 0, True, 256, False), (60, 324, 1, 0, True, 256, True),
+    (60, 196, 1, 1, True, 256, False), (60, 204, 1, 1, True, 256, True), (60, 78, 0, -1, False, 256, False), (60, 80, 0, -1, False, 256, True),
+    (130, 198, 1, -1, True, 256, False), (130, 201, 1, -1, True, 256, True),
+    (60, 99, 1, -1, True, 704, False), (60, 99, 1, -1, True, 736, True), (60, 100, 1, 0, True, 1503, True)])
+def test_many_short_sequences(batch, length, q_rank, kv_rank, causal, max_len, joint):
     """Both sides of the lines below which the passes of many short sequences are apart (streamed rows of a sequence by the
-    workgroups that rows and batch allow for), two ranks, 8 heads."""
+    workgroups that rows and batch allow for) and of the longest sequence that max_len allows for, two ranks, 8 heads."""
     import paper_2508_04711_amd as lib
     print("joint short", batch, length, q_rank, kv_rank, causal, flush=True)
     lengths = [length + (i % 3) - 1 for i in range(batch)]
     lengths[-1] += length * batch - sum(lengths)
-    w = workloads.custom("joint_short", lengths, 8, 128, 128, 256, dtype="bf16", seed=batch + length)
+    w = workloads.custom("joint_short", lengths, 8, 128, 128, max_len, dtype="bf16", seed=batch + length)
     vals = workloads.values(w)
     dev, f64 = _dev(vals), {k: workloads.to_f64(v) for k, v in vals.items()}
     off_np = w.seq_offsets()
